@@ -206,6 +206,21 @@ int talon_build_tree(const int32_t* root_token, const void* logits, int dtype, i
                      void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * talon_build_tree with rows by node id, for a caller whose rows are all in place: rows
+ * 0 .. rows-1 of every sequence may be read, whether or not the tree turns out to need them
+ * (row i at b*seq_stride + i*row_stride elements; a row the tree does not expand may hold
+ * anything, a NaN included, and has no effect).  With rows >= N-1 the launch scans rows ahead of
+ * the tree instead of one layer after the other; with fewer it is talon_build_tree.  Same
+ * results, arguments and errors; `workspace` as there.
+ */
+int talon_build_tree_ahead(const int32_t* root_token, const void* logits, int dtype, int64_t row_stride,
+                           int64_t seq_stride, int32_t rows, const talon_tree_state* st, int32_t vocab,
+                           int32_t k, float mu, int32_t K_init, int32_t init_layers, int32_t max_depth,
+                           int32_t* cand_token, float* cand_logit, float* cand_prob,
+                           double* cand_edge_logp, float* row_max, double* row_lse, uint64_t* mask,
+                           void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * talon_build_tree with the recovery from a launch that gave up (TALON_STATUS_ABORTED: the
  * device could not hold the whole grid at once, e.g. because other work was running on it).
  * Runs talon_build_tree, WAITS for `stream` (the only call of this library that synchronises

@@ -35,7 +35,7 @@ TALON_ROWS_BY_FRONTIER = 1
 EXPORTS = [
     "talon_last_error_string", "talon_tree_init", "talon_expand_workspace_bytes",
     "talon_expand_workspace_init", "talon_expand_layer", "talon_select_budget", "talon_expand_select_layer",
-    "talon_expand_tree", "talon_build_tree", "talon_build_tree_checked", "talon_set_spin_limit_us", "talon_profile_scan_launches", "talon_profile_read", "talon_probe_read", "talon_probe_mfma", "talon_probe_issue", "talon_probe_tile_loads", "talon_verify_workspace_bytes", "talon_target_argmax",
+    "talon_expand_tree", "talon_build_tree", "talon_build_tree_ahead", "talon_build_tree_checked", "talon_set_spin_limit_us", "talon_profile_scan_launches", "talon_profile_read", "talon_probe_read", "talon_probe_mfma", "talon_probe_issue", "talon_probe_tile_loads", "talon_verify_workspace_bytes", "talon_target_argmax",
     "talon_literal_workspace_bytes", "talon_expand_literal",
     "talon_greedy_accept", "talon_compact_kv", "talon_prune_tree",
     "talon_build_tree_mask", "talon_tree_attention_workspace_bytes", "talon_tree_attention",
@@ -86,6 +86,8 @@ def load_library() -> ctypes.CDLL:
                                               P, c_size_t, P]
     lib.talon_build_tree.argtypes = [P, P, c_int, c_int64, c_int64, c_int, POINTER(_CTreeState), c_int32, c_int32,
                                      c_float, c_int32, c_int32, c_int32, P, P, P, P, P, P, P, P, c_size_t, P]
+    lib.talon_build_tree_ahead.argtypes = [P, P, c_int, c_int64, c_int64, c_int32, POINTER(_CTreeState), c_int32, c_int32,
+                                           c_float, c_int32, c_int32, c_int32, P, P, P, P, P, P, P, P, c_size_t, P]
     lib.talon_build_tree_checked.argtypes = lib.talon_build_tree.argtypes + [POINTER(c_int32)]
     lib.talon_set_spin_limit_us.argtypes = [c_int64]
     lib.talon_profile_scan_launches.argtypes = [c_int]
@@ -245,7 +247,16 @@ def talon_expand_select_layer(logits, st: TreeState, k, mu, K_init, init_layers,
 
 def talon_build_tree(root_token, logits, st: TreeState, k, mu, K_init, init_layers, max_depth, cand: Candidates,
                      workspace, mask=None, row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
+    """With rows by node id the library may read any row of `logits` (a row per node: all are in
+    place), which lets it scan rows ahead of the tree; rows the tree does not expand have no effect."""
     dt, row_stride, seq_stride, V = _logits_meta(logits)
+    if row_mode == TALON_ROWS_BY_NODE and (vocab is None or vocab <= V) and logits.shape[0] >= st.B and logits.shape[1] > 0:
+        _check(load_library().talon_build_tree_ahead(
+            _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, logits.shape[1], ctypes.byref(st.c),
+            V if vocab is None else vocab, k, c_float(mu), K_init, init_layers, max_depth, _ptr(cand.token),
+            _ptr(cand.logit), _ptr(cand.prob), _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(mask),
+            _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+        return
     _check(load_library().talon_build_tree(
         _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, row_mode, ctypes.byref(st.c),
         V if vocab is None else vocab, k, c_float(mu), K_init, init_layers, max_depth, _ptr(cand.token),

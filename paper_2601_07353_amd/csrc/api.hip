@@ -152,6 +152,8 @@ ExpandArgs make_expand_args(const void* logits, int64_t row_stride, int64_t seq_
   a.spin_ticks = 0;
   a.tree_mask = nullptr;
   a.run_if = nullptr;
+  a.ahead_rows = 0;
+  a.ahead_chunks = 1;
   memset(&a.sel, 0, sizeof(a.sel));
   a.part_max = reinterpret_cast<float*>(w + L.off_max);
   a.part_sum = reinterpret_cast<double*>(w + L.off_sum);
@@ -385,6 +387,18 @@ int tree_grid_limit(int dtype) {
   return v;
 }
 
+// The same for the kernel that scans rows ahead of the tree.
+int ahead_grid_limit(int dtype) {
+  static std::atomic<int> cached[2] = {{-1}, {-1}};
+  std::atomic<int>& c = cached[dtype == TALON_DTYPE_F32 ? 0 : 1];
+  int v = c.load(std::memory_order_relaxed);
+  if (v < 0) {
+    v = build_ahead_resident(dtype);
+    c.store(v, std::memory_order_relaxed);
+  }
+  return v;
+}
+
 // Bound of the wait between two layers of the single-launch kernel, in ticks of the 100 MHz
 // wall clock (default 0.2 s; talon_set_spin_limit_us changes it).
 std::atomic<long long> g_spin_limit_us{200000};
@@ -513,6 +527,56 @@ int talon_build_tree(const int32_t* root_token, const void* logits, int dtype, i
   return run_fused_layers(true, root_token, mask, logits, dtype, row_stride, seq_stride, row_mode, 0, layers, st, vocab,
                           k, mu, K_init, init_layers, max_depth, cand_token, cand_logit, cand_prob, cand_edge_logp,
                           row_max, row_lse, workspace, workspace_bytes, stream);
+}
+
+int talon_build_tree_ahead(const int32_t* root_token, const void* logits, int dtype, int64_t row_stride, int64_t seq_stride,
+                           int32_t rows, const talon_tree_state* st, int32_t vocab, int32_t k, float mu, int32_t K_init,
+                           int32_t init_layers, int32_t max_depth, int32_t* cand_token, float* cand_logit, float* cand_prob,
+                           double* cand_edge_logp, float* row_max, double* row_lse, uint64_t* mask, void* workspace,
+                           size_t workspace_bytes, void* stream) {
+  if (rows < 1) { set_error("rows=%d must be >= 1", rows); return TALON_ERR_INVALID_ARG; }
+  // every node but the last one a tree can hold may have its row read; one node has nothing to scan ahead
+  if (!st || st->N < 2 || rows < st->N - 1 || max_depth < 1)
+    return talon_build_tree(root_token, logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, k, mu, K_init,
+                            init_layers, max_depth, cand_token, cand_logit, cand_prob, cand_edge_logp, row_max, row_lse,
+                            mask, workspace, workspace_bytes, stream);
+  if (!root_token) { set_error("root_token is NULL"); return TALON_ERR_INVALID_ARG; }
+  if (mask && (reinterpret_cast<uintptr_t>(mask) & 7u)) { set_error("mask is not 8-byte aligned"); return TALON_ERR_INVALID_ARG; }
+  ExpandLayout L;
+  int rc = check_expand_args(logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, k, cand_token, cand_logit,
+                             cand_prob, cand_edge_logp, row_max, row_lse, workspace, workspace_bytes, &L);
+  if (rc) return rc;
+  rc = check_select_args(st, k, cand_token, cand_prob, cand_edge_logp, mu, K_init, init_layers, max_depth);
+  if (rc) return rc;
+  ExpandArgs ea = make_expand_args(logits, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, k, cand_token, cand_logit,
+                                   cand_prob, cand_edge_logp, row_max, row_lse, workspace, L);
+  ea.sel.st = *st; ea.sel.k = k; ea.sel.cand_token = cand_token; ea.sel.cand_prob = cand_prob;
+  ea.sel.cand_edge_logp = cand_edge_logp; ea.sel.log_mu = log(static_cast<double>(mu)); ea.sel.K_init = K_init;
+  ea.sel.init_layers = init_layers; ea.sel.max_depth = max_depth;
+  ea.layers = max_depth < st->N - 1 ? max_depth : st->N - 1;
+  ea.root_token = root_token;
+  ea.tree_mask = mask;
+  ea.spin_ticks = spin_limit_ticks();
+  const int resident = ahead_grid_limit(dtype);
+  if (resident < 1) { set_error("occupancy query for the scan-ahead kernel failed"); return TALON_ERR_RUNTIME; }
+  ea.ahead_rows = st->N - 1;
+  const long long rows_all = static_cast<long long>(st->B) * ea.ahead_rows;
+  long long scanners = resident - st->B > resident / 2 ? resident - st->B : resident / 2;
+  // Runs of blocks per row: as many as give every scanner of a full grid at most one item.  Items
+  // that nobody has to queue for need no counter, and every further item of a workgroup costs it
+  // about 10 us between two streams (ranking, partial results, tickets): 508 rows of 304 KB take
+  // 52 us as 1016 items and 55-57 us as 1524 or 2032; 4080 rows 250 us whole and 280 us in two.
+  const int chunks = tuned_int("TALON_AHEAD_CHUNKS", static_cast<int>(scanners / rows_all < 1 ? 1 : (scanners / rows_all > L.chunks ? L.chunks : scanners / rows_all)));
+  const int bpc = (L.chunks + chunks - 1) / chunks;
+  ea.ahead_chunks = (L.chunks + bpc - 1) / bpc;
+  if (scanners > rows_all * ea.ahead_chunks) scanners = rows_all * ea.ahead_chunks;
+  const int grid = static_cast<int>(scanners) + st->B;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (g_profile.enabled && (rc = check_hip(profile_record(s), "profile event"))) return rc;
+  rc = check_hip(launch_build_ahead(ea, dtype, grid, s), "scan-ahead launch");
+  if (rc) return rc;
+  if (g_profile.enabled && (rc = check_hip(profile_record(s), "profile event"))) return rc;
+  return TALON_OK;
 }
 
 int talon_build_tree_checked(const int32_t* root_token, const void* logits, int dtype, int64_t row_stride,

@@ -52,6 +52,113 @@ __device__ __forceinline__ void st_(T* p, T v) {
   else *p = v;
 }
 
+// The candidates of one layer that are kept: keys >= thr_key, at most `limit` of them, the largest
+// first, equal keys in the order of the threads' slots.  Every thread passes its `per` <= 32 keys in
+// LDS (0 = no candidate; they may be rewritten) and the pool's largest key; bit i of the result: its
+// key i is kept.  *pos: kept candidates of the threads before it; *n_keep: of all.
+__device__ __forceinline__ unsigned int keep_best(unsigned long long* my, const int per, const unsigned long long anchor_key,
+                                                  const unsigned long long thr_key, const int limit, const SelectLds& lds,
+                                                  int* pos, int* n_keep) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  int* s_hist = lds.hist;
+  unsigned long long* s_red_u64 = lds.red_u64;
+  int* s_red_i32 = lds.red_i32;
+  int& s_digit = lds.misc[0];
+  int& s_remaining = lds.misc[1];
+  // candidates that pass the gate: where no more pass than may be kept (every layer but the one that
+  // exhausts the budget, as a rule), their prefix count settles the layer
+  unsigned int pass_bits = 0u;
+  unsigned long long inv_low = 0ull;   // max of ~key over the passing keys
+  for (int i = 0; i < per; ++i) {
+    const unsigned long long key = my[i];
+    if (key >= thr_key) { pass_bits |= 1u << i; inv_low = ~key > inv_low ? ~key : inv_low; }
+  }
+  int n_pass;
+  *pos = block_exclusive_scan_i32(__popc(pass_bits), s_red_i32, &n_pass);
+  if (n_pass <= limit) { *n_keep = n_pass; return pass_bits; }
+  unsigned long long T = 0ull;        // keep key > T, and the first need_eq keys == T
+  int need_eq = 0;
+  // ---- radix select: the limit-th largest key, 8 bits per pass from the top.
+  // Path scores of one layer lie close together, so their keys share their leading bits.
+  // The keys are first moved to the range they span: key' = (key - lowest + 1) << s with s
+  // such that the largest key' has its top bit set (order and ties are preserved, keys
+  // below the gate become 0 = no candidate).  The digits of key' are spread over the bins,
+  // and the search usually ends after two or three passes: as soon as the bin that holds
+  // the limit-th key holds exactly as many keys as are still wanted.
+  const unsigned long long low_key = ~block_max_u64(inv_low, s_red_u64);
+  const int sh = __clzll(static_cast<long long>(anchor_key - low_key + 1ull));
+  for (int i = 0; i < per; ++i) {
+    const unsigned long long key = my[i];
+    my[i] = key >= thr_key ? (key - low_key + 1ull) << sh : 0ull;
+  }
+  unsigned long long prefix = 0ull;
+  int remaining = limit;
+  bool found = false;
+  for (int pass = 0; pass < 8; ++pass) {
+    const int shift = 56 - 8 * pass;
+    s_hist[tid] = 0;
+    __syncthreads();
+    for (int i = 0; i < per; ++i) {
+      const unsigned long long key = my[i];
+      const bool match = pass == 0 || ((key ^ prefix) >> ((shift + 8) & 63)) == 0ull;
+      if (match && key != 0ull) atomicAdd(&s_hist[static_cast<int>(key >> shift) & 255], 1);
+    }
+    __syncthreads();
+    if (tid < 64) {
+      // lane l owns digits 255-4l .. 252-4l, walked from the largest digit down
+      int h[4], lane_sum = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { h[j] = s_hist[255 - 4 * tid - j]; lane_sum += h[j]; }
+      const int incl = wave_inclusive_scan_i32(lane_sum);
+      const unsigned long long hit = __ballot(incl >= remaining);
+      const int first = __ffsll(static_cast<long long>(hit)) - 1;
+      if (tid == first) {
+        int before = incl - lane_sum;
+        int dg = 255 - 4 * tid;
+        int j = 0;
+#pragma unroll
+        for (; j < 3; ++j) {
+          if (before + h[j] < remaining) { before += h[j]; --dg; } else break;
+        }
+        const int want = remaining - before;
+        // the bin holds exactly the keys still wanted: all of them are kept
+        s_digit = dg | ((h[j] == want) ? 256 : 0);
+        s_remaining = want;
+      }
+    }
+    __syncthreads();
+    const int dg = s_digit;
+    prefix |= static_cast<unsigned long long>(dg & 255) << shift;
+    remaining = s_remaining;
+    __syncthreads();
+    if (dg & 256) {   // keep every key >= prefix (lower digits zero): none equals prefix - 1 with a claim
+      T = prefix != 0ull ? prefix - 1ull : 0ull;   // prefix 0: every candidate left is kept
+      need_eq = 0;
+      found = true;
+      break;
+    }
+  }
+  if (!found) { T = prefix; need_eq = remaining; }
+
+  // ---- keep flags, ranks among equal keys, compaction
+  int eq_local = 0;
+  for (int i = 0; i < per; ++i) eq_local += (my[i] == T) ? 1 : 0;
+  int eq_total;
+  int eq_rank = block_exclusive_scan_i32(eq_local, s_red_i32, &eq_total);
+  unsigned int keep_bits = 0u;
+  int keep_local = 0;
+  for (int i = 0; i < per; ++i) {
+    const unsigned long long key = my[i];
+    bool keep = key > T;
+    if (key == T) { keep = eq_rank < need_eq; ++eq_rank; }
+    if (key == 0ull) keep = false;
+    if (keep) { keep_bits |= 1u << i; ++keep_local; }
+  }
+  *pos = block_exclusive_scan_i32(keep_local, s_red_i32, n_keep);
+  return keep_bits;
+}
+
 // Runs on all 256 threads of the workgroup.  F, fb: the frontier being expanded.  Returns, in
 // thread 0, the new frontier as begin + (count << 32), count 0 if the sequence is done.
 // n_known / d_known (>= 0): |T| and the layer index when the caller knows them (a launch that
@@ -72,11 +179,7 @@ __device__ __forceinline__ unsigned long long select_sequence(const SelectArgs& 
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   unsigned long long* s_key = lds.key;
-  int* s_hist = lds.hist;
   unsigned long long* s_red_u64 = lds.red_u64;
-  int* s_red_i32 = lds.red_i32;
-  int& s_digit = lds.misc[0];
-  int& s_remaining = lds.misc[1];
   const int n = n_known >= 0 ? n_known : ld<AGENT, int32_t>(st.n_nodes + b);
   const int d = d_known >= 0 ? d_known : ld<AGENT, int32_t>(st.depth_cur + b);
   const int R = st.N - n;
@@ -195,107 +298,13 @@ __device__ __forceinline__ unsigned long long select_sequence(const SelectArgs& 
     if (thr_key == 0ull) thr_key = 1ull;
   }
 
-  // candidates that pass the gate, and the lowest of their keys
-  int n_pass_local = 0;
-  unsigned long long inv_low = 0ull;   // max of ~key over the passing keys
-  for (int i = 0; i < per; ++i) {
-    const unsigned long long key = my[i];
-    if (key >= thr_key) { ++n_pass_local; inv_low = ~key > inv_low ? ~key : inv_low; }
-  }
-  n_pass_local = wave_sum_i32(n_pass_local);
-  inv_low = wave_max_u64(inv_low);
-  __syncthreads();
-  if ((tid & 63) == 0) { s_red_i32[tid >> 6] = n_pass_local; s_red_u64[tid >> 6] = inv_low; }
-  __syncthreads();
-  const int n_pass = s_red_i32[0] + s_red_i32[1] + s_red_i32[2] + s_red_i32[3];
-
-  unsigned long long T = thr_key;     // keep key > T, and the first need_eq keys == T
-  int need_eq = 0x7FFFFFFF;
-  if (n_pass > limit) {
-    // ---- radix select: the limit-th largest key, 8 bits per pass from the top.
-    // Path scores of one layer lie close together, so their keys share their leading bits.
-    // The keys are first moved to the range they span: key' = (key - lowest + 1) << s with s
-    // such that the largest key' has its top bit set (order and ties are preserved, keys
-    // below the gate become 0 = no candidate).  The digits of key' are spread over the bins,
-    // and the search usually ends after two or three passes: as soon as the bin that holds
-    // the limit-th key holds exactly as many keys as are still wanted.
-    unsigned long long a01 = s_red_u64[0] > s_red_u64[1] ? s_red_u64[0] : s_red_u64[1];
-    unsigned long long a23 = s_red_u64[2] > s_red_u64[3] ? s_red_u64[2] : s_red_u64[3];
-    const unsigned long long low_key = ~(a01 > a23 ? a01 : a23);
-    const int sh = __clzll(static_cast<long long>(anchor_key - low_key + 1ull));
-    for (int i = 0; i < per; ++i) {
-      const unsigned long long key = my[i];
-      my[i] = key >= thr_key ? (key - low_key + 1ull) << sh : 0ull;
-    }
-    unsigned long long prefix = 0ull;
-    int remaining = limit;
-    T = 0ull;
-    need_eq = 0;
-    bool found = false;
-    for (int pass = 0; pass < 8; ++pass) {
-      const int shift = 56 - 8 * pass;
-      s_hist[tid] = 0;
-      __syncthreads();
-      for (int i = 0; i < per; ++i) {
-        const unsigned long long key = my[i];
-        const bool match = pass == 0 || ((key ^ prefix) >> ((shift + 8) & 63)) == 0ull;
-        if (match && key != 0ull) atomicAdd(&s_hist[static_cast<int>(key >> shift) & 255], 1);
-      }
-      __syncthreads();
-      if (tid < 64) {
-        // lane l owns digits 255-4l .. 252-4l, walked from the largest digit down
-        int h[4], lane_sum = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { h[j] = s_hist[255 - 4 * tid - j]; lane_sum += h[j]; }
-        const int incl = wave_inclusive_scan_i32(lane_sum);
-        const unsigned long long hit = __ballot(incl >= remaining);
-        const int first = __ffsll(static_cast<long long>(hit)) - 1;
-        if (tid == first) {
-          int before = incl - lane_sum;
-          int dg = 255 - 4 * tid;
-          int j = 0;
-#pragma unroll
-          for (; j < 3; ++j) {
-            if (before + h[j] < remaining) { before += h[j]; --dg; } else break;
-          }
-          const int want = remaining - before;
-          // the bin holds exactly the keys still wanted: all of them are kept
-          s_digit = dg | ((h[j] == want) ? 256 : 0);
-          s_remaining = want;
-        }
-      }
-      __syncthreads();
-      const int dg = s_digit;
-      prefix |= static_cast<unsigned long long>(dg & 255) << shift;
-      remaining = s_remaining;
-      __syncthreads();
-      if (dg & 256) {   // keep every key >= prefix (lower digits zero): none equals prefix - 1 with a claim
-        T = prefix != 0ull ? prefix - 1ull : 0ull;   // prefix 0: every candidate left is kept
-        need_eq = 0;
-        found = true;
-        break;
-      }
-    }
-    if (!found) { T = prefix; need_eq = remaining; }
-  }
-
-  // ---- keep flags, ranks among equal keys, compaction
-  int eq_local = 0;
-  for (int i = 0; i < per; ++i) eq_local += (my[i] == T) ? 1 : 0;
-  int eq_total;
-  int eq_rank = block_exclusive_scan_i32(eq_local, s_red_i32, &eq_total);
-  unsigned int keep_bits = 0u;
-  int keep_local = 0;
-  for (int i = 0; i < per; ++i) {
-    const unsigned long long key = my[i];
-    bool keep = key > T;
-    if (key == T) { keep = eq_rank < need_eq; ++eq_rank; }
-    if (key == 0ull) keep = false;
-    if (keep) { keep_bits |= 1u << i; ++keep_local; }
-    if (keep && a.cap_hit && (c_begin + i) % k == k - 1) st_<true, uint32_t>(a.cap_hit, 1u);   // a row's last candidate
-  }
   int n_keep;
-  int pos = block_exclusive_scan_i32(keep_local, s_red_i32, &n_keep);
+  int pos;
+  const unsigned int keep_bits = keep_best(my, per, anchor_key, thr_key, limit, lds, &pos, &n_keep);
+  if (a.cap_hit) {   // was a row's last candidate kept?
+    for (int i = 0; i < per; ++i)
+      if ((keep_bits & (1u << i)) && (c_begin + i) % k == k - 1) st_<true, uint32_t>(a.cap_hit, 1u);
+  }
 #pragma unroll
   for (int i = 0; i < kRegCand; ++i) {
     if (i < per && (keep_bits & (1u << i))) {

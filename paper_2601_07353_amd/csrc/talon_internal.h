@@ -96,6 +96,9 @@ struct ExpandArgs {
   uint64_t* tree_mask;   // optional: ancestor masks written at the end of the single launch
   const int32_t* root_token;   // optional [B]
   const uint32_t* run_if;      // optional: the single launch does nothing unless this word is non-zero
+  // Launch that scans rows ahead of the tree: rows 0 .. ahead_rows - 1 of every sequence, each in
+  // ahead_chunks runs of blocks.
+  int ahead_rows, ahead_chunks;
 };
 
 // Start of a single launch that continues trees: what it does with the five per-sequence words
@@ -189,6 +192,8 @@ hipError_t launch_tile_load_probe(int loads, bool with_mfma, int waves, int iter
 hipError_t launch_fused_init(const talon_tree_state& st, const ExpandArgs& a, const FusedInitArgs& f, hipStream_t s);
 hipError_t launch_expand_tree(const ExpandArgs& a, int dtype, int grid, hipStream_t s);
 int expand_tree_max_grid(int dtype);
+hipError_t launch_build_ahead(const ExpandArgs& a, int dtype, int grid, hipStream_t s);
+int build_ahead_resident(int dtype);
 hipError_t launch_expand(const ExpandArgs& a, int dtype, int grid, bool fused, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_mask(const talon_tree_state& st, uint64_t* mask, hipStream_t s);

@@ -1,0 +1,119 @@
+"""talon_build_tree with rows scanned ahead of the tree (talon_build_tree_ahead) against the loop that
+scans one layer after the other, and against torch where the row order is adversarial."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_of(B, N, V, dtype, seed, lo=0.5, hi=4.0):
+    import torch
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn(B, N, V, generator=g) * (lo + (hi - lo) * torch.rand(B, N, 1, generator=g))
+    V8 = (V + 7) // 8 * 8
+    pool = torch.zeros(B, N, V8, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    pool[:, :, :V] = x.to(pool.dtype)
+    return pool.cuda()[:, :, :V]
+
+
+def build(logits, N, k, Dmax, ahead, K_init=None, init_layers=1, mu=0.03):
+    """One tree per sequence; candidate arrays start from a sentinel."""
+    import torch
+    import paper_2601_07353_amd as T
+    B, _, V = logits.shape
+    st = T.TreeState(B, N)
+    cand = T.Candidates(B, st.N_pad, k)
+    for t in (cand.token, cand.logit, cand.prob, cand.edge_logp, cand.row_max, cand.row_lse):
+        t.fill_(-77)
+    dt = T.TALON_DTYPE_F32 if logits.dtype == torch.float32 else T.TALON_DTYPE_BF16
+    ws = T.make_expand_workspace(B, st.N_pad, V, k, dt)
+    roots = torch.arange(B, dtype=torch.int32).cuda()
+    mask = torch.full((B, st.N_pad, st.N_pad // 64), -1, dtype=torch.int64, device="cuda")
+    for _ in range(2):   # the second call finds the workspace as the first one left it
+        if ahead:
+            T.talon_build_tree(roots, logits, st, k, mu, K_init or k, init_layers, Dmax, cand, ws, mask=mask)
+        else:
+            T.talon_tree_init(st, roots)
+            T.talon_expand_tree(logits, st, k, mu, K_init or k, init_layers, Dmax, cand, ws)
+            T.talon_build_tree_mask(st, mask)
+    torch.cuda.synchronize()
+    out = {n: getattr(st, n).cpu().numpy() for n in ("token", "parent", "depth", "prob", "logp", "n_nodes", "frontier_begin",
+                                                     "frontier_count", "depth_cur", "status")}
+    out["mask"] = mask.cpu().numpy()
+    out.update({"cand_" + n: getattr(cand, n).cpu().numpy() for n in ("token", "logit", "prob", "edge_logp", "row_max", "row_lse")})
+    return out
+
+
+def same(a, b):
+    for key in a:
+        if key in ("prob", "logp", "cand_prob", "cand_edge_logp", "cand_row_lse"):
+            # sums of a row's chunks in another order: 2e-6 on a log-sum-exp, one per layer of a path
+            np.testing.assert_allclose(a[key], b[key], rtol=1e-5, atol=2e-6 * 24, err_msg=key)
+        else:
+            np.testing.assert_array_equal(a[key], b[key], err_msg=key)
+
+
+@pytest.mark.parametrize("B,V,dtype,k,N,Dmax,init_layers", [
+    (1, 8, "f32", 2, 2, 4, 1),            # two nodes: one row
+    (2, 5, "bf16", 8, 17, 6, 1),          # fewer tokens than candidates
+    (3, 5003, "bf16", 31, 130, 12, 1),    # more than 128 frontier rows with the most candidates a row may have then
+    (2, 3001, "f32", 64, 64, 8, 1),       # the largest cap
+    (1, 70001, "f32", 4, 255, 24, 0),     # many short runs per row, no top-K layer
+    (70, 1025, "bf16", 4, 20, 5, 1),      # more sequences than a wavefront has lanes
+    (8, 20000, "bf16", 16, 256, 24, 2),   # 2040 rows: scanners take further items from the counter
+    (2, 8192, "bf16", 10, 60, 1, 1),      # one layer: all rows but the root's are scanned in vain
+])
+def test_rows_scanned_ahead_build_the_same_trees(B, V, dtype, k, N, Dmax, init_layers):
+    logits = rows_of(B, N, V, dtype, seed=100 * N + k)
+    same(build(logits, N, k, Dmax, True, init_layers=init_layers), build(logits, N, k, Dmax, False, init_layers=init_layers))
+
+
+@pytest.mark.parametrize("spare", [-1, 0, 1, -20])
+def test_rows_the_tree_does_not_need_have_no_effect(spare):
+    """N-1 rows are the most a tree expands.  The rows no node of this tree expands hold NaN; with
+    fewer rows than N-1 the call scans layer by layer and never touches what is not there."""
+    import torch
+    N, k = 60, 10
+    logits = rows_of(1, N, 30000, "bf16", seed=5)
+    want = build(logits, N, k, 12, False)
+    expanded = int(want["frontier_begin"][0])
+    rows = max(N + spare, expanded)
+    cut = logits[:, :rows].clone()
+    cut[:, expanded:] = float("nan")
+    got = build(cut, N, k, 12, True)
+    same(got, want)
+    assert got["status"][0] == 1
+
+
+def test_a_bad_row_stops_its_sequence_only():
+    import paper_2601_07353_amd as T
+    logits = rows_of(3, 40, 9000, "f32", seed=9)
+    logits[1, 3, 77] = float("nan")
+    a, b = build(logits, 40, 8, 8, True), build(logits, 40, 8, 8, False)
+    assert a["status"].tolist() == b["status"].tolist() and a["status"][1] == T.TALON_STATUS_BAD_ROW
+    for key in ("token", "parent", "n_nodes", "depth_cur", "frontier_begin", "frontier_count", "mask"):
+        np.testing.assert_array_equal(a[key], b[key], err_msg=key)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("order", ["ascending", "descending", "sawtooth", "ascending late"])
+def test_scan_of_rows_in_adversarial_order(dtype, order):
+    """Rows that rise along the token ids raise the scan's threshold group by group; the k best and
+    the log-sum-exp must not notice."""
+    import torch
+    V, k = 41003, 16
+    x = torch.arange(V, dtype=torch.float32) * (20.0 / V)
+    if order == "descending":
+        x = x.flip(0)
+    elif order == "sawtooth":
+        x = (torch.arange(V) * 2049 % V).float() * (20.0 / V)
+    elif order == "ascending late":
+        x[: V // 2] = 0.0
+    logits = torch.zeros(1, 12, (V + 7) // 8 * 8, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    logits[:, :, :V] = x.to(logits.dtype)
+    logits = logits.cuda()[:, :, :V]
+    got = build(logits, 12, k, 4, True)
+    row = logits[0, 0].double().cpu()
+    order_ids = torch.argsort(row, descending=True, stable=True)[:k]     # equal logits: lower token first
+    np.testing.assert_array_equal(got["cand_token"][0, 0], order_ids.numpy())
+    assert abs(got["cand_row_lse"][0, 0] - float(torch.logsumexp(row, 0))) < 2e-6
