@@ -12,6 +12,8 @@ from ctypes import POINTER, Structure, c_char_p, c_double, c_float, c_int, c_int
 
 import torch
 
+_byref = ctypes.byref
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "lib", "libtalon.so")
 
@@ -130,14 +132,24 @@ def _check(rc: int):
         raise TalonError(rc, load_library().talon_last_error_string().decode())
 
 
+# Marshalling is kept to plain integers: a call is one or two kernels of a few microseconds, and a
+# loop of such calls is bound by the host.  (torch.cuda.current_stream() builds a Stream object, 2.8 us;
+# the raw handle of the current stream is 0.2 us.  A layer of the per-layer loop: 9.3 us of host
+# time per call before, of which the launch itself is 4.1.)
 def _ptr(t):
-    return None if t is None else c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
-    return c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 class TreeState:
@@ -182,13 +194,14 @@ def _logits_meta(logits: torch.Tensor):
         dt = TALON_DTYPE_BF16
     else:
         raise TalonError(TALON_ERR_UNSUPPORTED, "logits dtype %s" % logits.dtype)
-    if logits.dim() != 3 or logits.stride(2) != 1:
+    strides = logits.stride()
+    if len(strides) != 3 or strides[2] != 1:
         raise TalonError(TALON_ERR_INVALID_ARG, "logits must be [B][rows][V] with contiguous rows")
-    return dt, logits.stride(1), logits.stride(0), logits.shape[2]
+    return dt, strides[1], strides[0], logits.shape[2]
 
 
 def talon_tree_init(st: TreeState, root_token: torch.Tensor, stream=None):
-    _check(load_library().talon_tree_init(ctypes.byref(st.c), _ptr(root_token), _stream(stream)))
+    _check(load_library().talon_tree_init(_byref(st.c), _ptr(root_token), _stream(stream)))
 
 
 def talon_expand_workspace_bytes(B, N_pad, vocab, k, dtype) -> int:
@@ -196,7 +209,7 @@ def talon_expand_workspace_bytes(B, N_pad, vocab, k, dtype) -> int:
 
 
 def talon_expand_workspace_init(workspace: torch.Tensor, stream=None):
-    _check(load_library().talon_expand_workspace_init(_ptr(workspace), workspace.numel() * workspace.element_size(),
+    _check(load_library().talon_expand_workspace_init(_ptr(workspace), workspace.nbytes,
                                                       _stream(stream)))
 
 
@@ -213,15 +226,15 @@ def talon_expand_layer(logits, st: TreeState, k, cand: Candidates, workspace, ro
                        layer=-1, vocab=None, stream=None):
     dt, row_stride, seq_stride, V = _logits_meta(logits)
     _check(load_library().talon_expand_layer(
-        _ptr(logits), dt, row_stride, seq_stride, row_mode, layer, ctypes.byref(st.c),
+        _ptr(logits), dt, row_stride, seq_stride, row_mode, layer, _byref(st.c),
         V if vocab is None else vocab, k,
         _ptr(cand.token), _ptr(cand.logit), _ptr(cand.prob), _ptr(cand.edge_logp), _ptr(cand.row_max),
-        _ptr(cand.row_lse), _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+        _ptr(cand.row_lse), _ptr(workspace), workspace.nbytes, _stream(stream)))
 
 
 def talon_select_budget(st: TreeState, k, cand: Candidates, mu, K_init, init_layers, max_depth, stream=None):
     _check(load_library().talon_select_budget(
-        ctypes.byref(st.c), k, _ptr(cand.token), _ptr(cand.prob), _ptr(cand.edge_logp), c_float(mu), K_init,
+        _byref(st.c), k, _ptr(cand.token), _ptr(cand.prob), _ptr(cand.edge_logp), mu, K_init,
         init_layers, max_depth, _stream(stream)))
 
 
@@ -229,20 +242,20 @@ def talon_expand_tree(logits, st: TreeState, k, mu, K_init, init_layers, max_dep
                       row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
     dt, row_stride, seq_stride, V = _logits_meta(logits)
     _check(load_library().talon_expand_tree(
-        _ptr(logits), dt, row_stride, seq_stride, row_mode, ctypes.byref(st.c), V if vocab is None else vocab, k,
-        c_float(mu), K_init, init_layers, max_depth, _ptr(cand.token), _ptr(cand.logit), _ptr(cand.prob),
+        _ptr(logits), dt, row_stride, seq_stride, row_mode, _byref(st.c), V if vocab is None else vocab, k,
+        mu, K_init, init_layers, max_depth, _ptr(cand.token), _ptr(cand.logit), _ptr(cand.prob),
         _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(stream)))
+        workspace.nbytes, _stream(stream)))
 
 
 def talon_expand_select_layer(logits, st: TreeState, k, mu, K_init, init_layers, max_depth, cand: Candidates,
                               workspace, layer=-1, row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
     dt, row_stride, seq_stride, V = _logits_meta(logits)
     _check(load_library().talon_expand_select_layer(
-        _ptr(logits), dt, row_stride, seq_stride, row_mode, layer, ctypes.byref(st.c), V if vocab is None else vocab,
-        k, c_float(mu), K_init, init_layers, max_depth, _ptr(cand.token), _ptr(cand.logit), _ptr(cand.prob),
+        _ptr(logits), dt, row_stride, seq_stride, row_mode, layer, _byref(st.c), V if vocab is None else vocab,
+        k, mu, K_init, init_layers, max_depth, _ptr(cand.token), _ptr(cand.logit), _ptr(cand.prob),
         _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(stream)))
+        workspace.nbytes, _stream(stream)))
 
 
 def talon_build_tree(root_token, logits, st: TreeState, k, mu, K_init, init_layers, max_depth, cand: Candidates,
@@ -252,16 +265,16 @@ def talon_build_tree(root_token, logits, st: TreeState, k, mu, K_init, init_laye
     dt, row_stride, seq_stride, V = _logits_meta(logits)
     if row_mode == TALON_ROWS_BY_NODE and (vocab is None or vocab <= V) and logits.shape[0] >= st.B and logits.shape[1] > 0:
         _check(load_library().talon_build_tree_ahead(
-            _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, logits.shape[1], ctypes.byref(st.c),
-            V if vocab is None else vocab, k, c_float(mu), K_init, init_layers, max_depth, _ptr(cand.token),
+            _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, logits.shape[1], _byref(st.c),
+            V if vocab is None else vocab, k, mu, K_init, init_layers, max_depth, _ptr(cand.token),
             _ptr(cand.logit), _ptr(cand.prob), _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(mask),
-            _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+            _ptr(workspace), workspace.nbytes, _stream(stream)))
         return
     _check(load_library().talon_build_tree(
-        _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, row_mode, ctypes.byref(st.c),
-        V if vocab is None else vocab, k, c_float(mu), K_init, init_layers, max_depth, _ptr(cand.token),
+        _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, row_mode, _byref(st.c),
+        V if vocab is None else vocab, k, mu, K_init, init_layers, max_depth, _ptr(cand.token),
         _ptr(cand.logit), _ptr(cand.prob), _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(mask),
-        _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+        _ptr(workspace), workspace.nbytes, _stream(stream)))
 
 
 def talon_build_tree_checked(root_token, logits, st: TreeState, k, mu, K_init, init_layers, max_depth,
@@ -272,10 +285,10 @@ def talon_build_tree_checked(root_token, logits, st: TreeState, k, mu, K_init, i
     dt, row_stride, seq_stride, V = _logits_meta(logits)
     fell = c_int32(0)
     _check(load_library().talon_build_tree_checked(
-        _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, row_mode, ctypes.byref(st.c),
-        V if vocab is None else vocab, k, c_float(mu), K_init, init_layers, max_depth, _ptr(cand.token),
+        _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, row_mode, _byref(st.c),
+        V if vocab is None else vocab, k, mu, K_init, init_layers, max_depth, _ptr(cand.token),
         _ptr(cand.logit), _ptr(cand.prob), _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(mask),
-        _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream), ctypes.byref(fell)))
+        _ptr(workspace), workspace.nbytes, _stream(stream), ctypes.byref(fell)))
     return bool(fell.value)
 
 
@@ -296,7 +309,7 @@ def talon_profile_read(capacity: int):
 
 
 def talon_probe_read(buf: torch.Tensor, sink: torch.Tensor, stream=None):
-    _check(load_library().talon_probe_read(_ptr(buf), buf.numel() * buf.element_size(), _ptr(sink), _stream(stream)))
+    _check(load_library().talon_probe_read(_ptr(buf), buf.nbytes, _ptr(sink), _stream(stream)))
 
 
 def talon_probe_mfma(workgroups: int, iters: int, sink: torch.Tensor, stream=None) -> float:
@@ -314,13 +327,13 @@ def talon_probe_issue(mode: int, waves: int, iters: int, cycles: torch.Tensor, s
 def talon_probe_tile_loads(window: torch.Tensor, loads: int, with_mfma: bool, waves: int, iters: int,
                            cycles: torch.Tensor, sink: torch.Tensor, stream=None):
     """window: at least 16 MiB on the device; cycles: 2048 int64 on the device, [workgroup][wavefront]."""
-    _check(load_library().talon_probe_tile_loads(_ptr(window), window.numel() * window.element_size(), loads,
+    _check(load_library().talon_probe_tile_loads(_ptr(window), window.nbytes, loads,
                                                  1 if with_mfma else 0, waves, iters, _ptr(cycles), _ptr(sink),
                                                  _stream(stream)))
 
 
 def talon_build_tree_mask(st: TreeState, mask: torch.Tensor, stream=None):
-    _check(load_library().talon_build_tree_mask(ctypes.byref(st.c), _ptr(mask), _stream(stream)))
+    _check(load_library().talon_build_tree_mask(_byref(st.c), _ptr(mask), _stream(stream)))
 
 
 def talon_tree_attention_workspace_bytes(B, N_pad, Hq, Hkv, Dh, max_prefix_len) -> int:
@@ -362,13 +375,13 @@ def talon_tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, mask, n_nodes, p
     if _static:
         _check(load_library().talon_tree_attention_static(
             _ptr(q), _ptr(k_prefix), _ptr(v_prefix), _ptr(k_tree), _ptr(v_tree), _ptr(mask), _ptr(n_nodes),
-            _ptr(prefix_len), B, N_pad, Hq, Hkv, Dh, max_prefix_len, sb, st_, sh, c_float(scale), _ptr(out),
+            _ptr(prefix_len), B, N_pad, Hq, Hkv, Dh, max_prefix_len, sb, st_, sh, scale, _ptr(out),
             _ptr(out_lse), _stream(stream)))
         return
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load_library().talon_tree_attention(
         _ptr(q), _ptr(k_prefix), _ptr(v_prefix), _ptr(k_tree), _ptr(v_tree), _ptr(mask), _ptr(n_nodes),
-        _ptr(prefix_len), B, N_pad, Hq, Hkv, Dh, max_prefix_len, sb, st_, sh, c_float(scale), _ptr(out),
+        _ptr(prefix_len), B, N_pad, Hq, Hkv, Dh, max_prefix_len, sb, st_, sh, scale, _ptr(out),
         _ptr(out_lse), _ptr(workspace), ws_bytes, _stream(stream)))
 
 
@@ -383,8 +396,8 @@ def talon_expand_literal(logits, st: TreeState, layers, mu, K_init, init_layers,
                          row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
     dt, row_stride, seq_stride, V = _logits_meta(logits)
     _check(load_library().talon_expand_literal(
-        _ptr(logits), dt, row_stride, seq_stride, row_mode, layers, ctypes.byref(st.c), V if vocab is None else vocab,
-        c_float(mu), K_init, init_layers, max_depth, _ptr(workspace), workspace.numel() * workspace.element_size(),
+        _ptr(logits), dt, row_stride, seq_stride, row_mode, layers, _byref(st.c), V if vocab is None else vocab,
+        mu, K_init, init_layers, max_depth, _ptr(workspace), workspace.nbytes,
         _stream(stream)))
 
 
@@ -399,13 +412,13 @@ def talon_target_argmax(logits, st: TreeState, target_token, target_prob, scan_s
                         stream=None):
     dt, row_stride, seq_stride, V = _logits_meta(logits)
     _check(load_library().talon_target_argmax(
-        _ptr(logits), dt, row_stride, seq_stride, ctypes.byref(st.c), V if vocab is None else vocab,
+        _ptr(logits), dt, row_stride, seq_stride, _byref(st.c), V if vocab is None else vocab,
         _ptr(target_token), _ptr(target_prob), _ptr(scan_status), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(stream)))
+        workspace.nbytes, _stream(stream)))
 
 
 def talon_greedy_accept(st: TreeState, target_token, scan_status, path, accept_len, bonus_token, stream=None):
-    _check(load_library().talon_greedy_accept(ctypes.byref(st.c), _ptr(target_token), _ptr(scan_status), _ptr(path),
+    _check(load_library().talon_greedy_accept(_byref(st.c), _ptr(target_token), _ptr(scan_status), _ptr(path),
                                               _ptr(accept_len), _ptr(bonus_token), _stream(stream)))
 
 
@@ -422,4 +435,4 @@ def talon_compact_kv(k_tree, v_tree, path, accept_len, prefix_len, new_prefix_le
 
 
 def talon_prune_tree(st: TreeState, n_keep: int, kept_ids, stream=None):
-    _check(load_library().talon_prune_tree(ctypes.byref(st.c), n_keep, _ptr(kept_ids), _stream(stream)))
+    _check(load_library().talon_prune_tree(_byref(st.c), n_keep, _ptr(kept_ids), _stream(stream)))
