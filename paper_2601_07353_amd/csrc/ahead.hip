@@ -64,11 +64,12 @@ struct SelectorLds {
 };
 constexpr size_t kAheadLds = sizeof(ScannerLds) > sizeof(SelectorLds) ? sizeof(ScannerLds) : sizeof(SelectorLds);
 
-// Words that scanners look at, in the descriptor array of the other launch forms (zero between
-// launches): the item counter, and the sequences' stop words, each on a memory line of its own.
-__device__ __forceinline__ uint32_t* item_counter(const ExpandArgs& a) { return a.exit_ticket + kStartedWord; }
+// Words that scanners look at: the item counter, and the sequences' stop words, each on a memory
+// line of its own (in the descriptors of layers >= 1 of the other launch forms, zero between
+// launches; those of layer 0 are not).
+__device__ __forceinline__ uint32_t* item_counter(const ExpandArgs& a) { return a.exit_ticket + kItemWord; }
 __device__ __forceinline__ int32_t* stop_word(const ExpandArgs& a, int b) {
-  return reinterpret_cast<int32_t*>(a.desc + static_cast<size_t>(b) * a.N_pad);
+  return reinterpret_cast<int32_t*>(a.desc + a.B + static_cast<size_t>(b) * (a.N_pad - 1));
 }
 
 // ---- scanner: workgroup `wg` of `n_wg`.  Its first item is its own number; the next ones come from

@@ -112,6 +112,15 @@ __device__ __forceinline__ bool write_row(const ExpandArgs& a, int b, int out_ro
 // or one launch that walks all layers.
 constexpr int kModeSplit = 0, kModeFused = 1, kModeTree = 2;
 
+// Launches of one layer: workgroups that have read the frontier, counted in kStartedWords words on
+// memory lines of their own (in the descriptors of layers >= 1, which these launches do not use and
+// every launch leaves zero).  An atomic on one word takes about 20 ns: 900 workgroups on a single
+// counter kept a selection waiting for 18 us, longer than the layer's scan.
+constexpr int kStartedWords = 8;
+__device__ __forceinline__ uint32_t* started_word(const ExpandArgs& a, int x) {
+  return reinterpret_cast<uint32_t*>(a.desc + a.B + static_cast<size_t>(x) * (a.B * (a.N_pad - 1) / kStartedWords));
+}
+
 // One layer: returns the number of frontier rows it found (0: every sequence is finished).
 template <int EPL, int MODE>
 __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch_idx) {
@@ -150,6 +159,7 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
+  const int wave = tid >> 6;
 
   // ---- frontier sizes of all sequences -> item map (identical in every workgroup)
   __shared__ int s_gave_up;
@@ -208,7 +218,7 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
   if constexpr (FUSED && !TREE) {
     // this workgroup has read the frontier (the loads fed the prefix sums that thread 0 has
     // waited for at the barrier above)
-    if (tid == 0) __hip_atomic_fetch_add(a.exit_ticket + kStartedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) __hip_atomic_fetch_add(started_word(a, blockIdx.x % kStartedWords), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   const int k = a.k;
 
@@ -352,10 +362,11 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
             // started yet start as others leave; only the at most B selecting workgroups wait,
             // so the others always get their turn).  The wait is bounded like the single
             // launch's: a workgroup that gives up marks the sequence aborted and selects nothing.
-            if (tid == 0) {
+            if (wave == 0) {
               const unsigned long long t0 = wall_clock64();
-              while (load_agent(a.exit_ticket + kStartedWord) != gridDim.x) {
-                if (wall_clock64() - t0 > a.spin_ticks) { s_last = 3; break; }
+              while (wave_sum_i32(lane < kStartedWords ? static_cast<int>(load_agent(started_word(a, lane))) : 0) !=
+                     static_cast<int>(gridDim.x)) {
+                if (wall_clock64() - t0 > a.spin_ticks) { if (lane == 0) s_last = 3; break; }
                 __builtin_amdgcn_s_sleep(2);
               }
             }
@@ -401,7 +412,7 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
               for (int q = 0; q < a.B; ++q) active += (s_prefix[q + 1] > s_prefix[q]) ? 1 : 0;
               const uint32_t done_before = __hip_atomic_fetch_add(a.exit_ticket + kSelectedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               if (static_cast<int>(done_before) + 1 == active) {
-                store_agent(a.exit_ticket + kStartedWord, 0u);
+                for (int x = 0; x < kStartedWords; ++x) store_agent(started_word(a, x), 0u);
                 store_agent(a.exit_ticket + kSelectedWord, 0u);
               }
             }

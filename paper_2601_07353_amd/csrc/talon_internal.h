@@ -39,9 +39,10 @@ struct SelectArgs {
 // Measured over 8 to 255 groups on grids of 300 to 700 workgroups: 128 is the fastest; fewer
 // groups lengthen the first level, more lengthen the second.
 constexpr int kExitGroups = 128;
-// Words of the exit-ticket array: the groups' count, one count per group, and two counters of the
-// launches of one layer (workgroups that have read the frontier; selections that have finished).
-constexpr int kStartedWord = kExitGroups + 1;
+// Words of the exit-ticket array: the groups' count, one count per group, the item counter of the
+// launch that scans ahead, and a counter of selections (one layer per launch) or sequences (scan
+// ahead) that have finished.
+constexpr int kItemWord = kExitGroups + 1;
 constexpr int kSelectedWord = kExitGroups + 2;
 constexpr int kExitWords = kExitGroups + 3;
 // One more word behind them, which no launch clears: the cap_hit flag of a speculative run.
@@ -76,7 +77,7 @@ struct ExpandArgs {
   // tree state, or known when the launch starts the trees itself) and its selections write
   // desc[i+1], so a workgroup that is late still sees the frontier of its own layer.  A launch
   // of one layer reads the public tree state instead and holds its selections back until every
-  // workgroup has done so (kStartedWord).
+  // workgroup has done so.
   SelectArgs sel;
   int launch_idx;
   int32_t* seq_ticket;   // [B]
@@ -91,7 +92,7 @@ struct ExpandArgs {
   // root row of every sequence, and the workgroup that writes that row initialises the
   // sequence's state first.
   int layers;
-  uint32_t* exit_ticket; // [kExitWords] workgroups that have left, counted per group, then the groups; see kStartedWord
+  uint32_t* exit_ticket; // [kExitWords] workgroups that have left, counted per group, then the groups; see kItemWord
   unsigned long long spin_ticks;
   uint64_t* tree_mask;   // optional: ancestor masks written at the end of the single launch
   const int32_t* root_token;   // optional [B]

@@ -95,6 +95,35 @@ def test_a_bad_row_stops_its_sequence_only():
         np.testing.assert_array_equal(a[key], b[key], err_msg=key)
 
 
+@pytest.mark.parametrize("B", [1, 66])
+def test_forms_take_turns_on_a_workspace_in_mid_tree(B):
+    """A tree continued from its second layer leaves descriptors whose first word is not zero; the other
+    forms must not read them."""
+    import torch
+    import paper_2601_07353_amd as T
+    N, k, Dmax = 40, 6, 8
+    logits = rows_of(B, N, 3000, "f32", seed=3)
+    want = build(logits, N, k, Dmax, False)
+    st = T.TreeState(B, N)
+    cand = T.Candidates(B, st.N_pad, k)
+    ws = T.make_expand_workspace(B, st.N_pad, 3000, k, T.TALON_DTYPE_F32)
+    roots = torch.arange(B, dtype=torch.int32).cuda()
+
+    def check():
+        torch.cuda.synchronize()
+        for key in ("token", "parent", "n_nodes", "status"):
+            np.testing.assert_array_equal(getattr(st, key).cpu().numpy(), want[key], err_msg=key)
+
+    for _ in range(2):
+        T.talon_tree_init(st, roots)
+        for d in range(2):
+            T.talon_expand_select_layer(logits, st, k, 0.03, k, 1, Dmax, cand, ws, layer=d)
+        T.talon_expand_tree(logits, st, k, 0.03, k, 1, Dmax, cand, ws)
+        check()
+        T.talon_build_tree(roots, logits, st, k, 0.03, k, 1, Dmax, cand, ws)
+        check()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("order", ["ascending", "descending", "sawtooth", "ascending late"])
 def test_scan_of_rows_in_adversarial_order(dtype, order):
