@@ -209,9 +209,10 @@ int talon_build_tree(const int32_t* root_token, const void* logits, int dtype, i
  * talon_build_tree with rows by node id, for a caller whose rows are all in place: rows
  * 0 .. rows-1 of every sequence may be read, whether or not the tree turns out to need them
  * (row i at b*seq_stride + i*row_stride elements; a row the tree does not expand may hold
- * anything, a NaN included, and has no effect).  With rows >= N-1 the launch scans rows ahead of
- * the tree instead of one layer after the other; with fewer it is talon_build_tree.  Same
- * results, arguments and errors; `workspace` as there.
+ * anything, a NaN included, and has no effect).  With rows >= N-1 the launch may scan rows ahead of
+ * the tree instead of one layer after the other (it does unless that would read far more than a
+ * tree of this budget is likely to expand); with fewer it is talon_build_tree.  Same results,
+ * arguments and errors; `workspace` as there.
  */
 int talon_build_tree_ahead(const int32_t* root_token, const void* logits, int dtype, int64_t row_stride,
                            int64_t seq_stride, int32_t rows, const talon_tree_state* st, int32_t vocab,

@@ -72,6 +72,10 @@ __device__ __forceinline__ int32_t* stop_word(const ExpandArgs& a, int b) {
   return reinterpret_cast<int32_t*>(a.desc + a.B + static_cast<size_t>(b) * (a.N_pad - 1));
 }
 
+__device__ __forceinline__ int ahead_items(const ExpandArgs& a) {
+  return a.B * (a.ahead_head * a.ahead_chunks_head + (a.ahead_rows - a.ahead_head) * a.ahead_chunks);
+}
+
 // ---- scanner: workgroup `wg` of `n_wg`.  Its first item is its own number; the next ones come from
 // a counter, in order: workgroups (and whole compute dies) progress at different speeds, and a
 // row that a slow one holds back may be the one a selector waits for.  (Counters per die were
@@ -88,16 +92,20 @@ __device__ __forceinline__ void scan_rows(const ExpandArgs& a, ScannerLds& s, co
   unsigned long long* s_cand = s_keys + kMergeCap;                              // ... then those that can still be chosen
   static_assert(kScanBytes >= static_cast<int>(sizeof(unsigned long long)) * (kMergeCap + kCandCap + 16), "the scan buffers stage a row merge");
   const int blocks_per_row = a.chunks;
-  const int chunks = a.ahead_chunks;
-  const int bpc = (blocks_per_row + chunks - 1) / chunks;
-  const int per_row = a.B * chunks;                 // items of one row id, all sequences
-  const int n_items = a.ahead_rows * per_row;
+  const int head_items = a.ahead_head * a.B * a.ahead_chunks_head;
+  const int n_items = ahead_items(a);
   int item = wg;
   if (tid == 0) s.stop = 0;
   __syncthreads();
   while (item < n_items) {
-    const int node = item / per_row;
-    const int rest = item - node * per_row;
+    const bool head = item < head_items;
+    const int chunks = head ? a.ahead_chunks_head : a.ahead_chunks;
+    const int bpc = (blocks_per_row + chunks - 1) / chunks;
+    const int per_row = a.B * chunks;                 // items of one row id, all sequences
+    const int in_part = head ? item : item - head_items;
+    const int row_id = in_part / per_row;
+    const int rest = in_part - row_id * per_row;
+    const int node = head ? row_id : a.ahead_head + row_id;
     const int b = rest / chunks;
     const int ch = rest - b * chunks;
     const int out_row = b * a.N_pad + node;
@@ -330,7 +338,7 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, SelectorLds& 
   // ---- the sequence needs no further rows; this workgroup has finished with tickets and counters
   if (tid == 0) {
     store_agent(stop_word(a, b), 1);
-    if (a.ahead_rows * a.B * a.ahead_chunks > static_cast<int>(gridDim.x) - a.B) {   // scanners take items from the counter
+    if (ahead_items(a) > static_cast<int>(gridDim.x) - a.B) {   // scanners take items from the counter
       // the last sequence to finish ends the list of items: nobody looks at the remaining ones
       const uint32_t finished = __hip_atomic_fetch_add(a.exit_ticket + kSelectedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (finished == static_cast<uint32_t>(a.B) - 1u)

@@ -152,8 +152,8 @@ ExpandArgs make_expand_args(const void* logits, int64_t row_stride, int64_t seq_
   a.spin_ticks = 0;
   a.tree_mask = nullptr;
   a.run_if = nullptr;
-  a.ahead_rows = 0;
-  a.ahead_chunks = 1;
+  a.ahead_rows = a.ahead_head = 0;
+  a.ahead_chunks = a.ahead_chunks_head = 1;
   memset(&a.sel, 0, sizeof(a.sel));
   a.part_max = reinterpret_cast<float*>(w + L.off_max);
   a.part_sum = reinterpret_cast<double*>(w + L.off_sum);
@@ -566,10 +566,44 @@ int talon_build_tree_ahead(const int32_t* root_token, const void* logits, int dt
   // that nobody has to queue for need no counter, and every further item of a workgroup costs it
   // about 10 us between two streams (ranking, partial results, tickets): 508 rows of 304 KB take
   // 52 us as 1016 items and 55-57 us as 1524 or 2032; 4080 rows 250 us whole and 280 us in two.
-  const int chunks = tuned_int("TALON_AHEAD_CHUNKS", static_cast<int>(scanners / rows_all < 1 ? 1 : (scanners / rows_all > L.chunks ? L.chunks : scanners / rows_all)));
-  const int bpc = (L.chunks + chunks - 1) / chunks;
-  ea.ahead_chunks = (L.chunks + bpc - 1) / bpc;
-  if (scanners > rows_all * ea.ahead_chunks) scanners = rows_all * ea.ahead_chunks;
+  auto runs = [&](long long want) {   // a number of equal runs of whole blocks
+    const int c = want < 1 ? 1 : (want > L.chunks ? L.chunks : static_cast<int>(want));
+    const int bpc = (L.chunks + c - 1) / c;
+    return (L.chunks + bpc - 1) / bpc;
+  };
+  ea.ahead_chunks = runs(tuned_int("TALON_AHEAD_CHUNKS", static_cast<int>(scanners / rows_all)));
+  ea.ahead_head = 0;
+  ea.ahead_chunks_head = 1;
+  const long long two_layers = 1 + (init_layers > 0 && K_init < k ? K_init : k);   // rows of the root and of layer 1
+  if (ea.ahead_chunks * 10 < L.chunks && ea.ahead_rows <= 5 * (two_layers - 1)) {
+    // A budget of at most five times the first layer's width is usually spent when that layer is
+    // expanded, and reading all rows would take several rounds of the grid: most of the scan would
+    // be in vain.  13 or 16 x 72 rows of 513 KB of which 17 per sequence are expanded: 74 us layer by
+    // layer, 82 and 87 ahead.  (Budgets above that, or rows that fit in one round, are faster ahead:
+    // 4 x 127 rows of 513 KB 78 against 104, 16 x 29 of 304 KB 49 against 65.)
+    return talon_build_tree(root_token, logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, k, mu, K_init,
+                            init_layers, max_depth, cand_token, cand_logit, cand_prob, cand_edge_logp, row_max, row_lse,
+                            mask, workspace, workspace_bytes, stream);
+  }
+  if (ea.ahead_chunks * 10 < L.chunks) {
+    // Runs of more than ten blocks (35 us and more at the full rate): a tree that ends after two or
+    // three layers would wait for whole rows of all sequences to be read before its root's row is
+    // there.  The first rows, as many as fill the grid once, are cut into shorter runs: of five blocks,
+    // or as long as it takes for the rows of the first two layers to fit.
+    const long long one_round = scanners / (st->B * two_layers);
+    const long long shortest = (L.chunks + 4) / 5;
+    ea.ahead_chunks_head = runs(one_round < shortest ? one_round : shortest);
+    const long long fill = scanners / (static_cast<long long>(st->B) * ea.ahead_chunks_head);
+    const long long head = fill > two_layers ? fill : two_layers;
+    ea.ahead_head = head < ea.ahead_rows ? static_cast<int>(head) : ea.ahead_rows;
+    const long long rest = static_cast<long long>(st->B) * (ea.ahead_rows - ea.ahead_head);
+    const int by_size = (L.chunks + 19) / 20;   // at most twenty blocks per run
+    const long long by_grid = rest > 0 ? scanners / rest : 1;
+    ea.ahead_chunks = runs(by_grid > by_size ? by_grid : by_size);
+  }
+  const long long items = static_cast<long long>(st->B) * (static_cast<long long>(ea.ahead_head) * ea.ahead_chunks_head +
+                                                           static_cast<long long>(ea.ahead_rows - ea.ahead_head) * ea.ahead_chunks);
+  if (scanners > items) scanners = items;
   const int grid = static_cast<int>(scanners) + st->B;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (g_profile.enabled && (rc = check_hip(profile_record(s), "profile event"))) return rc;
@@ -894,29 +928,30 @@ int talon_build_tree_mask(const talon_tree_state* st, uint64_t* mask, void* stre
   return check_hip(launch_mask(*st, mask, static_cast<hipStream_t>(stream)), "mask launch");
 }
 
-static int attention_layout(int32_t B, int32_t N_pad, int32_t Hq, int32_t Hkv, int32_t Dh, int32_t max_prefix_len,
-                            int* splits, int* tps, int* rows_pad, size_t* off_m, size_t* off_l, size_t* total) {
+static int check_attention_shape(int32_t B, int32_t N_pad, int32_t Hq, int32_t Hkv, int32_t Dh, int32_t max_prefix_len) {
   if (B < 1 || B > TALON_B_MAX) { set_error("B=%d outside [1, %d]", B, TALON_B_MAX); return TALON_ERR_INVALID_ARG; }
   if (N_pad < 64 || N_pad > TALON_N_MAX || N_pad % 64) { set_error("N_pad=%d must be a multiple of 64 in [64, %d]", N_pad, TALON_N_MAX); return TALON_ERR_INVALID_ARG; }
   if (Hq < 1 || Hkv < 1 || max_prefix_len < 0) { set_error("Hq, Hkv must be >= 1 and max_prefix_len >= 0"); return TALON_ERR_INVALID_ARG; }
   if (Dh != 64 && Dh != 128) { set_error("Dh=%d not supported (64 or 128)", Dh); return TALON_ERR_UNSUPPORTED; }
   if (Hq % Hkv) { set_error("Hq=%d is not a multiple of Hkv=%d", Hq, Hkv); return TALON_ERR_UNSUPPORTED; }
   if (Hq / Hkv > 16) { set_error("Hq/Hkv=%d above 16 is not supported", Hq / Hkv); return TALON_ERR_UNSUPPORTED; }
-  attention_plan(B, N_pad, Hq, Hkv, Dh, max_prefix_len, splits, tps, rows_pad);
-  const size_t prow = static_cast<size_t>(B) * Hkv * (*splits) * (*rows_pad);
-  *off_m = prow * Dh * sizeof(uint16_t);   // bf16 partial outputs, then fp32 maxima and denominators
-  *off_l = *off_m + prow * sizeof(float);
-  *total = *off_l + prow * sizeof(float);
-  if (*splits == 1) *total = 256;  // nothing is staged, keep a token size
   return TALON_OK;
+}
+
+// Workspace a plan may use beyond what a call must bring: short prefixes gain from more splits than
+// that, as long as the partial results stay small.  A caller whose workspace was sized for another
+// (longer) prefix gets the best plan that fits it.
+constexpr size_t kAttnPlanBytes = static_cast<size_t>(16) << 20;
+size_t attention_plan_limit(size_t least) {
+  return (least > kAttnPlanBytes ? least : kAttnPlanBytes) + TALON_B_MAX * sizeof(int32_t);   // + the table of run counts
 }
 
 size_t talon_tree_attention_workspace_bytes(int32_t B, int32_t N_pad, int32_t Hq, int32_t Hkv, int32_t Dh,
                                             int32_t max_prefix_len) {
-  int splits, tps, rows_pad;
-  size_t off_m, off_l, total;
-  if (attention_layout(B, N_pad, Hq, Hkv, Dh, max_prefix_len, &splits, &tps, &rows_pad, &off_m, &off_l, &total)) return 0;
-  return total;
+  if (check_attention_shape(B, N_pad, Hq, Hkv, Dh, max_prefix_len)) return 0;
+  const size_t least = attention_least_workspace(B, N_pad, Hq, Hkv, Dh, max_prefix_len);
+  const size_t plan = attention_plan(B, N_pad, Hq, Hkv, Dh, max_prefix_len, attention_plan_limit(least)).bytes;
+  return plan > least ? plan : least;
 }
 
 static int tree_attention_call(const void* q, const void* k_prefix, const void* v_prefix, const void* k_tree,
@@ -926,10 +961,10 @@ static int tree_attention_call(const void* q, const void* k_prefix, const void* 
                                float scale, void* out, float* out_lse, void* workspace, size_t workspace_bytes,
                                bool static_scratch, void* stream) {
   AttnArgs a;
-  size_t off_m, off_l, total;
-  int rc = attention_layout(B, N_pad, Hq, Hkv, Dh, max_prefix_len, &a.splits, &a.tiles_per_split, &a.rows_pad, &off_m,
-                            &off_l, &total);
+  int rc = check_attention_shape(B, N_pad, Hq, Hkv, Dh, max_prefix_len);
   if (rc) return rc;
+  const size_t total = attention_least_workspace(B, N_pad, Hq, Hkv, Dh, max_prefix_len);
+  const bool staged = total > 256;   // a workspace has to be there
   const void* ptrs[] = {q, k_tree, v_tree, mask, out};
   for (const void* p : ptrs) {
     if (!p) { set_error("NULL pointer argument"); return TALON_ERR_INVALID_ARG; }
@@ -953,7 +988,7 @@ static int tree_attention_call(const void* q, const void* k_prefix, const void* 
   if (static_scratch) {
     // the split-KV partial results go to the library's own device array: size first (a host
     // check), then the array's address on the current device
-    if (a.splits > 1 && total > kStaticScratchBytes) {
+    if (total > kStaticScratchBytes) {
       set_error("this shape needs %zu bytes of split-KV scratch; the call without a workspace holds at most %zu "
                 "(use talon_tree_attention with a caller-provided workspace)", total, kStaticScratchBytes);
       return TALON_ERR_WORKSPACE;
@@ -961,10 +996,18 @@ static int tree_attention_call(const void* q, const void* k_prefix, const void* 
     if ((rc = static_scratch_address(&workspace))) return rc;
     workspace_bytes = kStaticScratchBytes;
   }
-  if (a.splits > 1) {
+  if (staged) {
     if (!workspace || !aligned16(workspace)) { set_error("workspace is NULL or not 16-byte aligned"); return TALON_ERR_INVALID_ARG; }
     if (workspace_bytes < total) { set_error("workspace of %zu bytes is smaller than the %zu needed", workspace_bytes, total); return TALON_ERR_WORKSPACE; }
   }
+  const size_t most = attention_plan_limit(total);
+  const size_t usable = workspace && aligned16(workspace) ? workspace_bytes : 0;   // (optional where nothing has to be staged)
+  const AttnPlan plan = attention_plan(B, N_pad, Hq, Hkv, Dh, max_prefix_len, usable < most ? usable : most);
+  a.run_bound = plan.run_bound; a.split_max = plan.split_max; a.split_likely = plan.split_likely; a.balance = plan.balance; a.capacity_per_head = plan.capacity_per_head;
+  a.row_tiles = plan.row_tiles; a.row_tile_log2 = plan.waves == 8 ? 8 : 7;
+  const size_t prow = (static_cast<size_t>(B) * Hkv * plan.split_max * plan.row_tiles) << a.row_tile_log2;
+  const size_t off_m = prow * Dh * sizeof(uint16_t);   // bf16 partial outputs, then fp32 maxima and denominators
+  const size_t off_l = off_m + prow * sizeof(float);
   a.q = static_cast<const uint16_t*>(q);
   a.k_prefix = static_cast<const uint16_t*>(k_prefix);
   a.v_prefix = static_cast<const uint16_t*>(v_prefix);
@@ -981,7 +1024,8 @@ static int tree_attention_call(const void* q, const void* k_prefix, const void* 
   a.part_o = reinterpret_cast<uint16_t*>(w);
   a.part_m = reinterpret_cast<float*>(w + off_m);
   a.part_l = reinterpret_cast<float*>(w + off_l);
-  return check_hip(launch_attention(a, static_cast<hipStream_t>(stream)), "tree attention launch");
+  a.part_count = reinterpret_cast<int32_t*>(w + plan.partial);
+  return check_hip(launch_attention(a, plan.waves, static_cast<hipStream_t>(stream)), "tree attention launch");
 }
 
 int talon_tree_attention(const void* q, const void* k_prefix, const void* v_prefix, const void* k_tree,

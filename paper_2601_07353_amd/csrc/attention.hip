@@ -19,17 +19,12 @@
 // The ancestor mask is applied in-tile and only to the tree tiles (the last N_pad/64 tiles
 // of a sequence); prefix tiles need no mask except the ragged last one.
 //
-// Split-KV partial results (unnormalised O, running max, denominator) go to a workspace
-// and are merged by a second kernel; with a single split the output is written directly.
-#include <stdlib.h>
-
+// Split-KV partial results (O normalised by its own denominator, running max, denominator) go to a
+// workspace and are merged by a second kernel; a sequence of one split has its output written directly.
 #include <type_traits>
 
 #include "device_utils.h"
 #include "talon_internal.h"
-#ifdef TALON_TUNING
-#include "tuning.h"
-#endif
 
 namespace talon {
 
@@ -41,6 +36,9 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 
 constexpr int kKeyTile = 64;
+// Fewest key tiles of a run (of a prefix that has more than that): the fewer keys a run has, the
+// larger its normalised outputs are against the row's result, and their rounding to bf16 with them.
+constexpr int kLeastRun = 4;
 #ifndef TALON_AHEAD_PV
 #define TALON_AHEAD_PV 2
 #endif
@@ -87,7 +85,8 @@ struct Smem {
   __device__ static int vswz(int row) { return DH == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
 };
 
-template <int DH, int NW>
+// BALANCE: the run length is worked out from the sequences' lengths.
+template <int DH, int NW, bool BALANCE>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kernel(AttnArgs a) {
   constexpr int RB = 1;             // 32-row blocks per wavefront
   constexpr int kWgThreads = 64 * NW;
@@ -103,31 +102,122 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
   const int l32 = lane & 31;
   const int h = lane >> 5;
 
-  // Workgroup -> work item.  The hardware deals consecutive workgroup ids round-robin to the
-  // 8 XCDs, each with its own L2.  The row tiles of one (sequence, KV head, split) read the
-  // same K/V tiles, so they are given ids that are congruent modulo 8 and adjacent in time:
-  // they share one L2 and the tile is fetched from HBM once, not once per row tile.
-  const int per_xcd = (a.total_items + 7) / 8;
-  const int item = static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
-  if (item >= a.total_items) return;
-  const int rt = item % a.row_tiles;
-  const int split = (item / a.row_tiles) % a.splits;
-  const int bg = item / (a.row_tiles * a.splits);
-  const int b = bg / a.Hkv;
-  const int g = bg - b * a.Hkv;
+  // Workgroup -> work item.  A (sequence, KV head, row tile) is cut into runs of `run` key tiles.
+  // Items in the order sequence, KV head, run, row tile.  The hardware deals consecutive workgroup
+  // ids round-robin to the 8 XCDs, each with its own L2.  The row tiles of one (sequence, KV head,
+  // run) read the same K/V tiles, so they are given ids that are congruent modulo 8 and adjacent in
+  // time: they share one L2 and the tile is fetched from HBM once, not once per row tile.
+  constexpr int kRowTile = 32 * NW * RB;
+  const int id_in_xcd = static_cast<int>(blockIdx.x / 8);
+  int run = a.run_bound, row_tiles = a.row_tiles, splits = a.split_likely;
+  int b, local, n, L;   // the sequence, the item within it, its nodes, its prefix
+  {
+    const int per_seq = row_tiles * splits * a.Hkv;
+    const int item = static_cast<int>(blockIdx.x % 8) * ((per_seq * a.B + 7) / 8) + id_in_xcd;
+    b = item / per_seq;
+    local = item - b * per_seq;
+    if (id_in_xcd >= (per_seq * a.B + 7) / 8) b = a.B;   // an id beyond the items of full-length sequences
+  }
+  bool placed = false;
+  if constexpr (BALANCE) {
+    // Sequences shorter than the launch allows for: the run length is the smallest for which the
+    // batch needs at most capacity_per_head workgroups per KV head (and no row tile more than
+    // split_max runs), so that unequal prefixes fill the chip as evenly as equal ones.  Every
+    // workgroup works it out from the lengths, lane l for sequences l, l + 64, ...; run_bound, the
+    // answer for full-length prefixes, always fits.
+    int nodes_l[TALON_B_MAX / 64], prefix_l[TALON_B_MAX / 64], tiles_l[TALON_B_MAX / 64], rowt_l[TALON_B_MAX / 64];
+    int most_tiles = 0, sum_tiles = 0;
+    bool shorter = false;
+#pragma unroll
+    for (int c = 0; c < TALON_B_MAX / 64; ++c) {
+      tiles_l[c] = rowt_l[c] = nodes_l[c] = prefix_l[c] = 0;
+      if (c * 64 < a.B) {   // uniform
+        const int bb = c * 64 + lane;
+        if (bb < a.B) {
+          int nn = a.n_nodes[bb], ll = a.prefix_len[bb];
+          nn = nn < a.N_pad ? nn : a.N_pad;
+          ll = ll < 0 ? 0 : (ll > a.max_prefix_len ? a.max_prefix_len : ll);
+          nodes_l[c] = nn;
+          prefix_l[c] = ll;
+          rowt_l[c] = nn > 0 ? (nn * a.G + kRowTile - 1) / kRowTile : 0;
+          tiles_l[c] = (ll + kKeyTile - 1) / kKeyTile + (nn + kKeyTile - 1) / kKeyTile;
+          if (rowt_l[c] > 0) most_tiles = most_tiles > tiles_l[c] ? most_tiles : tiles_l[c];
+          sum_tiles += rowt_l[c] * tiles_l[c];
+          shorter = shorter || rowt_l[c] != row_tiles || ll != a.max_prefix_len || nn <= a.N_pad - kKeyTile;
+        }
+      }
+    }
+    if (__ballot(shorter) != 0ull) {
+      placed = true;
+      // (wave-uniform by construction; readfirstlane tells the compiler)
+      most_tiles = __builtin_amdgcn_readfirstlane(wave_max_i32(most_tiles));
+      sum_tiles = __builtin_amdgcn_readfirstlane(wave_sum_i32(sum_tiles));
+      int lo = (most_tiles + a.split_max - 1) / a.split_max;
+      const int even = (sum_tiles + a.capacity_per_head - 1) / a.capacity_per_head;
+      lo = lo > even ? lo : even;
+      lo = lo < kLeastRun ? kLeastRun : lo;   // (run_bound may be below that: then it stands)
+      while (lo < run) {
+        const int mid = (lo + run) >> 1;
+        int need = 0;
+#pragma unroll
+        for (int c = 0; c < TALON_B_MAX / 64; ++c)
+          if (c * 64 < a.B) need += rowt_l[c] * ((tiles_l[c] + mid - 1) / mid);
+        if (__builtin_amdgcn_readfirstlane(wave_sum_i32(need)) <= a.capacity_per_head) run = mid; else lo = mid + 1;
+      }
+      int first_l[TALON_B_MAX / 64], count_l[TALON_B_MAX / 64], total = 0;
+#pragma unroll
+      for (int c = 0; c < TALON_B_MAX / 64; ++c) {
+        first_l[c] = count_l[c] = 0;
+        if (c * 64 < a.B) {
+          count_l[c] = rowt_l[c] * ((tiles_l[c] + run - 1) / run) * a.Hkv;
+          const int incl = wave_inclusive_scan_i32(count_l[c]);
+          first_l[c] = total + incl - count_l[c];
+          total += __builtin_amdgcn_readlane(incl, 63);
+        }
+      }
+      const int per_xcd = (total + 7) / 8;
+      const int item = static_cast<int>(blockIdx.x % 8) * per_xcd + id_in_xcd;
+      if (id_in_xcd >= per_xcd || item >= total) return;
+#pragma unroll
+      for (int c = 0; c < TALON_B_MAX / 64; ++c) {
+        if (c * 64 < a.B) {
+          const unsigned long long in = __ballot(item >= first_l[c] && item < first_l[c] + count_l[c]);
+          if (in != 0ull) {
+            const int l = __ffsll(static_cast<long long>(in)) - 1;
+            b = c * 64 + l;
+            local = item - __builtin_amdgcn_readlane(first_l[c], l);
+            row_tiles = __builtin_amdgcn_readlane(rowt_l[c], l);
+            splits = (__builtin_amdgcn_readlane(tiles_l[c], l) + run - 1) / run;
+            n = __builtin_amdgcn_readlane(nodes_l[c], l);
+            L = __builtin_amdgcn_readlane(prefix_l[c], l);
+          }
+        }
+      }
+    }
+  }
+  if (!placed) {
+    if (b >= a.B) return;
+    n = a.n_nodes[b];
+    L = a.prefix_len[b];
+    n = n < a.N_pad ? n : a.N_pad;
+    L = L < 0 ? 0 : (L > a.max_prefix_len ? a.max_prefix_len : L);
+  }
   const int G = a.G;
-  const int n = a.n_nodes[b];
-  int L = a.prefix_len[b];
-  L = L < 0 ? 0 : (L > a.max_prefix_len ? a.max_prefix_len : L);
   const int rows = n * G;
-  const int row0 = rt * (32 * NW * RB);
-  if (row0 >= rows) return;
-
   const int nPT = (L + kKeyTile - 1) / kKeyTile;
   const int nTT = (n + kKeyTile - 1) / kKeyTile;
   const int T = nPT + nTT;
-  const int t_begin = split * a.tiles_per_split;
-  const int t_end = (t_begin + a.tiles_per_split < T) ? t_begin + a.tiles_per_split : T;
+  const int rt = local % row_tiles;
+  const int split = (local / row_tiles) % splits;
+  const int g = local / (row_tiles * splits);
+  const int bg = b * a.Hkv + g;
+  const int row0 = rt * kRowTile;
+  const int t_begin = split * run;
+  const int t_end = (t_begin + run < T) ? t_begin + run : T;
+  // (Without balancing, a run beyond the end of its sequence stores a maximum of -inf, so that the
+  // merge needs no count.)
+  if (row0 >= rows) return;
+  if (BALANCE && local == 0 && tid == 0) a.part_count[b] = splits;
   const int words = a.N_pad / 64;
 
   // ---- this lane's queries (one per row block): which node and head each is
@@ -502,7 +592,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
     if (rho_e >= rows) continue;
     const int node_e = rho_e / G;
     const size_t orow_e = (static_cast<size_t>(b) * a.N_pad + node_e) * a.Hq + g * G + (rho_e - node_e * G);
-    if (a.splits == 1) {
+    if ((BALANCE ? splits : a.split_likely) == 1) {
       const float inv = 1.f / l_tot;
       uint16_t* op = a.out + orow_e * DH;
 #pragma unroll
@@ -517,15 +607,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
       }
       if (a.out_lse && h == 0) a.out_lse[orow_e] = (m_run[rb] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f;
     } else {
-      // Partial O^T of a (KV head, split), normalised by the split's own denominator and rounded
-      // to bf16 (half the bytes of the round trip through memory; the rounding, 2^-9 relative
-      // per split, is below that of the final bf16 output), laid out in slabs of 8 head-dim
-      // values: [DH / 8][rows_pad][8], so that the 64 lanes of a store (32 rows x 2 halves of a
-      // slab entry) cover 512 consecutive bytes; row-major would give 8-byte pieces.
-      const int rho = rho_e;
-      const size_t pblock = (static_cast<size_t>(bg) * a.splits + split) * a.rows_pad;
-      const size_t prow = pblock + rho;
-      uint16_t* po = a.part_o + pblock * DH + static_cast<size_t>(rho) * 8 + 4 * h;
+      // Partial O^T of a run, normalised by the run's own denominator and rounded to bf16 (half the
+      // bytes of the round trip through memory; the rounding, 2^-9 relative per run, is below that
+      // of the final bf16 output), laid out in slabs of 8 head-dim values: [DH / 8][row tile][8], so
+      // that the 64 lanes of a store (32 rows x 2 halves of a slab entry) cover 512 consecutive
+      // bytes; row-major would give 8-byte pieces.
+      const size_t pblock = ((static_cast<size_t>(bg) * a.row_tiles + rt) * a.split_max + split) * kRowTile;
+      const size_t prow = pblock + (rho_e - row0);
+      uint16_t* po = a.part_o + pblock * DH + static_cast<size_t>(rho_e - row0) * 8 + 4 * h;
       const float inv_l = l_tot > 0.f ? 1.f / l_tot : 0.f;
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
@@ -534,7 +623,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
           bf16x4 v;
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = static_cast<__bf16>(o[db][rb][4 * q4 + e] * inv_l);
-          *reinterpret_cast<bf16x4*>(po + static_cast<size_t>(4 * db + q4) * a.rows_pad * 8) = v;
+          *reinterpret_cast<bf16x4*>(po + static_cast<size_t>(4 * db + q4) * kRowTile * 8) = v;
         }
       }
       if (h == 0) {
@@ -551,7 +640,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
 // reads the partial results in their slab order (thread = (slab, row, half): consecutive
 // threads, consecutive addresses) and turns its results through LDS to write whole output
 // rows.
-template <int DH>
+// BALANCE: the sequences' numbers of runs are in a table.
+template <int DH, bool BALANCE>
 __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnArgs a) {
   constexpr int QPR = DH / 4;            // threads per row
   constexpr int RPW = kThreads / QPR;    // rows per workgroup
@@ -566,18 +656,26 @@ __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnAr
   const int slab = t / (2 * RPW);        // 8 head-dim values: c = 2 * slab + h
   const int c = 2 * slab + h;
   const int rho = blockIdx.x * RPW + r;
-  // Every split of a row tile that has rows stores a partial result (one without key tiles stores
-  // a maximum of -inf), and the partial arrays have room for every row the grid covers, so no
-  // address here depends on the sequence's lengths: all loads of up to eight splits are issued
-  // together with the load of the node count, one memory round trip, and the running maximum is
-  // carried across blocks of eight.  Rows past the end read what nobody wrote and are dropped.
-  const size_t block0 = static_cast<size_t>(bg) * a.splits * a.rows_pad;
-  const size_t base = block0 + rho;
-  const size_t in_block = (static_cast<size_t>(slab) * a.rows_pad + rho) * 8 + 4 * h;
+  // Every run of a row tile that has rows stores a partial result, at a place that depends on no
+  // length, and a row tile has room for a.split_max of them.  The loads of the a.split_likely runs
+  // that full-length prefixes have, up to eight of them, are issued together with the loads of the
+  // node count and the number of runs, one memory round trip, and the running maximum is carried
+  // across blocks of eight.  What nobody wrote is dropped.
+  const int row_tile = 1 << a.row_tile_log2;
+  const int rt = (blockIdx.x * RPW) >> a.row_tile_log2;      // the workgroup's rows lie in one row tile
+  const int r_in = rho - rt * row_tile;
+  int splits = a.split_likely;
+  if constexpr (BALANCE) {
+    const int counted = a.part_count[b];               // (nobody writes it for a sequence without nodes)
+    splits = counted < a.split_max ? counted : a.split_max;
+  }
+  const size_t block0 = (static_cast<size_t>(bg) * a.row_tiles + rt) * a.split_max * row_tile;
+  const size_t base = block0 + r_in;
+  const size_t in_block = (static_cast<size_t>(slab) * row_tile + r_in) * 8 + 4 * h;
   float M = kNegInfF;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   float den = 0.f;
-  for (int s0 = 0; s0 < a.splits; s0 += 8) {
+  for (int s0 = 0; s0 < (BALANCE && s0 == 0 ? 1 : splits); s0 += 8) {
     float ms[8], ls[8];
     bf16x4 vs[8];
 #pragma unroll
@@ -586,13 +684,16 @@ __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnAr
       ms[u] = kNegInfF;
       ls[u] = 0.f;
       vs[u] = bf16x4{0, 0, 0, 0};
-      if (s < a.splits) {   // uniform
-        const size_t pr = base + static_cast<size_t>(s) * a.rows_pad;
+      if (s < a.split_likely || (BALANCE && s < splits)) {   // uniform; the first ones do not wait for the count
+        const size_t pr = base + static_cast<size_t>(s) * row_tile;
         ms[u] = a.part_m[pr];
         ls[u] = a.part_l[pr];
-        vs[u] = *reinterpret_cast<const bf16x4*>(a.part_o + (block0 + static_cast<size_t>(s) * a.rows_pad) * DH + in_block);
+        vs[u] = *reinterpret_cast<const bf16x4*>(a.part_o + (block0 + static_cast<size_t>(s) * row_tile) * DH + in_block);
       }
     }
+#pragma unroll
+    for (int u = 0; BALANCE && u < 8; ++u)
+      if (s0 + u >= splits) { ms[u] = kNegInfF; ls[u] = 0.f; vs[u] = bf16x4{0, 0, 0, 0}; }
     float Mb = M;
 #pragma unroll
     for (int u = 0; u < 8; ++u) Mb = fmaxf(Mb, ms[u]);
@@ -609,7 +710,7 @@ __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnAr
       acc.z += w * static_cast<float>(vs[u][2]); acc.w += w * static_cast<float>(vs[u][3]);
     }
   }
-  if (blockIdx.x * RPW >= rows) return;  // the whole workgroup is past the end
+  if (blockIdx.x * RPW >= rows || (BALANCE && splits == 1)) return;  // past the end, or written by the main kernel
   const bool valid = rho < rows;
   const float inv = 1.f / den;
   bf16x4 v;
@@ -634,24 +735,21 @@ __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnAr
   }
 }
 
-template <int DH, int NW>
-hipError_t launch_one(const AttnArgs& a_in, hipStream_t s) {
-  AttnArgs a = a_in;
-  a.row_tiles = (a.N_pad * a.G + 32 * NW - 1) / (32 * NW);
-  a.total_items = a.row_tiles * a.splits * a.B * a.Hkv;
-  auto kern = tree_attention_kernel<DH, NW>;
+template <int DH, int NW, bool BALANCE>
+hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
+  auto kern = tree_attention_kernel<DH, NW, BALANCE>;
   // (initialisation of a function-local static is thread-safe: two host threads making their
   // first call together set the attribute once)
   static const hipError_t attr_result = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Smem<DH>::BYTES);
   if (attr_result != hipSuccess) return attr_result;
-  hipLaunchKernelGGL(kern, dim3(8 * ((a.total_items + 7) / 8)), dim3(64 * NW), Smem<DH>::BYTES, s, a);
+  hipLaunchKernelGGL(kern, dim3(8 * ((a.capacity_per_head * a.Hkv + 7) / 8)), dim3(64 * NW), Smem<DH>::BYTES, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (a.splits > 1) {
+  if (a.split_max > 1) {
     const int threads = a.N_pad * a.G * (DH / 4);
-    hipLaunchKernelGGL(tree_attention_combine_kernel<DH>, dim3((threads + kThreads - 1) / kThreads, a.B * a.Hkv),
-                       dim3(kThreads), 0, s, a);
+    const dim3 grid((threads + kThreads - 1) / kThreads, a.B * a.Hkv);
+    hipLaunchKernelGGL((tree_attention_combine_kernel<DH, BALANCE>), grid, dim3(kThreads), 0, s, a);
     e = hipGetLastError();
   }
   return e;
@@ -659,49 +757,123 @@ hipError_t launch_one(const AttnArgs& a_in, hipStream_t s) {
 
 }  // namespace
 
-// Launch plan: rows per workgroup and the number of KV splits.  A workgroup is 4 wavefronts
-// (128 packed rows, two workgroups per compute unit) or, when a (sequence, KV head) has at
-// least 512 packed rows, 8 wavefronts (256 rows, one per compute unit): the same 8 wavefronts
-// per compute unit, but a K/V tile is loaded once for 256 rows instead of twice.  Either way
-// the grid aims at filling 256 compute units; but a split must keep enough key tiles to
-// amortise its fixed work (query load, first tile, the partial result it writes and the
-// merge reads back).
-#ifndef TALON_TUNING
-constexpr int tuned_int(const char*, int dflt) { return dflt; }
-#endif
+// ---- Launch plan: rows per workgroup and the number of KV splits.
+// A workgroup is 4 wavefronts (128 packed rows, two workgroups per compute unit) or 8 wavefronts
+// (256 rows, one per compute unit: a K/V tile is loaded once for 256 rows instead of twice).  A split
+// takes a run of key tiles; more splits shorten the runs but add workgroups, which run in rounds of
+// what the chip holds, and partial results, which are written and read back by the merge.
+// The plan is the cheapest of all (width, splits) by this estimate, in microseconds, whose constants
+// were fitted to 220 measured plans of eleven shapes, 1 x 8 to 10 x 8 (sequence, KV head) pairs and
+// 700 to 16000 keys (7 % standard error; it picks the fastest plan of each shape):
+//   a round     a run of key tiles, plus 2.3 (queries, first tile, last stores)
+//   a tile      8 wavefronts: 1.88, or 1.58 while at most half of the chip works; 4: 1.98 while two
+//               workgroups share a compute unit, 1.28 alone; Dh = 64: 1.20, and 0.97 alone
+//   merge       5.6, 0.07 per split beyond six, and the partial results' bytes, twice, at 7.2 TB/s
+// The rule before (as many splits as fill the chip, rounded up, 8 wavefronts from 512 rows on) left
+// 288 workgroups on 256 places: 3 sequences of 200 nodes x 2 heads at 6000 keys 76 us against 52,
+// 6 x 250 x 4 at 9000 keys 186 against 140, 5 x 100 x 3 of 64 at 3001 keys 22 (ragged) against 19.
 
-int attention_waves(int rows) {
-  const int forced = tuned_int("TALON_ATTN_WAVES", 0);   // tuning builds: 4 or 8
-  if (forced == 4 || forced == 8) return forced;
-  return rows >= 512 ? 8 : 4;
+namespace {
+
+int legacy_waves(int rows) { return rows >= 512 ? 8 : 4; }
+
+size_t partial_bytes(long long row_tiles_all, int splits, int row_tile, int Dh) {
+  if (splits == 1) return 256;   // nothing is staged, keep a token size
+  return static_cast<size_t>(row_tiles_all) * splits * row_tile * (Dh * sizeof(uint16_t) + 2 * sizeof(float));
 }
 
-void attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len, int* splits,
-                    int* tiles_per_split, int* rows_pad) {
-  (void)Dh;
-  const int min_tiles = tuned_int("TALON_ATTN_MIN_TILES", 4);   // key tiles a split must keep
-  const int G = Hq / Hkv;
-  const int rows = N_pad * G;
-  const int waves = attention_waves(rows);
-  const int mt = 32 * waves;
-  const int row_tiles = (rows + mt - 1) / mt;
-  const int tiles = (max_prefix_len + kKeyTile - 1) / kKeyTile + N_pad / kKeyTile;
-  const long long base = static_cast<long long>(B) * Hkv * row_tiles;
+int key_tiles(int N_pad, int max_prefix_len) { return (max_prefix_len + kKeyTile - 1) / kKeyTile + N_pad / kKeyTile; }
+
+double plan_us(int waves, long long wgs, int run, int splits, int Dh, size_t bytes) {
   const long long slots = waves == 8 ? 256 : 512;
-  long long want = (slots + base - 1) / base;
-  const long long cap = tiles / min_tiles > 1 ? tiles / min_tiles : 1;
-  if (want > cap) want = cap;
-  if (want < 1) want = 1;
-  const int tps = static_cast<int>((tiles + want - 1) / want);
-  *tiles_per_split = tps;
-  *splits = (tiles + tps - 1) / tps;
-  *rows_pad = row_tiles * mt;
+  const long long full = wgs / slots, rest = wgs % slots;
+  const double shared = Dh == 64 ? 1.20 : (waves == 8 ? 1.88 : 1.98);
+  const double alone = Dh == 64 ? (waves == 8 ? 1.20 : 0.97) : (waves == 8 ? 1.58 : 1.28);
+  const bool crowded = waves == 8 ? full > 0 || rest > 128 : rest > 256;   // the last round's workgroups
+  double us = full * (run * shared + 2.3);
+  if (rest) us += run * (crowded ? shared : alone) + 2.3;
+  if (splits > 1) us += 5.6 + 0.07 * (splits > 6 ? splits - 6 : 0) + 2.0 * static_cast<double>(bytes) / 7.2e6;
+  return us;
 }
 
-hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
-  const bool wide = attention_waves(a.N_pad * a.G) == 8;
-  if (a.Dh == 128) return wide ? launch_one<128, 8>(a, s) : launch_one<128, 4>(a, s);
-  return wide ? launch_one<64, 8>(a, s) : launch_one<64, 4>(a, s);
+}  // namespace
+
+// Bytes of workspace that a call must bring.
+size_t attention_least_workspace(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len) {
+  const int rows = N_pad * (Hq / Hkv);
+  const int mt = 32 * legacy_waves(rows);
+  const int row_tiles = (rows + mt - 1) / mt;
+  const int tiles = key_tiles(N_pad, max_prefix_len);
+  const long long pairs = static_cast<long long>(B) * Hkv * row_tiles;
+  long long want = ((mt == 256 ? 256 : 512) + pairs - 1) / pairs;
+  const long long cap = tiles / 4 > 1 ? tiles / 4 : 1;
+  if (want > cap) want = cap;
+  const int tps = static_cast<int>((tiles + want - 1) / want);
+  return partial_bytes(pairs, (tiles + tps - 1) / tps, mt, Dh);
+}
+
+// The plan of a call that may use `bytes` of workspace (at least attention_least_workspace).
+AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len, size_t bytes) {
+  const int rows = N_pad * (Hq / Hkv);
+  const int tiles = key_tiles(N_pad, max_prefix_len);
+  const size_t table = (static_cast<size_t>(B) * sizeof(int32_t) + 15) & ~static_cast<size_t>(15);   // runs per sequence
+  AttnPlan best = {};
+  int best_splits = 1;
+  double best_us = 0.0;
+  for (int waves = 8; waves >= 4; waves -= 4) {
+    const int mt = 32 * waves;
+    const int row_tiles = (rows + mt - 1) / mt;
+    const long long all = static_cast<long long>(B) * Hkv * row_tiles;
+    const int most = tiles / kLeastRun < 64 ? (tiles / kLeastRun > 1 ? tiles / kLeastRun : 1) : 64;
+    for (int splits = 1; splits <= most; ++splits) {
+      const int run = (tiles + splits - 1) / splits;
+      if ((tiles + run - 1) / run != splits) continue;   // a smaller number of splits has the same run length
+      const size_t need = partial_bytes(all, splits, mt, Dh);
+      if (splits > 1 && need > bytes) break;
+      const double us = plan_us(waves, all * splits, run, splits, Dh, need);
+      if (best.waves == 0 || us < best_us) {
+        best.waves = waves;
+        best.row_tiles = row_tiles;
+        best.run_bound = run;
+        best_splits = splits;
+        best_us = us;
+      }
+    }
+  }
+  // Balancing of unequal sequences: a row tile may take up to twice as many runs, as far as the
+  // workspace goes, and the grid grows to what its rounds hold, short of what would give full-length
+  // sequences one split more.  It costs a workgroup about 0.5 us before its first load, so runs
+  // have to be long enough for it to matter.
+  const int mt = 32 * best.waves;
+  const long long all = static_cast<long long>(B) * Hkv * best.row_tiles;
+  const long long slots = best.waves == 8 ? 256 : 512;
+  best.split_max = best.split_likely = best_splits;
+  long long wgs = all * best_splits;
+  if (B > 1 && best.run_bound >= 2 * kLeastRun) {
+    const long long rounds = (wgs + slots - 1) / slots;
+    for (int m = 2 * best_splits; m > best_splits; --m)
+      if (partial_bytes(all, m, mt, Dh) + table <= bytes) { best.split_max = m; break; }
+    if (best.split_max > best_splits) {
+      best.balance = 1;
+      long long grown = all * (best_splits + 1) - 1;
+      if (grown > rounds * slots) grown = rounds * slots;
+      if (grown > wgs) wgs = grown;
+    }
+  }
+  best.capacity_per_head = static_cast<int>(wgs / Hkv);   // (wgs >= all * splits, a multiple of Hkv)
+  best.partial = partial_bytes(all, best.split_max, mt, Dh);
+  best.bytes = best.balance ? best.partial + table : best.partial;
+  return best;
+}
+
+template <int DH>
+static hipError_t launch_dh(const AttnArgs& a, int waves, hipStream_t s) {
+  if (a.balance) return waves == 8 ? launch_one<DH, 8, true>(a, s) : launch_one<DH, 4, true>(a, s);
+  return waves == 8 ? launch_one<DH, 8, false>(a, s) : launch_one<DH, 4, false>(a, s);
+}
+
+hipError_t launch_attention(const AttnArgs& a, int waves, hipStream_t s) {
+  return a.Dh == 128 ? launch_dh<128>(a, waves, s) : launch_dh<64>(a, waves, s);
 }
 
 }  // namespace talon

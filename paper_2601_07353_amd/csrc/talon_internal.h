@@ -97,9 +97,9 @@ struct ExpandArgs {
   uint64_t* tree_mask;   // optional: ancestor masks written at the end of the single launch
   const int32_t* root_token;   // optional [B]
   const uint32_t* run_if;      // optional: the single launch does nothing unless this word is non-zero
-  // Launch that scans rows ahead of the tree: rows 0 .. ahead_rows - 1 of every sequence, each in
-  // ahead_chunks runs of blocks.
-  int ahead_rows, ahead_chunks;
+  // Launch that scans rows ahead of the tree: rows 0 .. ahead_rows - 1 of every sequence; the first
+  // ahead_head of them in ahead_chunks_head runs of blocks each, the others in ahead_chunks.
+  int ahead_rows, ahead_head, ahead_chunks_head, ahead_chunks;
 };
 
 // Start of a single launch that continues trees: what it does with the five per-sequence words
@@ -164,14 +164,18 @@ struct AttnArgs {
   float scale_log2e;     // scale * log2(e): scores are kept in base-2 units
   uint16_t* out;
   float* out_lse;
-  int splits;            // KV splits per (sequence, kv head, row tile)
-  int tiles_per_split;   // key tiles of kAttnKeyTile per split
-  uint16_t* part_o;      // [B][Hkv][splits][Dh/8][rows_pad][8] bf16: each split's output, normalised by its own denominator
-  float* part_m;         // [B][Hkv][splits][rows_pad]      running max (base-2 units)
-  float* part_l;         // [B][Hkv][splits][rows_pad]      running denominator
-  int rows_pad;          // N_pad * G rounded up to the row tile
+  // Split-KV: a (sequence, KV head, row tile) is cut into runs of key tiles, see attention.hip.
+  int run_bound;         // run length that fits the grid whatever the prefixes are
+  int split_max;         // most runs of one row tile (1: nothing is staged)
+  int split_likely;      // runs of a full-length prefix
+  int capacity_per_head; // most workgroups per KV head
+  int balance;           // the run length is worked out on the device from the sequences' lengths
   int row_tiles;         // row tiles per (sequence, KV head)
-  int total_items;       // row_tiles * splits * B * Hkv work items of the main kernel
+  int row_tile_log2;     // rows of a tile: 128 or 256
+  uint16_t* part_o;      // [B][Hkv][row tile][split_max][Dh/8][rows of a tile][8] bf16: each run's output, normalised by its own denominator
+  float* part_m;         // [B][Hkv][row tile][split_max][rows of a tile]  running max (base-2 units)
+  float* part_l;         // the same: running denominator
+  int32_t* part_count;   // [B] runs per row tile of the sequence (with balance)
 };
 
 // launchers (each checks nothing: arguments were validated by the ABI layer)
@@ -199,10 +203,16 @@ hipError_t launch_expand(const ExpandArgs& a, int dtype, int grid, bool fused, h
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_mask(const talon_tree_state& st, uint64_t* mask, hipStream_t s);
 hipError_t launch_literal_layer(const LiteralArgs& a, int dtype, hipStream_t s);
-hipError_t launch_attention(const AttnArgs& a, hipStream_t s);
+hipError_t launch_attention(const AttnArgs& a, int waves, hipStream_t s);
 
 int expand_chunk_elems(int dtype);
-void attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len, int* splits,
-                    int* tiles_per_split, int* rows_pad);
+struct AttnPlan {
+  int waves;             // wavefronts per workgroup
+  int row_tiles, run_bound, split_max, split_likely, capacity_per_head, balance;   // as in AttnArgs
+  size_t partial;        // bytes of the partial results ...
+  size_t bytes;          // ... and with the table of run counts
+};
+size_t attention_least_workspace(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len);
+AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len, size_t bytes);
 
 }  // namespace talon
