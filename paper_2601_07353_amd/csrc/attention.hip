@@ -762,13 +762,14 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
 // (256 rows, one per compute unit: a K/V tile is loaded once for 256 rows instead of twice).  A split
 // takes a run of key tiles; more splits shorten the runs but add workgroups, which run in rounds of
 // what the chip holds, and partial results, which are written and read back by the merge.
-// The plan is the cheapest of all (width, splits) by this estimate, in microseconds, whose constants
-// were fitted to 220 measured plans of eleven shapes, 1 x 8 to 10 x 8 (sequence, KV head) pairs and
-// 700 to 16000 keys (7 % standard error; it picks the fastest plan of each shape):
+// The plan is the cheapest of all (width, splits) by this estimate, in microseconds.  Its constants
+// are fitted to 330 measured plans of 22 shapes, 1 x 8 to 16 x 16 (sequence, KV head) pairs and 300
+// to 16000 keys (its picks are 0.7 % off the fastest plans on average, 7 % at most):
 //   a round     a run of key tiles, plus 2.3 (queries, first tile, last stores)
-//   a tile      8 wavefronts: 1.88, or 1.58 while at most half of the chip works; 4: 1.98 while two
-//               workgroups share a compute unit, 1.28 alone; Dh = 64: 1.20, and 0.97 alone
-//   merge       5.6, 0.07 per split beyond six, and the partial results' bytes, twice, at 7.2 TB/s
+//   a tile      8 wavefronts: 1.88; 4: 1.98 while two workgroups share a compute unit, 1.70 alone
+//               (1.28 when the keys are in the Infinity Cache, which a model's many layers do not
+//               leave them in); Dh = 64: 1.15, 1.20 and 1.10
+//   merge       3.5, 0.07 per split beyond six, and the partial results' bytes, twice, at 5 TB/s
 // The rule before (as many splits as fill the chip, rounded up, 8 wavefronts from 512 rows on) left
 // 288 workgroups on 256 places: 3 sequences of 200 nodes x 2 heads at 6000 keys 76 us against 52,
 // 6 x 250 x 4 at 9000 keys 186 against 140, 5 x 100 x 3 of 64 at 3001 keys 22 (ragged) against 19.
@@ -787,12 +788,11 @@ int key_tiles(int N_pad, int max_prefix_len) { return (max_prefix_len + kKeyTile
 double plan_us(int waves, long long wgs, int run, int splits, int Dh, size_t bytes) {
   const long long slots = waves == 8 ? 256 : 512;
   const long long full = wgs / slots, rest = wgs % slots;
-  const double shared = Dh == 64 ? 1.20 : (waves == 8 ? 1.88 : 1.98);
-  const double alone = Dh == 64 ? (waves == 8 ? 1.20 : 0.97) : (waves == 8 ? 1.58 : 1.28);
-  const bool crowded = waves == 8 ? full > 0 || rest > 128 : rest > 256;   // the last round's workgroups
+  const double shared = Dh == 64 ? (waves == 8 ? 1.15 : 1.20) : (waves == 8 ? 1.88 : 1.98);
+  const double alone = waves == 8 ? shared : (Dh == 64 ? 1.10 : 1.70);
   double us = full * (run * shared + 2.3);
-  if (rest) us += run * (crowded ? shared : alone) + 2.3;
-  if (splits > 1) us += 5.6 + 0.07 * (splits > 6 ? splits - 6 : 0) + 2.0 * static_cast<double>(bytes) / 7.2e6;
+  if (rest) us += run * (rest > 256 ? shared : alone) + 2.3;   // the last round's workgroups
+  if (splits > 1) us += 3.5 + 0.07 * (splits > 6 ? splits - 6 : 0) + 2.0 * static_cast<double>(bytes) / 5e6;
   return us;
 }
 
