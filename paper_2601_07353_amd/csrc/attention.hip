@@ -39,6 +39,7 @@ constexpr int kKeyTile = 64;
 // Fewest key tiles of a run (of a prefix that has more than that): the fewer keys a run has, the
 // larger its normalised outputs are against the row's result, and their rounding to bf16 with them.
 constexpr int kLeastRun = 4;
+constexpr int kMostSplits = 64;
 #ifndef TALON_AHEAD_PV
 #define TALON_AHEAD_PV 2
 #endif
@@ -798,18 +799,23 @@ double plan_us(int waves, long long wgs, int run, int splits, int Dh, size_t byt
 
 }  // namespace
 
+// Splits that fill the chip, rounded up: where the estimate starts from.
+static int filling_splits(long long pairs, int waves, int tiles) {
+  long long want = ((waves == 8 ? 256 : 512) + pairs - 1) / pairs;
+  const long long cap = tiles / kLeastRun > 1 ? tiles / kLeastRun : 1;
+  if (want > cap) want = cap;
+  const int run = static_cast<int>((tiles + want - 1) / want);
+  return (tiles + run - 1) / run;
+}
+
 // Bytes of workspace that a call must bring.
 size_t attention_least_workspace(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len) {
   const int rows = N_pad * (Hq / Hkv);
-  const int mt = 32 * legacy_waves(rows);
+  const int waves = legacy_waves(rows);
+  const int mt = 32 * waves;
   const int row_tiles = (rows + mt - 1) / mt;
-  const int tiles = key_tiles(N_pad, max_prefix_len);
   const long long pairs = static_cast<long long>(B) * Hkv * row_tiles;
-  long long want = ((mt == 256 ? 256 : 512) + pairs - 1) / pairs;
-  const long long cap = tiles / 4 > 1 ? tiles / 4 : 1;
-  if (want > cap) want = cap;
-  const int tps = static_cast<int>((tiles + want - 1) / want);
-  return partial_bytes(pairs, (tiles + tps - 1) / tps, mt, Dh);
+  return partial_bytes(pairs, filling_splits(pairs, waves, key_tiles(N_pad, max_prefix_len)), mt, Dh);
 }
 
 // The plan of a call that may use `bytes` of workspace (at least attention_least_workspace).
@@ -820,11 +826,28 @@ AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefi
   AttnPlan best = {};
   int best_splits = 1;
   double best_us = 0.0;
+  // Another plan than the one that fills the chip has to promise a tenth less: differences of a few
+  // percent are within the estimate's error (8 -> 4 wavefronts promised 5 % at 3 sequences of 227
+  // nodes x 4 heads and 376 keys and cost 7 %), the plans it is for gain a quarter or more.
+  {
+    const int waves = legacy_waves(rows);
+    const int mt = 32 * waves;
+    const int row_tiles = (rows + mt - 1) / mt;
+    const long long all = static_cast<long long>(B) * Hkv * row_tiles;
+    const int splits = filling_splits(all, waves, tiles);
+    if (splits <= kMostSplits) {
+      best.waves = waves;
+      best.row_tiles = row_tiles;
+      best.run_bound = (tiles + splits - 1) / splits;
+      best_splits = splits;
+      best_us = 0.9 * plan_us(waves, all * splits, best.run_bound, splits, Dh, partial_bytes(all, splits, mt, Dh));
+    }
+  }
   for (int waves = 8; waves >= 4; waves -= 4) {
     const int mt = 32 * waves;
     const int row_tiles = (rows + mt - 1) / mt;
     const long long all = static_cast<long long>(B) * Hkv * row_tiles;
-    const int most = tiles / kLeastRun < 64 ? (tiles / kLeastRun > 1 ? tiles / kLeastRun : 1) : 64;
+    const int most = tiles / kLeastRun < kMostSplits ? (tiles / kLeastRun > 1 ? tiles / kLeastRun : 1) : kMostSplits;
     for (int splits = 1; splits <= most; ++splits) {
       const int run = (tiles + splits - 1) / splits;
       if ((tiles + run - 1) / run != splits) continue;   // a smaller number of splits has the same run length
