@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include "attention_plan.h"
 #include "talon_internal.h"
 #ifdef TALON_TUNING
 #include "tuning.h"
@@ -936,14 +937,6 @@ static int check_attention_shape(int32_t B, int32_t N_pad, int32_t Hq, int32_t H
   if (Hq % Hkv) { set_error("Hq=%d is not a multiple of Hkv=%d", Hq, Hkv); return TALON_ERR_UNSUPPORTED; }
   if (Hq / Hkv > 16) { set_error("Hq/Hkv=%d above 16 is not supported", Hq / Hkv); return TALON_ERR_UNSUPPORTED; }
   return TALON_OK;
-}
-
-// Workspace a plan may use beyond what a call must bring: short prefixes gain from more splits than
-// that, as long as the partial results stay small.  A caller whose workspace was sized for another
-// (longer) prefix gets the best plan that fits it.
-constexpr size_t kAttnPlanBytes = static_cast<size_t>(16) << 20;
-size_t attention_plan_limit(size_t least) {
-  return (least > kAttnPlanBytes ? least : kAttnPlanBytes) + TALON_B_MAX * sizeof(int32_t);   // + the table of run counts
 }
 
 size_t talon_tree_attention_workspace_bytes(int32_t B, int32_t N_pad, int32_t Hq, int32_t Hkv, int32_t Dh,

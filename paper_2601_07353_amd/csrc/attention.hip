@@ -23,6 +23,7 @@
 // workspace and are merged by a second kernel; a sequence of one split has its output written directly.
 #include <type_traits>
 
+#include "attention_plan.h"
 #include "device_utils.h"
 #include "talon_internal.h"
 
@@ -35,11 +36,6 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 
-constexpr int kKeyTile = 64;
-// Fewest key tiles of a run (of a prefix that has more than that): the fewer keys a run has, the
-// larger its normalised outputs are against the row's result, and their rounding to bf16 with them.
-constexpr int kLeastRun = 4;
-constexpr int kMostSplits = 64;
 #ifndef TALON_AHEAD_PV
 #define TALON_AHEAD_PV 2
 #endif
@@ -757,137 +753,6 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
 }
 
 }  // namespace
-
-// ---- Launch plan: rows per workgroup and the number of KV splits.
-// A workgroup is 4 wavefronts (128 packed rows, two workgroups per compute unit) or 8 wavefronts
-// (256 rows, one per compute unit: a K/V tile is loaded once for 256 rows instead of twice).  A split
-// takes a run of key tiles; more splits shorten the runs but add workgroups, which run in rounds of
-// what the chip holds, and partial results, which are written and read back by the merge.
-// The plan is the cheapest of all (width, splits) by this estimate, in microseconds.  Its constants
-// are fitted to 330 measured plans of 22 shapes, 1 x 8 to 16 x 16 (sequence, KV head) pairs and 300
-// to 16000 keys (its picks are 0.7 % off the fastest plans on average, 7 % at most):
-//   a round     a run of key tiles, plus 2.3 (queries, first tile, last stores)
-//   a tile      8 wavefronts: 1.88; 4: 1.98 while two workgroups share a compute unit, 1.70 alone
-//               (1.28 when the keys are in the Infinity Cache, which a model's many layers do not
-//               leave them in); Dh = 64: 1.15, 1.20 and 1.10
-//   merge       3.5, 0.07 per split beyond six, and the partial results' bytes, twice, at 5 TB/s
-// The rule before (as many splits as fill the chip, rounded up, 8 wavefronts from 512 rows on) left
-// 288 workgroups on 256 places: 3 sequences of 200 nodes x 2 heads at 6000 keys 76 us against 52,
-// 6 x 250 x 4 at 9000 keys 186 against 140, 5 x 100 x 3 of 64 at 3001 keys 22 (ragged) against 19.
-
-namespace {
-
-int legacy_waves(int rows) { return rows >= 512 ? 8 : 4; }
-
-size_t partial_bytes(long long row_tiles_all, int splits, int row_tile, int Dh) {
-  if (splits == 1) return 256;   // nothing is staged, keep a token size
-  return static_cast<size_t>(row_tiles_all) * splits * row_tile * (Dh * sizeof(uint16_t) + 2 * sizeof(float));
-}
-
-int key_tiles(int N_pad, int max_prefix_len) { return (max_prefix_len + kKeyTile - 1) / kKeyTile + N_pad / kKeyTile; }
-
-double plan_us(int waves, long long wgs, int run, int splits, int Dh, size_t bytes) {
-  const long long slots = waves == 8 ? 256 : 512;
-  const long long full = wgs / slots, rest = wgs % slots;
-  const double shared = Dh == 64 ? (waves == 8 ? 1.15 : 1.20) : (waves == 8 ? 1.88 : 1.98);
-  const double alone = waves == 8 ? shared : (Dh == 64 ? 1.10 : 1.70);
-  double us = full * (run * shared + 2.3);
-  if (rest) us += run * (rest > 256 ? shared : alone) + 2.3;   // the last round's workgroups
-  if (splits > 1) us += 3.5 + 0.07 * (splits > 6 ? splits - 6 : 0) + 2.0 * static_cast<double>(bytes) / 5e6;
-  return us;
-}
-
-}  // namespace
-
-// Splits that fill the chip, rounded up: where the estimate starts from.
-static int filling_splits(long long pairs, int waves, int tiles) {
-  long long want = ((waves == 8 ? 256 : 512) + pairs - 1) / pairs;
-  const long long cap = tiles / kLeastRun > 1 ? tiles / kLeastRun : 1;
-  if (want > cap) want = cap;
-  const int run = static_cast<int>((tiles + want - 1) / want);
-  return (tiles + run - 1) / run;
-}
-
-// Bytes of workspace that a call must bring.
-size_t attention_least_workspace(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len) {
-  const int rows = N_pad * (Hq / Hkv);
-  const int waves = legacy_waves(rows);
-  const int mt = 32 * waves;
-  const int row_tiles = (rows + mt - 1) / mt;
-  const long long pairs = static_cast<long long>(B) * Hkv * row_tiles;
-  return partial_bytes(pairs, filling_splits(pairs, waves, key_tiles(N_pad, max_prefix_len)), mt, Dh);
-}
-
-// The plan of a call that may use `bytes` of workspace (at least attention_least_workspace).
-AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len, size_t bytes) {
-  const int rows = N_pad * (Hq / Hkv);
-  const int tiles = key_tiles(N_pad, max_prefix_len);
-  const size_t table = (static_cast<size_t>(B) * sizeof(int32_t) + 15) & ~static_cast<size_t>(15);   // runs per sequence
-  AttnPlan best = {};
-  int best_splits = 1;
-  double best_us = 0.0;
-  // Another plan than the one that fills the chip has to promise a tenth less: differences of a few
-  // percent are within the estimate's error (8 -> 4 wavefronts promised 5 % at 3 sequences of 227
-  // nodes x 4 heads and 376 keys and cost 7 %), the plans it is for gain a quarter or more.
-  {
-    const int waves = legacy_waves(rows);
-    const int mt = 32 * waves;
-    const int row_tiles = (rows + mt - 1) / mt;
-    const long long all = static_cast<long long>(B) * Hkv * row_tiles;
-    const int splits = filling_splits(all, waves, tiles);
-    if (splits <= kMostSplits) {
-      best.waves = waves;
-      best.row_tiles = row_tiles;
-      best.run_bound = (tiles + splits - 1) / splits;
-      best_splits = splits;
-      best_us = 0.9 * plan_us(waves, all * splits, best.run_bound, splits, Dh, partial_bytes(all, splits, mt, Dh));
-    }
-  }
-  for (int waves = 8; waves >= 4; waves -= 4) {
-    const int mt = 32 * waves;
-    const int row_tiles = (rows + mt - 1) / mt;
-    const long long all = static_cast<long long>(B) * Hkv * row_tiles;
-    const int most = tiles / kLeastRun < kMostSplits ? (tiles / kLeastRun > 1 ? tiles / kLeastRun : 1) : kMostSplits;
-    for (int splits = 1; splits <= most; ++splits) {
-      const int run = (tiles + splits - 1) / splits;
-      if ((tiles + run - 1) / run != splits) continue;   // a smaller number of splits has the same run length
-      const size_t need = partial_bytes(all, splits, mt, Dh);
-      if (splits > 1 && need > bytes) break;
-      const double us = plan_us(waves, all * splits, run, splits, Dh, need);
-      if (best.waves == 0 || us < best_us) {
-        best.waves = waves;
-        best.row_tiles = row_tiles;
-        best.run_bound = run;
-        best_splits = splits;
-        best_us = us;
-      }
-    }
-  }
-  // Balancing of unequal sequences: a row tile may take up to twice as many runs, as far as the
-  // workspace goes, and the grid grows to what its rounds hold, short of what would give full-length
-  // sequences one split more.  It costs a workgroup about 0.5 us before its first load, so runs
-  // have to be long enough for it to matter.
-  const int mt = 32 * best.waves;
-  const long long all = static_cast<long long>(B) * Hkv * best.row_tiles;
-  const long long slots = best.waves == 8 ? 256 : 512;
-  best.split_max = best.split_likely = best_splits;
-  long long wgs = all * best_splits;
-  if (B > 1 && best.run_bound >= 2 * kLeastRun) {
-    const long long rounds = (wgs + slots - 1) / slots;
-    for (int m = 2 * best_splits; m > best_splits; --m)
-      if (partial_bytes(all, m, mt, Dh) + table <= bytes) { best.split_max = m; break; }
-    if (best.split_max > best_splits) {
-      best.balance = 1;
-      long long grown = all * (best_splits + 1) - 1;
-      if (grown > rounds * slots) grown = rounds * slots;
-      if (grown > wgs) wgs = grown;
-    }
-  }
-  best.capacity_per_head = static_cast<int>(wgs / Hkv);   // (wgs >= all * splits, a multiple of Hkv)
-  best.partial = partial_bytes(all, best.split_max, mt, Dh);
-  best.bytes = best.balance ? best.partial + table : best.partial;
-  return best;
-}
 
 template <int DH>
 static hipError_t launch_dh(const AttnArgs& a, int waves, hipStream_t s) {

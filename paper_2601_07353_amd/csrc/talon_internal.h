@@ -206,13 +206,5 @@ hipError_t launch_literal_layer(const LiteralArgs& a, int dtype, hipStream_t s);
 hipError_t launch_attention(const AttnArgs& a, int waves, hipStream_t s);
 
 int expand_chunk_elems(int dtype);
-struct AttnPlan {
-  int waves;             // wavefronts per workgroup
-  int row_tiles, run_bound, split_max, split_likely, capacity_per_head, balance;   // as in AttnArgs
-  size_t partial;        // bytes of the partial results ...
-  size_t bytes;          // ... and with the table of run counts
-};
-size_t attention_least_workspace(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len);
-AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len, size_t bytes);
 
 }  // namespace talon

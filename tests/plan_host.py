@@ -1,0 +1,54 @@
+"""The launch plans (host headers of the library without HIP) compiled with g++ for tests that run
+without a GPU.  Test infrastructure only."""
+from __future__ import annotations
+
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SHIM = r"""
+#include "attention_plan.h"
+extern "C" {
+size_t t_least(int B, int N_pad, int Hq, int Hkv, int Dh, int L) { return talon::attention_least_workspace(B, N_pad, Hq, Hkv, Dh, L); }
+size_t t_limit(size_t least) { return talon::attention_plan_limit(least); }
+void t_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int L, size_t bytes, long long* out) {
+  const talon::AttnPlan p = talon::attention_plan(B, N_pad, Hq, Hkv, Dh, L, bytes);
+  const long long v[] = {p.waves, p.row_tiles, p.run_bound, p.split_max, p.split_likely, p.capacity_per_head, p.balance,
+                         static_cast<long long>(p.partial), static_cast<long long>(p.bytes)};
+  for (int i = 0; i < 9; ++i) out[i] = v[i];
+}
+}
+"""
+FIELDS = ("waves", "row_tiles", "run_bound", "split_max", "split_likely", "capacity_per_head", "balance", "partial", "bytes")
+
+
+@functools.lru_cache(maxsize=None)
+def _lib():
+    with tempfile.TemporaryDirectory() as d:
+        src, so = os.path.join(d, "plans.cpp"), os.path.join(d, "plans.so")
+        with open(src, "w") as f:
+            f.write(SHIM)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"),
+                        "-I", os.path.join(ROOT, "paper_2601_07353_amd", "csrc"), src, "-o", so], check=True)
+        lib = ctypes.CDLL(so)      # (the mapping outlives the file)
+    lib.t_least.restype = lib.t_limit.restype = ctypes.c_size_t
+    lib.t_limit.argtypes = [ctypes.c_size_t]
+    lib.t_plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_void_p]
+    return lib
+
+
+def least_workspace(B, N_pad, Hq, Hkv, Dh, L):
+    return _lib().t_least(B, N_pad, Hq, Hkv, Dh, L)
+
+
+def attention_plan(B, N_pad, Hq, Hkv, Dh, L, nbytes=None):
+    """The plan of a call; by default with the workspace that the library's query asks for."""
+    if nbytes is None:
+        nbytes = _lib().t_limit(least_workspace(B, N_pad, Hq, Hkv, Dh, L))
+    out = (ctypes.c_longlong * 9)()
+    _lib().t_plan(B, N_pad, Hq, Hkv, Dh, L, nbytes, out)
+    return dict(zip(FIELDS, out))

@@ -1,0 +1,47 @@
+"""Launch plan of tree attention, evaluated on the host (no GPU)."""
+import random
+
+import pytest
+
+from tests import plan_host as P
+
+
+def shapes(count, seed):
+    r = random.Random(seed)
+    for _ in range(count):
+        Hkv = r.choice([1, 2, 3, 4, 8, 16])
+        yield (r.randint(1, 70), 64 * r.randint(1, 4), Hkv * r.choice([1, 2, 3, 4, 8, 16]), Hkv, r.choice([64, 128]),
+               int(2 ** r.uniform(0, 17.5)) - 1)
+
+
+def tiles_of(N_pad, L):
+    return (L + 63) // 64 + N_pad // 64
+
+
+def filling(B, N_pad, Hq, Hkv, L):
+    """Wavefronts and splits that fill the chip: 256 workgroups of 8 wavefronts or 512 of 4, rounded up, with at
+    least four key tiles a split."""
+    rows = N_pad * (Hq // Hkv)
+    waves = 8 if rows >= 512 else 4
+    pairs = B * Hkv * (-(-rows // (32 * waves)))
+    tiles = tiles_of(N_pad, L)
+    want = max(1, min(-(-(256 if waves == 8 else 512) // pairs), max(1, tiles // 4)))
+    run = -(-tiles // want)
+    return waves, -(-tiles // run)
+
+
+@pytest.mark.parametrize("part", [1.0, 0.5, 0.0])
+def test_a_plan_covers_every_key_and_fits_its_workspace(part):
+    for B, N_pad, Hq, Hkv, Dh, L in shapes(3000, 1):
+        least = P.least_workspace(B, N_pad, Hq, Hkv, Dh, L)
+        nbytes = least + int(part * max(0, P.attention_plan(B, N_pad, Hq, Hkv, Dh, L)["bytes"] - least))
+        p = P.attention_plan(B, N_pad, Hq, Hkv, Dh, L, nbytes)
+        where = (B, N_pad, Hq, Hkv, Dh, L, nbytes, p)
+        tiles, rows = tiles_of(N_pad, L), N_pad * (Hq // Hkv)
+        assert p["waves"] in (4, 8) and p["row_tiles"] == -(-rows // (32 * p["waves"])), where
+        assert p["split_likely"] == -(-tiles // p["run_bound"]) <= p["split_max"], where
+        assert p["capacity_per_head"] >= B * p["row_tiles"] * p["split_likely"], where
+        assert p["bytes"] <= max(nbytes, 256), where
+        assert p["balance"] == (p["split_max"] > p["split_likely"]), where
+        staged = p["split_max"] > 1
+        assert p["partial"] == (B * Hkv * p["row_tiles"] * p["split_max"] * 32 * p["waves"] * (2 * Dh + 8) if staged else 256), where
