@@ -996,9 +996,11 @@ static int tree_attention_call(const void* q, const void* k_prefix, const void* 
   const size_t most = attention_plan_limit(total);
   const size_t usable = workspace && aligned16(workspace) ? workspace_bytes : 0;   // (optional where nothing has to be staged)
   const AttnPlan plan = attention_plan(B, N_pad, Hq, Hkv, Dh, max_prefix_len, usable < most ? usable : most);
-  a.run_bound = plan.run_bound; a.split_max = plan.split_max; a.split_likely = plan.split_likely; a.balance = plan.balance; a.capacity_per_head = plan.capacity_per_head;
-  a.row_tiles = plan.row_tiles; a.row_tile_log2 = plan.waves == 8 ? 8 : 7;
-  const size_t prow = (static_cast<size_t>(B) * Hkv * plan.split_max * plan.row_tiles) << a.row_tile_log2;
+  a.run_bound = plan.run_bound; a.split_max = plan.split_max; a.split_likely = plan.split_likely; a.capacity_per_head = plan.capacity_per_head;
+  a.row_tiles = plan.row_tiles;
+  a.rows_pad = plan.row_tiles * 32 * plan.waves;
+  a.total_items = plan.row_tiles * plan.split_likely * B * Hkv;
+  const size_t prow = static_cast<size_t>(B) * Hkv * plan.split_max * a.rows_pad;
   const size_t off_m = prow * Dh * sizeof(uint16_t);   // bf16 partial outputs, then fp32 maxima and denominators
   const size_t off_l = off_m + prow * sizeof(float);
   a.q = static_cast<const uint16_t*>(q);
@@ -1007,7 +1009,7 @@ static int tree_attention_call(const void* q, const void* k_prefix, const void* 
   a.k_tree = static_cast<const uint16_t*>(k_tree);
   a.v_tree = static_cast<const uint16_t*>(v_tree);
   a.mask = mask; a.n_nodes = n_nodes; a.prefix_len = prefix_len;
-  a.B = B; a.N_pad = N_pad; a.Hq = Hq; a.Hkv = Hkv; a.G = Hq / Hkv; a.Dh = Dh; a.max_prefix_len = max_prefix_len;
+  a.B = B; a.N_pad = N_pad; a.Hkv = Hkv; a.G = Hq / Hkv; a.max_prefix_len = max_prefix_len;
   a.kv_stride_b = kv_stride_b; a.kv_stride_t = kv_stride_t; a.kv_stride_h = kv_stride_h;
   const float sc = scale == 0.f ? 1.f / sqrtf(static_cast<float>(Dh)) : scale;
   a.scale_log2e = sc * 1.4426950408889634f;
@@ -1018,7 +1020,7 @@ static int tree_attention_call(const void* q, const void* k_prefix, const void* 
   a.part_m = reinterpret_cast<float*>(w + off_m);
   a.part_l = reinterpret_cast<float*>(w + off_l);
   a.part_count = reinterpret_cast<int32_t*>(w + plan.partial);
-  return check_hip(launch_attention(a, plan.waves, static_cast<hipStream_t>(stream)), "tree attention launch");
+  return check_hip(launch_attention(a, Dh, plan.waves, plan.balance != 0, static_cast<hipStream_t>(stream)), "tree attention launch");
 }
 
 int talon_tree_attention(const void* q, const void* k_prefix, const void* v_prefix, const void* k_tree,

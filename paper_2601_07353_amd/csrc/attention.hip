@@ -104,17 +104,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
   // ids round-robin to the 8 XCDs, each with its own L2.  The row tiles of one (sequence, KV head,
   // run) read the same K/V tiles, so they are given ids that are congruent modulo 8 and adjacent in
   // time: they share one L2 and the tile is fetched from HBM once, not once per row tile.
+  // (The divisions sit in front of a workgroup's first load: the map of equal sequences has to
+  // stay this short, 0.5 us of 15 at one sequence of 60 nodes and 2048 keys.)
   constexpr int kRowTile = 32 * NW * RB;
-  const int id_in_xcd = static_cast<int>(blockIdx.x / 8);
-  int run = a.run_bound, row_tiles = a.row_tiles, splits = a.split_likely;
-  int b, local, n, L;   // the sequence, the item within it, its nodes, its prefix
-  {
-    const int per_seq = row_tiles * splits * a.Hkv;
-    const int item = static_cast<int>(blockIdx.x % 8) * ((per_seq * a.B + 7) / 8) + id_in_xcd;
-    b = item / per_seq;
-    local = item - b * per_seq;
-    if (id_in_xcd >= (per_seq * a.B + 7) / 8) b = a.B;   // an id beyond the items of full-length sequences
-  }
+  const int per_xcd = (a.total_items + 7) / 8;
+  const int item = static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
+  int run = a.run_bound, splits = a.split_likely;
+  int rt, split, bg, b = 0, n = 0, L = 0;   // the row tile, the run, the (sequence, KV head), the sequence, its nodes, its prefix
   bool placed = false;
   if constexpr (BALANCE) {
     // Sequences shorter than the launch allows for: the run length is the smallest for which the
@@ -140,7 +136,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
           tiles_l[c] = (ll + kKeyTile - 1) / kKeyTile + (nn + kKeyTile - 1) / kKeyTile;
           if (rowt_l[c] > 0) most_tiles = most_tiles > tiles_l[c] ? most_tiles : tiles_l[c];
           sum_tiles += rowt_l[c] * tiles_l[c];
-          shorter = shorter || rowt_l[c] != row_tiles || ll != a.max_prefix_len || nn <= a.N_pad - kKeyTile;
+          shorter = shorter || rowt_l[c] != a.row_tiles || ll != a.max_prefix_len || nn <= a.N_pad - kKeyTile;
         }
       }
     }
@@ -173,8 +169,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
         }
       }
       const int per_xcd = (total + 7) / 8;
-      const int item = static_cast<int>(blockIdx.x % 8) * per_xcd + id_in_xcd;
-      if (id_in_xcd >= per_xcd || item >= total) return;
+      const int item = static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
+      if (static_cast<int>(blockIdx.x / 8) >= per_xcd || item >= total) return;
+      int local = 0, row_tiles = 1;
 #pragma unroll
       for (int c = 0; c < TALON_B_MAX / 64; ++c) {
         if (c * 64 < a.B) {
@@ -190,31 +187,38 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
           }
         }
       }
+      if (local == 0 && tid == 0) a.part_count[b] = splits;
+      rt = __builtin_amdgcn_readfirstlane(local % row_tiles);
+      split = __builtin_amdgcn_readfirstlane((local / row_tiles) % splits);
+      bg = __builtin_amdgcn_readfirstlane(b * a.Hkv + local / (row_tiles * splits));
     }
   }
   if (!placed) {
-    if (b >= a.B) return;
+    // (with balancing the grid holds more than these items: ids beyond them belong to no row tile)
+    if (item >= a.total_items || (BALANCE && static_cast<int>(blockIdx.x / 8) >= per_xcd)) return;
+    rt = item % a.row_tiles;
+    split = (item / a.row_tiles) % splits;
+    bg = item / (a.row_tiles * splits);
+    b = bg / a.Hkv;
     n = a.n_nodes[b];
     L = a.prefix_len[b];
     n = n < a.N_pad ? n : a.N_pad;
     L = L < 0 ? 0 : (L > a.max_prefix_len ? a.max_prefix_len : L);
+    if (BALANCE && split == 0 && rt == 0 && bg == b * a.Hkv && tid == 0) a.part_count[b] = splits;
   }
+  const int g = bg - b * a.Hkv;
   const int G = a.G;
   const int rows = n * G;
-  const int nPT = (L + kKeyTile - 1) / kKeyTile;
-  const int nTT = (n + kKeyTile - 1) / kKeyTile;
-  const int T = nPT + nTT;
-  const int rt = local % row_tiles;
-  const int split = (local / row_tiles) % splits;
-  const int g = local / (row_tiles * splits);
-  const int bg = b * a.Hkv + g;
   const int row0 = rt * kRowTile;
-  const int t_begin = split * run;
-  const int t_end = (t_begin + run < T) ? t_begin + run : T;
   // (Without balancing, a run beyond the end of its sequence stores a maximum of -inf, so that the
   // merge needs no count.)
   if (row0 >= rows) return;
-  if (BALANCE && local == 0 && tid == 0) a.part_count[b] = splits;
+
+  const int nPT = (L + kKeyTile - 1) / kKeyTile;
+  const int nTT = (n + kKeyTile - 1) / kKeyTile;
+  const int T = nPT + nTT;
+  const int t_begin = split * run;
+  const int t_end = (t_begin + run < T) ? t_begin + run : T;
   const int words = a.N_pad / 64;
 
   // ---- this lane's queries (one per row block): which node and head each is
@@ -231,7 +235,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
     const int j = valid ? rho - node * G : 0;
     node_rb[rb] = node;
     valid_rb[rb] = valid;
-    orow_rb[rb] = (static_cast<size_t>(b) * a.N_pad + node) * a.Hq + g * G + j;
+    orow_rb[rb] = (static_cast<size_t>(b) * a.N_pad + node) * (a.Hkv * G) + g * G + j;
   }
 
   float m_run[RB], l_run[RB];
@@ -588,8 +592,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
     const int rho_e = wrow0 + 32 * rb + l32_e;
     if (rho_e >= rows) continue;
     const int node_e = rho_e / G;
-    const size_t orow_e = (static_cast<size_t>(b) * a.N_pad + node_e) * a.Hq + g * G + (rho_e - node_e * G);
-    if ((BALANCE ? splits : a.split_likely) == 1) {
+    const size_t orow_e = (static_cast<size_t>(b) * a.N_pad + node_e) * (a.Hkv * G) + g * G + (rho_e - node_e * G);
+    if ((BALANCE ? splits : a.split_max) == 1) {
       const float inv = 1.f / l_tot;
       uint16_t* op = a.out + orow_e * DH;
 #pragma unroll
@@ -606,12 +610,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
     } else {
       // Partial O^T of a run, normalised by the run's own denominator and rounded to bf16 (half the
       // bytes of the round trip through memory; the rounding, 2^-9 relative per run, is below that
-      // of the final bf16 output), laid out in slabs of 8 head-dim values: [DH / 8][row tile][8], so
+      // of the final bf16 output), laid out in slabs of 8 head-dim values: [DH / 8][rows_pad][8], so
       // that the 64 lanes of a store (32 rows x 2 halves of a slab entry) cover 512 consecutive
       // bytes; row-major would give 8-byte pieces.
-      const size_t pblock = ((static_cast<size_t>(bg) * a.row_tiles + rt) * a.split_max + split) * kRowTile;
-      const size_t prow = pblock + (rho_e - row0);
-      uint16_t* po = a.part_o + pblock * DH + static_cast<size_t>(rho_e - row0) * 8 + 4 * h;
+      const int rho = rho_e;
+      const size_t pblock = (static_cast<size_t>(bg) * a.split_max + split) * a.rows_pad;
+      const size_t prow = pblock + rho;
+      uint16_t* po = a.part_o + pblock * DH + static_cast<size_t>(rho) * 8 + 4 * h;
       const float inv_l = l_tot > 0.f ? 1.f / l_tot : 0.f;
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
@@ -620,7 +625,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
           bf16x4 v;
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = static_cast<__bf16>(o[db][rb][4 * q4 + e] * inv_l);
-          *reinterpret_cast<bf16x4*>(po + static_cast<size_t>(4 * db + q4) * kRowTile * 8) = v;
+          *reinterpret_cast<bf16x4*>(po + static_cast<size_t>(4 * db + q4) * a.rows_pad * 8) = v;
         }
       }
       if (h == 0) {
@@ -654,21 +659,18 @@ __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnAr
   const int c = 2 * slab + h;
   const int rho = blockIdx.x * RPW + r;
   // Every run of a row tile that has rows stores a partial result, at a place that depends on no
-  // length, and a row tile has room for a.split_max of them.  The loads of the a.split_likely runs
-  // that full-length prefixes have, up to eight of them, are issued together with the loads of the
-  // node count and the number of runs, one memory round trip, and the running maximum is carried
-  // across blocks of eight.  What nobody wrote is dropped.
-  const int row_tile = 1 << a.row_tile_log2;
-  const int rt = (blockIdx.x * RPW) >> a.row_tile_log2;      // the workgroup's rows lie in one row tile
-  const int r_in = rho - rt * row_tile;
-  int splits = a.split_likely;
+  // length, and the arrays have room for every row the grid covers.  The loads of the
+  // a.split_likely runs that full-length prefixes have, up to eight of them, are issued together
+  // with the loads of the node count and the number of runs, one memory round trip, and the
+  // running maximum is carried across blocks of eight.  What nobody wrote is dropped.
+  int splits = a.split_max;
   if constexpr (BALANCE) {
     const int counted = a.part_count[b];               // (nobody writes it for a sequence without nodes)
     splits = counted < a.split_max ? counted : a.split_max;
   }
-  const size_t block0 = (static_cast<size_t>(bg) * a.row_tiles + rt) * a.split_max * row_tile;
-  const size_t base = block0 + r_in;
-  const size_t in_block = (static_cast<size_t>(slab) * row_tile + r_in) * 8 + 4 * h;
+  const size_t block0 = static_cast<size_t>(bg) * a.split_max * a.rows_pad;
+  const size_t base = block0 + rho;
+  const size_t in_block = (static_cast<size_t>(slab) * a.rows_pad + rho) * 8 + 4 * h;
   float M = kNegInfF;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   float den = 0.f;
@@ -681,11 +683,11 @@ __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnAr
       ms[u] = kNegInfF;
       ls[u] = 0.f;
       vs[u] = bf16x4{0, 0, 0, 0};
-      if (s < a.split_likely || (BALANCE && s < splits)) {   // uniform; the first ones do not wait for the count
-        const size_t pr = base + static_cast<size_t>(s) * row_tile;
+      if (s < (BALANCE ? a.split_likely : a.split_max) || (BALANCE && s < splits)) {   // uniform; the first ones do not wait for the count
+        const size_t pr = base + static_cast<size_t>(s) * a.rows_pad;
         ms[u] = a.part_m[pr];
         ls[u] = a.part_l[pr];
-        vs[u] = *reinterpret_cast<const bf16x4*>(a.part_o + (block0 + static_cast<size_t>(s) * row_tile) * DH + in_block);
+        vs[u] = *reinterpret_cast<const bf16x4*>(a.part_o + (block0 + static_cast<size_t>(s) * a.rows_pad) * DH + in_block);
       }
     }
 #pragma unroll
@@ -718,7 +720,7 @@ __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnAr
   s_out[r][c] = v;
   if (a.out_lse && c == 0 && valid) {
     const int node = rho / a.G;
-    const size_t orow = (static_cast<size_t>(b) * a.N_pad + node) * a.Hq + g * a.G + (rho - node * a.G);
+    const size_t orow = (static_cast<size_t>(b) * a.N_pad + node) * (a.Hkv * a.G) + g * a.G + (rho - node * a.G);
     a.out_lse[orow] = (M + __builtin_amdgcn_logf(den)) * 0.6931471805599453f;
   }
   __syncthreads();
@@ -727,7 +729,7 @@ __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnAr
   const int rho2 = blockIdx.x * RPW + r2;
   if (rho2 < rows) {
     const int node = rho2 / a.G;
-    const size_t orow = (static_cast<size_t>(b) * a.N_pad + node) * a.Hq + g * a.G + (rho2 - node * a.G);
+    const size_t orow = (static_cast<size_t>(b) * a.N_pad + node) * (a.Hkv * a.G) + g * a.G + (rho2 - node * a.G);
     *reinterpret_cast<bf16x4*>(a.out + orow * DH + 4 * c2) = s_out[r2][c2];
   }
 }
@@ -740,7 +742,7 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
   static const hipError_t attr_result = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Smem<DH>::BYTES);
   if (attr_result != hipSuccess) return attr_result;
-  hipLaunchKernelGGL(kern, dim3(8 * ((a.capacity_per_head * a.Hkv + 7) / 8)), dim3(64 * NW), Smem<DH>::BYTES, s, a);
+  hipLaunchKernelGGL(kern, dim3(8 * (((BALANCE ? a.capacity_per_head * a.Hkv : a.total_items) + 7) / 8)), dim3(64 * NW), Smem<DH>::BYTES, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.split_max > 1) {
@@ -755,13 +757,13 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t s) {
 }  // namespace
 
 template <int DH>
-static hipError_t launch_dh(const AttnArgs& a, int waves, hipStream_t s) {
-  if (a.balance) return waves == 8 ? launch_one<DH, 8, true>(a, s) : launch_one<DH, 4, true>(a, s);
+static hipError_t launch_dh(const AttnArgs& a, int waves, bool balance, hipStream_t s) {
+  if (balance) return waves == 8 ? launch_one<DH, 8, true>(a, s) : launch_one<DH, 4, true>(a, s);
   return waves == 8 ? launch_one<DH, 8, false>(a, s) : launch_one<DH, 4, false>(a, s);
 }
 
-hipError_t launch_attention(const AttnArgs& a, int waves, hipStream_t s) {
-  return a.Dh == 128 ? launch_dh<128>(a, waves, s) : launch_dh<64>(a, waves, s);
+hipError_t launch_attention(const AttnArgs& a, int Dh, int waves, bool balance, hipStream_t s) {
+  return Dh == 128 ? launch_dh<128>(a, waves, balance, s) : launch_dh<64>(a, waves, balance, s);
 }
 
 }  // namespace talon

@@ -149,6 +149,8 @@ struct LiteralArgs {
   int32_t* row_ticket;             // [B*N_pad] parts of a row that have finished; zero between launches
 };
 
+// (Kernel arguments are fetched in lines of 64 bytes, a round trip each: with a fourth line a call of
+// 15 us took 0.2 us longer.  What the kernels use together lies together.)
 struct AttnArgs {
   const uint16_t* q;
   const uint16_t* k_prefix;
@@ -158,25 +160,26 @@ struct AttnArgs {
   const uint64_t* mask;
   const int32_t* n_nodes;
   const int32_t* prefix_len;
-  int B, N_pad, Hq, Hkv, G, Dh;
+  int B, N_pad, Hkv, G;  // G: query heads per KV head
   int max_prefix_len;
-  int64_t kv_stride_b, kv_stride_t, kv_stride_h;
   float scale_log2e;     // scale * log2(e): scores are kept in base-2 units
+  int64_t kv_stride_b, kv_stride_t, kv_stride_h;
   uint16_t* out;
   float* out_lse;
   // Split-KV: a (sequence, KV head, row tile) is cut into runs of key tiles, see attention.hip.
+  uint16_t* part_o;      // [B][Hkv][split_max][Dh/8][rows_pad][8] bf16: each run's output, normalised by its own denominator
+  float* part_m;         // [B][Hkv][split_max][rows_pad]  running max (base-2 units)
+  float* part_l;         // the same: running denominator
+  int32_t* part_count;   // [B] runs per row tile of the sequence (where the run length is worked out on the device)
+  int capacity_per_head; // most workgroups per KV head (there)
   int run_bound;         // run length that fits the grid whatever the prefixes are
   int split_max;         // most runs of one row tile (1: nothing is staged)
   int split_likely;      // runs of a full-length prefix
-  int capacity_per_head; // most workgroups per KV head
-  int balance;           // the run length is worked out on the device from the sequences' lengths
   int row_tiles;         // row tiles per (sequence, KV head)
-  int row_tile_log2;     // rows of a tile: 128 or 256
-  uint16_t* part_o;      // [B][Hkv][row tile][split_max][Dh/8][rows of a tile][8] bf16: each run's output, normalised by its own denominator
-  float* part_m;         // [B][Hkv][row tile][split_max][rows of a tile]  running max (base-2 units)
-  float* part_l;         // the same: running denominator
-  int32_t* part_count;   // [B] runs per row tile of the sequence (with balance)
+  int rows_pad;          // rows of all of them
+  int total_items;       // row_tiles * split_likely * B * Hkv: workgroups of full-length prefixes
 };
+static_assert(sizeof(AttnArgs) <= 192, "three lines");
 
 // launchers (each checks nothing: arguments were validated by the ABI layer)
 hipError_t launch_tree_init(const talon_tree_state& st, const int32_t* root_token, hipStream_t s);
@@ -203,7 +206,7 @@ hipError_t launch_expand(const ExpandArgs& a, int dtype, int grid, bool fused, h
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_mask(const talon_tree_state& st, uint64_t* mask, hipStream_t s);
 hipError_t launch_literal_layer(const LiteralArgs& a, int dtype, hipStream_t s);
-hipError_t launch_attention(const AttnArgs& a, int waves, hipStream_t s);
+hipError_t launch_attention(const AttnArgs& a, int Dh, int waves, bool balance, hipStream_t s);
 
 int expand_chunk_elems(int dtype);
 
