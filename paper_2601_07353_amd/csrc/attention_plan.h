@@ -94,6 +94,7 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
   AttnPlan best = {};
   int best_splits = 1;
   double best_us = 0.0;
+  bool staged;   // may partial results be staged?  They are rounded to bf16: only where the plan that fills the chip has them too
   // Another plan than the one that fills the chip has to promise a tenth less: differences of a few
   // percent are within the estimate's error (8 -> 4 wavefronts promised 5 % at 3 sequences of 227
   // nodes x 4 heads and 376 keys and cost 7 %), the plans it is for gain a quarter or more.
@@ -103,6 +104,7 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
     const int row_tiles = (rows + mt - 1) / mt;
     const long long all = static_cast<long long>(B) * Hkv * row_tiles;
     const int splits = filling_splits(all, waves, tiles);
+    staged = splits > 1;
     if (splits <= kMostSplits) {
       best.waves = waves;
       best.row_tiles = row_tiles;
@@ -115,7 +117,7 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
     const int mt = 32 * waves;
     const int row_tiles = (rows + mt - 1) / mt;
     const long long all = static_cast<long long>(B) * Hkv * row_tiles;
-    const int most = tiles / kLeastRun < kMostSplits ? (tiles / kLeastRun > 1 ? tiles / kLeastRun : 1) : kMostSplits;
+    const int most = !staged || tiles < 2 * kLeastRun ? 1 : (tiles / kLeastRun < kMostSplits ? tiles / kLeastRun : kMostSplits);
     for (int splits = 1; splits <= most; ++splits) {
       const int run = (tiles + splits - 1) / splits;
       if ((tiles + run - 1) / run != splits) continue;   // a smaller number of splits has the same run length
@@ -140,7 +142,7 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
   const long long slots = best.waves == 8 ? 256 : 512;
   best.split_max = best.split_likely = best_splits;
   long long wgs = all * best_splits;
-  if (B > 1 && best.run_bound >= 2 * kLeastRun) {
+  if (B > 1 && staged && best.run_bound >= 2 * kLeastRun) {
     const long long rounds = (wgs + slots - 1) / slots;
     for (int m = 2 * best_splits; m > best_splits; --m)
       if (partial_bytes(all, m, mt, Dh) + table <= bytes) { best.split_max = m; break; }

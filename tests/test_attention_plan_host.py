@@ -45,3 +45,16 @@ def test_a_plan_covers_every_key_and_fits_its_workspace(part):
         assert p["balance"] == (p["split_max"] > p["split_likely"]), where
         staged = p["split_max"] > 1
         assert p["partial"] == (B * Hkv * p["row_tiles"] * p["split_max"] * 32 * p["waves"] * (2 * Dh + 8) if staged else 256), where
+
+
+def test_rows_the_filling_plan_leaves_in_registers_are_not_staged():
+    """Staged partial results are rounded to bf16.  Where one run per row tile fills the chip, a row goes from
+    fp32 registers to the output, and no other plan (more splits, unequal prefixes sharing the grid) may stage it."""
+    seen = 0
+    for B, N_pad, Hq, Hkv, Dh, L in shapes(4000, 2):
+        if filling(B, N_pad, Hq, Hkv, L)[1] > 1:
+            continue
+        p = P.attention_plan(B, N_pad, Hq, Hkv, Dh, L)
+        assert p["split_max"] == 1 and not p["balance"], (B, N_pad, Hq, Hkv, Dh, L, p)
+        seen += 1
+    assert seen > 500
