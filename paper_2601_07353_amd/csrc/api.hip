@@ -996,7 +996,7 @@ static int tree_attention_call(const void* q, const void* k_prefix, const void* 
   const size_t most = attention_plan_limit(total);
   const size_t usable = workspace && aligned16(workspace) ? workspace_bytes : 0;   // (optional where nothing has to be staged)
   const AttnPlan plan = attention_plan(B, N_pad, Hq, Hkv, Dh, max_prefix_len, usable < most ? usable : most);
-  a.run_bound = plan.run_bound; a.split_max = plan.split_max; a.split_likely = plan.split_likely; a.capacity_per_head = plan.capacity_per_head;
+  a.run_bound = plan.run_bound; a.run_single = plan.run_single; a.split_max = plan.split_max; a.split_likely = plan.split_likely; a.capacity_per_head = plan.capacity_per_head;
   a.row_tiles = plan.row_tiles;
   a.rows_pad = plan.row_tiles * 32 * plan.waves;
   a.total_items = plan.row_tiles * plan.split_likely * B * Hkv;

@@ -118,6 +118,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
     // split_max runs), so that unequal prefixes fill the chip as evenly as equal ones.  Every
     // workgroup works it out from the lengths, lane l for sequences l, l + 64, ...; run_bound, the
     // answer for full-length prefixes, always fits.
+    // (Sequences of at most run_single tiles, one run where the chip is filled with splits, stay one
+    // run: a row with a single partial result is rounded to bf16 once, a merged one twice.)
     int nodes_l[TALON_B_MAX / 64], prefix_l[TALON_B_MAX / 64], tiles_l[TALON_B_MAX / 64], rowt_l[TALON_B_MAX / 64];
     int most_tiles = 0, sum_tiles = 0;
     bool shorter = false;
@@ -154,7 +156,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
         int need = 0;
 #pragma unroll
         for (int c = 0; c < TALON_B_MAX / 64; ++c)
-          if (c * 64 < a.B) need += rowt_l[c] * ((tiles_l[c] + mid - 1) / mid);
+          if (c * 64 < a.B) need += rowt_l[c] * (tiles_l[c] <= a.run_single ? 1 : (tiles_l[c] + mid - 1) / mid);
         if (__builtin_amdgcn_readfirstlane(wave_sum_i32(need)) <= a.capacity_per_head) run = mid; else lo = mid + 1;
       }
       int first_l[TALON_B_MAX / 64], count_l[TALON_B_MAX / 64], total = 0;
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
       for (int c = 0; c < TALON_B_MAX / 64; ++c) {
         first_l[c] = count_l[c] = 0;
         if (c * 64 < a.B) {
-          count_l[c] = rowt_l[c] * ((tiles_l[c] + run - 1) / run) * a.Hkv;
+          count_l[c] = rowt_l[c] * (tiles_l[c] <= a.run_single ? 1 : (tiles_l[c] + run - 1) / run) * a.Hkv;
           const int incl = wave_inclusive_scan_i32(count_l[c]);
           first_l[c] = total + incl - count_l[c];
           total += __builtin_amdgcn_readlane(incl, 63);
@@ -181,7 +183,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
             b = c * 64 + l;
             local = item - __builtin_amdgcn_readlane(first_l[c], l);
             row_tiles = __builtin_amdgcn_readlane(rowt_l[c], l);
-            splits = (__builtin_amdgcn_readlane(tiles_l[c], l) + run - 1) / run;
+            const int tiles = __builtin_amdgcn_readlane(tiles_l[c], l);
+            splits = tiles <= a.run_single ? 1 : (tiles + run - 1) / run;
             n = __builtin_amdgcn_readlane(nodes_l[c], l);
             L = __builtin_amdgcn_readlane(prefix_l[c], l);
           }
@@ -217,6 +220,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void tree_attention_kerne
   const int nPT = (L + kKeyTile - 1) / kKeyTile;
   const int nTT = (n + kKeyTile - 1) / kKeyTile;
   const int T = nPT + nTT;
+  run = T <= a.run_single ? a.run_single : run;
   const int t_begin = split * run;
   const int t_end = (t_begin + run < T) ? t_begin + run : T;
   const int words = a.N_pad / 64;

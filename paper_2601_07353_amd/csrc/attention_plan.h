@@ -17,7 +17,7 @@ constexpr int kMostSplits = 64;
 
 struct AttnPlan {
   int waves;             // wavefronts per workgroup
-  int row_tiles, run_bound, split_max, split_likely, capacity_per_head, balance;   // as in AttnArgs
+  int row_tiles, run_bound, run_single, split_max, split_likely, capacity_per_head, balance;   // as in AttnArgs
   size_t partial;        // bytes of the partial results ...
   size_t bytes;          // ... and with the table of run counts
 };
@@ -105,6 +105,7 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
     const long long all = static_cast<long long>(B) * Hkv * row_tiles;
     const int splits = filling_splits(all, waves, tiles);
     staged = splits > 1;
+    best.run_single = staged ? (tiles + splits - 1) / splits : 0;
     if (splits <= kMostSplits) {
       best.waves = waves;
       best.row_tiles = row_tiles;

@@ -173,6 +173,7 @@ struct AttnArgs {
   int32_t* part_count;   // [B] runs per row tile of the sequence (where the run length is worked out on the device)
   int capacity_per_head; // most workgroups per KV head (there)
   int run_bound;         // run length that fits the grid whatever the prefixes are
+  int run_single;        // a sequence of at most this many key tiles is one run, whatever the run length is
   int split_max;         // most runs of one row tile (1: nothing is staged)
   int split_likely;      // runs of a full-length prefix
   int row_tiles;         // row tiles per (sequence, KV head)

@@ -17,13 +17,13 @@ size_t t_least(int B, int N_pad, int Hq, int Hkv, int Dh, int L) { return talon:
 size_t t_limit(size_t least) { return talon::attention_plan_limit(least); }
 void t_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int L, size_t bytes, long long* out) {
   const talon::AttnPlan p = talon::attention_plan(B, N_pad, Hq, Hkv, Dh, L, bytes);
-  const long long v[] = {p.waves, p.row_tiles, p.run_bound, p.split_max, p.split_likely, p.capacity_per_head, p.balance,
+  const long long v[] = {p.waves, p.row_tiles, p.run_bound, p.split_max, p.split_likely, p.capacity_per_head, p.balance, p.run_single,
                          static_cast<long long>(p.partial), static_cast<long long>(p.bytes)};
-  for (int i = 0; i < 9; ++i) out[i] = v[i];
+  for (int i = 0; i < 10; ++i) out[i] = v[i];
 }
 }
 """
-FIELDS = ("waves", "row_tiles", "run_bound", "split_max", "split_likely", "capacity_per_head", "balance", "partial", "bytes")
+FIELDS = ("waves", "row_tiles", "run_bound", "split_max", "split_likely", "capacity_per_head", "balance", "run_single", "partial", "bytes")
 
 
 @functools.lru_cache(maxsize=None)
@@ -49,6 +49,6 @@ def attention_plan(B, N_pad, Hq, Hkv, Dh, L, nbytes=None):
     """The plan of a call; by default with the workspace that the library's query asks for."""
     if nbytes is None:
         nbytes = _lib().t_limit(least_workspace(B, N_pad, Hq, Hkv, Dh, L))
-    out = (ctypes.c_longlong * 9)()
+    out = (ctypes.c_longlong * 10)()
     _lib().t_plan(B, N_pad, Hq, Hkv, Dh, L, nbytes, out)
     return dict(zip(FIELDS, out))

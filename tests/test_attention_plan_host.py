@@ -58,3 +58,13 @@ def test_rows_the_filling_plan_leaves_in_registers_are_not_staged():
         assert p["split_max"] == 1 and not p["balance"], (B, N_pad, Hq, Hkv, Dh, L, p)
         seen += 1
     assert seen > 500
+
+
+def test_one_filling_run_stays_one_run():
+    """The kernels keep a sequence of at most run_single key tiles in one run (one rounding to bf16): the run
+    length of the plan that fills the chip, none where that plan has a single run for everybody."""
+    for B, N_pad, Hq, Hkv, Dh, L in shapes(3000, 3):
+        splits = filling(B, N_pad, Hq, Hkv, L)[1]
+        want = -(-tiles_of(N_pad, L) // splits) if splits > 1 else 0
+        assert P.attention_plan(B, N_pad, Hq, Hkv, Dh, L)["run_single"] == want, (B, N_pad, Hq, Hkv, Dh, L)
+    assert (P.attention_plan(3, 192, 64, 16, 64, 793)["run_single"], P.attention_plan(5, 256, 32, 4, 64, 2000)["run_single"]) == (8, 18)
