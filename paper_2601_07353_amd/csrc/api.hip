@@ -943,7 +943,7 @@ size_t talon_tree_attention_workspace_bytes(int32_t B, int32_t N_pad, int32_t Hq
                                             int32_t max_prefix_len) {
   if (check_attention_shape(B, N_pad, Hq, Hkv, Dh, max_prefix_len)) return 0;
   const size_t least = attention_least_workspace(B, N_pad, Hq, Hkv, Dh, max_prefix_len);
-  const size_t plan = attention_plan(B, N_pad, Hq, Hkv, Dh, max_prefix_len, attention_plan_limit(least)).bytes;
+  const size_t plan = attention_plan(B, N_pad, Hq, Hkv, Dh, max_prefix_len, SIZE_MAX).bytes;
   return plan > least ? plan : least;
 }
 
@@ -993,9 +993,8 @@ static int tree_attention_call(const void* q, const void* k_prefix, const void* 
     if (!workspace || !aligned16(workspace)) { set_error("workspace is NULL or not 16-byte aligned"); return TALON_ERR_INVALID_ARG; }
     if (workspace_bytes < total) { set_error("workspace of %zu bytes is smaller than the %zu needed", workspace_bytes, total); return TALON_ERR_WORKSPACE; }
   }
-  const size_t most = attention_plan_limit(total);
   const size_t usable = workspace && aligned16(workspace) ? workspace_bytes : 0;   // (optional where nothing has to be staged)
-  const AttnPlan plan = attention_plan(B, N_pad, Hq, Hkv, Dh, max_prefix_len, usable < most ? usable : most);
+  const AttnPlan plan = attention_plan(B, N_pad, Hq, Hkv, Dh, max_prefix_len, usable);
   a.run_bound = plan.run_bound; a.run_single = plan.run_single; a.split_max = plan.split_max; a.split_likely = plan.split_likely; a.capacity_per_head = plan.capacity_per_head;
   a.row_tiles = plan.row_tiles;
   a.rows_pad = plan.row_tiles * 32 * plan.waves;

@@ -78,22 +78,26 @@ inline size_t attention_least_workspace(int B, int N_pad, int Hq, int Hkv, int D
   return partial_bytes(pairs, filling_splits(pairs, waves, key_tiles(N_pad, max_prefix_len)), mt, Dh);
 }
 
-// Workspace a plan may use beyond what a call must bring: short prefixes gain from more splits than
-// that, as long as the partial results stay small.  A caller whose workspace was sized for another
-// (longer) prefix gets the best plan that fits it.
+// Workspace whose splits a plan may choose from beyond what a call must bring: short prefixes gain from
+// more splits than that, as long as the partial results stay small.  A caller whose workspace was sized
+// for another (longer) prefix gets the best plan that fits it.
 constexpr size_t kAttnPlanBytes = static_cast<size_t>(16) << 20;
 inline size_t attention_plan_limit(size_t least) {
   return (least > kAttnPlanBytes ? least : kAttnPlanBytes) + TALON_B_MAX * sizeof(int32_t);   // + the table of run counts
 }
 
-// The plan of a call that may use `bytes` of workspace (at least attention_least_workspace).
+// The plan of a call that may use `bytes` of workspace (at least attention_least_workspace; a plan needs
+// plan.bytes of them).
 inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int max_prefix_len, size_t bytes) {
+  const size_t limit = attention_plan_limit(attention_least_workspace(B, N_pad, Hq, Hkv, Dh, max_prefix_len));
+  const size_t search_bytes = bytes < limit ? bytes : limit;
   const int rows = N_pad * (Hq / Hkv);
   const int tiles = key_tiles(N_pad, max_prefix_len);
   const size_t table = (static_cast<size_t>(B) * sizeof(int32_t) + 15) & ~static_cast<size_t>(15);   // runs per sequence
   AttnPlan best = {};
   int best_splits = 1;
   double best_us = 0.0;
+  bool other = false;   // another plan than the one that fills the chip
   bool staged;   // may partial results be staged?  They are rounded to bf16: only where the plan that fills the chip has them too
   // Another plan than the one that fills the chip has to promise a tenth less: differences of a few
   // percent are within the estimate's error (8 -> 4 wavefronts promised 5 % at 3 sequences of 227
@@ -123,7 +127,7 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
       const int run = (tiles + splits - 1) / splits;
       if ((tiles + run - 1) / run != splits) continue;   // a smaller number of splits has the same run length
       const size_t need = partial_bytes(all, splits, mt, Dh);
-      if (splits > 1 && need > bytes) break;
+      if (splits > 1 && need > search_bytes) break;
       const double us = plan_us(waves, all * splits, run, splits, Dh, need);
       if (best.waves == 0 || us < best_us) {
         best.waves = waves;
@@ -131,6 +135,7 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
         best.run_bound = run;
         best_splits = splits;
         best_us = us;
+        other = true;
       }
     }
   }
@@ -138,6 +143,12 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
   // workspace goes, and the grid grows to what its rounds hold, short of what would give full-length
   // sequences one split more.  It costs a workgroup about 0.5 us before its first load, so runs
   // have to be long enough for it to matter.
+  // The plan that fills the chip balances within the workspace of the search only: at heads of 128 that
+  // leaves it as it is for 2, 4, 8 or 16 sequences of 8 KV heads, whose partial results fill it.
+  // Another plan may take what twice its runs need.  It was chosen for full-length prefixes, and
+  // unequal ones can leave it slower than the filling one: 3 sequences of 68 nodes, 64/16 heads of 64,
+  // prefixes of 4525, 6643 and 9213 of 14916 keys took 119 us unbalanced, 97 with the filling plan, 100 balanced; 7 of
+  // 93 nodes, 16/2 heads of 128, up to 9396 keys 64, 108 and 50.
   const int mt = 32 * best.waves;
   const long long all = static_cast<long long>(B) * Hkv * best.row_tiles;
   const long long slots = best.waves == 8 ? 256 : 512;
@@ -145,8 +156,9 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
   long long wgs = all * best_splits;
   if (B > 1 && staged && best.run_bound >= 2 * kLeastRun) {
     const long long rounds = (wgs + slots - 1) / slots;
+    const size_t room = other ? bytes : search_bytes;
     for (int m = 2 * best_splits; m > best_splits; --m)
-      if (partial_bytes(all, m, mt, Dh) + table <= bytes) { best.split_max = m; break; }
+      if (partial_bytes(all, m, mt, Dh) + table <= room) { best.split_max = m; break; }
     if (best.split_max > best_splits) {
       best.balance = 1;
       long long grown = all * (best_splits + 1) - 1;

@@ -14,7 +14,6 @@ SHIM = r"""
 #include "attention_plan.h"
 extern "C" {
 size_t t_least(int B, int N_pad, int Hq, int Hkv, int Dh, int L) { return talon::attention_least_workspace(B, N_pad, Hq, Hkv, Dh, L); }
-size_t t_limit(size_t least) { return talon::attention_plan_limit(least); }
 void t_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int L, size_t bytes, long long* out) {
   const talon::AttnPlan p = talon::attention_plan(B, N_pad, Hq, Hkv, Dh, L, bytes);
   const long long v[] = {p.waves, p.row_tiles, p.run_bound, p.split_max, p.split_likely, p.capacity_per_head, p.balance, p.run_single,
@@ -35,8 +34,7 @@ def _lib():
         subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"),
                         "-I", os.path.join(ROOT, "paper_2601_07353_amd", "csrc"), src, "-o", so], check=True)
         lib = ctypes.CDLL(so)      # (the mapping outlives the file)
-    lib.t_least.restype = lib.t_limit.restype = ctypes.c_size_t
-    lib.t_limit.argtypes = [ctypes.c_size_t]
+    lib.t_least.restype = ctypes.c_size_t
     lib.t_plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_void_p]
     return lib
 
@@ -48,7 +46,7 @@ def least_workspace(B, N_pad, Hq, Hkv, Dh, L):
 def attention_plan(B, N_pad, Hq, Hkv, Dh, L, nbytes=None):
     """The plan of a call; by default with the workspace that the library's query asks for."""
     if nbytes is None:
-        nbytes = _lib().t_limit(least_workspace(B, N_pad, Hq, Hkv, Dh, L))
+        nbytes = 2 ** 64 - 1
     out = (ctypes.c_longlong * 10)()
     _lib().t_plan(B, N_pad, Hq, Hkv, Dh, L, nbytes, out)
     return dict(zip(FIELDS, out))
