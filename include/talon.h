@@ -382,7 +382,9 @@ int talon_build_tree_mask(const talon_tree_state* st, uint64_t* mask, void* stre
 
 /*
  * Scratch for talon_tree_attention (split-KV partial results).  max_prefix_len is the
- * largest prefix length any call will pass.
+ * largest prefix length any call will pass.  This is what the call's best plan uses; a call is
+ * accepted with less, down to what splits that just fill the chip need (TALON_ERR_WORKSPACE below
+ * that), and then takes the best plan that fits.
  */
 size_t talon_tree_attention_workspace_bytes(int32_t B, int32_t N_pad, int32_t Hq, int32_t Hkv,
                                             int32_t Dh, int32_t max_prefix_len);
@@ -404,7 +406,11 @@ size_t talon_tree_attention_workspace_bytes(int32_t B, int32_t N_pad, int32_t Hq
  *   out_lse            optional (NULL to skip) float [B][N_pad][Hq]: natural-log softmax
  *                      denominator of the scaled scores
  *   Arithmetic: bf16 MFMA with fp32 accumulation, fp32 online softmax, probabilities
- *   rounded to bf16 before the P.V product, output rounded to bf16.
+ *   rounded to bf16 before the P.V product, output rounded to bf16.  A long prefix is cut into runs
+ *   of keys whose partial outputs are rounded to bf16 and merged in fp32.  Where the cuts lie depends on
+ *   the shape, on max_prefix_len and on the workspace's size, and for batches of unequal sequences
+ *   also on the lengths of the other sequences: the low bits of a sequence's result may differ
+ *   between batches it is part of.  The same call on the same data repeats its result bit for bit.
  *   Errors: INVALID_ARG, UNSUPPORTED (Dh != 64 and != 128, Hq % Hkv != 0, Hq/Hkv > 16),
  *   WORKSPACE.
  */
@@ -419,12 +425,12 @@ int talon_tree_attention(const void* q, const void* k_prefix, const void* v_pref
 /*
  * talon_tree_attention for callers that cannot allocate device memory or pass a workspace
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the
- * same call, the same kernels and the same results, with the split-KV partial results kept in
- * a device array that is part of the library itself (talon_static_scratch_bytes() = 32 MiB per
+ * same call and the same kernels (and the same results as with a workspace of that size), with the
+ * split-KV partial results kept in a device array that is part of the library itself (talon_static_scratch_bytes() = 32 MiB per
  * GPU, held from the moment the library is loaded on that GPU until the process ends).  The
  * call allocates nothing and frees nothing.
- *   - Shapes whose partial results need more than that (talon_tree_attention_workspace_bytes
- *     says how much) are refused with TALON_ERR_WORKSPACE; nothing is launched then.
+ *   - Shapes whose partial results need more than that with splits that just fill the chip are
+ *     refused with TALON_ERR_WORKSPACE; nothing is launched then.
  *   - The array's device address is looked up on the first call on a device;
  *     talon_static_scratch_init() does the same lookup ahead of time (call it once per device,
  *     with that device current, before capturing a graph).
