@@ -13,7 +13,6 @@ constexpr int kKeyTile = 64;
 // Fewest key tiles of a run (of a prefix that has more than that): the fewer keys a run has, the
 // larger its normalised outputs are against the row's result, and their rounding to bf16 with them.
 constexpr int kLeastRun = 4;
-constexpr int kMostSplits = 64;
 
 struct AttnPlan {
   int waves;             // wavefronts per workgroup
@@ -27,17 +26,21 @@ struct AttnPlan {
 // (256 rows, one per compute unit: a K/V tile is loaded once for 256 rows instead of twice).  A split
 // takes a run of key tiles; more splits shorten the runs but add workgroups, which run in rounds of
 // what the chip holds, and partial results, which are written and read back by the merge.
-// The plan is the cheapest of all (width, splits) by this estimate, in microseconds.  Its constants
-// are fitted to 330 measured plans of 22 shapes, 1 x 8 to 16 x 16 (sequence, KV head) pairs and 300
-// to 16000 keys (its picks are 0.7 % off the fastest plans on average, 7 % at most):
+// The plan is the one that fills the chip (as many splits as that takes, rounded up; 8 wavefronts from
+// 512 rows on) unless another (width, splits) is estimated to be at least a tenth cheaper; with more
+// than 64 splits, where the chip is filled by a costly merge, unless another is cheaper at all.  The
+// estimate, in microseconds, is fitted to 330 measured plans of 22 shapes, 1 x 8 to 16 x 16 (sequence,
+// KV head) pairs and 300 to 16000 keys (the cheapest by it are 0.7 % off the fastest plans on average, 7 %
+// at most), and the merge of many splits to 1 to 8 KV heads of one sequence at 16384 to 262144 keys:
 //   a round     a run of key tiles, plus 2.3 (queries, first tile, last stores)
 //   a tile      8 wavefronts: 1.88; 4: 1.98 while two workgroups share a compute unit, 1.70 alone
 //               (1.28 when the keys are in the Infinity Cache, which a model's many layers do not
 //               leave them in); Dh = 64: 1.15, 1.20 and 1.10
-//   merge       3.5, 0.07 per split beyond six, and the partial results' bytes, twice, at 5 TB/s
-// The rule before (as many splits as fill the chip, rounded up, 8 wavefronts from 512 rows on) left
-// 288 workgroups on 256 places: 3 sequences of 200 nodes x 2 heads at 6000 keys 76 us against 52,
-// 6 x 250 x 4 at 9000 keys 186 against 140, 5 x 100 x 3 of 64 at 3001 keys 22 (ragged) against 19.
+//   merge       3.5, 0.07 per split beyond six and 0.05 more beyond 64, and the partial results' bytes,
+//               twice, at 5 TB/s
+// The filling plan alone leaves 288 workgroups on 256 places: 3 sequences of 200 nodes x 2 heads at 6000
+// keys 76 us against 52, 6 x 250 x 4 at 9000 keys 186 against 140, 5 x 100 x 3 of 64 at 3001 keys 22 (ragged)
+// against 19; and 410 splits of one head of 64 rows at 131072 keys: 65 us against 42 with 158.
 
 inline int legacy_waves(int rows) { return rows >= 512 ? 8 : 4; }
 
@@ -55,7 +58,8 @@ inline double plan_us(int waves, long long wgs, int run, int splits, int Dh, siz
   const double alone = waves == 8 ? shared : (Dh == 64 ? 1.10 : 1.70);
   double us = full * (run * shared + 2.3);
   if (rest) us += run * (rest > 256 ? shared : alone) + 2.3;   // the last round's workgroups
-  if (splits > 1) us += 3.5 + 0.07 * (splits > 6 ? splits - 6 : 0) + 2.0 * static_cast<double>(bytes) / 5e6;
+  if (splits > 1)
+    us += 3.5 + 0.07 * (splits > 6 ? splits - 6 : 0) + 0.05 * (splits > 64 ? splits - 64 : 0) + 2.0 * static_cast<double>(bytes) / 5e6;
   return us;
 }
 
@@ -110,26 +114,23 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
     const int splits = filling_splits(all, waves, tiles);
     staged = splits > 1;
     best.run_single = staged ? (tiles + splits - 1) / splits : 0;
-    if (splits <= kMostSplits) {
-      best.waves = waves;
-      best.row_tiles = row_tiles;
-      best.run_bound = (tiles + splits - 1) / splits;
-      best_splits = splits;
-      best_us = 0.9 * plan_us(waves, all * splits, best.run_bound, splits, Dh, partial_bytes(all, splits, mt, Dh));
-    }
+    best.waves = waves;
+    best.row_tiles = row_tiles;
+    best.run_bound = (tiles + splits - 1) / splits;
+    best_splits = splits;
+    best_us = (splits <= 64 ? 0.9 : 1.0) * plan_us(waves, all * splits, best.run_bound, splits, Dh, partial_bytes(all, splits, mt, Dh));
   }
   for (int waves = 8; waves >= 4; waves -= 4) {
     const int mt = 32 * waves;
     const int row_tiles = (rows + mt - 1) / mt;
     const long long all = static_cast<long long>(B) * Hkv * row_tiles;
-    const int most = !staged || tiles < 2 * kLeastRun ? 1 : (tiles / kLeastRun < kMostSplits ? tiles / kLeastRun : kMostSplits);
-    for (int splits = 1; splits <= most; ++splits) {
+    const int most = !staged || tiles < 2 * kLeastRun ? 1 : tiles / kLeastRun;
+    for (int splits = 1; splits <= most;) {   // the fewest splits of every run length
       const int run = (tiles + splits - 1) / splits;
-      if ((tiles + run - 1) / run != splits) continue;   // a smaller number of splits has the same run length
       const size_t need = partial_bytes(all, splits, mt, Dh);
       if (splits > 1 && need > search_bytes) break;
       const double us = plan_us(waves, all * splits, run, splits, Dh, need);
-      if (best.waves == 0 || us < best_us) {
+      if (us < best_us) {
         best.waves = waves;
         best.row_tiles = row_tiles;
         best.run_bound = run;
@@ -137,6 +138,8 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
         best_us = us;
         other = true;
       }
+      if (run == 1) break;
+      splits = (tiles + run - 2) / (run - 1);
     }
   }
   // Balancing of unequal sequences: a row tile may take up to twice as many runs, as far as the

@@ -14,6 +14,7 @@ SHIM = r"""
 #include "attention_plan.h"
 extern "C" {
 size_t t_least(int B, int N_pad, int Hq, int Hkv, int Dh, int L) { return talon::attention_least_workspace(B, N_pad, Hq, Hkv, Dh, L); }
+double t_us(int waves, long long wgs, int run, int splits, int Dh, size_t bytes) { return talon::plan_us(waves, wgs, run, splits, Dh, bytes); }
 void t_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int L, size_t bytes, long long* out) {
   const talon::AttnPlan p = talon::attention_plan(B, N_pad, Hq, Hkv, Dh, L, bytes);
   const long long v[] = {p.waves, p.row_tiles, p.run_bound, p.split_max, p.split_likely, p.capacity_per_head, p.balance, p.run_single,
@@ -35,6 +36,8 @@ def _lib():
                         "-I", os.path.join(ROOT, "paper_2601_07353_amd", "csrc"), src, "-o", so], check=True)
         lib = ctypes.CDLL(so)      # (the mapping outlives the file)
     lib.t_least.restype = ctypes.c_size_t
+    lib.t_us.restype = ctypes.c_double
+    lib.t_us.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
     lib.t_plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_void_p]
     return lib
 
@@ -50,3 +53,11 @@ def attention_plan(B, N_pad, Hq, Hkv, Dh, L, nbytes=None):
     out = (ctypes.c_longlong * 10)()
     _lib().t_plan(B, N_pad, Hq, Hkv, Dh, L, nbytes, out)
     return dict(zip(FIELDS, out))
+
+
+def plan_us(B, N_pad, Hq, Hkv, Dh, L, waves, splits):
+    """The estimate for a number of splits."""
+    row_tiles = -(-N_pad * (Hq // Hkv) // (32 * waves))
+    wgs = B * Hkv * row_tiles * splits
+    return _lib().t_us(waves, wgs, -(-((L + 63) // 64 + N_pad // 64) // splits), splits, Dh,
+                       wgs * 32 * waves * (2 * Dh + 8) if splits > 1 else 256)

@@ -83,3 +83,16 @@ def test_plans_that_leave_the_filling_one_share_the_grid_among_unequal_prefixes(
         seen += 1
         assert p["balance"] and p["split_max"] == 2 * p["split_likely"], (B, N_pad, Hq, Hkv, Dh, L, p)
     assert seen > 200
+
+
+def test_long_prefixes_of_few_heads_fill_the_chip():
+    """The number of splits has no cap of its own: 64 runs of a 262144-key prefix leave three quarters of the chip
+    idle (one KV head of 64 query rows: 93 us, 57 with 228 runs).  The filling plan is always a candidate."""
+    for Hkv, G, L in [(1, 1, 131072), (1, 4, 131072), (2, 2, 131072), (1, 1, 262144), (2, 4, 262144)]:
+        for Dh in (64, 128):
+            assert P.attention_plan(1, 64, Hkv * G, Hkv, Dh, L)["split_likely"] > 64, (Hkv, G, Dh, L)
+    for B, N_pad, Hq, Hkv, Dh, L in shapes(3000, 5):
+        waves, splits = filling(B, N_pad, Hq, Hkv, L)
+        p = P.attention_plan(B, N_pad, Hq, Hkv, Dh, L)
+        us = P.plan_us(B, N_pad, Hq, Hkv, Dh, L, p["waves"], p["split_likely"])
+        assert us <= P.plan_us(B, N_pad, Hq, Hkv, Dh, L, waves, splits) + 1e-9, (B, N_pad, Hq, Hkv, Dh, L, p)

@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
     (2, [100, 1], 4, 2, 64, [1500, 0]),                               # a lone root without a prefix beside a full tree
     (70, [1 + (7 * i) % 60 for i in range(70)], 4, 4, 64, [(37 * i) % 1100 for i in range(70)]),   # two sequences per lane
     (5, [90, 30, 128, 70, 1], 24, 8, 64, [1100, 64, 65, 700, 4500]),  # more runs for the long ones than full lengths would get
+    (1, [30], 2, 1, 128, [33000]),                                    # more than 64 runs
 ])
 def test_unequal_prefixes(B, n_list, Hq, Hkv, Dh, L_list):
     attention_case(B, n_list, Hq, Hkv, Dh, L_list, seed=11)
