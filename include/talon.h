@@ -210,9 +210,10 @@ int talon_build_tree(const int32_t* root_token, const void* logits, int dtype, i
  * 0 .. rows-1 of every sequence may be read, whether or not the tree turns out to need them
  * (row i at b*seq_stride + i*row_stride elements; a row the tree does not expand may hold
  * anything, a NaN included, and has no effect).  With rows >= N-1 the launch may scan rows ahead of
- * the tree instead of one layer after the other (it does unless that would read far more than a
- * tree of this budget is likely to expand); with fewer it is talon_build_tree.  Same results,
- * arguments and errors; `workspace` as there.
+ * the tree instead of one layer after the other; it reads no more of them than max_depth, K_init
+ * and k allow a tree to expand, and it goes layer by layer where trees have one layer, or where the
+ * scan would read far more than a tree of this budget or depth is likely to expand.  With fewer
+ * rows it is talon_build_tree.  Same results, arguments and errors; `workspace` as there.
  */
 int talon_build_tree_ahead(const int32_t* root_token, const void* logits, int dtype, int64_t row_stride,
                            int64_t seq_stride, int32_t rows, const talon_tree_state* st, int32_t vocab,

@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include "ahead_plan.h"
 #include "attention_plan.h"
 #include "talon_internal.h"
 #ifdef TALON_TUNING
@@ -560,52 +561,16 @@ int talon_build_tree_ahead(const int32_t* root_token, const void* logits, int dt
   ea.spin_ticks = spin_limit_ticks();
   const int resident = ahead_grid_limit(dtype);
   if (resident < 1) { set_error("occupancy query for the scan-ahead kernel failed"); return TALON_ERR_RUNTIME; }
-  ea.ahead_rows = st->N - 1;
-  const long long rows_all = static_cast<long long>(st->B) * ea.ahead_rows;
-  long long scanners = resident - st->B > resident / 2 ? resident - st->B : resident / 2;
-  // Runs of blocks per row: as many as give every scanner of a full grid at most one item.  Items
-  // that nobody has to queue for need no counter, and every further item of a workgroup costs it
-  // about 10 us between two streams (ranking, partial results, tickets): 508 rows of 304 KB take
-  // 52 us as 1016 items and 55-57 us as 1524 or 2032; 4080 rows 250 us whole and 280 us in two.
-  auto runs = [&](long long want) {   // a number of equal runs of whole blocks
-    const int c = want < 1 ? 1 : (want > L.chunks ? L.chunks : static_cast<int>(want));
-    const int bpc = (L.chunks + c - 1) / c;
-    return (L.chunks + bpc - 1) / bpc;
-  };
-  ea.ahead_chunks = runs(tuned_int("TALON_AHEAD_CHUNKS", static_cast<int>(scanners / rows_all)));
-  ea.ahead_head = 0;
-  ea.ahead_chunks_head = 1;
-  const long long two_layers = 1 + (init_layers > 0 && K_init < k ? K_init : k);   // rows of the root and of layer 1
-  if (ea.ahead_chunks * 10 < L.chunks && ea.ahead_rows <= 5 * (two_layers - 1)) {
-    // A budget of at most five times the first layer's width is usually spent when that layer is
-    // expanded, and reading all rows would take several rounds of the grid: most of the scan would
-    // be in vain.  13 or 16 x 72 rows of 513 KB of which 17 per sequence are expanded: 74 us layer by
-    // layer, 82 and 87 ahead.  (Budgets above that, or rows that fit in one round, are faster ahead:
-    // 4 x 127 rows of 513 KB 78 against 104, 16 x 29 of 304 KB 49 against 65.)
+  const AheadPlan plan = ahead_plan(st->B, st->N, L.chunks, k, K_init, init_layers, max_depth, resident);
+  if (plan.layered)
     return talon_build_tree(root_token, logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, k, mu, K_init,
                             init_layers, max_depth, cand_token, cand_logit, cand_prob, cand_edge_logp, row_max, row_lse,
                             mask, workspace, workspace_bytes, stream);
-  }
-  if (ea.ahead_chunks * 10 < L.chunks) {
-    // Runs of more than ten blocks (35 us and more at the full rate): a tree that ends after two or
-    // three layers would wait for whole rows of all sequences to be read before its root's row is
-    // there.  The first rows, as many as fill the grid once, are cut into shorter runs: of five blocks,
-    // or as long as it takes for the rows of the first two layers to fit.
-    const long long one_round = scanners / (st->B * two_layers);
-    const long long shortest = (L.chunks + 4) / 5;
-    ea.ahead_chunks_head = runs(one_round < shortest ? one_round : shortest);
-    const long long fill = scanners / (static_cast<long long>(st->B) * ea.ahead_chunks_head);
-    const long long head = fill > two_layers ? fill : two_layers;
-    ea.ahead_head = head < ea.ahead_rows ? static_cast<int>(head) : ea.ahead_rows;
-    const long long rest = static_cast<long long>(st->B) * (ea.ahead_rows - ea.ahead_head);
-    const int by_size = (L.chunks + 19) / 20;   // at most twenty blocks per run
-    const long long by_grid = rest > 0 ? scanners / rest : 1;
-    ea.ahead_chunks = runs(by_grid > by_size ? by_grid : by_size);
-  }
-  const long long items = static_cast<long long>(st->B) * (static_cast<long long>(ea.ahead_head) * ea.ahead_chunks_head +
-                                                           static_cast<long long>(ea.ahead_rows - ea.ahead_head) * ea.ahead_chunks);
-  if (scanners > items) scanners = items;
-  const int grid = static_cast<int>(scanners) + st->B;
+  ea.ahead_rows = plan.rows;
+  ea.ahead_head = plan.head;
+  ea.ahead_chunks_head = plan.chunks_head;
+  ea.ahead_chunks = plan.chunks;
+  const int grid = plan.scanners + st->B;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (g_profile.enabled && (rc = check_hip(profile_record(s), "profile event"))) return rc;
   rc = check_hip(launch_build_ahead(ea, dtype, grid, s), "scan-ahead launch");

@@ -11,10 +11,16 @@ import tempfile
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SHIM = r"""
+#include "ahead_plan.h"
 #include "attention_plan.h"
 extern "C" {
 size_t t_least(int B, int N_pad, int Hq, int Hkv, int Dh, int L) { return talon::attention_least_workspace(B, N_pad, Hq, Hkv, Dh, L); }
 double t_us(int waves, long long wgs, int run, int splits, int Dh, size_t bytes) { return talon::plan_us(waves, wgs, run, splits, Dh, bytes); }
+void t_ahead(int B, int N, int blocks, int k, int K_init, int init_layers, int max_depth, int resident, int* out) {
+  const talon::AheadPlan p = talon::ahead_plan(B, N, blocks, k, K_init, init_layers, max_depth, resident);
+  const int v[] = {p.layered, p.rows, p.head, p.chunks_head, p.chunks, p.scanners};
+  for (int i = 0; i < 6; ++i) out[i] = v[i];
+}
 void t_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int L, size_t bytes, long long* out) {
   const talon::AttnPlan p = talon::attention_plan(B, N_pad, Hq, Hkv, Dh, L, bytes);
   const long long v[] = {p.waves, p.row_tiles, p.run_bound, p.split_max, p.split_likely, p.capacity_per_head, p.balance, p.run_single,
@@ -61,3 +67,12 @@ def plan_us(B, N_pad, Hq, Hkv, Dh, L, waves, splits):
     wgs = B * Hkv * row_tiles * splits
     return _lib().t_us(waves, wgs, -(-((L + 63) // 64 + N_pad // 64) // splits), splits, Dh,
                        wgs * 32 * waves * (2 * Dh + 8) if splits > 1 else 256)
+
+
+def ahead_plan(B, N, vocab, dtype, k, max_depth, K_init=None, init_layers=1, resident=1024):
+    """The plan of talon_build_tree_ahead (resident: four workgroups on each of 256 compute units)."""
+    out = (ctypes.c_int * 6)()
+    per_block = 4096 if dtype == "f32" else 8192
+    _lib().t_ahead(B, N, -(-vocab // per_block), k, K_init or k, init_layers, max_depth, resident, out)
+    p = dict(zip(("layered", "rows", "head", "chunks_head", "chunks", "scanners"), out))
+    return dict(p, blocks=-(-vocab // per_block))

@@ -8,10 +8,11 @@ pytestmark = pytest.mark.gpu
 
 def rows_of(B, N, V, dtype, seed, lo=0.5, hi=4.0):
     import torch
-    g = torch.Generator().manual_seed(seed)
-    x = torch.randn(B, N, V, generator=g) * (lo + (hi - lo) * torch.rand(B, N, 1, generator=g))
+    on = "cuda" if B * N * V > 5e7 else "cpu"
+    g = torch.Generator(device=on).manual_seed(seed)
+    x = torch.randn(B, N, V, generator=g, device=on) * (lo + (hi - lo) * torch.rand(B, N, 1, generator=g, device=on))
     V8 = (V + 7) // 8 * 8
-    pool = torch.zeros(B, N, V8, dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    pool = torch.zeros(B, N, V8, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device=on)
     pool[:, :, :V] = x.to(pool.dtype)
     return pool.cuda()[:, :, :V]
 
@@ -61,7 +62,11 @@ def same(a, b):
     (1, 70001, "f32", 4, 255, 24, 0),     # many short runs per row, no top-K layer
     (70, 1025, "bf16", 4, 20, 5, 1),      # more sequences than a wavefront has lanes
     (8, 20000, "bf16", 16, 256, 24, 2),   # 2040 rows: scanners take further items from the counter
-    (2, 8192, "bf16", 10, 60, 1, 1),      # one layer: all rows but the root's are scanned in vain
+    (2, 8192, "bf16", 10, 60, 1, 1),      # one layer: scanned layer by layer
+    (16, 151936, "bf16", 16, 60, 12, 1),  # a budget near the first layer's width: scanned layer by layer
+    (3, 128256, "bf16", 8, 200, 2, 1),    # two layers: 9 rows of 199 are scanned
+    (2, 20000, "f32", 8, 128, 3, 0),      # three layers: 73 rows of 127
+    (8, 128256, "f32", 16, 256, 24, 1),   # several runs per row, shorter ones for the first rows
 ])
 def test_rows_scanned_ahead_build_the_same_trees(B, V, dtype, k, N, Dmax, init_layers):
     logits = rows_of(B, N, V, dtype, seed=100 * N + k)
