@@ -80,7 +80,7 @@ __device__ __forceinline__ int ahead_items(const ExpandArgs& a) {
 // a counter, in order: workgroups (and whole compute dies) progress at different speeds, and a
 // row that a slow one holds back may be the one a selector waits for.  (Counters per die were
 // tried: the slowest die's rows came 30 us late in a launch of 250 us.)
-template <int EPL, bool PREFETCH>
+template <int EPL>
 __device__ __forceinline__ void scan_rows(const ExpandArgs& a, ScannerLds& s, const int wg, const int n_wg) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -115,7 +115,7 @@ __device__ __forceinline__ void scan_rows(const ExpandArgs& a, ScannerLds& s, co
     const int blk1 = blk0 + bpc < blocks_per_row ? blk0 + bpc : blocks_per_row;
     float m;
     double sum;
-    const bool scanned = scan_chunk<EPL, PREFETCH, true>(row, a.vocab, k, blk0, blk1, L, m, sum, stop_word(a, b), &s.stop);
+    const bool scanned = scan_chunk<EPL, false, true>(row, a.vocab, k, blk0, blk1, L, m, sum, stop_word(a, b), &s.stop);
     // (the counter is asked here: at the start of an item the row's first loads would wait behind a
     // thousand atomics on one word, about 20 ns each)
     int next = n_items;
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(kThreads, 4) void build_ahead_kernel(ExpandArgs a) 
   const bool scanner = static_cast<int>(blockIdx.x) < scanners;
   const uint32_t group = blockIdx.x % kExitGroups;
   if (scanner) {
-    scan_rows<EPL, false>(a, *reinterpret_cast<ScannerLds*>(s_lds), blockIdx.x, scanners);
+    scan_rows<EPL>(a, *reinterpret_cast<ScannerLds*>(s_lds), blockIdx.x, scanners);
     stores_performed();
     __syncthreads();
     exit_ticket(a.exit_ticket + 1 + group, true);

@@ -222,12 +222,14 @@ constexpr int kScanBytes = kHitvBytes + kHithBytes + kCkBytes;
 // PREFETCH: issue the loads of the next block before the current one is processed.
 // WATCH: the first wavefront polls `stop` every kWatchBlocks blocks (the load travels with the block's
 // own loads) and tells the others through *s_stop (LDS, zero on entry); once the word is non-zero the
-// run is given up, and the call returns false in every thread.
+// run is given up, and the call returns false in every thread.  (Not together with PREFETCH: the
+// scanners that watch have no registers for it.)
 constexpr int kWatchBlocks = 2;   // a thousand workgroups polling a word per block and wavefront hold up its memory channel
 template <int EPL, bool PREFETCH, bool WATCH>
 __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, const int k, const int blk0, const int blk1,
                                            const ScanLds& L, float& cm, double& csum, const int32_t* stop = nullptr,
                                            int* s_stop = nullptr) {
+  static_assert(!(PREFETCH && WATCH), "the word is polled with a block's own loads");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -318,9 +320,7 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
     if (wave_u == 0 && __builtin_amdgcn_readfirstlane(word) != 0) *reinterpret_cast<volatile int*>(s_stop) = 1;
     return *reinterpret_cast<volatile int*>(s_stop) != 0;
   };
-  int32_t stop_next = 0;
   if constexpr (PREFETCH) {
-    if constexpr (WATCH) stop_next = watch_issue(tb);
     if (tb < t1) load_group(tb, raw_next);
   }
   while (!done) {
@@ -332,16 +332,13 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
       if constexpr (PREFETCH) {
 #pragma unroll
         for (int q = 0; q < kScanTiles; ++q) raw[q] = raw_next[q];
-        if constexpr (WATCH) {
-          if (watch_test(stop_next)) { given_up = true; break; }
-          stop_next = watch_issue(tb + kScanTiles);
-        }
         if (tb + kScanTiles < t1) load_group(tb + kScanTiles, raw_next);
       } else {
-        if constexpr (WATCH) stop_next = watch_issue(tb);
+        int32_t stop_now = 0;
+        if constexpr (WATCH) stop_now = watch_issue(tb);
         load_group(tb, raw);
         if constexpr (WATCH) {
-          if (watch_test(stop_next)) { given_up = true; break; }
+          if (watch_test(stop_now)) { given_up = true; break; }
         }
       }
       // lane maxima of the 4 tiles first; the running max moves at most once per group
