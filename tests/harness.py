@@ -24,6 +24,14 @@ LSE_ATOL = 2e-6     # row log-sum-exp, absolute
 #                        six standard deviations (millions of elements are compared)
 ATTN_OUT_RTOL = 2.0 ** -8
 ATTN_KEYS_ATOL = 2.2e-2      # divided by sqrt(number of keys the row attends to)
+# Where a prefix is cut into runs, their outputs are rounded to bf16 before the merge: a relative
+# delta_r per run, |delta_r| <= 2^-8, independent.  A run of keys_r keys has an output of about
+# sqrt(e / keys_r) and a weight of keys_r / keys, so the error has a standard deviation of
+# 2^-8 / sqrt(3) * sqrt(sum_r (keys_r / keys)^2 e / keys_r) = 3.7e-3 / sqrt(keys), however many runs there
+# are: as much again as the weights' rounding, independent of it.  (Over eight seeds of each of the four balanced
+# batches of the plan tests the largest element is 0.62 to 1.05 of the bound without this term, 0.62 to 1.00
+# with the plan that only fills the chip.)
+ATTN_KEYS_ATOL_CUT = ATTN_KEYS_ATOL * math.sqrt(2.0)
 ATTN_LSE_ATOL = 2e-5         # fp32 scores and denominators against fp64 (observed worst 1.6e-6)
 
 
@@ -109,11 +117,23 @@ def run_oracle_step(cfg: WorkloadConfig, seeds=None, pool=None, attn=None, attn_
 
 
 # --------------------------------------------------------------------------- GPU side
+def build_tree_layered(roots, logits, st, k, mu, K_init, init_layers, max_depth, cand, ws, mask=None):
+    """The C call talon_build_tree: one launch that scans one layer after the other.  (The binding's
+    talon_build_tree goes through talon_build_tree_ahead, which serves rows by node with another launch.)"""
+    from paper_2601_07353_amd import binding as N
+    dt, row_stride, seq_stride, V = N._logits_meta(logits)
+    N._check(N.load_library().talon_build_tree(
+        N._ptr(roots), N._ptr(logits), dt, row_stride, seq_stride, N.TALON_ROWS_BY_NODE, N._byref(st.c), V, k, mu, K_init,
+        init_layers, max_depth, N._ptr(cand.token), N._ptr(cand.logit), N._ptr(cand.prob), N._ptr(cand.edge_logp),
+        N._ptr(cand.row_max), N._ptr(cand.row_lse), N._ptr(mask), N._ptr(ws), ws.nbytes, N._stream(None)))
+
+
 def run_gpu_expand(cfg: WorkloadConfig, pool_dev, init_layers=1, mu=None, K_init=None, layerwise=False):
-    """Whole expansion loop on the GPU.  Default: talon_build_tree (init, loop and mask in two
-    launches; the mask is returned).  layerwise="tree": talon_tree_init + talon_expand_tree;
+    """Whole expansion loop on the GPU.  Default: talon_build_tree (init, loop and mask in one
+    launch; the mask is returned), rows scanned ahead of the tree.  layerwise="layered": the C call
+    talon_build_tree, one layer after the other (the mask is returned).  layerwise="tree": talon_tree_init + talon_expand_tree;
     "fused": one talon_expand_select_layer per layer; True / "split": talon_expand_layer +
-    talon_select_budget per layer.  Those three return no mask."""
+    talon_select_budget per layer.  Those last three return no mask."""
     import torch
     import paper_2601_07353_amd as T
     st = T.TreeState(cfg.B, cfg.N)
@@ -132,14 +152,15 @@ def run_gpu_expand(cfg: WorkloadConfig, pool_dev, init_layers=1, mu=None, K_init
     elif layerwise == "tree":
         T.talon_tree_init(st, roots)
         T.talon_expand_tree(pool_dev, st, cfg.K, mu, K_init, init_layers, cfg.Dmax, cand, ws)
-    elif layerwise:
+    elif layerwise and layerwise != "layered":
         T.talon_tree_init(st, roots)
         for d in range(cfg.Dmax):
             T.talon_expand_layer(pool_dev, st, cfg.K, cand, ws, layer=d if d % 2 == 0 else -1)
             T.talon_select_budget(st, cfg.K, cand, mu, K_init, init_layers, cfg.Dmax)
     else:
         mask = torch.full((cfg.B, st.N_pad, st.N_pad // 64), -1, dtype=torch.int64, device="cuda")
-        T.talon_build_tree(roots, pool_dev, st, cfg.K, mu, K_init, init_layers, cfg.Dmax, cand, ws, mask=mask)
+        build = build_tree_layered if layerwise == "layered" else T.talon_build_tree
+        build(roots, pool_dev, st, cfg.K, mu, K_init, init_layers, cfg.Dmax, cand, ws, mask=mask)
     torch.cuda.synchronize()
     return st, cand, ws, mask
 
@@ -257,7 +278,7 @@ def compare_mask(cfg: WorkloadConfig, gpu: dict, masks):
         np.testing.assert_array_equal(gpu["mask"][b], O.mask_to_words(m, cfg.N_pad))
 
 
-def check_attention_rows(got_out, got_lse, want_out, want_lse, keys, where=()):
+def check_attention_rows(got_out, got_lse, want_out, want_lse, keys, where=(), keys_atol=ATTN_KEYS_ATOL):
     """Rows [n][Hq][Dh] of one sequence against the oracle's (NaN = not computed, skipped).
     `keys`: keys each node attends to (a number, or one per node).  Two bounds on every element:
     the stated 2e-2 absolute, and the signal-tied one derived above.  Returns the worst output
@@ -269,7 +290,7 @@ def check_attention_rows(got_out, got_lse, want_out, want_lse, keys, where=()):
     worst = float(err.max())
     assert worst <= ATTN_ATOL, (where, worst)
     keys = np.broadcast_to(np.asarray(keys, dtype=np.float64), want_out.shape[:1])
-    tol = ATTN_OUT_RTOL * np.abs(np.where(sel, want_out, 0.0)) + (ATTN_KEYS_ATOL / np.sqrt(keys))[:, None, None]
+    tol = ATTN_OUT_RTOL * np.abs(np.where(sel, want_out, 0.0)) + (keys_atol / np.sqrt(keys))[:, None, None]
     bad = err > tol
     assert not bad.any(), (where, "signal-tied bound", float((err / tol).max()), np.argwhere(bad)[:4].tolist())
     worst_lse = 0.0

@@ -96,3 +96,23 @@ def test_long_prefixes_of_few_heads_fill_the_chip():
         p = P.attention_plan(B, N_pad, Hq, Hkv, Dh, L)
         us = P.plan_us(B, N_pad, Hq, Hkv, Dh, L, p["waves"], p["split_likely"])
         assert us <= P.plan_us(B, N_pad, Hq, Hkv, Dh, L, waves, splits) + 1e-9, (B, N_pad, Hq, Hkv, Dh, L, p)
+
+
+def device_run(p, n_list, G, L_list):
+    """The run length the balanced kernels work out from the lengths of a batch."""
+    tiles = [-(-L // 64) + -(-n // 64) for n, L in zip(n_list, L_list)]
+    row_tiles = [-(-n * G // (32 * p["waves"])) for n in n_list]
+    for run in range(max(4, -(-max(tiles) // p["split_max"])), p["run_bound"]):
+        if sum(r * (1 if t <= p["run_single"] else -(-t // run)) for r, t in zip(row_tiles, tiles)) <= p["capacity_per_head"]:
+            return run
+    return p["run_bound"]
+
+
+def test_the_balanced_batches_of_the_gpu_tests_reach_all_four_kernels():
+    from tests.test_gpu_attention_plan import BALANCED
+    reached = set()
+    for B, n_list, Hq, Hkv, Dh, L_list in BALANCED:
+        p = P.attention_plan(B, (max(n_list) + 63) // 64 * 64, Hq, Hkv, Dh, max(L_list))
+        assert p["balance"] and device_run(p, n_list, Hq // Hkv, L_list) < p["run_bound"], (p, n_list, L_list)
+        reached.add((Dh, p["waves"]))
+    assert reached == {(64, 4), (64, 8), (128, 4), (128, 8)}

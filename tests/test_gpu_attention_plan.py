@@ -1,5 +1,6 @@
-"""Split-KV plans of tree attention: batches of unequal prefixes (the run length is worked out on the
-device), and calls whose workspace was sized for another prefix."""
+"""Split-KV plans of tree attention: batches of unequal prefixes (with the balancing, the run length is
+worked out on the device; without it, runs beyond the end of a sequence are empty), and calls whose
+workspace was sized for another prefix."""
 import numpy as np
 import pytest
 
@@ -7,6 +8,21 @@ from tests import harness as H
 from tests.test_gpu_parity import attention_case
 
 pytestmark = pytest.mark.gpu
+
+
+# Batches that balance, with runs shorter than full-length prefixes would get: one for each of the four
+# kernels (heads of 64 and 128, 4 and 8 wavefronts).
+BALANCED = [
+    (3, [115, 10, 4], 32, 4, 128, [4, 299, 2471]),                    # 128, 8 wavefronts
+    (5, [129, 42, 49, 38, 61], 12, 4, 128, [37, 603, 707, 2363, 196]),   # 128, 4
+    (3, [3, 104, 6], 32, 4, 64, [2596, 43, 217]),                     # 64, 8
+    (5, [130, 19, 17, 24, 14], 12, 4, 64, [70, 244, 2061, 473, 1487]),   # 64, 4
+]
+
+
+@pytest.mark.parametrize("B,n_list,Hq,Hkv,Dh,L_list", BALANCED)
+def test_unequal_prefixes_that_share_the_grid(B, n_list, Hq, Hkv, Dh, L_list):
+    attention_case(B, n_list, Hq, Hkv, Dh, L_list, seed=12, keys_atol=H.ATTN_KEYS_ATOL_CUT)
 
 
 @pytest.mark.parametrize("B,n_list,Hq,Hkv,Dh,L_list", [
@@ -87,6 +103,10 @@ def test_sequences_of_one_filling_run_are_rounded_once(n_list, Hq, Hkv, Dh, most
     ws = torch.empty(T.talon_tree_attention_workspace_bytes(B, P, Hq, Hkv, Dh, most), dtype=torch.uint8, device="cuda")
     out = torch.zeros(B, P, Hq, Dh, dtype=torch.bfloat16, device="cuda")
     T.talon_tree_attention(q, kp, vp, kt, vt, mask, st.n_nodes, plen, most, out, workspace=ws)
+    again = torch.zeros_like(out)
+    ws.fill_(0x7F)
+    T.talon_tree_attention(q, kp, vp, kt, vt, mask, st.n_nodes, plen, most, again, workspace=ws)
+    assert torch.equal(out, again)          # the same call on the same data repeats itself bit for bit
     single = 0
     for b in range(B):
         n, L = n_list[b], L_list[b]

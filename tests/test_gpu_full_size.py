@@ -84,6 +84,10 @@ def run_config(cfg_name):
         np.testing.assert_array_equal(gpu["mask"][b], O.mask_to_words(masks[b], cfg.N_pad))
         # rows of nodes beyond n_nodes are untouched
         assert not gpu["attn_out"][b, int(gpu["n_nodes"][b]):].any()
+    # ... and the launch that scans one layer after the other, which the C call talon_build_tree makes
+    layered = H.run_gpu_step(cfg, seeds, pool=pool, with_attention=False, layerwise="layered")
+    H.compare_tree(cfg, layered, trees)
+    H.compare_mask(cfg, layered, masks)
     return cfg, gpu, trees, masks, attn, pool
 
 

@@ -39,7 +39,7 @@ def test_c1_tiny_step():
     assert ref["trees"][0].n == 16
 
 
-@pytest.mark.parametrize("mode", ["split", "fused", "tree"])
+@pytest.mark.parametrize("mode", ["split", "fused", "tree", "layered"])
 def test_c1_layerwise_entry_points_match_single_call(mode):
     cfg = CONFIGS["c1"]
     seeds = admissible_seeds(cfg)
@@ -49,20 +49,22 @@ def test_c1_layerwise_entry_points_match_single_call(mode):
         np.testing.assert_array_equal(a[key], b[key])
 
 
-def test_tree_launch_gives_up_cleanly_when_the_wait_is_cut_short():
-    """The single-launch loop bounds its wait between layers.  With the bound forced to zero from
-    the host, a workgroup either finds the layer already complete or gives up: the launch must
-    end, and every sequence is then either expanded exactly as usual or marked ABORTED."""
+@pytest.mark.parametrize("form", [False, "layered"])
+def test_tree_launch_gives_up_cleanly_when_the_wait_is_cut_short(form):
+    """Both single launches (rows scanned ahead of the tree, one layer after the other) bound their
+    waits.  With the bound forced to zero from the host, a workgroup either finds what it waits for
+    or gives up: the launch must end, and every sequence is then either expanded exactly as usual or
+    marked ABORTED."""
     import torch
     import paper_2601_07353_amd as T
     cfg = small(name="abort", V=40000, logits_dtype="bf16", K=8, N=100, Dmax=12, B=3,
                 recipe=(("gauss", 6.0, 8.0), ("gauss", 0.5, 1.0), ("gauss", 2.0, 8.0)))
     seeds = admissible_seeds(cfg)
     pool = H.build_pool(cfg, seeds)
-    ref = H.run_gpu_step(cfg, seeds, pool=pool, with_attention=False)
+    ref = H.run_gpu_step(cfg, seeds, pool=pool, with_attention=False, layerwise=form)
     T.talon_set_spin_limit_us(0)
     try:
-        got = H.run_gpu_step(cfg, seeds, pool=pool, with_attention=False)
+        got = H.run_gpu_step(cfg, seeds, pool=pool, with_attention=False, layerwise=form)
         torch.cuda.synchronize()
     finally:
         T.talon_set_spin_limit_us(200000)
@@ -73,7 +75,7 @@ def test_tree_launch_gives_up_cleanly_when_the_wait_is_cut_short():
             np.testing.assert_array_equal(got[key], ref[key])
     else:
         assert np.all(got["n_nodes"] >= 1) and np.all(got["n_nodes"] <= cfg.N)
-    again = H.run_gpu_step(cfg, seeds, pool=pool, with_attention=False)
+    again = H.run_gpu_step(cfg, seeds, pool=pool, with_attention=False, layerwise=form)
     for key in ("token", "parent", "depth", "n_nodes", "status"):
         np.testing.assert_array_equal(again[key], ref[key])
 
@@ -122,10 +124,11 @@ def test_a_launch_that_gives_up_is_rebuilt_layer_by_layer():
     H.compare_mask(cfg, got, ref["mask"])
 
 
-def _expand_on(cfg, pool_dev, st, cand, ws, mask, roots):
+def _expand_on(cfg, pool_dev, st, cand, ws, mask, roots, form="ahead"):
     import torch
     import paper_2601_07353_amd as T
-    T.talon_build_tree(roots, pool_dev, st, cfg.K, cfg.mu, cfg.K, 1, cfg.Dmax, cand, ws, mask=mask)
+    build = H.build_tree_layered if form == "layered" else T.talon_build_tree
+    build(roots, pool_dev, st, cfg.K, cfg.mu, cfg.K, 1, cfg.Dmax, cand, ws, mask=mask)
     torch.cuda.synchronize()
     n = [int(x) for x in st.n_nodes.cpu()]
     return {"n": n, "status": st.status.cpu().numpy().copy(),
@@ -143,9 +146,10 @@ def _same_trees(a, b):
             np.testing.assert_array_equal(x, y)
 
 
-def test_one_workspace_serves_call_after_call():
-    """talon_build_tree leaves its workspace as it found it: the same workspace, tree state and
-    output buffers serve 40 calls that alternate between two inputs, then a launch that is
+@pytest.mark.parametrize("form", ["ahead", "layered"])
+def test_one_workspace_serves_call_after_call(form):
+    """talon_build_tree (rows scanned ahead of the tree, or one layer after the other) leaves its
+    workspace as it found it: the same workspace, tree state and output buffers serve 40 calls that alternate between two inputs, then a launch that is
     made to give up (wait bound forced to zero from the host), then the two inputs again;
     every complete call must give exactly what a call on a fresh workspace gives."""
     import torch
@@ -166,25 +170,25 @@ def test_one_workspace_serves_call_after_call():
     want = []
     for p in pools:
         st, cand, ws, mask = fresh()
-        want.append(_expand_on(cfg, p, st, cand, ws, mask, roots))
+        want.append(_expand_on(cfg, p, st, cand, ws, mask, roots, form))
     assert want[0]["token"][0].tolist() != want[1]["token"][0].tolist()
     st, cand, ws, mask = fresh()
     for i in range(40):
-        _same_trees(_expand_on(cfg, pools[i % 2], st, cand, ws, mask, roots), want[i % 2])
+        _same_trees(_expand_on(cfg, pools[i % 2], st, cand, ws, mask, roots, form), want[i % 2])
     T.talon_set_spin_limit_us(0)
     try:
-        cut = _expand_on(cfg, pools[0], st, cand, ws, mask, roots)
+        cut = _expand_on(cfg, pools[0], st, cand, ws, mask, roots, form)
     finally:
         T.talon_set_spin_limit_us(200000)
     aborted = (cut["status"] & T.TALON_STATUS_ABORTED) != 0
     assert aborted.all() or not aborted.any()
     for i in range(6):
-        _same_trees(_expand_on(cfg, pools[i % 2], st, cand, ws, mask, roots), want[i % 2])
+        _same_trees(_expand_on(cfg, pools[i % 2], st, cand, ws, mask, roots, form), want[i % 2])
 
 
 def test_launch_forms_share_one_workspace():
-    """All four launch forms (whole tree in one launch, continued tree in one launch, one fused
-    launch per layer, scan and selection as separate launches) take turns on ONE workspace and
+    """All five launch forms (whole tree in one launch, rows scanned ahead or one layer after the
+    other, continued tree in one launch, one fused launch per layer, scan and selection as separate launches) take turns on ONE workspace and
     tree state, on two inputs: none may leave anything behind that another one trips over."""
     import torch
     import paper_2601_07353_amd as T
@@ -222,6 +226,9 @@ def test_launch_forms_share_one_workspace():
     def whole(p):
         T.talon_build_tree(roots, p, st, cfg.K, cfg.mu, cfg.K, 1, cfg.Dmax, cand, ws, mask=mask)
 
+    def layered(p):
+        H.build_tree_layered(roots, p, st, cfg.K, cfg.mu, cfg.K, 1, cfg.Dmax, cand, ws, mask)
+
     def continued(p):
         T.talon_tree_init(st, roots)
         T.talon_expand_tree(p, st, cfg.K, cfg.mu, cfg.K, 1, cfg.Dmax, cand, ws)
@@ -242,15 +249,17 @@ def test_launch_forms_share_one_workspace():
         whole(p)
         want.append(snapshot())
     order = [(whole, 0), (per_layer, 1), (whole, 0), (continued, 1), (split, 0), (whole, 1), (continued, 0),
-             (per_layer, 0), (whole, 1), (split, 1), (continued, 1), (whole, 0)]
+             (per_layer, 0), (whole, 1), (split, 1), (continued, 1), (whole, 0), (layered, 1), (whole, 0), (layered, 0),
+             (per_layer, 1), (layered, 0), (continued, 1), (layered, 1), (split, 0), (layered, 0)]
     for form, which in order:
         form(pools[which])
         same(snapshot(), want[which])
 
 
 def test_captured_steps_replay_like_eager_ones():
-    """A serving loop captures its step once and replays it.  Two graphs over ONE workspace and tree
-    state (one launch per layer + mask; the whole tree in one launch) are replayed in turns, with
+    """A serving loop captures its step once and replays it.  Three graphs over ONE workspace and
+    tree state (one launch per layer + mask; the whole tree in one launch, rows scanned ahead or
+    layer by layer) are replayed in turns, with
     the logits buffer they read rewritten, eager launches of the other forms and synchronisations
     between the replays: every replay must give the tree and mask the eager launch gives, so the
     counters the launches share (row tickets, the two per-layer counts, exit tickets) have to be
@@ -292,6 +301,9 @@ def test_captured_steps_replay_like_eager_ones():
     def whole(p):
         T.talon_build_tree(roots, p, st, cfg.K, cfg.mu, cfg.K, 1, cfg.Dmax, cand, ws, mask=mask)
 
+    def layered(p):
+        H.build_tree_layered(roots, p, st, cfg.K, cfg.mu, cfg.K, 1, cfg.Dmax, cand, ws, mask)
+
     want = []
     for p in pools:
         per_layer(p)
@@ -305,16 +317,17 @@ def test_captured_steps_replay_like_eager_ones():
         live.copy_(pools[0])
         per_layer(live)
         whole(live)
+        layered(live)
     torch.cuda.current_stream().wait_stream(side)
     torch.cuda.synchronize()
-    for name, form in (("per_layer", per_layer), ("whole", whole)):
+    for name, form in (("per_layer", per_layer), ("whole", whole), ("layered", layered)):
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g, stream=side):
             form(live)
         graphs[name] = g
 
     order = [("per_layer", 1), ("per_layer", 2), ("whole", 0), ("per_layer", 0), ("whole", 1), ("per_layer", 1),
-             ("per_layer", 2), ("whole", 2), ("per_layer", 0)]
+             ("per_layer", 2), ("whole", 2), ("per_layer", 0), ("layered", 1), ("whole", 2), ("layered", 0)]
     for i, (name, which) in enumerate(order):
         live.copy_(pools[which])
         mask.fill_(-1)
@@ -569,7 +582,7 @@ def test_integer_outputs_are_reproducible_run_to_run():
 
 
 # ----------------------------------------------------------------------------- attention only
-def attention_case(B, n_list, Hq, Hkv, Dh, L_list, seed, parents=None):
+def attention_case(B, n_list, Hq, Hkv, Dh, L_list, seed, parents=None, keys_atol=H.ATTN_KEYS_ATOL):
     """Random trees (random parent pointers) straight into mask + attention, ragged prefix lengths."""
     import torch
     import paper_2601_07353_amd as T
@@ -610,7 +623,7 @@ def attention_case(B, n_list, Hq, Hkv, Dh, L_list, seed, parents=None):
         np.testing.assert_array_equal(gmask[b], O.mask_to_words(m, N_pad))
         f = H.bf16_bits_to_f64
         want, wlse = O.tree_attention(f(q[b, :n]), f(kp[b, :L]), f(vp[b, :L]), f(kt[b, :n]), f(vt[b, :n]), m)
-        err, _ = H.check_attention_rows(got[b, :n], got_lse[b, :n], want, wlse, L + m.sum(axis=1), (b,))
+        err, _ = H.check_attention_rows(got[b, :n], got_lse[b, :n], want, wlse, L + m.sum(axis=1), (b,), keys_atol)
         worst = max(worst, err)
         assert not got[b, n:].any()
     return worst
