@@ -671,6 +671,8 @@ __global__ __launch_bounds__(kThreads) void tree_attention_combine_kernel(AttnAr
   if constexpr (BALANCE) {
     const int counted = a.part_count[b];               // (nobody writes it for a sequence without nodes)
     splits = counted < a.split_max ? counted : a.split_max;
+    // (where full-length prefixes have one run, most sequences have nothing to merge: no loads on a guess)
+    if (a.split_likely == 1 && splits <= 1) return;
   }
   const size_t block0 = static_cast<size_t>(bg) * a.split_max * a.rows_pad;
   const size_t base = block0 + rho;

@@ -148,7 +148,8 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
   // have to be long enough for it to matter.
   // The plan that fills the chip balances within the workspace of the search only: at heads of 128 that
   // leaves it as it is for 2, 4, 8 or 16 sequences of 8 KV heads, whose partial results fill it.
-  // Another plan may take what twice its runs need.  It was chosen for full-length prefixes, and
+  // Another plan of two runs or more may take what twice its runs need (one of a single run would stage
+  // rows that it otherwise passes to the output in fp32).  It was chosen for full-length prefixes, and
   // unequal ones can leave it slower than the filling one: 3 sequences of 68 nodes, 64/16 heads of 64,
   // prefixes of 4525, 6643 and 9213 of 14916 keys took 119 us unbalanced, 97 with the filling plan, 100 balanced; 7 of
   // 93 nodes, 16/2 heads of 128, up to 9396 keys 64, 108 and 50.
@@ -159,7 +160,7 @@ inline AttnPlan attention_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int ma
   long long wgs = all * best_splits;
   if (B > 1 && staged && best.run_bound >= 2 * kLeastRun) {
     const long long rounds = (wgs + slots - 1) / slots;
-    const size_t room = other ? bytes : search_bytes;
+    const size_t room = other && best_splits > 1 ? bytes : search_bytes;
     for (int m = 2 * best_splits; m > best_splits; --m)
       if (partial_bytes(all, m, mt, Dh) + table <= room) { best.split_max = m; break; }
     if (best.split_max > best_splits) {

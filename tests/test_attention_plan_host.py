@@ -78,7 +78,7 @@ def test_plans_that_leave_the_filling_one_share_the_grid_among_unequal_prefixes(
     for B, N_pad, Hq, Hkv, Dh, L in shapes(4000, 4):
         waves, splits = filling(B, N_pad, Hq, Hkv, L)
         p = P.attention_plan(B, N_pad, Hq, Hkv, Dh, L)
-        if B == 1 or splits == 1 or (p["waves"], p["split_likely"]) == (waves, splits) or p["run_bound"] < 8:
+        if B == 1 or p["split_likely"] == 1 or (p["waves"], p["split_likely"]) == (waves, splits) or p["run_bound"] < 8:
             continue
         seen += 1
         assert p["balance"] and p["split_max"] == 2 * p["split_likely"], (B, N_pad, Hq, Hkv, Dh, L, p)
