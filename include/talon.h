@@ -7,9 +7,9 @@
  *   - Every pointer is a DEVICE pointer unless it is marked "host".  The caller owns every
  *     buffer and the library allocates no device memory.  State it keeps between calls, all of
  *     it host-side and per process: the measurement hook's HIP events (created on demand while
- *     the hook is enabled), the wait bound of talon_set_spin_limit_us, two cached launch facts
- *     (how many workgroups of the single-launch kernel the device holds at once; that the
- *     attention kernel's LDS size has been raised), and the device address of the scratch
+ *     the hook is enabled), the wait bound of talon_set_spin_limit_us, cached launch facts
+ *     (how many workgroups of the two single-launch kernels the device holds at once; that the
+ *     attention kernels' LDS size has been raised), and the device address of the scratch
  *     array of talon_tree_attention_static.  None of it depends on the arguments of a call.
  *   - Calls only enqueue work on `stream` (a hipStream_t passed as void*; NULL = the null
  *     stream) and return at once.  Nothing synchronises with the host.
@@ -52,7 +52,7 @@ extern "C" {
 #define TALON_STATUS_DONE_BUDGET 1u /* |T| reached N (Alg. 2 loop condition false)    */
 #define TALON_STATUS_DONE_DEPTH 2u  /* max_depth layers built before the budget ran out */
 #define TALON_STATUS_BAD_ROW 4u     /* NaN / +inf logit or a row with no finite maximum */
-#define TALON_STATUS_ABORTED 8u     /* talon_expand_tree gave up waiting between two layers */
+#define TALON_STATUS_ABORTED 8u     /* a single launch gave up waiting (talon_set_spin_limit_us) */
 
 /* logits row addressing for talon_expand_layer */
 #define TALON_ROWS_BY_NODE 0     /* row of node i of sequence b = i                        */
@@ -180,8 +180,8 @@ int talon_expand_tree(const void* logits, int dtype, int64_t row_stride, int64_t
                       void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * Bound of the wait between two layers inside talon_expand_tree / talon_build_tree, in
- * microseconds (default 200000).  A launch whose workgroups cannot all be resident (the device
+ * Bound of the waits inside a single launch, in microseconds (default 200000): between two layers in
+ * talon_expand_tree and talon_build_tree, for the rows of a layer in talon_build_tree_ahead.  A launch whose workgroups cannot all be resident (the device
  * is shared with other work) ends after this long with TALON_STATUS_ABORTED on every sequence
  * instead of hanging; the caller then re-runs the step layer by layer with
  * talon_tree_init + talon_expand_select_layer on the same workspace.  0 makes every wait give
@@ -277,9 +277,9 @@ int talon_expand_literal(const void* logits, int dtype, int64_t row_stride, int6
                          void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * Measurement hook (no counterpart in the paper).  While enabled, talon_expand_tree and
- * talon_expand_select_layer record a HIP event on the launch stream before and after every
- * fused scan launch; talon_profile_read waits for them, writes the first `capacity`
+ * Measurement hook (no counterpart in the paper).  While enabled, talon_expand_tree,
+ * talon_build_tree, talon_build_tree_ahead and talon_expand_select_layer record a HIP event on the
+ * launch stream before and after every fused scan launch; talon_profile_read waits for them, writes the first `capacity`
  * durations in microseconds (launch order) to the host array `durations_us`, stores the
  * number of launches recorded since the last read in *n_launches and starts over.  Not to
  * be enabled while a stream is being captured into a graph.  Not thread-safe.

@@ -112,10 +112,11 @@ __device__ __forceinline__ bool write_row(const ExpandArgs& a, int b, int out_ro
 // or one launch that walks all layers.
 constexpr int kModeSplit = 0, kModeFused = 1, kModeTree = 2;
 
-// Launches of one layer: workgroups that have read the frontier, counted in kStartedWords words on
-// memory lines of their own (in the descriptors of layers >= 1, which these launches do not use and
-// every launch leaves zero).  An atomic on one word takes about 20 ns: 900 workgroups on a single
-// counter kept a selection waiting for 18 us, longer than the layer's scan.
+// Launches of one layer: workgroups that have read the frontier, counted in kStartedWords words spread
+// evenly over the descriptors of layers >= 1 (which these launches do not use and every launch leaves
+// zero): on memory lines of their own from B * (N_pad - 1) = 128 descriptors on, two or three to a
+// line for one sequence of 64 nodes.  An atomic on one word takes about 20 ns: 900 workgroups on a
+// single counter kept a selection waiting for 18 us, longer than the layer's scan.
 constexpr int kStartedWords = 8;
 __device__ __forceinline__ uint32_t* started_word(const ExpandArgs& a, int x) {
   return reinterpret_cast<uint32_t*>(a.desc + a.B + static_cast<size_t>(x) * (a.B * (a.N_pad - 1) / kStartedWords));
