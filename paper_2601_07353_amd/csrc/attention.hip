@@ -20,7 +20,8 @@
 // of a sequence); prefix tiles need no mask except the ragged last one.
 //
 // Split-KV partial results (O normalised by its own denominator, running max, denominator) go to a
-// workspace and are merged by a second kernel; a sequence of one split has its output written directly.
+// workspace and are merged by a second kernel.  Where nothing has more than one run, and with BALANCE
+// for every sequence of one run, the output is written directly.
 #include <type_traits>
 
 #include "attention_plan.h"
