@@ -309,7 +309,7 @@ int talon_prune_tree(const talon_tree_state* st, int32_t n_keep, int32_t* kept_i
  *   target_token [B][N_pad] int32 (largest logit, lowest id among equals; rows >= n_nodes
  *   untouched), target_prob [B][N_pad] float (softmax probability of that token; may be
  *   NULL), scan_status [B] uint32 (TALON_STATUS_BAD_ROW if a row of the sequence held a NaN
- *   or +inf).  One pass of the vocabulary scan with k = 1 over n_nodes rows per sequence.
+ *   or +inf).  One pass over n_nodes rows per sequence.
  *   `workspace`: talon_verify_workspace_bytes bytes of device memory, no initialisation
  *   needed.  Errors as talon_expand_layer.
  *

@@ -185,28 +185,15 @@ int expand_grid(const talon_tree_state* st, int chunks, int layer, int k, int K_
   return static_cast<int>(items);
 }
 
-// Workspace of talon_target_argmax: the scan's workspace for k = 1, then the stand-in frontier
-// {begin, count, status}[B] and the scan outputs nobody asked for.
-struct VerifyLayout {
-  ExpandLayout scan;
-  size_t off_begin, off_count, off_status, off_logit, off_prob, off_edge, off_max, off_lse, total;
-};
-
-int verify_layout(int B, int N_pad, int vocab, int dtype, VerifyLayout* V) {
-  int rc = expand_layout(B, N_pad, vocab, 1, dtype, &V->scan);
-  if (rc) return rc;
-  const size_t rows = static_cast<size_t>(B) * N_pad;
-  size_t o = V->scan.total;
-  V->off_begin = o;  o += align_up(B * sizeof(int32_t), 256);
-  V->off_count = o;  o += align_up(B * sizeof(int32_t), 256);
-  V->off_status = o; o += align_up(B * sizeof(uint32_t), 256);
-  V->off_logit = o;  o += align_up(rows * sizeof(float), 256);
-  V->off_prob = o;   o += align_up(rows * sizeof(float), 256);
-  V->off_edge = o;   o += align_up(rows * sizeof(double), 256);
-  V->off_max = o;    o += align_up(rows * sizeof(float), 256);
-  V->off_lse = o;    o += align_up(rows * sizeof(double), 256);
-  V->total = o;
-  return TALON_OK;
+// Blocks of 16 KiB per run of the target argmax.  2048 workgroups are resident at once (eight per compute
+// unit): up to that many blocks every block is a run of its own.  Beyond, longer runs save the per-run
+// reduction, and runs of more than five blocks make the last round longer: 1800 f32 rows of 513 KB take
+// 173 us with at most 5, 185 with at most 20; 4096 bf16 rows of 304 KB 231 with 5, 235 with 2, 229 with 20.
+int argmax_blocks_per_run(long long rows, int blocks) {
+  long long per = rows * blocks / 2048;
+  if (per > 5) per = 5;
+  if (per < 1) per = 1;
+  return static_cast<int>(per < blocks ? per : blocks);
 }
 
 // Workspace of talon_expand_literal: the scan's workspace and its outputs (laid out for the
@@ -768,10 +755,11 @@ int talon_prune_tree(const talon_tree_state* st, int32_t n_keep, int32_t* kept_i
   return check_hip(launch_prune(*st, n_keep, kept_ids, static_cast<hipStream_t>(stream)), "prune launch");
 }
 
+// Workspace of talon_target_argmax: the layout of a scan with k = 1, of which the partial results are used.
 size_t talon_verify_workspace_bytes(int32_t B, int32_t N_pad, int32_t vocab, int dtype) {
-  VerifyLayout V;
-  if (verify_layout(B, N_pad, vocab, dtype, &V)) return 0;
-  return V.total;
+  ExpandLayout L;
+  if (expand_layout(B, N_pad, vocab, 1, dtype, &L)) return 0;
+  return L.total + 256;
 }
 
 int talon_target_argmax(const void* logits, int dtype, int64_t row_stride, int64_t seq_stride,
@@ -779,36 +767,28 @@ int talon_target_argmax(const void* logits, int dtype, int64_t row_stride, int64
                         uint32_t* scan_status, void* workspace, size_t workspace_bytes, void* stream) {
   int rc = check_state(st);
   if (rc) return rc;
-  VerifyLayout V;
-  rc = verify_layout(st->B, st->N_pad, vocab, dtype, &V);
-  if (rc) return rc;
-  if (!scan_status) { set_error("scan_status is NULL"); return TALON_ERR_INVALID_ARG; }
-  char* w = static_cast<char*>(workspace);
   ExpandLayout L;
-  // the scan's own checks (pointers, alignment, strides), with the unused outputs in the workspace
-  float* prob = target_prob ? target_prob : (w ? reinterpret_cast<float*>(w + V.off_prob) : nullptr);
-  rc = check_expand_args(logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, 1, target_token,
-                         w ? w + V.off_logit : nullptr, prob, w ? w + V.off_edge : nullptr, w ? w + V.off_max : nullptr,
-                         w ? w + V.off_lse : nullptr, workspace, workspace_bytes, &L);
+  if ((rc = expand_layout(st->B, st->N_pad, vocab, 1, dtype, &L))) return rc;
+  if (!scan_status) { set_error("scan_status is NULL"); return TALON_ERR_INVALID_ARG; }
+  // the scan's own checks (pointers, alignment, strides); outputs of it that this call has not stand in as the workspace
+  rc = check_expand_args(logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, 1, target_token, workspace,
+                         target_prob ? target_prob : workspace, workspace, workspace, workspace, workspace, workspace_bytes, &L);
   if (rc) return rc;
-  if (workspace_bytes < V.total) {
-    set_error("workspace of %zu bytes is smaller than the %zu needed", workspace_bytes, V.total);
+  if (workspace_bytes < L.total + 256) {
+    set_error("workspace of %zu bytes is smaller than the %zu needed", workspace_bytes, L.total + 256);
     return TALON_ERR_WORKSPACE;
   }
-  ExpandArgs a = make_expand_args(logits, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, 1, target_token,
-                                  reinterpret_cast<float*>(w + V.off_logit), prob,
-                                  reinterpret_cast<double*>(w + V.off_edge), reinterpret_cast<float*>(w + V.off_max),
-                                  reinterpret_cast<double*>(w + V.off_lse), workspace, L);
-  int32_t* begin = reinterpret_cast<int32_t*>(w + V.off_begin);
-  int32_t* count = reinterpret_cast<int32_t*>(w + V.off_count);
-  a.frontier_begin = begin; a.frontier_count = count; a.status = scan_status;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  rc = check_hip(launch_all_nodes_frontier(*st, begin, count, scan_status, a.ticket, s), "frontier launch");
-  if (rc) return rc;
-  // every node of every tree is a row: N rows per sequence at most
-  long long items = static_cast<long long>(st->B) * st->N * L.chunks;
-  const int grid = static_cast<int>(items > 1024 ? 1024 : (items < 1 ? 1 : items));
-  return check_hip(launch_expand(a, dtype, grid, false, s), "target scan launch");
+  ArgmaxArgs a;
+  a.logits = logits; a.row_stride = row_stride; a.seq_stride = seq_stride; a.n_nodes = st->n_nodes; a.N_pad = st->N_pad;
+  a.vocab = vocab; a.blocks = L.chunks;
+  a.blocks_per_run = argmax_blocks_per_run(static_cast<long long>(st->B) * st->N, L.chunks);
+  a.runs = (L.chunks + a.blocks_per_run - 1) / a.blocks_per_run;
+  char* w = static_cast<char*>(workspace);
+  a.part_max = reinterpret_cast<float*>(w + L.off_max);
+  a.part_sum = reinterpret_cast<double*>(w + L.off_sum);
+  a.part_key = reinterpret_cast<unsigned long long*>(w + L.off_keys);
+  a.target_token = target_token; a.target_prob = target_prob; a.scan_status = scan_status;
+  return check_hip(launch_argmax(a, dtype, st->B, static_cast<hipStream_t>(stream)), "target argmax launch");
 }
 
 int talon_greedy_accept(const talon_tree_state* st, const int32_t* target_token, const uint32_t* scan_status,

@@ -97,6 +97,38 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x)
   return x;
 }
 
+// The same over the 16 lanes of a row (lanes 16i .. 16i+15).
+#define TALON_ROW16_ALLREDUCE_64(T, x, COMBINE)                                              \
+  do {                                                                                       \
+    union { T t; int w[2]; } a_, b_;                                                         \
+    a_.t = x;                                                                                \
+    b_.w[0] = dpp_i32<kDppXor1>(a_.w[0]); b_.w[1] = dpp_i32<kDppXor1>(a_.w[1]);              \
+    a_.t = COMBINE(a_.t, b_.t);                                                              \
+    b_.w[0] = dpp_i32<kDppXor2>(a_.w[0]); b_.w[1] = dpp_i32<kDppXor2>(a_.w[1]);              \
+    a_.t = COMBINE(a_.t, b_.t);                                                              \
+    b_.w[0] = dpp_i32<kDppHalfMirror>(a_.w[0]); b_.w[1] = dpp_i32<kDppHalfMirror>(a_.w[1]);  \
+    a_.t = COMBINE(a_.t, b_.t);                                                              \
+    b_.w[0] = dpp_i32<kDppMirror>(a_.w[0]); b_.w[1] = dpp_i32<kDppMirror>(a_.w[1]);          \
+    a_.t = COMBINE(a_.t, b_.t);                                                              \
+    x = a_.t;                                                                                \
+  } while (0)
+__device__ __forceinline__ double row16_sum_f64(double x) {
+  TALON_ROW16_ALLREDUCE_64(double, x, combine_add_f64);
+  return x;
+}
+__device__ __forceinline__ unsigned long long row16_max_u64(unsigned long long x) {
+  TALON_ROW16_ALLREDUCE_64(unsigned long long, x, combine_max_u64);
+  return x;
+}
+__device__ __forceinline__ float row16_max_f32(float x) {
+  int v = __float_as_int(x);
+  v = combine_max_f32(v, dpp_i32<kDppXor1>(v));
+  v = combine_max_f32(v, dpp_i32<kDppXor2>(v));
+  v = combine_max_f32(v, dpp_i32<kDppHalfMirror>(v));
+  v = combine_max_f32(v, dpp_i32<kDppMirror>(v));
+  return __int_as_float(v);
+}
+
 // Inclusive prefix sum across the 64 lanes of a wavefront (all lanes active): a
 // Kogge-Stone scan inside each row of 16 lanes (row_shr 1, 2, 4, 8; lanes shifted in from
 // outside the row read 0), then the last lane of row 0/2 is added to row 1/3 (row_bcast:15)

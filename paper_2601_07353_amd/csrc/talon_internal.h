@@ -149,6 +149,22 @@ struct LiteralArgs {
   int32_t* row_ticket;             // [B*N_pad] parts of a row that have finished; zero between launches
 };
 
+// Target argmax over every node of every tree.
+struct ArgmaxArgs {
+  const void* logits;
+  int64_t row_stride, seq_stride;
+  const int32_t* n_nodes;          // [B]
+  int N_pad, vocab;
+  int blocks;                      // 16 KiB blocks of a row
+  int runs, blocks_per_run;        // runs a row is cut into
+  float* part_max;                 // [B*N_pad][blocks] per run: maximum ...
+  double* part_sum;                // ... sum of exp(logit - maximum) ...
+  unsigned long long* part_key;    // ... and (sortable maximum << 32 | ~token); 0: no logit above -inf
+  int32_t* target_token;           // [B][N_pad]
+  float* target_prob;              // [B][N_pad] or NULL
+  uint32_t* scan_status;           // [B]
+};
+
 // (Kernel arguments are fetched in lines of 64 bytes, a round trip each: with a fourth line a call of
 // 15 us took 0.2 us longer.  What the kernels use together lies together.)
 struct AttnArgs {
@@ -186,8 +202,7 @@ static_assert(sizeof(AttnArgs) <= 192, "three lines");
 hipError_t launch_tree_init(const talon_tree_state& st, const int32_t* root_token, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_prune(const talon_tree_state& st, int n_keep, int32_t* kept_ids, hipStream_t s);
-hipError_t launch_all_nodes_frontier(const talon_tree_state& st, int32_t* begin, int32_t* count, uint32_t* status,
-                                     int32_t* ticket, hipStream_t s);
+hipError_t launch_argmax(const ArgmaxArgs& a, int dtype, int B, hipStream_t s);
 hipError_t launch_accept(const talon_tree_state& st, const int32_t* target_token, const uint32_t* scan_status,
                          int32_t* path, int32_t* accept_len, int32_t* bonus_token, hipStream_t s);
 hipError_t launch_compact_kv(const uint16_t* k_tree, const uint16_t* v_tree, const int32_t* path, const int32_t* accept_len,

@@ -87,3 +87,53 @@ def test_nan_target_row_is_reported():
     n0 = int(st.n_nodes[0])
     rows = [storage_to_f64(tpool[0, i]) for i in range(n0)]
     H.compare_verify(cfg, gpu, 0, st.token[0, :n0].cpu().numpy(), st.parent[0, :n0].cpu().numpy(), rows, attn[0])
+
+
+# Vocabularies around a vector, a tile (256 vectors), a block (4 tiles) and a run of blocks, more runs
+# than the merge's 16 lanes, and enough rows for runs of several blocks.
+@pytest.mark.parametrize("dtype,V,B,N", [("f32", 1, 1, 2), ("bf16", 7, 2, 5), ("bf16", 8, 1, 64), ("f32", 1023, 3, 9),
+                                         ("bf16", 2049, 2, 17), ("f32", 4097, 1, 33), ("bf16", 8192, 2, 70), ("bf16", 24571, 1, 40),
+                                         ("f32", 70001, 1, 12), ("bf16", 151936, 1, 6), ("f32", 33000, 16, 40), ("bf16", 60013, 8, 200)])
+def test_target_argmax_edges(dtype, V, B, N):
+    import torch
+    import paper_2601_07353_amd as T
+    print("case", dtype, V, B, N, flush=True)
+    rng = np.random.default_rng(V + N)
+    st = T.TreeState(B, N)
+    sizes = [N] + [int(x) for x in rng.integers(1, N + 1, B - 1)]
+    st.n_nodes.copy_(torch.tensor(sizes, dtype=torch.int32))
+    x = rng.standard_normal((B, N, V)).astype(np.float32) * rng.uniform(0.01, 6.0, (B, N, 1)).astype(np.float32)
+    for b in range(B):
+        for i in range(N):
+            kind = (b + i) % 5
+            if kind == 1:    # ties of the maximum, anywhere and next to one another
+                x[b, i, rng.integers(0, V, 6)] = 30.0
+                x[b, i, min(V - 1, V // 2 + 1)] = 30.0
+            elif kind == 2:  # mostly -inf, the maximum last
+                x[b, i, rng.random(V) < 0.9] = -np.inf
+                x[b, i, V - 1] = 2.0
+            elif kind == 3:  # all equal: the lowest id
+                x[b, i] = -0.0
+    stride = (V + 7) // 8 * 8
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    dev = torch.full((B, N, stride), 100.0, dtype=dt, device="cuda")   # what lies behind a row has no effect
+    dev[:, :, :V] = torch.from_numpy(x).to(dt).cuda()
+    logits = dev[:, :, :V]
+    code = T.TALON_DTYPE_F32 if dtype == "f32" else T.TALON_DTYPE_BF16
+    ws = T.make_verify_workspace(B, st.N_pad, V, code)
+    ws.fill_(0xFF)                                                     # (no initial value needed)
+    tok = torch.full((B, st.N_pad), -7, dtype=torch.int32, device="cuda")
+    prob = torch.full((B, st.N_pad), -7.0, device="cuda")
+    status = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    for with_prob in (True, False):
+        T.talon_target_argmax(logits, st, tok, prob if with_prob else None, status, ws)
+    rows = logits.float().cpu().double().numpy() + 0.0
+    tok, prob = tok.cpu().numpy(), prob.cpu().numpy()
+    assert not status.cpu().numpy().any()
+    for b in range(B):
+        n = sizes[b]
+        want = rows[b, :n].argmax(-1)
+        np.testing.assert_array_equal(tok[b, :n], want)
+        top = rows[b, :n].max(-1, keepdims=True)
+        np.testing.assert_allclose(prob[b, :n], 1.0 / np.exp(rows[b, :n] - top).sum(-1), rtol=H.PROB_RTOL)
+        assert (tok[b, n:] == -7).all() and (prob[b, n:] == -7.0).all()   # rows beyond the tree untouched
