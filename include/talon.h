@@ -277,6 +277,22 @@ int talon_expand_literal(const void* logits, int dtype, int64_t row_stride, int6
                          void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * talon_expand_literal for rows by node id that are all in place: `rows` rows of every sequence may
+ * be read from the start of the call on, whatever the tree comes to ask for (rows it does not expand have no
+ * effect).  With rows >= N - 1 and at least four layers to go they are scanned ahead of the trees in
+ * one launch, as in talon_build_tree_ahead, with the 16 best tokens per row; a layer that keeps a
+ * row's 16th streams that row a second time, from the lowest score on that can still be chosen.
+ * Same tree as talon_expand_literal (row statistics may differ in the last bit of a double);
+ * the launch's waits (for rows that are being scanned, bounded by two seconds) do not
+ * depend on workgroups being resident together.  Otherwise the call is talon_expand_literal with
+ * TALON_ROWS_BY_NODE.  Workspace and errors as there, plus INVALID_ARG for rows < 1.
+ */
+int talon_expand_literal_ahead(const void* logits, int dtype, int64_t row_stride, int64_t seq_stride,
+                               int32_t rows, int32_t layers, const talon_tree_state* st, int32_t vocab,
+                               float mu, int32_t K_init, int32_t init_layers, int32_t max_depth,
+                               void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Measurement hook (no counterpart in the paper).  While enabled, talon_expand_tree,
  * talon_build_tree, talon_build_tree_ahead and talon_expand_select_layer record a HIP event on the
  * launch stream before and after every fused scan launch; talon_profile_read waits for them, writes the first `capacity`

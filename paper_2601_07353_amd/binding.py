@@ -38,7 +38,7 @@ EXPORTS = [
     "talon_last_error_string", "talon_tree_init", "talon_expand_workspace_bytes",
     "talon_expand_workspace_init", "talon_expand_layer", "talon_select_budget", "talon_expand_select_layer",
     "talon_expand_tree", "talon_build_tree", "talon_build_tree_ahead", "talon_build_tree_checked", "talon_set_spin_limit_us", "talon_profile_scan_launches", "talon_profile_read", "talon_probe_read", "talon_probe_mfma", "talon_probe_issue", "talon_probe_tile_loads", "talon_verify_workspace_bytes", "talon_target_argmax",
-    "talon_literal_workspace_bytes", "talon_expand_literal",
+    "talon_literal_workspace_bytes", "talon_expand_literal", "talon_expand_literal_ahead",
     "talon_greedy_accept", "talon_compact_kv", "talon_prune_tree",
     "talon_build_tree_mask", "talon_tree_attention_workspace_bytes", "talon_tree_attention",
     "talon_static_scratch_bytes", "talon_static_scratch_init", "talon_tree_attention_static",
@@ -98,6 +98,7 @@ def load_library() -> ctypes.CDLL:
     lib.talon_literal_workspace_bytes.argtypes = [c_int32, c_int32, c_int32, c_int]
     lib.talon_expand_literal.argtypes = [P, c_int, c_int64, c_int64, c_int, c_int32, POINTER(_CTreeState), c_int32,
                                          c_float, c_int32, c_int32, c_int32, P, c_size_t, P]
+    lib.talon_expand_literal_ahead.argtypes = lib.talon_expand_literal.argtypes
     lib.talon_verify_workspace_bytes.restype = c_size_t
     lib.talon_verify_workspace_bytes.argtypes = [c_int32, c_int32, c_int32, c_int]
     lib.talon_target_argmax.argtypes = [P, c_int, c_int64, c_int64, POINTER(_CTreeState), c_int32, P, P, P, P, c_size_t, P]
@@ -394,7 +395,13 @@ def make_literal_workspace(B, N_pad, vocab, dtype) -> torch.Tensor:
 
 def talon_expand_literal(logits, st: TreeState, layers, mu, K_init, init_layers, max_depth, workspace,
                          row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
+    """With rows by node id the library may read any row of `logits` ahead of the trees, as in talon_build_tree."""
     dt, row_stride, seq_stride, V = _logits_meta(logits)
+    if row_mode == TALON_ROWS_BY_NODE and (vocab is None or vocab <= V) and logits.shape[0] >= st.B and logits.shape[1] > 0:
+        _check(load_library().talon_expand_literal_ahead(
+            _ptr(logits), dt, row_stride, seq_stride, logits.shape[1], layers, _byref(st.c), V if vocab is None else vocab,
+            mu, K_init, init_layers, max_depth, _ptr(workspace), workspace.nbytes, _stream(stream)))
+        return
     _check(load_library().talon_expand_literal(
         _ptr(logits), dt, row_stride, seq_stride, row_mode, layers, _byref(st.c), V if vocab is None else vocab,
         mu, K_init, init_layers, max_depth, _ptr(workspace), workspace.nbytes,

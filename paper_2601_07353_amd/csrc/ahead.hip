@@ -27,26 +27,20 @@
 // Measured, this launch against the loop of expand.hip (tree and mask, resident inputs):
 //   1 x 1024 f32, 16 nodes: 17 us (42);  1 x 128256 bf16, 60 nodes: 24 us (54);
 //   4 x 151936, 128 nodes: 53 us (107);  16 x 151936, 256 nodes: 233-250 us (280).
-#include "scan_device.h"
+//
+// The same launch builds trees from the uncapped pool (talon_expand_literal_ahead): scanners rank the 16
+// best of every row, and a layer that keeps a row's 16th reads that row once more (see below).  What was three
+// launches per layer of the depth cap (or, up to 64 nodes, the capped loop with 32 and more candidates per row), tree
+// and mask of resident inputs, before and now: 1 x 128256 bf16, 60 nodes: 72 us, 43;  4 x 151936, 128 nodes,
+// two of the sequences flat: 250, 97;  8 x 100003, 100 nodes: 248, 115;  2 x 128256, 250 nodes, flat: 203, 95.
+#include "ahead_device.h"
+#include "literal_device.h"
 
 namespace talon {
 
 namespace {
 
-constexpr int32_t kRowReady = 1 << 30;   // row ticket: merged results are in the workspace ...
-constexpr int32_t kRowBad = 1;           // ... and the row could not be normalised
-
 // LDS: a workgroup is a scanner or a selector.
-struct ScannerLds {
-  unsigned char pool[kScanBytes];
-  unsigned long long topw[4][TALON_K_MAX];
-  int part[4][64];
-  unsigned long long top[TALON_K_MAX];
-  double wsum[4];
-  float wmax[4];
-  int wcnt[4];
-  int nc, last, next, stop;
-};
 // Slots of the selector's key array: the threads of a row hold at most k + 2^lt - 1 candidates
 // between them, and every thread's slots are padded to an odd number; F * k <= kMaxCand and
 // F * 2^lt <= kThreads.
@@ -61,143 +55,417 @@ struct SelectorLds {
   int misc[2];
   int state;                  // what the wait for a layer's rows found
   unsigned long long ready[TALON_N_MAX / 64];   // rows known to be ready (and normalised)
+  // uncapped pool only (want: also whether a row has to be read again)
+  int digit, want, nkeep, nfin;
 };
+// A part of a row read again: every wavefront keeps the keys above the bound in a buffer of its own
+// and cuts it to the `limit` best when half of it is full (a step adds at most 512 keys).
+constexpr int kPartBuf = 960;
+struct PartLds {
+  unsigned long long buf[4][kPartBuf];
+  int hist[4][256];
+  unsigned long long floor[4];
+  int count[4];
+  int item;
+};
+constexpr int kAheadLists = 320;   // 255 rows, and up to 64 parts of rows that are read again
+constexpr int kDeepPool = 2048;
+struct DeepPickLds {
+  PickLds<kDeepPool, kAheadLists> pick;
+  double lse[TALON_N_MAX];
+  unsigned int src[kAheadLists];   // where a list's keys are: frontier row, or kDeepList + part
+  unsigned char par[kAheadLists];
+};
+constexpr unsigned int kDeepList = 1u << 31;
+static_assert(sizeof(PartLds) <= sizeof(unsigned long long) * kAheadKeySlots && sizeof(DeepPickLds) <= sizeof(unsigned long long) * kAheadKeySlots,
+              "both lie over the key array");
 constexpr size_t kAheadLds = sizeof(ScannerLds) > sizeof(SelectorLds) ? sizeof(ScannerLds) : sizeof(SelectorLds);
 
-// Words that scanners look at: the item counter, and the sequences' stop words, each on a memory
-// line of its own (in the descriptors of layers >= 1 of the other launch forms, zero between
-// launches; those of layer 0 are not).
-__device__ __forceinline__ uint32_t* item_counter(const ExpandArgs& a) { return a.exit_ticket + kItemWord; }
-__device__ __forceinline__ int32_t* stop_word(const ExpandArgs& a, int b) {
-  return reinterpret_cast<int32_t*>(a.desc + a.B + static_cast<size_t>(b) * (a.N_pad - 1));
+// ---- uncapped pool: is there anything to expand in sequence b?
+__device__ __forceinline__ bool has_frontier(const talon_tree_state& st, int b) {
+  const int n = st.n_nodes[b], fb = st.frontier_begin[b], F = st.frontier_count[b];
+  return !(st.status[b] & (kDoneMask | TALON_STATUS_BAD_ROW)) && F > 0 && fb >= 0 && fb + F <= n && n < st.N;
 }
 
-__device__ __forceinline__ int ahead_items(const ExpandArgs& a) {
-  return a.B * (a.ahead_head * a.ahead_chunks_head + (a.ahead_rows - a.ahead_head) * a.ahead_chunks);
+// ---- uncapped pool: rows that are read again.
+// The selection takes the `limit` best of the rows' 16 best.  Where it keeps a row's 16th, tokens beyond
+// it may belong to the tree, and exactly those whose path score reaches the lowest one kept (or, with
+// budget left, the gate).  That bound turns into one on the row's logits, and the row is streamed
+// again, in parts: by helper workgroups, which wait for such work, and by the selector itself, whoever
+// claims a part first.  The request lies in the workspace: a header (most and least keys, parts per row) and one word
+// per row (node, logit bound); the claim word holds the number of parts and the next one, and storing
+// it is the signal.  A part leaves at most `most` keys: as many as let all parts' keys lie in LDS when the selection
+// is made again, or all of `limit` where that left out one that could have been chosen.
+__device__ __forceinline__ unsigned long long* claim_word(const ExpandArgs& a, int b) {
+  return a.desc + a.B + static_cast<size_t>(b) * (a.N_pad - 1) + 16;
+}
+__device__ __forceinline__ uint32_t* parts_done_word(const ExpandArgs& a, int b) {
+  return reinterpret_cast<uint32_t*>(a.desc + a.B + static_cast<size_t>(b) * (a.N_pad - 1) + 32);
+}
+__device__ __forceinline__ unsigned long long* request_words(const LiteralAhead& la, const ExpandArgs& a, int b) {
+  return la.request + static_cast<size_t>(b) * (a.N_pad + 1);
 }
 
-// ---- scanner: workgroup `wg` of `n_wg`.  Its first item is its own number; the next ones come from
-// a counter, in order: workgroups (and whole compute dies) progress at different speeds, and a
-// row that a slow one holds back may be the one a selector waits for.  (Counters per die were
-// tried: the slowest die's rows came 30 us late in a launch of 250 us.)
-template <int EPL>
-__device__ __forceinline__ void scan_rows(const ExpandArgs& a, ScannerLds& s, const int wg, const int n_wg) {
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int k = a.k;
-  const ScanLds L{reinterpret_cast<uint4 (*)[kHitCap]>(s.pool), reinterpret_cast<int (*)[kHitCap]>(s.pool + kHitvBytes),
-                  reinterpret_cast<unsigned long long (*)[kSubKeys]>(s.pool + kHitvBytes + kHithBytes), s.topw, s.part, s.top,
-                  s.wmax, s.wsum, s.wcnt};
-  unsigned long long* s_keys = reinterpret_cast<unsigned long long*>(s.pool);   // row merge: partial keys,
-  unsigned long long* s_cand = s_keys + kMergeCap;                              // ... then those that can still be chosen
-  static_assert(kScanBytes >= static_cast<int>(sizeof(unsigned long long)) * (kMergeCap + kCandCap + 16), "the scan buffers stage a row merge");
-  const int blocks_per_row = a.chunks;
-  const int head_items = a.ahead_head * a.B * a.ahead_chunks_head;
-  const int n_items = ahead_items(a);
-  int item = wg;
-  if (tid == 0) s.stop = 0;
-  __syncthreads();
-  while (item < n_items) {
-    const bool head = item < head_items;
-    const int chunks = head ? a.ahead_chunks_head : a.ahead_chunks;
-    const int bpc = (blocks_per_row + chunks - 1) / chunks;
-    const int per_row = a.B * chunks;                 // items of one row id, all sequences
-    const int in_part = head ? item : item - head_items;
-    const int row_id = in_part / per_row;
-    const int rest = in_part - row_id * per_row;
-    const int node = head ? row_id : a.ahead_head + row_id;
-    const int b = rest / chunks;
-    const int ch = rest - b * chunks;
-    const int out_row = b * a.N_pad + node;
-    const char* row = static_cast<const char*>(a.logits) +
-                      (static_cast<int64_t>(b) * a.seq_stride + static_cast<int64_t>(node) * a.row_stride) * (16 / EPL);
-    const int blk0 = ch * bpc;
-    const int blk1 = blk0 + bpc < blocks_per_row ? blk0 + bpc : blocks_per_row;
-    float m;
-    double sum;
-    const bool scanned = scan_chunk<EPL, false, true>(row, a.vocab, k, blk0, blk1, L, m, sum, stop_word(a, b), &s.stop);
-    // (the counter is asked here: at the start of an item the row's first loads would wait behind a
-    // thousand atomics on one word, about 20 ns each)
-    int next = n_items;
-    if (tid == 0 && n_items > n_wg)
-      next = n_wg + static_cast<int>(__hip_atomic_fetch_add(item_counter(a), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    if (scanned) {
-      const size_t slot0 = static_cast<size_t>(out_row) * blocks_per_row;
-      unsigned long long* keys = a.part_keys + slot0 * k;
-      bool row_done = chunks == 1;
-      if (chunks > 1) {
-        if (tid < k) store_agent(keys + static_cast<size_t>(ch) * k + tid, s.top[tid]);
-        if (tid == 0) {
-          store_agent(a.part_max + slot0 + ch, m);
-          store_agent(a.part_sum + slot0 + ch, sum);
-        }
-        stores_performed();   // every partial store has completed before the ticket is taken
-        __syncthreads();
-        if (tid == 0) s.last = __hip_atomic_fetch_add(&a.ticket[out_row], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == chunks - 1;
-        __syncthreads();
-        if (s.last) {
-          // (statistics: one chunk per lane, in every wavefront; more only for very long rows)
-          row_done = true;
-          const int nkeys = chunks * k;
-          const int nkeys_pad = (nkeys + 15) & ~15;
-          float mc0 = kNegInf;
-          double sc0 = 0.0;
-          if (lane < chunks) { mc0 = load_agent(a.part_max + slot0 + lane); sc0 = load_agent(a.part_sum + slot0 + lane); }
-          for (int i = tid; i < nkeys_pad; i += kThreads) s_keys[i] = i < nkeys ? load_agent(keys + i) : 0ull;
-          m = mc0;
-          for (int c = lane + 64; c < chunks; c += 64) m = fmaxf(m, load_agent(a.part_max + slot0 + c));
-          m = wave_max_f32(m);
-          sum = (mc0 != kNegInf) ? sc0 * static_cast<double>(__expf(mc0 - m)) : 0.0;
-          for (int c = lane + 64; c < chunks; c += 64) {
-            const float mc = load_agent(a.part_max + slot0 + c);
-            if (mc != kNegInf) sum += load_agent(a.part_sum + slot0 + c) * static_cast<double>(__expf(mc - m));
-          }
-          sum = wave_sum_f64(sum);
-          __syncthreads();   // the partial results have been read: slot 0 may be written
-        }
+// Where a part has left keys out: none of them is above this word (else 0).
+__device__ __forceinline__ unsigned long long* part_floor(const LiteralAhead& la, const ExpandArgs& a, int b) {
+  return la.request + static_cast<size_t>(a.B) * (a.N_pad + 1) + static_cast<size_t>(b) * kAheadLists;
+}
+
+// One wavefront: cuts the n keys in `keys` (LDS, unique) to the best ones, at least `want` and at most `room` of them,
+// in place, in any order; returns how many are left and their smallest.  hist: 256 words of LDS of this
+// wavefront.  (LDS operations of one wavefront complete in order.)
+__device__ __forceinline__ int wave_cut(unsigned long long* keys, const int n, const int want, const int room, int* hist, unsigned long long* smallest) {
+  const int lane = threadIdx.x & 63;
+  unsigned long long prefix = 0ull;
+  if (n > room) {
+    int remaining = want;
+    for (int sh = 56; sh >= 0; sh -= 8) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) hist[4 * lane + j] = 0;
+      for (int i = lane; i < n; i += 64) {
+        const unsigned long long key = keys[i];
+        if (sh == 56 || ((key ^ prefix) >> (sh + 8)) == 0ull) atomicAdd(&hist[static_cast<int>(key >> sh) & 255], 1);
       }
-      if (row_done) {
-        // ---- the row's results: k keys in descending order (zero: none), log-sum-exp, maximum
-        int t = tid;
-        asm volatile("" : "+v"(t));   // addresses are computed here, not kept across the streaming loop
-        if (chunks == 1) {
-          if (t < k) store_agent(keys + t, s.top[t]);
-        } else {
-          const int valid = a.vocab < k ? a.vocab : k;
-          if (t >= valid && t < k) store_agent(keys + t, 0ull);
-          rank_lists(k, s_keys, chunks, t, s_cand, &s.nc, [&](unsigned long long key, int r) { store_agent(keys + r, key); });
-        }
-        const double lse = static_cast<double>(m) + log_of_sum(sum);
-        const bool bad = !(fabs(lse) <= 1.7e308);
-        if (t == 0) {
-          store_agent(a.part_max + slot0, m);
-          store_agent(a.part_sum + slot0, lse);
-        }
-        stores_performed();
-        __syncthreads();
-        if (t == 0) store_agent(a.ticket + out_row, bad ? (kRowReady | kRowBad) : kRowReady);
+      int h[4], lane_sum = 0;   // lane l owns digits 255-4l .. 252-4l
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { h[j] = hist[255 - 4 * lane - j]; lane_sum += h[j]; }
+      const int incl = wave_inclusive_scan_i32(lane_sum);
+      const unsigned long long hit = __ballot(incl >= remaining);
+      const int first = hit ? __ffsll(static_cast<long long>(hit)) - 1 : 63;
+      int before = incl - lane_sum, dg = 255 - 4 * lane, j = 0;
+#pragma unroll
+      for (; j < 3; ++j) {
+        if (before + h[j] < remaining) { before += h[j]; --dg; } else break;
+      }
+      const int left = remaining - before;
+      const int word = __builtin_amdgcn_readlane(dg | ((h[j] - left <= room - want) ? 256 : 0), first);
+      remaining = __builtin_amdgcn_readlane(left, first);
+      prefix |= static_cast<unsigned long long>(word & 255) << sh;
+      if (word & 256) break;
+    }
+  }
+  int kept = 0;
+  unsigned long long inv = 0ull;
+  for (int i0 = 0; i0 < n; i0 += 64) {   // (a key moves to a place at or before its own)
+    const unsigned long long key = i0 + lane < n ? keys[i0 + lane] : 0ull;
+    const bool keep = i0 + lane < n && key >= prefix;
+    const unsigned long long bal = __ballot(keep);
+    if (keep) {
+      keys[kept + __popcll(bal & ((1ull << lane) - 1ull))] = key;
+      inv = ~key > inv ? ~key : inv;
+    }
+    kept += __popcll(bal);
+  }
+  *smallest = ~wave_max_u64(inv);
+  return kept;
+}
+
+// Part `item` of sequence b's request.  Starts without and ends with a barrier.
+template <int EPL>
+__device__ __forceinline__ void read_part(const ExpandArgs& a, const LiteralAhead& la, PartLds& s, const int b, const int item) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const unsigned long long* request = request_words(la, a, b);
+  const unsigned long long header = load_agent(request);
+  const int most = static_cast<int>(header & 0xFFFFu), least = static_cast<int>((header >> 16) & 0xFFFFu), parts = static_cast<int>(header >> 32);
+  const int o = item / parts, part = item - o * parts;
+  const unsigned long long row_word = load_agent(request + 1 + o);
+  const int node = static_cast<int>(row_word >> 32);
+  float x_lo = unsortable_f32(static_cast<uint32_t>(row_word));
+  const uint4* row = reinterpret_cast<const uint4*>(
+      static_cast<const char*>(a.logits) +
+      (static_cast<int64_t>(b) * a.seq_stride + static_cast<int64_t>(node) * a.row_stride) * (16 / EPL));
+  const int nvec = (a.vocab + EPL - 1) / EPL;
+  const int per = (nvec + parts - 1) / parts;
+  const int v_end = (part + 1) * per < nvec ? (part + 1) * per : nvec;
+  unsigned long long* buf = s.buf[wave];
+  int count = 0;
+  unsigned long long floor = 0ull;   // where keys above the bound have been left out: the smallest that was not
+  unsigned long long smallest;
+  // Four vectors of a lane are in flight, each in registers of its own (moved on from one to the next, a vector
+  // would be waited for when it is moved).
+  auto load = [&](int v) { return v < v_end ? row[v] : make_uint4(0u, 0u, 0u, 0u); };
+  auto take = [&](const uint4& r, int v) __attribute__((always_inline)) {
+    float x[EPL];
+    unpack_vec<EPL>(r, x);
+    unsigned int bits = 0u;
+    float top = kNegInf;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      if (x[e] >= x_lo && v < v_end && v * EPL + e < a.vocab) { bits |= 1u << e; top = fmaxf(top, x[e]); }
+    }
+    const unsigned long long hits = __ballot(bits != 0u);
+    if (hits == 0ull) return;
+    if (most <= 64 && __popcll(hits) > most + kRaiseHits) {
+      // (flat rows) at least `most` lanes hold a logit that reaches the `most`-th of the lanes' largest ones
+      const float raised = kth_of_lanes(top, most);
+      if (raised > x_lo) {
+        x_lo = raised;
+        const unsigned long long below = static_cast<unsigned long long>(sortable_u32(x_lo)) << 32;
+        floor = below > floor ? below : floor;
+        unsigned int keep = 0u;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) keep |= x[e] >= x_lo ? 1u << e : 0u;
+        bits &= keep;
       }
     }
-    __syncthreads();   // every wavefront has looked at the stop flag
-    if (tid == 0) { s.next = next; s.stop = 0; }
-    __syncthreads();   // LDS is reused by the next item
-    item = s.next;
+    const int incl = wave_inclusive_scan_i32(__popc(bits));
+    int pos = count + incl - __popc(bits);
+#pragma unroll
+    for (int e = 0; e < EPL; ++e)
+      if (bits & (1u << e)) buf[pos++] = make_key(x[e], v * EPL + e);
+    count += __builtin_amdgcn_readlane(incl, 63);
+    if (count > kPartBuf - 64 * EPL) {
+      count = wave_cut(buf, count, most, 4 * most < kPartBuf - 64 * EPL ? 4 * most : kPartBuf - 64 * EPL, s.hist[wave], &smallest);
+      x_lo = float_above(key_logit(smallest));   // a later equal logit has a larger token id and loses
+      floor = smallest > floor ? smallest : floor;
+    }
+  };
+  int v = part * per + wave * 64 + lane;
+  uint4 r0 = load(v), r1 = load(v + kThreads), r2 = load(v + 2 * kThreads), r3 = load(v + 3 * kThreads);
+  for (int v0 = part * per + wave * 64; v0 < v_end; v0 += 4 * kThreads) {
+    take(r0, v); r0 = load(v + 4 * kThreads); v += kThreads;
+    take(r1, v); r1 = load(v + 4 * kThreads); v += kThreads;
+    take(r2, v); r2 = load(v + 4 * kThreads); v += kThreads;
+    take(r3, v); r3 = load(v + 4 * kThreads); v += kThreads;
+  }
+  const bool over = count > 255;
+  count = wave_cut(buf, count, most, 255, s.hist[wave], &smallest);
+  if (over && smallest > floor) floor = smallest;
+  if (lane == 0) { s.count[wave] = count; s.floor[wave] = floor; }
+  __syncthreads();
+  // the four lists behind one another (each at most 255 keys: up to four per lane), and cut once more
+  const int c0 = s.count[0], c1 = s.count[1], c2 = s.count[2], c3 = s.count[3];
+  unsigned long long mine[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) mine[j] = 64 * j + lane < count ? buf[64 * j + lane] : 0ull;
+  __syncthreads();
+  unsigned long long* all = s.buf[0];
+  const int at = wave == 0 ? 0 : (wave == 1 ? c0 : (wave == 2 ? c0 + c1 : c0 + c1 + c2));
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (64 * j + lane < count) all[at + 64 * j + lane] = mine[j];
+  __syncthreads();
+  if (wave == 0) {
+    for (int w = 0; w < 4; ++w) floor = s.floor[w] > floor ? s.floor[w] : floor;
+    const int n = wave_cut(all, c0 + c1 + c2 + c3, least, most, s.hist[0], &smallest);
+    unsigned long long* out = la.part_key + static_cast<size_t>(b) * la.part_keys_per_seq + static_cast<size_t>(item) * most;
+    for (int i = lane; i < n; i += 64) store_agent(out + i, all[i]);
+    if (lane == 0) {
+      store_agent(la.part_count + static_cast<size_t>(b) * a.N_pad * kLiteralChunks + item, n);
+      store_agent(part_floor(la, a, b) + item, n < c0 + c1 + c2 + c3 && smallest > floor ? smallest : floor);
+    }
+    stores_performed();
+    if (lane == 0) __hip_atomic_fetch_add(parts_done_word(a, b), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+}
+
+// ---- helper: parts of any sequence's request, its own number's sequence first, until every selector has
+// finished.  (Helpers are the last workgroups of the grid: whoever they wait for has started before them.)
+template <int EPL>
+__device__ __forceinline__ void help_read(const ExpandArgs& a, const LiteralAhead& la, PartLds& s, const int h) {
+  const int tid = threadIdx.x;
+  while (true) {
+    if (tid < 64) {
+      int found = -1, item = 0, nb = 0;
+      for (int c = 0; c < a.B && found == -1; c += 64) {
+        const int bb = (h + c + tid) % a.B;
+        unsigned long long w = c + tid < a.B ? load_agent(claim_word(a, bb)) : 0ull;
+        const unsigned long long work = __ballot(static_cast<uint32_t>(w) < static_cast<uint32_t>(w >> 32));
+        if (work != 0ull) {
+          const int first = __ffsll(static_cast<long long>(work)) - 1;
+          nb = __builtin_amdgcn_readlane(bb, first);
+          if (tid == 0) w = __hip_atomic_fetch_add(claim_word(a, nb), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          const uint32_t next = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(w));
+          const uint32_t parts = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(w >> 32));
+          found = next < parts ? nb : -2;   // (-2: somebody else was faster; look again)
+          item = static_cast<int>(next);
+        }
+      }
+      if (found == -1) {
+        if (load_agent(a.exit_ticket + kSelectedWord) == static_cast<uint32_t>(a.B)) found = -3;
+        else __builtin_amdgcn_s_sleep(16);
+      }
+      if (tid == 0) { s.item = found >= 0 ? item : found; s.count[0] = nb; }
+    }
+    __syncthreads();
+    const int item = s.item, b = s.count[0];
+    __syncthreads();
+    if (item == -3) return;
+    if (item >= 0) read_part<EPL>(a, la, s, b, item);
   }
 }
 
-// ---- selector: the loop of Alg. 2 for sequence b.  
+// The selection of a layer some of whose rows have to be read again: `low`, the lowest path score that can
+// still be chosen; kept (in the threads of row p): candidates that the capped pool keeps of the row up to
+// this thread's.  Appends the nodes and returns their number.
+template <int EPL>
+__device__ __forceinline__ int deep_select(const ExpandArgs& a, const LiteralAhead& la, SelectorLds& s, const int b, const int F, const int fb,
+                                           const int n, const int d, const int limit, double low, const int kept, const int p,
+                                           bool* waited_out) {
+  const talon_tree_state& st = a.sel.st;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int k = a.k;
+  const size_t base = static_cast<size_t>(b) * st.N_pad;
+  // candidates kept per row; the rows to read again, in order
+  s.hist[tid] = 0;
+  __syncthreads();
+  if (kept > 0) atomicMax(&s.hist[p], kept);
+  __syncthreads();
+  const int row_kept = tid < F ? s.hist[tid] : 0;
+  const bool open = row_kept == k;
+  int n_open;
+  const int o = block_exclusive_scan_i32(open ? 1 : 0, s.red_i32, &n_open);
+  const int nvec = (a.vocab + EPL - 1) / EPL;
+  int parts = 64 / n_open;
+  const int by_size = nvec / 512;
+  parts = parts < by_size ? parts : by_size;
+  parts = parts < 1 ? 1 : (parts > kLiteralChunks ? kLiteralChunks : parts);
+  const int n_items = n_open * parts;
+  unsigned long long* request = request_words(la, a, b);
+  int most = (kDeepPool - TALON_N_MAX) / n_items;   // (at most 15 rows have their 16th kept, 64 parts; other rows keep at most 255 in all)
+  most = most < 64 ? most : 64;
+  most = most < limit ? most : limit;
+  int n_keep = 0;
+  while (true) {
+    if (open) {
+      // inside a row the path score rises with the logit: the smallest logit image whose score reaches
+      // `low`, by bisection with the very expression the score is computed with
+      const double lp = s.logp[fb + tid], lse = load_agent(a.part_sum + (base + fb + tid) * a.chunks);
+      uint32_t l = 0x007FFFFFu, h = 0xFF800000u;   // images of -inf and +inf
+      while (l < h) {
+        const uint32_t mid = l + ((h - l) >> 1);
+        if (lp + (static_cast<double>(unsortable_f32(mid)) - lse) >= low) h = mid; else l = mid + 1u;
+      }
+      store_agent(request + 1 + o, (static_cast<unsigned long long>(fb + tid) << 32) | l);
+    }
+    if (tid == 0) {
+      const int least = most == limit ? most : most - most / 4;   // (a cut that need not be exact takes half as long)
+      store_agent(request, static_cast<unsigned long long>(parts) << 32 | static_cast<unsigned long long>(least << 16 | most));
+      store_agent(parts_done_word(a, b), 0u);
+    }
+    stores_performed();
+    __syncthreads();
+    if (tid == 0) store_agent(claim_word(a, b), static_cast<unsigned long long>(n_items) << 32);
+    PartLds& part = *reinterpret_cast<PartLds*>(s.key);
+    // (This barrier keeps thread 0's store apart from thread 0's claim below.  Without it the compiler joined the two
+    // conditions, the loop got two entries, and its barriers ran for thread 0 and for the others separately.)
+    __syncthreads();
+    while (true) {
+      if (tid == 0) part.item = static_cast<int>(static_cast<uint32_t>(__hip_atomic_fetch_add(claim_word(a, b), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+      __syncthreads();
+      const int item = part.item;
+      __syncthreads();
+      if (item >= n_items) break;
+      read_part<EPL>(a, la, part, b, item);
+    }
+    // parts that helpers have claimed (they are being worked on: this wait ends)
+    if (tid == 0) {
+      const unsigned long long t0 = wall_clock64();
+      while (load_agent(parts_done_word(a, b)) != static_cast<uint32_t>(n_items)) {
+        if (wall_clock64() - t0 > a.spin_ticks) { s.state |= 2; break; }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+    __syncthreads();
+    if (s.state & 2) { *waited_out = true; return 0; }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    // ---- lists of keys: a row's kept candidates, or what its parts left
+    DeepPickLds& L = *reinterpret_cast<DeepPickLds*>(s.key);
+    const int32_t* part_count = la.part_count + static_cast<size_t>(b) * a.N_pad * kLiteralChunks;
+    const unsigned long long* floors = part_floor(la, a, b);
+    const int own_lists = open ? parts : (row_kept > 0 ? 1 : 0);
+    int n_lists;
+    const int first_list = block_exclusive_scan_i32(own_lists, s.red_i32, &n_lists);
+    if (tid < F) L.lse[tid] = load_agent(a.part_sum + (base + fb + tid) * a.chunks);
+    for (int c = 0; c < own_lists; ++c) {
+      const int l = first_list + c;
+      L.par[l] = static_cast<unsigned char>(tid);
+      L.src[l] = open ? kDeepList + static_cast<unsigned int>(o * parts + c) : static_cast<unsigned int>(tid);
+      L.pick.cnt[l] = open ? load_agent(part_count + o * parts + c) : row_kept;
+    }
+    __syncthreads();
+    const int l0 = 2 * tid;   // (two lists per thread: up to 320 of them)
+    const int n0 = l0 < n_lists ? L.pick.cnt[l0] : 0, n1 = l0 + 1 < n_lists ? L.pick.cnt[l0 + 1] : 0;
+    int total;
+    const int off = block_exclusive_scan_i32(n0 + n1, s.red_i32, &total);
+    if (l0 < n_lists) L.pick.off[l0] = off;
+    if (l0 + 1 < n_lists) L.pick.off[l0 + 1] = off + n0;
+    if (tid == 0) s.state &= 2;
+    __syncthreads();
+    const unsigned long long* part_key = la.part_key + static_cast<size_t>(b) * la.part_keys_per_seq;
+    n_keep = pick_best<kThreads>(
+        n_lists, total, limit, L.pick, s, s.logp + fb, L.lse, [&](int list) { return static_cast<int>(L.par[list]); },
+        [&](int list, int i) {
+          const unsigned int src = L.src[list];
+          const unsigned long long* keys = src & kDeepList ? part_key + static_cast<size_t>(src - kDeepList) * most
+                                                           : a.part_keys + (base + fb + src) * a.chunks * k;
+          return load_agent(keys + i);
+        },
+        [&](int rank, int j, unsigned long long key, double edge) {
+          const int id = n + rank;
+          const double score = s.logp[fb + j] + edge;
+          s.logp[id] = score;
+          st.token[base + id] = static_cast<int32_t>(0xFFFFFFFFu - static_cast<uint32_t>(key));
+          st.parent[base + id] = fb + j;
+          st.depth[base + id] = d + 1;
+          st.prob[base + id] = __expf(static_cast<float>(edge));
+          st.logp[base + id] = score;
+        });
+    if (most == limit) break;
+    // Could a key that a part has left out have been chosen?
+    unsigned long long inv_low = 0ull;   // of the lowest score chosen
+    if (tid < n_keep) {
+      const int j = L.pick.kj[tid];
+      inv_low = ~sortable_u64(s.logp[fb + j] + (static_cast<double>(key_logit(L.pick.kkey[tid])) - L.lse[j]));
+    }
+    inv_low = block_max_u64(inv_low, s.red_u64);
+    bool missed = false;
+#pragma unroll
+    for (int c = 0; c < kLiteralChunks; ++c) {
+      const unsigned long long floor = open && c < parts ? load_agent(floors + o * parts + c) : 0ull;
+      if (floor != 0ull)
+        missed = missed || n_keep < limit || sortable_u64(s.logp[fb + tid] + (static_cast<double>(key_logit(floor)) - L.lse[tid])) >= ~inv_low;
+    }
+    if (missed) atomicOr(&s.state, 4);
+    __syncthreads();
+    if (!(s.state & 4)) break;
+    // (the lowest score chosen bounds what can be chosen, closely: this time the parts are short)
+    if (n_keep == limit) low = unsortable_f64(~inv_low);
+    most = limit;
+    __syncthreads();
+  }
+  return n_keep;
+}
+
+// ---- selector: the loop of Alg. 2 for sequence b.
 // exit_ticket(ok): takes the workgroup's exit ticket; called when everything other workgroups
 // of the launch look at has been performed.
-template <typename Exit>
-__device__ __forceinline__ void select_layers(const ExpandArgs& a, SelectorLds& s, const int b, Exit&& exit_ticket) {
+// UNCAPPED: the pool as Alg. 2 writes it, from the tree state as it stands, at most a.layers layers.
+template <int EPL, bool UNCAPPED, typename Exit>
+__device__ __forceinline__ void select_layers(const ExpandArgs& a, const LiteralAhead& la, SelectorLds& s, const int b, Exit&& exit_ticket) {
   const SelectArgs& sa = a.sel;
   const talon_tree_state& st = sa.st;
   const int tid = threadIdx.x;
   const int k = a.k;
   const size_t base = static_cast<size_t>(b) * st.N_pad;
   const int blocks_per_row = a.chunks;
-  // Alg. 2 line 1: T = {x_t}, p(x_t) = 1
-  if (tid == 0) {
+  int n = 1, fb = 0, F = 1, d = 0;
+  uint32_t status = 0u;
+  bool waited_out = false, active = true;
+  if constexpr (UNCAPPED) {
+    status = st.status[b];
+    n = st.n_nodes[b];
+    fb = st.frontier_begin[b];
+    F = st.frontier_count[b];
+    d = st.depth_cur[b];
+    active = has_frontier(st, b);
+    if (active && tid < F) s.logp[fb + tid] = st.logp[base + fb + tid];
+    if (tid == 0) s.state = 0;
+  } else if (tid == 0) {
+    // Alg. 2 line 1: T = {x_t}, p(x_t) = 1
     st.token[base] = a.root_token[b];
     st.parent[base] = -1;
     st.depth[base] = 0;
@@ -206,13 +474,11 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, SelectorLds& 
     s.logp[0] = 0.0;
     s.state = 0;
   }
+  const int d_end = UNCAPPED ? d + a.layers : a.layers;
   if (tid < TALON_N_MAX / 64) s.ready[tid] = 0ull;
   bool own_ready = false;   // row `tid` of the sequence is known to be ready
-  int n = 1, fb = 0, F = 1, d = 0;
-  uint32_t status = 0u;
-  bool waited_out = false;
   __syncthreads();
-  while (true) {
+  while (active) {
     // ---- scores of the pool.  A frontier row is shared by 2^lt consecutive threads; thread t owns
     // `per` <= 32 consecutive candidates of row t >> lt, so that the threads' candidates follow
     // one another in (parent, rank) order.  Every thread waits for its own row and goes on from
@@ -282,6 +548,7 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, SelectorLds& 
       double score_x[kRegCand];
       score_group(i0, tok_x, prob_x, score_x);
     }
+    if (UNCAPPED && tid == 0) s.want = 0;   // (no row has to be read again)
     anchor = block_max_u64(anchor, s.red_u64);   // (its barriers: every thread's wait has ended)
     const int found = s.state;
     if (found & 2) { waited_out = true; break; }
@@ -290,7 +557,7 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, SelectorLds& 
     // Which of all rows are ready by now?  Thread t asks for row t; the answer arrives under the
     // selection and spares the next layer a round trip in front of its loads.
     int32_t own = 0;
-    if (!own_ready && tid < a.ahead_rows) own = load_agent(a.ticket + base + tid);
+    if (!own_ready && tid < (UNCAPPED ? st.N - 1 : a.ahead_rows)) own = load_agent(a.ticket + base + tid);
     const int R = st.N - n;
     const bool init = d < sa.init_layers;
     const int limit = init ? (sa.K_init < R ? sa.K_init : R) : R;
@@ -303,25 +570,48 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, SelectorLds& 
     int n_keep;
     int pos;
     const unsigned int keep_bits = keep_best(my, per, anchor, thr, limit, lds, &pos, &n_keep);
-    auto append = [&](const int tok, const float prob, const double score) __attribute__((always_inline)) {
-      const int id = n + pos;
-      s.parent[id] = static_cast<unsigned char>(fb + p);
-      s.logp[id] = score;
-      st.token[base + id] = tok;
-      st.parent[base + id] = fb + p;
-      st.depth[base + id] = d + 1;
-      st.prob[base + id] = prob;
-      st.logp[base + id] = score;
-      ++pos;
-    };
+    bool again = false;
+    if constexpr (UNCAPPED) {
+      // Was a row's last candidate kept?  (Of a single row the `limit` best are its first ones.)
+      const int last = k - 1 - rank0;
+      if (a.vocab > k && !(F == 1 && n_keep == limit) && last >= 0 && last < per && ((keep_bits >> last) & 1u)) s.want = 1;
+      __syncthreads();
+      again = s.want != 0;
+    }
+    if (UNCAPPED && again) {
+      if (tid == 0 && n + n_keep >= st.N) store_agent(stop_word(a, b), 1);   // the budget will be spent: no further rows are needed
+      double low = init || anchor == 0ull ? -__builtin_huge_val() : sa.log_mu + unsortable_f64(anchor);
+      unsigned long long inv_low = 0ull;   // of the lowest score kept
+      const int kept_last = 31 - __clz(static_cast<int>(keep_bits));   // a row's kept candidates are its first ones
+      if (keep_bits != 0u) {
+        const unsigned long long key = load_agent(row_keys + rank0 + kept_last);
+        inv_low = ~sortable_u64(plogp + (static_cast<double>(unsortable_f32(static_cast<uint32_t>(key >> 32))) - lse));
+      }
+      inv_low = block_max_u64(inv_low, s.red_u64);
+      if (n_keep == limit) low = unsortable_f64(~inv_low);   // nothing below it can be chosen
+      n_keep = deep_select<EPL>(a, la, s, b, F, fb, n, d, limit, low, keep_bits != 0u ? rank0 + kept_last + 1 : 0, p, &waited_out);
+      if (waited_out) break;
+    } else {
+      auto append = [&](const int tok, const float prob, const double score) __attribute__((always_inline)) {
+        const int id = n + pos;
+        s.parent[id] = static_cast<unsigned char>(fb + p);
+        s.logp[id] = score;
+        st.token[base + id] = tok;
+        st.parent[base + id] = fb + p;
+        st.depth[base + id] = d + 1;
+        st.prob[base + id] = prob;
+        st.logp[base + id] = score;
+        ++pos;
+      };
 #pragma unroll
-    for (int i = 0; i < kRegCand; ++i)
-      if (keep_bits & (1u << i)) append(tok_r[i], prob_r[i], score_r[i]);
-    for (int i = kRegCand; i < per; ++i) {
-      if (!(keep_bits & (1u << i))) continue;
-      const unsigned long long key = load_agent(row_keys + rank0 + i);
-      const double edge = static_cast<double>(unsortable_f32(static_cast<uint32_t>(key >> 32))) - lse;
-      append(static_cast<int32_t>(0xFFFFFFFFu - static_cast<uint32_t>(key)), __expf(static_cast<float>(edge)), plogp + edge);
+      for (int i = 0; i < kRegCand; ++i)
+        if (keep_bits & (1u << i)) append(tok_r[i], prob_r[i], score_r[i]);
+      for (int i = kRegCand; i < per; ++i) {
+        if (!(keep_bits & (1u << i))) continue;
+        const unsigned long long key = load_agent(row_keys + rank0 + i);
+        const double edge = static_cast<double>(unsortable_f32(static_cast<uint32_t>(key >> 32))) - lse;
+        append(static_cast<int32_t>(0xFFFFFFFFu - static_cast<uint32_t>(key)), __expf(static_cast<float>(edge)), plogp + edge);
+      }
     }
     fb = n;
     F = n_keep;
@@ -329,7 +619,7 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, SelectorLds& 
     ++d;
     if (n >= st.N) status |= TALON_STATUS_DONE_BUDGET;
     else if (d >= sa.max_depth) status |= TALON_STATUS_DONE_DEPTH;
-    if (status != 0u || F == 0 || d >= a.layers) break;
+    if (status != 0u || F == 0 || d >= d_end) break;
     own_ready = own_ready || own == kRowReady;
     const unsigned long long ready = __ballot(own_ready);
     if ((tid & 63) == 0) s.ready[tid >> 6] = ready;
@@ -338,25 +628,31 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, SelectorLds& 
   // ---- the sequence needs no further rows; this workgroup has finished with tickets and counters
   if (tid == 0) {
     store_agent(stop_word(a, b), 1);
-    if (ahead_items(a) > static_cast<int>(gridDim.x) - a.B) {   // scanners take items from the counter
+    if (UNCAPPED || ahead_items(a) > static_cast<int>(gridDim.x) - a.B) {   // scanners take items from the counter, helpers look at it
       // the last sequence to finish ends the list of items: nobody looks at the remaining ones
       const uint32_t finished = __hip_atomic_fetch_add(a.exit_ticket + kSelectedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (finished == static_cast<uint32_t>(a.B) - 1u)
         __hip_atomic_fetch_add(item_counter(a), 1u << 30, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    store_agent(st.status + b, waited_out ? (status | TALON_STATUS_ABORTED) : status);   // (the last workgroup may add to it)
+    if (!UNCAPPED || active) store_agent(st.status + b, waited_out ? (status | TALON_STATUS_ABORTED) : status);   // (the last workgroup may add to it)
   }
   stores_performed();
   __syncthreads();
   exit_ticket(a.exit_ticket, !waited_out);
   const bool bad_row = (status & TALON_STATUS_BAD_ROW) != 0u;
+  if constexpr (UNCAPPED) {
+    if (!active) {   // nothing to expand; a row of an earlier layer could not be normalised: the sequence stops here
+      if (tid == 0 && bad_row && !(status & kDoneMask) && F > 0) st.frontier_count[b] = 0;
+      return;
+    }
+  }
   if (tid == 0) {
     st.n_nodes[b] = n;
     st.frontier_begin[b] = fb;
     st.frontier_count[b] = bad_row ? 0 : F;
     st.depth_cur[b] = d;
   }
-  if (waited_out) return;
+  if (UNCAPPED || waited_out) return;
   // ---- candidate arrays and statistics of the rows that were expanded: rows 0 .. rows-1
   const int rows = bad_row ? fb + F : fb;
   for (int r = tid; r < rows; r += kThreads) {
@@ -409,12 +705,13 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, SelectorLds& 
   }
 }
 
-template <int EPL>
-__global__ __launch_bounds__(kThreads, 4) void build_ahead_kernel(ExpandArgs a) {
+// Workgroups: scanners, then one selector per sequence, then (uncapped pool) helpers.
+template <int EPL, bool UNCAPPED>
+__device__ __forceinline__ void ahead_body(const ExpandArgs& a, const LiteralAhead& la) {
   __shared__ __attribute__((aligned(16))) unsigned char s_lds[kAheadLds];
   __shared__ int s_go;
   // Exit ticket: taken when everything a workgroup has written to row tickets, stop words and the
-  // counter has been performed.  Scanners count in kExitGroups groups whose last arrivals count
+  // counter has been performed.  Scanners (and helpers) count in kExitGroups groups whose last arrivals count
   // the group (one word for all would serialise a thousand atomics); selectors, which leave last
   // and whose way out is the launch's tail, count at the top themselves.
   uint32_t before = 0u;
@@ -423,25 +720,28 @@ __global__ __launch_bounds__(kThreads, 4) void build_ahead_kernel(ExpandArgs a) 
     gave_up = !ok;
     if (threadIdx.x == 0) before = __hip_atomic_fetch_add(word, ok ? 1u : 0x10001u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  const int scanners = static_cast<int>(gridDim.x) - a.B;
-  const bool scanner = static_cast<int>(blockIdx.x) < scanners;
-  const uint32_t group = blockIdx.x % kExitGroups;
-  if (scanner) {
-    scan_rows<EPL>(a, *reinterpret_cast<ScannerLds*>(s_lds), blockIdx.x, scanners);
+  const int others = static_cast<int>(gridDim.x) - a.B;                  // scanners and helpers
+  const int scanners = UNCAPPED ? others - la.helpers : others;
+  const int wg = static_cast<int>(blockIdx.x);
+  const bool selector = wg >= scanners && wg < scanners + a.B;
+  const uint32_t group = (wg < scanners ? wg : wg - a.B) % kExitGroups;
+  if (!selector) {
+    if (!UNCAPPED || wg < scanners) scan_rows<EPL, UNCAPPED>(a, *reinterpret_cast<ScannerLds*>(s_lds), wg, scanners, la.first_row);
+    else help_read<EPL>(a, la, *reinterpret_cast<PartLds*>(s_lds), wg - scanners - a.B);
     stores_performed();
     __syncthreads();
     exit_ticket(a.exit_ticket + 1 + group, true);
   } else {
     __builtin_amdgcn_s_setprio(3);   // its instructions are the launch's critical path; the scanners it shares a compute unit with wait for memory anyway
-    select_layers(a, *reinterpret_cast<SelectorLds*>(s_lds), static_cast<int>(blockIdx.x) - scanners, exit_ticket);
+    select_layers<EPL, UNCAPPED>(a, la, *reinterpret_cast<SelectorLds*>(s_lds), wg - scanners, exit_ticket);
   }
   // ---- the last workgroup to leave puts row tickets, sequence words and counters back to zero
   if (threadIdx.x == 0) {
-    const uint32_t n_groups = scanners < static_cast<int>(kExitGroups) ? scanners : kExitGroups;
-    const uint32_t in_group = (scanners - group + kExitGroups - 1) / kExitGroups;
+    const uint32_t n_groups = others < static_cast<int>(kExitGroups) ? others : kExitGroups;
+    const uint32_t in_group = (others - group + kExitGroups - 1) / kExitGroups;
     uint32_t top = before;
-    bool counted = !scanner;
-    if (scanner && (before & 0xFFFFu) == in_group - 1u) {   // last of its group
+    bool counted = selector;
+    if (!selector && (before & 0xFFFFu) == in_group - 1u) {   // last of its group
       top = __hip_atomic_fetch_add(a.exit_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       counted = true;
     }
@@ -455,9 +755,37 @@ __global__ __launch_bounds__(kThreads, 4) void build_ahead_kernel(ExpandArgs a) 
   for (int i = t; i < a.B * a.N_pad; i += kThreads) store_agent(a.ticket + i, 0);
   for (int i = t; i < a.B; i += kThreads) {
     store_agent(stop_word(a, i), 0);
+    if constexpr (UNCAPPED) {
+      store_agent(claim_word(a, i), 0ull);
+      store_agent(parts_done_word(a, i), 0u);
+      store_agent(la.first_row + i, 0);
+    }
     if (s_go == 2) atomicOr(&a.status[i], TALON_STATUS_ABORTED);
   }
   for (int i = t; i < kExitWords; i += kThreads) store_agent(a.exit_ticket + i, 0u);
+}
+
+template <int EPL>
+__global__ __launch_bounds__(kThreads, 4) void build_ahead_kernel(ExpandArgs a) {
+  ahead_body<EPL, false>(a, LiteralAhead{});
+}
+
+// The uncapped pool (talon_expand_literal_ahead).
+template <int EPL>
+__global__ __launch_bounds__(kThreads, 4) void literal_ahead_kernel(ExpandArgs a, LiteralAhead la) {
+  ahead_body<EPL, true>(a, la);
+}
+
+// In front of it: the counters at zero, and the first row of every sequence that has to be scanned.
+__global__ __launch_bounds__(kThreads) void literal_ahead_init_kernel(talon_tree_state st, uint32_t* words, int n_words, int32_t* first_row) {
+  for (int i = blockIdx.x * kThreads + threadIdx.x; i < n_words; i += gridDim.x * kThreads) {
+    const int b = i - static_cast<int>(first_row - reinterpret_cast<int32_t*>(words));
+    uint32_t v = 0u;
+    if (b >= 0 && b < st.B) {
+      v = has_frontier(st, b) ? static_cast<uint32_t>(st.frontier_begin[b]) : static_cast<uint32_t>(st.N);
+    }
+    words[i] = v;
+  }
 }
 
 }  // namespace
@@ -468,15 +796,34 @@ hipError_t launch_build_ahead(const ExpandArgs& a, int dtype, int grid, hipStrea
   return hipGetLastError();
 }
 
-int build_ahead_resident(int dtype) {
+hipError_t launch_literal_ahead(const ExpandArgs& a, const LiteralAhead& la, int dtype, int grid, void* counters, size_t counter_bytes, hipStream_t s) {
+  const int n_words = static_cast<int>(counter_bytes / 4);
+  hipLaunchKernelGGL(literal_ahead_init_kernel, dim3((n_words + kThreads - 1) / kThreads), dim3(kThreads), 0, s, a.sel.st,
+                     static_cast<uint32_t*>(counters), n_words, la.first_row);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (dtype == TALON_DTYPE_F32) hipLaunchKernelGGL(literal_ahead_kernel<4>, dim3(grid), dim3(kThreads), 0, s, a, la);
+  else hipLaunchKernelGGL(literal_ahead_kernel<8>, dim3(grid), dim3(kThreads), 0, s, a, la);
+  return hipGetLastError();
+}
+
+namespace {
+template <typename Kernel>
+int resident_workgroups(Kernel* kernel) {
   int dev = 0, per_cu = 0;
   hipDeviceProp_t prop;
   if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-  const hipError_t e = dtype == TALON_DTYPE_F32
-      ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, build_ahead_kernel<4>, kThreads, 0)
-      : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, build_ahead_kernel<8>, kThreads, 0);
-  if (e != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) != hipSuccess) return 0;
   return per_cu * prop.multiProcessorCount;
+}
+}  // namespace
+
+int build_ahead_resident(int dtype) {
+  return dtype == TALON_DTYPE_F32 ? resident_workgroups(build_ahead_kernel<4>) : resident_workgroups(build_ahead_kernel<8>);
+}
+
+int literal_ahead_resident(int dtype) {
+  return dtype == TALON_DTYPE_F32 ? resident_workgroups(literal_ahead_kernel<4>) : resident_workgroups(literal_ahead_kernel<8>);
 }
 
 }  // namespace talon

@@ -388,6 +388,18 @@ int ahead_grid_limit(int dtype) {
   return v;
 }
 
+// ... and for its form with the uncapped pool.
+int literal_ahead_grid_limit(int dtype) {
+  static std::atomic<int> cached[2] = {{-1}, {-1}};
+  std::atomic<int>& c = cached[dtype == TALON_DTYPE_F32 ? 0 : 1];
+  int v = c.load(std::memory_order_relaxed);
+  if (v < 0) {
+    v = literal_ahead_resident(dtype);
+    c.store(v, std::memory_order_relaxed);
+  }
+  return v;
+}
+
 // Bound of the wait between two layers of the single-launch kernel, in ticks of the 100 MHz
 // wall clock (default 0.2 s; talon_set_spin_limit_us changes it).
 std::atomic<long long> g_spin_limit_us{200000};
@@ -605,6 +617,43 @@ int talon_build_tree_checked(const int32_t* root_token, const void* logits, int 
   return rc;
 }
 
+namespace {
+// The checks of the uncapped calls (the layout has been worked out already).
+int check_literal_args(const void* logits, int dtype, int64_t row_stride, int64_t seq_stride, int row_mode, int32_t layers,
+                       const talon_tree_state* st, int32_t vocab, float mu, int32_t K_init, int32_t init_layers, int32_t max_depth,
+                       void* workspace, size_t workspace_bytes, const LiteralLayout& V, ExpandLayout* L) {
+  char* w = static_cast<char*>(workspace);
+  // the scan's own checks (pointers, alignment, strides), its outputs in the workspace
+  int rc = check_expand_args(logits, dtype, row_stride, seq_stride, row_mode, st, vocab, V.k_max, w ? w + V.off_token : nullptr,
+                         w ? w + V.off_logit : nullptr, w ? w + V.off_prob : nullptr, w ? w + V.off_edge : nullptr,
+                         w ? w + V.off_max : nullptr, w ? w + V.off_lse : nullptr, workspace, workspace_bytes, L);
+  if (rc) return rc;
+  if (workspace_bytes < V.total) {
+    set_error("workspace of %zu bytes is smaller than the %zu needed", workspace_bytes, V.total);
+    return TALON_ERR_WORKSPACE;
+  }
+  if (!(mu > 0.f && mu <= 1.f)) { set_error("mu=%g outside (0, 1]", (double)mu); return TALON_ERR_INVALID_ARG; }
+  if (K_init < 1) { set_error("K_init=%d must be >= 1", K_init); return TALON_ERR_INVALID_ARG; }
+  if (init_layers < 0) { set_error("init_layers=%d must be >= 0", init_layers); return TALON_ERR_INVALID_ARG; }
+  if (max_depth < 1) { set_error("max_depth=%d must be >= 1", max_depth); return TALON_ERR_INVALID_ARG; }
+  if (layers < 1) { set_error("layers=%d must be >= 1", layers); return TALON_ERR_INVALID_ARG; }
+  return TALON_OK;
+}
+
+// Fewest layers of an uncapped call whose rows are scanned ahead.
+constexpr int kLiteralAheadLayers = 4;
+
+// Workgroups that read parts of rows again: 64 (a request has up to 64 parts, more for more than 64 rows).
+// They come last in the grid, behind the scanners; where the scan takes several rounds, as many scanners
+// fewer are started, so that helpers are there from the beginning.
+int literal_helpers(int B, int resident, int scanners, long long items, int* scanners_out) {
+  const int helpers = 64;
+  if (items > scanners && scanners + B + helpers > resident && scanners > 2 * helpers) scanners -= helpers;
+  *scanners_out = scanners;
+  return helpers;
+}
+}  // namespace
+
 size_t talon_literal_workspace_bytes(int32_t B, int32_t N_pad, int32_t vocab, int dtype) {
   LiteralLayout V;
   if (literal_layout(B, N_pad, vocab, dtype, &V)) return 0;
@@ -620,26 +669,15 @@ int talon_expand_literal(const void* logits, int dtype, int64_t row_stride, int6
   LiteralLayout V;
   rc = literal_layout(st->B, st->N_pad, vocab, dtype, &V);
   if (rc) return rc;
-  char* w = static_cast<char*>(workspace);
-  ExpandLayout L;
   // The scan ranks the 16 best tokens of every row where the workspace has room for them: on
   // top-K layers with K_init <= 16 they are the row's survivors, and on gated layers they settle
   // every row of which fewer than 16 tokens pass the gate; other rows are read a second time.
   const int k_scan = V.k_max;
-  // the scan's own checks (pointers, alignment, strides), its outputs in the workspace
-  rc = check_expand_args(logits, dtype, row_stride, seq_stride, row_mode, st, vocab, k_scan, w ? w + V.off_token : nullptr,
-                         w ? w + V.off_logit : nullptr, w ? w + V.off_prob : nullptr, w ? w + V.off_edge : nullptr,
-                         w ? w + V.off_max : nullptr, w ? w + V.off_lse : nullptr, workspace, workspace_bytes, &L);
-  if (rc) return rc;
-  if (workspace_bytes < V.total) {
-    set_error("workspace of %zu bytes is smaller than the %zu needed", workspace_bytes, V.total);
-    return TALON_ERR_WORKSPACE;
-  }
-  if (!(mu > 0.f && mu <= 1.f)) { set_error("mu=%g outside (0, 1]", (double)mu); return TALON_ERR_INVALID_ARG; }
-  if (K_init < 1) { set_error("K_init=%d must be >= 1", K_init); return TALON_ERR_INVALID_ARG; }
-  if (init_layers < 0) { set_error("init_layers=%d must be >= 0", init_layers); return TALON_ERR_INVALID_ARG; }
-  if (max_depth < 1) { set_error("max_depth=%d must be >= 1", max_depth); return TALON_ERR_INVALID_ARG; }
-  if (layers < 1) { set_error("layers=%d must be >= 1", layers); return TALON_ERR_INVALID_ARG; }
+  ExpandLayout L;
+  if ((rc = check_literal_args(logits, dtype, row_stride, seq_stride, row_mode, layers, st, vocab, mu, K_init, init_layers, max_depth,
+                               workspace, workspace_bytes, V, &L)))
+    return rc;
+  char* w = static_cast<char*>(workspace);
   if (V.capped_loop_fits && st->N >= 2) {
     // At most 64 nodes: with a per-row cap of N - 1 (the whole row, if the vocabulary is smaller)
     // no row is ever cut short, so the capped loop in its single launch builds the same tree
@@ -713,6 +751,65 @@ int talon_expand_literal(const void* logits, int dtype, int64_t row_stride, int6
     if (rc) return rc;
   }
   return TALON_OK;
+}
+
+int talon_expand_literal_ahead(const void* logits, int dtype, int64_t row_stride, int64_t seq_stride, int32_t rows,
+                               int32_t layers, const talon_tree_state* st, int32_t vocab, float mu, int32_t K_init,
+                               int32_t init_layers, int32_t max_depth, void* workspace, size_t workspace_bytes,
+                               void* stream) {
+  if (rows < 1) { set_error("rows=%d must be >= 1", rows); return TALON_ERR_INVALID_ARG; }
+  LiteralLayout V;
+  const int least = max_depth < layers ? max_depth : layers;
+  // Layer by layer where rows the trees may ask for are not there, where the workspace has no room for the 16 best
+  // of a row, and for calls of few layers, which would mostly scan rows in vain (three launches a layer, about
+  // 15 us each, against one scan of all rows).
+  // So too small trees of which a top-K layer is all there is to select: the capped loop takes 31 us for 8 sequences of
+  // 30 nodes and 33 for 26 of 19, the scan of all rows 75 and 113.
+  if (check_state(st) || st->N < 2 || rows < st->N - 1 || least < kLiteralAheadLayers ||
+      literal_layout(st->B, st->N_pad, vocab, dtype, &V) || V.k_max < kLiteralScanK ||
+      (V.capped_loop_fits && init_layers > 0 && K_init >= st->N - 1))
+    return talon_expand_literal(logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, layers, st, vocab, mu, K_init,
+                                init_layers, max_depth, workspace, workspace_bytes, stream);
+  ExpandLayout L;
+  int rc = check_literal_args(logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, layers, st, vocab, mu, K_init, init_layers,
+                              max_depth, workspace, workspace_bytes, V, &L);
+  if (rc) return rc;
+  char* w = static_cast<char*>(workspace);
+  L = V.scan;
+  ExpandArgs ea = make_expand_args(logits, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, kLiteralScanK, nullptr, nullptr,
+                                   nullptr, nullptr, nullptr, nullptr, workspace, L);
+  ea.sel.st = *st; ea.sel.k = kLiteralScanK; ea.sel.log_mu = log(static_cast<double>(mu)); ea.sel.K_init = K_init;
+  ea.sel.init_layers = init_layers; ea.sel.max_depth = max_depth;
+  ea.layers = layers;
+  ea.spin_ticks = 200000000ull;   // two seconds of the 100 MHz clock: scanners and claimed parts never wait, so these waits end; the bound is a safety net
+  const int resident = literal_ahead_grid_limit(dtype);
+  if (resident < 1) { set_error("occupancy query for the scan-ahead kernel failed"); return TALON_ERR_RUNTIME; }
+  // (every row from a sequence's frontier on may be asked for, whatever its depth)
+  AheadPlan plan = ahead_plan(st->B, st->N, L.chunks, kLiteralScanK, K_init, init_layers, st->N, resident);
+  // Layer by layer too where the scan of all rows is long, more than 40 blocks per scanner (650 MB in all): trees of flat
+  // rows end after two layers, and most of it would be in vain.  16 x 249 rows of 200 KB, flat: 240 us, 368 ahead; 16 x 127
+  // of 513 KB in at most four layers: 217, 255 (peaked rows and many layers would gain: 16 x 255 of 304 KB, a depth cap of
+  // 24: 511, 350).  Below that line peaked, mixed and most flat batches are faster ahead: 13 x 59 of 513 KB 524 -> 146, 16 x 71
+  // 327 -> 195, 2 x 249 of 257 KB flat 203 -> 95; 4 x 249 of 304 KB, all flat, is the exception: 130 -> 190.
+  if (static_cast<long long>(st->B) * plan.rows * L.chunks > 40ll * resident)
+    return talon_expand_literal(logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, layers, st, vocab, mu, K_init,
+                                init_layers, max_depth, workspace, workspace_bytes, stream);
+  LiteralAhead la;
+  la.helpers = literal_helpers(st->B, resident, plan.scanners,
+                               static_cast<long long>(st->B) * (static_cast<long long>(plan.head) * plan.chunks_head +
+                                                                static_cast<long long>(plan.rows - plan.head) * plan.chunks),
+                               &plan.scanners);
+  ea.ahead_rows = plan.rows;
+  ea.ahead_head = plan.head;
+  ea.ahead_chunks_head = plan.chunks_head;
+  ea.ahead_chunks = plan.chunks;
+  la.first_row = ea.seq_ticket;
+  la.request = reinterpret_cast<unsigned long long*>(w + V.off_keys);
+  la.part_key = reinterpret_cast<unsigned long long*>(w + V.off_part_keys);
+  la.part_keys_per_seq = V.part_keys_per_seq;
+  la.part_count = reinterpret_cast<int32_t*>(w + V.off_part_count);
+  return check_hip(launch_literal_ahead(ea, la, dtype, plan.scanners + st->B + la.helpers, w + L.off_ticket, L.off_max - L.off_ticket,
+                                        static_cast<hipStream_t>(stream)), "literal scan-ahead launch");
 }
 
 int talon_set_spin_limit_us(int64_t microseconds) {

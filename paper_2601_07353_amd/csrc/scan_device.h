@@ -199,6 +199,21 @@ __device__ __forceinline__ void rank_lists(const int k, const unsigned long long
   }
 }
 
+// The largest value with a 16-bit (sign, exponent, 7 mantissa bits) pattern that at least k of
+// the 64 values v reach, found bit by bit on their order-preserving integer images (-inf if
+// fewer than k lanes hold a logit).  For bf16 logits this is the k-th largest of them itself.
+// With the lane maxima of a group it bounds the k best of all logits met so far from below.
+__device__ __forceinline__ float kth_of_lanes(const float v, const int k) {
+  const uint32_t u = sortable_u32(v);
+  uint32_t prefix = 0u;
+#pragma unroll
+  for (int bit = 31; bit >= 16; --bit) {
+    const uint32_t cand = prefix | (1u << bit);
+    if (__popcll(__ballot(u >= cand)) >= k) prefix = cand;
+  }
+  return prefix <= 0x007FFFFFu ? kNegInf : unsortable_f32(prefix);   // at or below the image of -inf
+}
+
 // LDS of a scan, provided by the kernel.
 struct ScanLds {
   uint4 (*hitv)[kHitCap];                    // [4] buffered vectors per wavefront
@@ -269,21 +284,6 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
       cnt += nh;
     }
     return true;
-  };
-
-  // The largest value with a 16-bit (sign, exponent, 7 mantissa bits) pattern that at least k of
-  // the 64 values v reach, found bit by bit on their order-preserving integer images (-inf if
-  // fewer than k lanes hold a logit).  For bf16 logits this is the k-th largest of them itself.
-  // With the lane maxima of a group it bounds the k best of all logits met so far from below.
-  auto kth_of_lanes = [&](float v) -> float {
-    const uint32_t u = sortable_u32(v);
-    uint32_t prefix = 0u;
-#pragma unroll
-    for (int bit = 31; bit >= 16; --bit) {
-      const uint32_t cand = prefix | (1u << bit);
-      if (__popcll(__ballot(u >= cand)) >= k) prefix = cand;
-    }
-    return prefix <= 0x007FFFFFu ? kNegInf : unsortable_f32(prefix);   // at or below the image of -inf
   };
 
   // Streaming state machine.  A step is a group of 4 tiles.  Tiles whose hits do not fit the
@@ -377,13 +377,13 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
       }
       s_l += static_cast<double>(acc * __builtin_amdgcn_exp2f(-c_err));
       if (tb == t0) {
-        tau = kth_of_lanes(gmax);
+        tau = kth_of_lanes(gmax, k);
         force = true;
       } else if (__popcll(__ballot(gmax >= tau)) > k + kRaiseHits) {
         // Many lanes hold a new candidate: the row rises along the token ids (a sorted row, or a
         // permutation with a short period).  The group's own maxima raise the threshold before
         // anything is buffered, so that such a row does not rank every one of its vectors.
-        tau = fmaxf(tau, kth_of_lanes(gmax));
+        tau = fmaxf(tau, kth_of_lanes(gmax, k));
       }
 #pragma unroll
       for (int q = 0; q < kScanTiles; ++q)

@@ -149,6 +149,16 @@ struct LiteralArgs {
   int32_t* row_ticket;             // [B*N_pad] parts of a row that have finished; zero between launches
 };
 
+// The uncapped pool with rows scanned ahead (ahead.hip).
+struct LiteralAhead {
+  int helpers;                     // workgroups that read parts of rows again
+  int32_t* first_row;              // [B] first row to scan
+  unsigned long long* request;     // [B][N_pad + 1] rows to read again: header, then node << 32 | logit bound; behind them [B][320] floors of the parts
+  unsigned long long* part_key;    // [B][part_keys_per_seq] keys of the parts
+  size_t part_keys_per_seq;
+  int32_t* part_count;             // [B][N_pad * kLiteralChunks]
+};
+
 // Target argmax over every node of every tree.
 struct ArgmaxArgs {
   const void* logits;
@@ -217,7 +227,9 @@ hipError_t launch_fused_init(const talon_tree_state& st, const ExpandArgs& a, co
 hipError_t launch_expand_tree(const ExpandArgs& a, int dtype, int grid, hipStream_t s);
 int expand_tree_max_grid(int dtype);
 hipError_t launch_build_ahead(const ExpandArgs& a, int dtype, int grid, hipStream_t s);
+hipError_t launch_literal_ahead(const ExpandArgs& a, const LiteralAhead& la, int dtype, int grid, void* counters, size_t counter_bytes, hipStream_t s);
 int build_ahead_resident(int dtype);
+int literal_ahead_resident(int dtype);
 hipError_t launch_expand(const ExpandArgs& a, int dtype, int grid, bool fused, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_mask(const talon_tree_state& st, uint64_t* mask, hipStream_t s);

@@ -364,3 +364,73 @@ def test_dense_frontier_batches_with_padded_rows():
         np.testing.assert_array_equal(st.parent[b, :t.n].cpu().numpy(), np.asarray(t.parent, dtype=np.int32))
         np.testing.assert_allclose(np.exp(st.logp[b, :t.n].cpu().numpy()), t.confidence(), rtol=H.PROB_RTOL, atol=0)
     assert max(int(np.bincount(np.asarray(t.parent[1:])).max()) for t in trees) > cfg.K
+
+
+# B, V, dtype, N, K_init, init_layers, mu, rows: one row kind per sequence in turn
+AHEAD_SHAPES = [
+    (1, 8, "f32", 12, 3, 1, 0.03, "mixed"),            # fewer tokens than the 16 that a scan ranks
+    (1, 17, "bf16", 64, 20, 1, 1e-6, "flat"),          # top-K layer wider than that; every token passes the gate
+    (2, 4099, "f32", 33, 16, 0, 0.03, "mixed"),        # no top-K layer: the root's row is read again
+    (3, 20011, "bf16", 60, 10, 1, 0.03, "mixed"),
+    (2, 5003, "f32", 130, 4, 2, 0.1, "equal"),         # every score ties; one part of a row holds all its children
+    (70, 1021, "bf16", 20, 5, 1, 0.03, "mixed"),       # more sequences than a helper polls at once and than helpers
+    (4, 151936, "bf16", 128, 8, 1, 0.03, "mixed"),     # eight parts per row
+    (2, 40001, "f32", 256, 2, 1, 0.003, "flat"),       # two rows share 253 children
+    (16, 60001, "bf16", 250, 16, 1, 0.03, "mixed"),    # several rounds of rows, helpers from the start
+]
+
+
+@pytest.mark.parametrize("shape", AHEAD_SHAPES, ids=lambda s: "-".join(str(x) for x in s))
+@pytest.mark.parametrize("steps", [(24,), (4, 24)])
+def test_rows_scanned_ahead_give_the_layered_trees(shape, steps):
+    """talon_expand_literal_ahead against talon_expand_literal, in one call and continued in the
+    middle of the trees, with a sequence that is finished from the start and one that has a bad row."""
+    import ctypes
+    import torch
+    import paper_2601_07353_amd as T
+    B, V, dtype, N, K_init, init_layers, mu, kind = shape
+    print("case", shape, steps, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V * 1000 + N)
+    dt, code = (torch.float32, T.TALON_DTYPE_F32) if dtype == "f32" else (torch.bfloat16, T.TALON_DTYPE_BF16)
+    stride = (V + 7) // 8 * 8
+    st = [T.TreeState(B, N) for _ in range(2)]
+    P = st[0].N_pad
+    pool = torch.full((B, P, stride), 60.0, dtype=dt, device="cuda")
+    for b in range(B):
+        scale = torch.rand(P, 1, generator=g, device="cuda")
+        scale = 0.3 + 0.2 * scale if kind == "flat" or (kind == "mixed" and b % 3 == 1) else 0.5 + 7.5 * scale
+        pool[b, :, :V] = (torch.randn(P, V, generator=g, device="cuda") * scale).to(dt) if kind != "equal" else 1.5
+    if B > 2:
+        pool[2, 1, V // 2] = float("nan")
+    logits = pool[:, :, :V]
+    roots = torch.arange(B, dtype=torch.int32, device="cuda")
+    ws = T.make_literal_workspace(B, P, V, code)
+    lib = T.load_library()
+    lib.talon_expand_literal.restype = lib.talon_expand_literal_ahead.restype = ctypes.c_int
+    for i, s in enumerate(st):
+        T.talon_tree_init(s, roots)
+        if B > 1:
+            s.status[1] = T.TALON_STATUS_DONE_DEPTH
+        ws.fill_(0xA5)
+        for layers in steps:
+            if i == 0:
+                rc = lib.talon_expand_literal(logits.data_ptr(), code, stride, stride * P, T.TALON_ROWS_BY_NODE, layers, ctypes.byref(s.c),
+                                              V, mu, K_init, init_layers, 24, ws.data_ptr(), ws.numel(), None)
+            else:
+                rc = lib.talon_expand_literal_ahead(logits.data_ptr(), code, stride, stride * P, N - 1, layers, ctypes.byref(s.c),
+                                                    V, mu, K_init, init_layers, 24, ws.data_ptr(), ws.numel(), None)
+            assert rc == T.TALON_OK
+            torch.cuda.synchronize()
+    # the ahead form leaves its counters at zero, as the other forms of one workspace want them
+    assert not ws[:(B * P * 4 + 255) // 256 * 256].any()
+    want, got = ({k: getattr(s, k).cpu().numpy() for k in ("n_nodes", "status", "depth_cur", "frontier_begin", "frontier_count",
+                                                          "token", "parent", "depth", "prob", "logp")} for s in st)
+    for name in ("n_nodes", "status", "depth_cur", "frontier_begin", "frontier_count", "token", "parent", "depth"):
+        np.testing.assert_array_equal(got[name], want[name], err_msg=name)
+    if B > 2:
+        assert int(want["status"][2]) & T.TALON_STATUS_BAD_ROW and int(want["n_nodes"][1]) == 1
+    # sums of the same fp32 exponentials, grouped otherwise (at most 32 in single precision either way): a few
+    # of their roundings, 2^-24 each
+    np.testing.assert_allclose(got["logp"], want["logp"], rtol=0, atol=24 * 4 * 2.0 ** -24)
+    np.testing.assert_allclose(got["prob"], want["prob"], rtol=16 * 2.0 ** -24)

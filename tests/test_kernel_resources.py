@@ -36,3 +36,29 @@ def test_attention_kernels_do_not_spill(attention_kernels):
         assert r["VGPRs"] <= 256 and r["ScratchSize"] == 0 and r["VGPRs Spill"] == 0, (key, r)
         if not key[2]:
             assert r["SGPRs Spill"] == 0, (key, r)
+
+
+def _assembly(source, tmp_path_factory):
+    path = str(tmp_path_factory.mktemp("s") / "out.s")
+    subprocess.run([B._hipcc(), *B.FLAGS, "--cuda-device-only", "-S", os.path.join(B.CSRC, source), "-o", path],
+                   stdout=subprocess.PIPE, stderr=subprocess.STDOUT, check=True)
+    return open(path).read().splitlines()
+
+
+@pytest.mark.parametrize("source", ["ahead.hip"])
+def test_no_barrier_runs_for_a_part_of_a_wavefront(source, tmp_path_factory):
+    """A loop that starts with `if (threadIdx.x == 0)` right behind another such condition got two entries from
+    the compiler, and its barriers ran once for thread 0 and once for the others: a barrier right behind the
+    instruction that takes lanes out."""
+    narrowed = False
+    for line in _assembly(source, tmp_path_factory):
+        op = line.split(";")[0].split()
+        if not op or op[0].startswith("."):
+            continue
+        if op[0].endswith(":") or op[0] in ("s_branch", "s_endpgm"):
+            narrowed = False
+        elif "saveexec" in op[0]:
+            narrowed = True
+        elif len(op) > 1 and op[1].startswith("exec") and op[0] in ("s_or_b64", "s_mov_b64"):
+            narrowed = False
+        assert not (narrowed and op[0] == "s_barrier"), line
