@@ -1,4 +1,5 @@
-"""ctypes binding of libtalon.so: same names as the C ABI, argument marshalling only.
+"""Binding of libtalon.so: same names as the C ABI, argument marshalling only (the calls a decoding loop
+makes through csrc/marshal.cpp, the others through ctypes).
 
 Tensors are torch CUDA tensors used purely as device buffers; every step of the path runs
 in the library's HIP kernels.  There is no CPU fallback: if the library is missing, or a
@@ -7,6 +8,7 @@ call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from ctypes import POINTER, Structure, c_char_p, c_double, c_float, c_int, c_int32, c_int64, c_size_t, c_void_p
 
@@ -16,6 +18,7 @@ _byref = ctypes.byref
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "lib", "libtalon.so")
+MARSHAL_PATH = os.path.join(_PKG, "lib", "_talon_marshal.so")
 
 TALON_OK = 0
 TALON_ERR_INVALID_ARG = -1
@@ -60,6 +63,36 @@ class _CTreeState(Structure):
 
 
 _lib = None
+
+# what csrc/marshal.cpp calls, in its order
+_MARSHALLED = ["talon_last_error_string", "talon_tree_init", "talon_expand_layer", "talon_select_budget", "talon_expand_select_layer",
+               "talon_expand_tree", "talon_build_tree", "talon_build_tree_ahead", "talon_expand_literal", "talon_expand_literal_ahead",
+               "talon_target_argmax", "talon_greedy_accept", "talon_compact_kv", "talon_build_tree_mask", "talon_tree_attention",
+               "talon_tree_attention_static"]
+
+
+class _Unloaded:
+    """Stands in for the marshalling module until the library is first needed."""
+
+    def __getattr__(self, name):
+        load_library()
+        return getattr(_native, name)
+
+
+_native = _Unloaded()
+
+
+def _load_marshal(lib):
+    global _native
+    if not os.path.exists(MARSHAL_PATH):
+        raise RuntimeError("_talon_marshal.so is not built (%s): run `python -m paper_2601_07353_amd.build` "
+                           "or __graft_entry__.build()" % MARSHAL_PATH)
+    spec = importlib.util.spec_from_file_location("_talon_marshal", MARSHAL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    module.bind(tuple(ctypes.cast(getattr(lib, name), c_void_p).value for name in _MARSHALLED), TalonError, torch.float32, torch.bfloat16,
+                _stream, _raw_stream, _current_device, torch.cuda.is_initialized)
+    _native = module
 
 
 def load_library() -> ctypes.CDLL:
@@ -124,6 +157,7 @@ def load_library() -> ctypes.CDLL:
         fn = getattr(lib, name)
         if fn.restype is c_int:
             fn.restype = c_int
+    _load_marshal(lib)
     _lib = lib
     return lib
 
@@ -133,10 +167,7 @@ def _check(rc: int):
         raise TalonError(rc, load_library().talon_last_error_string().decode())
 
 
-# Marshalling is kept to plain integers: a call is one or two kernels of a few microseconds, and a
-# loop of such calls is bound by the host.  (torch.cuda.current_stream() builds a Stream object, 2.8 us;
-# the raw handle of the current stream is 0.2 us.  A layer of the per-layer loop: 9.3 us of host
-# time per call before, of which the launch itself is 4.1.)
+# (torch.cuda.current_stream() builds a Stream object, 2.8 us; the raw handle of the current stream is 0.2 us.)
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -202,7 +233,7 @@ def _logits_meta(logits: torch.Tensor):
 
 
 def talon_tree_init(st: TreeState, root_token: torch.Tensor, stream=None):
-    _check(load_library().talon_tree_init(_byref(st.c), _ptr(root_token), _stream(stream)))
+    _native.tree_init(st.c, root_token, stream)
 
 
 def talon_expand_workspace_bytes(B, N_pad, vocab, k, dtype) -> int:
@@ -225,57 +256,28 @@ def make_expand_workspace(B, N_pad, vocab, k, dtype, device="cuda") -> torch.Ten
 
 def talon_expand_layer(logits, st: TreeState, k, cand: Candidates, workspace, row_mode=TALON_ROWS_BY_NODE,
                        layer=-1, vocab=None, stream=None):
-    dt, row_stride, seq_stride, V = _logits_meta(logits)
-    _check(load_library().talon_expand_layer(
-        _ptr(logits), dt, row_stride, seq_stride, row_mode, layer, _byref(st.c),
-        V if vocab is None else vocab, k,
-        _ptr(cand.token), _ptr(cand.logit), _ptr(cand.prob), _ptr(cand.edge_logp), _ptr(cand.row_max),
-        _ptr(cand.row_lse), _ptr(workspace), workspace.nbytes, _stream(stream)))
+    _native.expand_layer(logits, st.c, k, cand, workspace, row_mode, layer, vocab, stream)
 
 
 def talon_select_budget(st: TreeState, k, cand: Candidates, mu, K_init, init_layers, max_depth, stream=None):
-    _check(load_library().talon_select_budget(
-        _byref(st.c), k, _ptr(cand.token), _ptr(cand.prob), _ptr(cand.edge_logp), mu, K_init,
-        init_layers, max_depth, _stream(stream)))
+    _native.select_budget(st.c, k, cand, mu, K_init, init_layers, max_depth, stream)
 
 
 def talon_expand_tree(logits, st: TreeState, k, mu, K_init, init_layers, max_depth, cand: Candidates, workspace,
                       row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
-    dt, row_stride, seq_stride, V = _logits_meta(logits)
-    _check(load_library().talon_expand_tree(
-        _ptr(logits), dt, row_stride, seq_stride, row_mode, _byref(st.c), V if vocab is None else vocab, k,
-        mu, K_init, init_layers, max_depth, _ptr(cand.token), _ptr(cand.logit), _ptr(cand.prob),
-        _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(workspace),
-        workspace.nbytes, _stream(stream)))
+    _native.expand_tree(logits, st.c, k, mu, K_init, init_layers, max_depth, cand, workspace, 0, row_mode, vocab, stream)
 
 
 def talon_expand_select_layer(logits, st: TreeState, k, mu, K_init, init_layers, max_depth, cand: Candidates,
                               workspace, layer=-1, row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
-    dt, row_stride, seq_stride, V = _logits_meta(logits)
-    _check(load_library().talon_expand_select_layer(
-        _ptr(logits), dt, row_stride, seq_stride, row_mode, layer, _byref(st.c), V if vocab is None else vocab,
-        k, mu, K_init, init_layers, max_depth, _ptr(cand.token), _ptr(cand.logit), _ptr(cand.prob),
-        _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(workspace),
-        workspace.nbytes, _stream(stream)))
+    _native.expand_select_layer(logits, st.c, k, mu, K_init, init_layers, max_depth, cand, workspace, layer, row_mode, vocab, stream)
 
 
 def talon_build_tree(root_token, logits, st: TreeState, k, mu, K_init, init_layers, max_depth, cand: Candidates,
                      workspace, mask=None, row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
     """With rows by node id the library may read any row of `logits` (a row per node: all are in
     place), which lets it scan rows ahead of the tree; rows the tree does not expand have no effect."""
-    dt, row_stride, seq_stride, V = _logits_meta(logits)
-    if row_mode == TALON_ROWS_BY_NODE and (vocab is None or vocab <= V) and logits.shape[0] >= st.B and logits.shape[1] > 0:
-        _check(load_library().talon_build_tree_ahead(
-            _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, logits.shape[1], _byref(st.c),
-            V if vocab is None else vocab, k, mu, K_init, init_layers, max_depth, _ptr(cand.token),
-            _ptr(cand.logit), _ptr(cand.prob), _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(mask),
-            _ptr(workspace), workspace.nbytes, _stream(stream)))
-        return
-    _check(load_library().talon_build_tree(
-        _ptr(root_token), _ptr(logits), dt, row_stride, seq_stride, row_mode, _byref(st.c),
-        V if vocab is None else vocab, k, mu, K_init, init_layers, max_depth, _ptr(cand.token),
-        _ptr(cand.logit), _ptr(cand.prob), _ptr(cand.edge_logp), _ptr(cand.row_max), _ptr(cand.row_lse), _ptr(mask),
-        _ptr(workspace), workspace.nbytes, _stream(stream)))
+    _native.build_tree(root_token, logits, st.c, k, mu, K_init, init_layers, max_depth, cand, workspace, mask, row_mode, vocab, stream)
 
 
 def talon_build_tree_checked(root_token, logits, st: TreeState, k, mu, K_init, init_layers, max_depth,
@@ -334,7 +336,7 @@ def talon_probe_tile_loads(window: torch.Tensor, loads: int, with_mfma: bool, wa
 
 
 def talon_build_tree_mask(st: TreeState, mask: torch.Tensor, stream=None):
-    _check(load_library().talon_build_tree_mask(_byref(st.c), _ptr(mask), _stream(stream)))
+    _native.build_tree_mask(st.c, mask, stream)
 
 
 def talon_tree_attention_workspace_bytes(B, N_pad, Hq, Hkv, Dh, max_prefix_len) -> int:
@@ -352,38 +354,16 @@ def talon_static_scratch_init():
 def talon_tree_attention_static(q, k_prefix, v_prefix, k_tree, v_tree, mask, n_nodes, prefix_len, max_prefix_len, out,
                                 out_lse=None, scale=0.0, stream=None):
     """talon_tree_attention without a workspace argument (the library's own scratch array)."""
-    return talon_tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, mask, n_nodes, prefix_len, max_prefix_len,
-                                out, out_lse, None, scale, stream, _static=True)
+    _native.tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, mask, n_nodes, prefix_len, max_prefix_len, out, out_lse, None, scale,
+                           stream, True)
 
 
 def talon_tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, mask, n_nodes, prefix_len, max_prefix_len, out,
                          out_lse=None, workspace=None, scale=0.0, stream=None, _static=False):
     """q/k_tree/v_tree [B][N_pad][H][Dh] bf16 dense; k_prefix/v_prefix [B][L][Hkv][Dh] views (any strides
     with a contiguous Dh run); mask [B][N_pad][N_pad/64] int64."""
-    B, N_pad, Hq, Dh = q.shape
-    Hkv = k_tree.shape[2]
-    for t in (q, k_tree, v_tree, out, mask):
-        if not t.is_contiguous():
-            raise TalonError(TALON_ERR_INVALID_ARG, "q, k_tree, v_tree, mask and out must be contiguous")
-    if max_prefix_len == 0 or (k_prefix is not None and k_prefix.numel() == 0):
-        k_prefix = v_prefix = None     # no prefix: the tree attends to itself only
-    if k_prefix is not None:
-        if k_prefix.stride() != v_prefix.stride() or k_prefix.stride(3) != 1:
-            raise TalonError(TALON_ERR_INVALID_ARG, "k_prefix and v_prefix must share strides, Dh contiguous")
-        sb, st_, sh = k_prefix.stride(0), k_prefix.stride(1), k_prefix.stride(2)
-    else:
-        sb = st_ = sh = Dh
-    if _static:
-        _check(load_library().talon_tree_attention_static(
-            _ptr(q), _ptr(k_prefix), _ptr(v_prefix), _ptr(k_tree), _ptr(v_tree), _ptr(mask), _ptr(n_nodes),
-            _ptr(prefix_len), B, N_pad, Hq, Hkv, Dh, max_prefix_len, sb, st_, sh, scale, _ptr(out),
-            _ptr(out_lse), _stream(stream)))
-        return
-    ws_bytes = 0 if workspace is None else workspace.nbytes
-    _check(load_library().talon_tree_attention(
-        _ptr(q), _ptr(k_prefix), _ptr(v_prefix), _ptr(k_tree), _ptr(v_tree), _ptr(mask), _ptr(n_nodes),
-        _ptr(prefix_len), B, N_pad, Hq, Hkv, Dh, max_prefix_len, sb, st_, sh, scale, _ptr(out),
-        _ptr(out_lse), _ptr(workspace), ws_bytes, _stream(stream)))
+    _native.tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, mask, n_nodes, prefix_len, max_prefix_len, out, out_lse, workspace, scale,
+                           stream, _static)
 
 
 def make_literal_workspace(B, N_pad, vocab, dtype) -> torch.Tensor:
@@ -396,16 +376,7 @@ def make_literal_workspace(B, N_pad, vocab, dtype) -> torch.Tensor:
 def talon_expand_literal(logits, st: TreeState, layers, mu, K_init, init_layers, max_depth, workspace,
                          row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
     """With rows by node id the library may read any row of `logits` ahead of the trees, as in talon_build_tree."""
-    dt, row_stride, seq_stride, V = _logits_meta(logits)
-    if row_mode == TALON_ROWS_BY_NODE and (vocab is None or vocab <= V) and logits.shape[0] >= st.B and logits.shape[1] > 0:
-        _check(load_library().talon_expand_literal_ahead(
-            _ptr(logits), dt, row_stride, seq_stride, logits.shape[1], layers, _byref(st.c), V if vocab is None else vocab,
-            mu, K_init, init_layers, max_depth, _ptr(workspace), workspace.nbytes, _stream(stream)))
-        return
-    _check(load_library().talon_expand_literal(
-        _ptr(logits), dt, row_stride, seq_stride, row_mode, layers, _byref(st.c), V if vocab is None else vocab,
-        mu, K_init, init_layers, max_depth, _ptr(workspace), workspace.nbytes,
-        _stream(stream)))
+    _native.expand_literal(logits, st.c, layers, mu, K_init, init_layers, max_depth, workspace, row_mode, vocab, stream)
 
 
 def make_verify_workspace(B, N_pad, vocab, dtype) -> torch.Tensor:
@@ -417,28 +388,17 @@ def make_verify_workspace(B, N_pad, vocab, dtype) -> torch.Tensor:
 
 def talon_target_argmax(logits, st: TreeState, target_token, target_prob, scan_status, workspace, vocab=None,
                         stream=None):
-    dt, row_stride, seq_stride, V = _logits_meta(logits)
-    _check(load_library().talon_target_argmax(
-        _ptr(logits), dt, row_stride, seq_stride, _byref(st.c), V if vocab is None else vocab,
-        _ptr(target_token), _ptr(target_prob), _ptr(scan_status), _ptr(workspace),
-        workspace.nbytes, _stream(stream)))
+    _native.target_argmax(logits, st.c, target_token, target_prob, scan_status, workspace, vocab, stream)
 
 
 def talon_greedy_accept(st: TreeState, target_token, scan_status, path, accept_len, bonus_token, stream=None):
-    _check(load_library().talon_greedy_accept(_byref(st.c), _ptr(target_token), _ptr(scan_status), _ptr(path),
-                                              _ptr(accept_len), _ptr(bonus_token), _stream(stream)))
+    _native.greedy_accept(st.c, target_token, scan_status, path, accept_len, bonus_token, stream)
 
 
 def talon_compact_kv(k_tree, v_tree, path, accept_len, prefix_len, new_prefix_len, k_prefix, v_prefix, stream=None):
     """k_tree/v_tree [B][N_pad][Hkv][Dh] bf16 dense; k_prefix/v_prefix [B][capacity][Hkv][Dh] views sharing
     strides, Dh contiguous."""
-    B, N_pad, Hkv, Dh = k_tree.shape
-    if k_prefix.stride() != v_prefix.stride() or k_prefix.stride(3) != 1:
-        raise TalonError(TALON_ERR_INVALID_ARG, "k_prefix and v_prefix must share strides, Dh contiguous")
-    _check(load_library().talon_compact_kv(
-        _ptr(k_tree), _ptr(v_tree), _ptr(path), _ptr(accept_len), _ptr(prefix_len), _ptr(new_prefix_len),
-        _ptr(k_prefix), _ptr(v_prefix), B, N_pad, Hkv, Dh, k_prefix.shape[1], k_prefix.stride(0), k_prefix.stride(1),
-        k_prefix.stride(2), _stream(stream)))
+    _native.compact_kv(k_tree, v_tree, path, accept_len, prefix_len, new_prefix_len, k_prefix, v_prefix, stream)
 
 
 def talon_prune_tree(st: TreeState, n_keep: int, kept_ids, stream=None):

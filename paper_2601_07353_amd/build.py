@@ -1,9 +1,10 @@
-"""Compile libtalon.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Compile libtalon.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python marshalling module, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +12,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB_DIR = os.path.join(PKG, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libtalon.so")
+MARSHAL_PATH = os.path.join(LIB_DIR, "_talon_marshal.so")
 OBJ_DIR = os.path.join(PKG, "_build")
 
 SOURCES = ["api.hip", "expand.hip", "ahead.hip", "select.hip", "literal.hip", "attention.hip", "accept.hip", "calibrate.hip"]
@@ -52,6 +54,8 @@ def build(verbose: bool = False) -> str:
             if verbose and out.strip():
                 print(out)
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH])
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+          "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH])
     return LIB_PATH
 
 
