@@ -131,6 +131,7 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
   constexpr int BLOCK = kThreads * NX;          // logits per block
   __shared__ int s_prefix[TALON_B_MAX + 1];     // exclusive prefix of frontier sizes
   __shared__ int s_begin[TALON_B_MAX];          // first frontier node of every sequence
+  __shared__ uint32_t s_stat[FUSED && !TREE ? TALON_B_MAX : 1];   // its status when the launch began
   // One LDS pool: the scan's buffers (buffered vectors per wavefront, their tile*64+lane tags,
   // ranking scratch per wavefront; the vector buffers double as row-merge staging) and, in
   // fused mode, the key array and histogram of the budget selection, which runs when the
@@ -198,6 +199,7 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
         const uint32_t stat = a.status[tid];
         const int fc = a.frontier_count[tid];
         s_begin[tid] = a.frontier_begin[tid];
+        if constexpr (FUSED) s_stat[tid] = stat;
         c = (stat & kDoneMask) ? 0 : fc;
       }
       // a finished sequence gets no selection in this launch: carry its empty frontier over
@@ -356,43 +358,70 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
           if (tid == 0) s_last = row_bad ? 2 : 1;   // a one-row frontier: the workgroup that wrote the row selects right away
         }
         __syncthreads();
-        if constexpr (!TREE) {
-          if (s_last) {
-            // One layer per launch: the selection rewrites the state the item map is made from.
-            // Wait until every workgroup of the grid has read it (workgroups that have not
-            // started yet start as others leave; only the at most B selecting workgroups wait,
-            // so the others always get their turn).  The wait is bounded like the single
-            // launch's: a workgroup that gives up marks the sequence aborted and selects nothing.
+        if (s_last) {
+          TL_ANY(launch_idx, 2);
+          // One layer per launch: the selection rewrites the state the item map is made from, so it
+          // writes nothing before every workgroup of the grid has read it (workgroups that have not
+          // started yet start as others leave; only the at most B selecting workgroups wait, so the
+          // others always get their turn).  The wait is bounded like the single launch's: a
+          // workgroup that gives up marks the sequence aborted and selects nothing.
+          // A selection's time is its chain of memory round trips.  The counters
+          // are read here, so that they arrive with the candidates, and looked at before the first
+          // write; the status is the one read when the launch began (this launch itself can only
+          // have added a bad row, which the ticket tells); and which selection is the launch's last
+          // is asked before the writes, and only where there are several.  (Each in its own turn, with
+          // the counters awaited before the selection began: 70.5 us for 12 layers of one sequence of 60
+          // nodes, three of them with rows; this: 68.4, and 65.9 with a grid that is resident at once.)
+          int started = 0;
+          uint32_t selected_before = 0u;
+          int active = 1;
+          bool gave_up = false;
+          auto read_started = [&]() { return lane < kStartedWords ? static_cast<int>(load_agent(started_word(a, lane))) : 0; };
+          if constexpr (!TREE) {
+            if (wave == 0) started = read_started();
+          }
+          auto all_started = [&]() -> bool {
+            if constexpr (TREE) return true;
             if (wave == 0) {
               const unsigned long long t0 = wall_clock64();
-              while (wave_sum_i32(lane < kStartedWords ? static_cast<int>(load_agent(started_word(a, lane))) : 0) !=
-                     static_cast<int>(gridDim.x)) {
-                if (wall_clock64() - t0 > a.spin_ticks) { if (lane == 0) s_last = 3; break; }
+              bool all = true;
+              while (wave_sum_i32(started) != static_cast<int>(gridDim.x)) {
+                if (wall_clock64() - t0 > a.spin_ticks) { all = false; break; }
                 __builtin_amdgcn_s_sleep(2);
+                started = read_started();
               }
+              if (a.B > 1) {   // which selection of the launch is the last to come by here
+                active = 0;
+                for (int q = lane; q < a.B; q += 64) active += s_prefix[q + 1] > s_prefix[q] ? 1 : 0;
+                active = wave_sum_i32(active);
+                if (lane == 0) selected_before = __hip_atomic_fetch_add(a.exit_ticket + kSelectedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              }
+              if (lane == 0) s_misc[0] = all ? 0 : 1;
             }
             __syncthreads();
-          }
-        }
-        if (s_last == 3) {
-          if (tid == 0) atomicOr(&a.status[b], static_cast<uint32_t>(TALON_STATUS_ABORTED));
-        } else if (s_last) {
-          TL_ANY(launch_idx, 2);
+            gave_up = s_misc[0] != 0;
+            return !gave_up;
+          };
           // A launch that started the tree itself knows the sequence's status (nothing but a
           // row that cannot be normalised can have touched it), its size and its layer
           // without asking memory.
           const bool own = TREE && a.root_token != nullptr;
-          const uint32_t status = own ? (s_last == 2 ? static_cast<uint32_t>(TALON_STATUS_BAD_ROW) : 0u)
-                                      : __hip_atomic_load(&a.status[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          uint32_t status;
+          if constexpr (TREE) {
+            status = own ? (s_last == 2 ? static_cast<uint32_t>(TALON_STATUS_BAD_ROW) : 0u)
+                         : __hip_atomic_load(&a.status[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          } else {
+            status = s_stat[b] | (s_last == 2 ? static_cast<uint32_t>(TALON_STATUS_BAD_ROW) : 0u);
+          }
           unsigned long long next = static_cast<unsigned long long>(static_cast<uint32_t>(fbegin));   // count 0
           if (status & TALON_STATUS_BAD_ROW) {   // a row could not be normalised: stop the sequence here
-            if (tid == 0) st_<TREE, int32_t>(a.sel.st.frontier_count + b, 0);
+            if (all_started() && tid == 0) st_<TREE, int32_t>(a.sel.st.frontier_count + b, 0);
           } else {
             const SelectLds lds{reinterpret_cast<unsigned long long*>(s_pool),
                                 reinterpret_cast<int*>(s_pool + sizeof(unsigned long long) * kSelectKeySlots),
                                 s_red_u64, s_red_i32, s_misc};
             next = select_sequence<true>(a.sel, b, F, fbegin, status, lds, own ? fbegin + F : -1,
-                                         own ? launch_idx : -1);
+                                         own ? launch_idx : -1, all_started);
           }
           if constexpr (TREE) {
             // everything this layer wrote for the sequence has been performed before the
@@ -402,19 +431,14 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
             if (tid == 0 && launch_idx + 1 < a.N_pad)
               st_<true, unsigned long long>(a.desc + ((launch_idx + 1) * a.B + b), next | kDescReady);
             TL_ANY(launch_idx, 3);
-          }   // (a launch of one layer leaves no descriptor: the next call starts from the public state)
-        }
-        if constexpr (!TREE) {
-          if (s_last) {
-            // the last selection of the launch puts the two counters back to zero (every
-            // workgroup has started by now, so nobody counts after this)
+          } else {   // (a launch of one layer leaves no descriptor: the next call starts from the public state)
             if (tid == 0) {
-              int active = 0;
-              for (int q = 0; q < a.B; ++q) active += (s_prefix[q + 1] > s_prefix[q]) ? 1 : 0;
-              const uint32_t done_before = __hip_atomic_fetch_add(a.exit_ticket + kSelectedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              if (static_cast<int>(done_before) + 1 == active) {
+              if (gave_up) atomicOr(&a.status[b], static_cast<uint32_t>(TALON_STATUS_ABORTED));
+              // the last selection of the launch puts the counters back to zero (every workgroup has
+              // started by now and every selection has seen it, so nobody counts or looks after this)
+              if (static_cast<int>(selected_before) + 1 == active) {
                 for (int x = 0; x < kStartedWords; ++x) store_agent(started_word(a, x), 0u);
-                store_agent(a.exit_ticket + kSelectedWord, 0u);
+                if (a.B > 1) store_agent(a.exit_ticket + kSelectedWord, 0u);
               }
             }
           }

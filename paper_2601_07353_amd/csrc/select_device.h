@@ -167,11 +167,17 @@ __device__ __forceinline__ unsigned int keep_best(unsigned long long* my, const 
 // trips, which is what its time is made of, so it avoids every one it can: the token, edge
 // probability and path score of a thread's first kRegCand candidates stay in registers from
 // the scoring pass to the append.
+// may_write(): asked once, by all threads, before anything is written (same answer in every thread);
+// false: nothing is written and 0 returned.
 constexpr int kRegCand = 4;
-template <bool AGENT>
+struct WriteAtOnce {
+  __device__ __forceinline__ bool operator()() const { return true; }
+};
+template <bool AGENT, typename Gate = WriteAtOnce>
 __device__ __forceinline__ unsigned long long select_sequence(const SelectArgs& a, int b, int F, int fb,
                                                               uint32_t status, const SelectLds& lds,
-                                                              int n_known = -1, int d_known = -1) {
+                                                              int n_known = -1, int d_known = -1,
+                                                              Gate&& may_write = Gate{}) {
   const talon_tree_state& st = a.st;
   // (the thread index is taken afresh, through an empty asm statement: a caller that inlines this
   // into a long kernel would otherwise keep the per-thread addresses computed from it alive, or
@@ -201,6 +207,7 @@ __device__ __forceinline__ unsigned long long select_sequence(const SelectArgs& 
       pr = ld<AGENT, float>(a.cand_prob + ci);
       score = ld<AGENT, double>(st.logp + base + fb) + ld<AGENT, double>(a.cand_edge_logp + ci);
     }
+    if (!may_write()) return 0ull;
     if (tid < 64) {   // the first wavefront holds the whole row
       const bool valid = tid < k && tok >= 0 && score == score;
       const unsigned long long vb = __ballot(valid);
@@ -301,6 +308,7 @@ __device__ __forceinline__ unsigned long long select_sequence(const SelectArgs& 
   int n_keep;
   int pos;
   const unsigned int keep_bits = keep_best(my, per, anchor_key, thr_key, limit, lds, &pos, &n_keep);
+  if (!may_write()) return 0ull;
   if (a.cap_hit) {   // was a row's last candidate kept?
     for (int i = 0; i < per; ++i)
       if ((keep_bits & (1u << i)) && (c_begin + i) % k == k - 1) st_<true, uint32_t>(a.cap_hit, 1u);

@@ -95,7 +95,7 @@ def test_a_bad_row_stops_its_sequence_only():
     logits = rows_of(3, 40, 9000, "f32", seed=9)
     logits[1, 3, 77] = float("nan")
     a, b = build(logits, 40, 8, 8, True), build(logits, 40, 8, 8, False)
-    assert a["status"].tolist() == b["status"].tolist() and a["status"][1] == T.TALON_STATUS_BAD_ROW
+    assert a["status"].tolist() == b["status"].tolist() and a["status"][1] == T.binding.TALON_STATUS_BAD_ROW
     for key in ("token", "parent", "n_nodes", "depth_cur", "frontier_begin", "frontier_count", "mask"):
         np.testing.assert_array_equal(a[key], b[key], err_msg=key)
 
@@ -151,3 +151,45 @@ def test_scan_of_rows_in_adversarial_order(dtype, order):
     order_ids = torch.argsort(row, descending=True, stable=True)[:k]     # equal logits: lower token first
     np.testing.assert_array_equal(got["cand_token"][0, 0], order_ids.numpy())
     assert abs(got["cand_row_lse"][0, 0] - float(torch.logsumexp(row, 0))) < 2e-6
+
+
+@pytest.mark.parametrize("B", [1, 2, 65, 150])
+def test_one_launch_per_layer_with_bad_rows_and_finished_sequences(B):
+    """A launch per layer takes the status of a sequence from the launch's start and counts the selections
+    that have seen the whole grid start: more sequences than a wavefront has lanes, rows that cannot be
+    normalised (in the first layer and in later ones), sequences that end early; twice over one
+    workspace.  Reference: the separate calls, with the same trees to the last bit (same chunks of one)."""
+    import torch
+    import paper_2601_07353_amd as T
+    V, N, k, Dmax = 700, 12, 3, 5
+    logits = rows_of(B, N, V, "f32", seed=11).clone()
+    logits[::7, 0, 5] = float("nan")        # no first layer
+    logits[1::5, 2, 9] = float("inf")       # none below node 2, where a tree has one
+    logits[B - 1, 0, 3] = 80.0              # a sure row
+    st = T.TreeState(B, N)
+    cand = T.Candidates(B, st.N_pad, k)
+    ws = T.make_expand_workspace(B, st.N_pad, V, k, T.TALON_DTYPE_F32)
+    roots = torch.arange(B, dtype=torch.int32).cuda()
+    fields = ("token", "parent", "depth", "prob", "logp", "n_nodes", "frontier_begin", "frontier_count", "depth_cur", "status")
+
+    def snapshot():
+        torch.cuda.synchronize()
+        n = st.n_nodes.cpu()
+        return {f: [getattr(st, f)[b, : n[b]].cpu().numpy() if getattr(st, f).dim() == 2 else int(getattr(st, f)[b]) for b in range(B)]
+                for f in fields}
+
+    T.talon_tree_init(st, roots)
+    for d in range(Dmax):
+        T.talon_expand_layer(logits, st, k, cand, ws, layer=d)
+        T.talon_select_budget(st, k, cand, 0.03, k, 1, Dmax)
+    want = snapshot()
+    bad = T.binding.TALON_STATUS_BAD_ROW
+    assert want["status"][0] & bad and (B < 3 or not want["status"][2] & bad)
+    for _ in range(2):
+        T.talon_tree_init(st, roots)
+        for d in range(Dmax):
+            T.talon_expand_select_layer(logits, st, k, 0.03, k, 1, Dmax, cand, ws, layer=d)
+        got = snapshot()
+        for f in fields:
+            for b in range(B):
+                np.testing.assert_array_equal(got[f][b], want[f][b], err_msg="%s of sequence %d" % (f, b))
