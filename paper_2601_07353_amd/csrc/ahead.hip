@@ -569,7 +569,7 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, const Literal
     const SelectLds lds{s.key, s.hist, s.red_u64, s.red_i32, s.misc};
     int n_keep;
     int pos;
-    const unsigned int keep_bits = keep_best(my, per, anchor, thr, limit, lds, &pos, &n_keep);
+    const unsigned int keep_bits = keep_best<!UNCAPPED>(my, per, anchor, thr, limit, lds, &pos, &n_keep);
     bool again = false;
     if constexpr (UNCAPPED) {
       // Was a row's last candidate kept?  (Of a single row the `limit` best are its first ones.)

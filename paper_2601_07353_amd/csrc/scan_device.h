@@ -89,21 +89,6 @@ __device__ __forceinline__ int count_greater(const unsigned long long* s, int n,
   return r;
 }
 
-// Number of keys in s[0..n) greater than key, for a 16-byte aligned array padded with zero keys
-// to a multiple of 16 keys: 8 two-key LDS broadcast reads in flight per round.
-__device__ __forceinline__ int count_greater_pad16(const unsigned long long* s, int n, unsigned long long key) {
-  const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(s);
-  int r = 0;
-  for (int j = 0; j < n; j += 16) {
-    ulonglong2 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = kp[(j >> 1) + u];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) r += ((v[u].x > key) ? 1 : 0) + ((v[u].y > key) ? 1 : 0);
-  }
-  return r;
-}
-
 // Number of keys greater than `key` in a list sorted in descending order (zeros, if any, at
 // the end): binary search.
 __device__ __forceinline__ int count_greater_sorted(const unsigned long long* s, int n, unsigned long long key) {

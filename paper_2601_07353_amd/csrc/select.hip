@@ -8,7 +8,7 @@ namespace {
 
 __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
   __shared__ unsigned long long s_key[kSelectKeySlots];
-  __shared__ int s_hist[256];
+  __shared__ __attribute__((aligned(16))) int s_hist[256];
   __shared__ unsigned long long s_red_u64[8];
   __shared__ int s_red_i32[8];
   __shared__ int s_misc[2];

@@ -7,8 +7,8 @@
 //   layer < init_layers: keep the K_init best                   (Eq. 5)
 //   else: anchor m_d = max score, keep score >= log(mu) + m_d   (Eq. 4)
 //   more than R = N - |T| left: keep the R best                 (budget check)
-// The R-th best score is found by an 8-pass radix select over order-preserving 64-bit
-// images of the fp64 scores; equal scores are taken in (parent, rank) order.  Kept
+// The R-th best score is found by ranking (small pools) or by an 8-pass radix select over
+// order-preserving 64-bit images of the fp64 scores; equal scores are taken in (parent, rank) order.  Kept
 // candidates are appended by a prefix-sum compaction, which yields node ids ordered
 // (parent ascending, rank ascending) without a sort.
 #pragma once
@@ -26,7 +26,7 @@ constexpr int kSelectKeySlots = kThreads * (kPerThread + 1);
 // that are idle by then).
 struct SelectLds {
   unsigned long long* key;      // [kSelectKeySlots]
-  int* hist;                    // [256]
+  int* hist;                    // [256], 16-byte aligned
   unsigned long long* red_u64;  // [8]
   int* red_i32;                 // [8]
   int* misc;                    // [2]
@@ -52,10 +52,29 @@ __device__ __forceinline__ void st_(T* p, T v) {
   else *p = v;
 }
 
+// Number of keys in s[0..n) greater than key, for a 16-byte aligned array padded with zero keys
+// to a multiple of 16 keys: 8 two-key LDS broadcast reads in flight per round.
+__device__ __forceinline__ int count_greater_pad16(const unsigned long long* s, int n, unsigned long long key) {
+  const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(s);
+  int r = 0;
+  for (int j = 0; j < n; j += 16) {
+    ulonglong2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = kp[(j >> 1) + u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) r += ((v[u].x > key) ? 1 : 0) + ((v[u].y > key) ? 1 : 0);
+  }
+  return r;
+}
+
+constexpr int kRankedPass = 128;   // passing keys that are ranked one against another: as many as the histogram's LDS holds
+
 // The candidates of one layer that are kept: keys >= thr_key, at most `limit` of them, the largest
 // first, equal keys in the order of the threads' slots.  Every thread passes its `per` <= 32 keys in
 // LDS (0 = no candidate; they may be rewritten) and the pool's largest key; bit i of the result: its
 // key i is kept.  *pos: kept candidates of the threads before it; *n_keep: of all.
+// RANKED: see below (not in a kernel that has no registers left for it: its spills cost what it gains).
+template <bool RANKED = true>
 __device__ __forceinline__ unsigned int keep_best(unsigned long long* my, const int per, const unsigned long long anchor_key,
                                                   const unsigned long long thr_key, const int limit, const SelectLds& lds,
                                                   int* pos, int* n_keep) {
@@ -77,6 +96,39 @@ __device__ __forceinline__ unsigned int keep_best(unsigned long long* my, const 
   int n_pass;
   *pos = block_exclusive_scan_i32(__popc(pass_bits), s_red_i32, &n_pass);
   if (n_pass <= limit) { *n_keep = n_pass; return pass_bits; }
+  // ---- a few too many pass (the layer that exhausts the budget, as a rule): every passing key is ranked
+  // against all of them.  Equal keys share a rank: if that makes more than `limit` of them the best
+  // ones, the search below sorts it out.  (Two barriers and at most eight rounds of LDS reads, against four
+  // barriers per digit of the search: 16 nodes over 1024 tokens 25.3 us for the whole step before, 24.8 now;
+  // 60 nodes over 128256, 41.2 and 40.8; three sequences of 48 nodes by the separate calls, 66.6 and 66.0.)
+  if (RANKED && n_pass <= kRankedPass) {
+    unsigned long long* s_pass = reinterpret_cast<unsigned long long*>(s_hist);
+    int at = *pos;
+    for (int i = 0; i < per; ++i)
+      if ((pass_bits >> i) & 1u) s_pass[at++] = my[i];
+    if (tid < 16 && n_pass + tid < kRankedPass) s_pass[n_pass + tid] = 0ull;
+    __syncthreads();
+    if (tid < kRankedPass) {
+      const unsigned long long key = tid < n_pass ? s_pass[tid] : ~0ull;
+      const int r = count_greater_pad16(s_pass, n_pass, key);
+      const unsigned long long kept = __ballot(tid < n_pass && r < limit);
+      if ((tid & 63) == 0) s_red_u64[4 + (tid >> 6)] = kept;
+    }
+    __syncthreads();
+    const unsigned long long kept0 = s_red_u64[4], kept1 = s_red_u64[5];
+    if (__popcll(kept0) + __popcll(kept1) == limit) {
+      unsigned int keep_bits = 0u;
+      at = *pos;
+      *pos = at < 64 ? __popcll(kept0 & ((1ull << at) - 1ull)) : __popcll(kept0) + __popcll(kept1 & ((1ull << (at & 63)) - 1ull));
+      for (int i = 0; i < per; ++i) {
+        if (!((pass_bits >> i) & 1u)) continue;
+        if (((at < 64 ? kept0 : kept1) >> (at & 63)) & 1ull) keep_bits |= 1u << i;
+        ++at;
+      }
+      *n_keep = limit;
+      return keep_bits;
+    }
+  }
   unsigned long long T = 0ull;        // keep key > T, and the first need_eq keys == T
   int need_eq = 0;
   // ---- radix select: the limit-th largest key, 8 bits per pass from the top.

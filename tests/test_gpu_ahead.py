@@ -193,3 +193,53 @@ def test_one_launch_per_layer_with_bad_rows_and_finished_sequences(B):
         for f in fields:
             for b in range(B):
                 np.testing.assert_array_equal(got[f][b], want[f][b], err_msg="%s of sequence %d" % (f, b))
+
+
+@pytest.mark.parametrize("rows,k,N,equal", [
+    (2, 16, 20, True),       # 32 equal scores, 17 of them fit: the first ones in (parent, rank) order
+    (2, 60, 67, True),       # 120 equal scores, 64 places
+    (4, 5, 18, False),       # 20 candidates for 13 places
+    (8, 16, 109, False),     # 128 for 100: the most that are ranked so
+    (3, 43, 90, False),      # 129 for 86: the first pool that is searched digit by digit
+    (8, 16, 136, False),     # 128 for 127
+])
+def test_the_layer_that_exhausts_the_budget(rows, k, N, equal):
+    """The best of a pool with more candidates than places, at the edges of the two ways it is done.  The
+    scores are sums of two log-softmaxes, compared on the host in the same fp64 (gaps far above 1e-6)."""
+    import torch
+    import paper_2601_07353_amd as T
+    V = 256
+    rng = np.random.default_rng(7 * rows + k)
+    x = rng.permuted(np.tile(np.arange(V, dtype=np.float32) * 0.0625, (N, 1)), axis=1) if not equal else np.full((N, V), -5, np.float32)
+    if equal:
+        x[0, :rows] = 5.0
+        x[1:, :k] = 3.0
+    else:
+        x += rng.uniform(0.0, 0.03, size=(N, 1)).astype(np.float32) * (np.arange(V) % 7 == 3)
+    logp = x.astype(np.float64) - np.logaddexp.reduce(x.astype(np.float64), axis=1, keepdims=True)
+    best = lambda row, n: np.argsort(-x[row], kind="stable")[:n]
+    first = best(0, max(k, rows))[:rows]
+    pool = [(j, t, logp[0, first[j]] + logp[1 + j, t]) for j in range(rows) for t in best(1 + j, k)]
+    scores = np.array([s for _, _, s in pool])
+    places = N - 1 - rows
+    if not equal:
+        ordered = np.sort(scores)[::-1]
+        assert ordered[places - 1] - ordered[places] > 1e-5, "the host cannot tell these apart"
+    keep = sorted(np.argsort(-np.round(scores, 9), kind="stable")[:places])
+    token = list(first) + [pool[i][1] for i in keep]
+    parent = [0] * rows + [1 + pool[i][0] for i in keep]
+
+    logits = torch.from_numpy(x).cuda().reshape(1, N, V)
+    got = [build(logits, N, k, 2, ahead, K_init=rows, mu=1e-30) for ahead in (True, False)]
+    st = T.TreeState(1, N)
+    cand = T.Candidates(1, st.N_pad, k)
+    ws = T.make_expand_workspace(1, st.N_pad, V, k, T.TALON_DTYPE_F32)
+    T.talon_tree_init(st, torch.zeros(1, dtype=torch.int32).cuda())
+    for d in range(2):
+        T.talon_expand_layer(logits, st, k, cand, ws, layer=d)
+        T.talon_select_budget(st, k, cand, 1e-30, rows, 1, 2)
+    got.append({n: getattr(st, n).cpu().numpy() for n in ("token", "parent", "n_nodes")})
+    for g in got:
+        assert int(g["n_nodes"][0]) == N
+        np.testing.assert_array_equal(g["token"][0, 1:N], token)
+        np.testing.assert_array_equal(g["parent"][0, 1:N], parent)
