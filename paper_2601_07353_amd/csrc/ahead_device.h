@@ -14,7 +14,6 @@ constexpr int32_t kRowBad = 1;           // ... and the row could not be normali
 struct ScannerLds {
   unsigned char pool[kScanBytes];
   unsigned long long topw[4][TALON_K_MAX];
-  int part[4][64];
   unsigned long long top[TALON_K_MAX];
   double wsum[4];
   float wmax[4];
@@ -45,7 +44,7 @@ __device__ __forceinline__ void scan_rows(const ExpandArgs& a, ScannerLds& s, co
   const int lane = tid & 63;
   const int k = a.k;
   const ScanLds L{reinterpret_cast<uint4 (*)[kHitCap]>(s.pool), reinterpret_cast<int (*)[kHitCap]>(s.pool + kHitvBytes),
-                  reinterpret_cast<unsigned long long (*)[kSubKeys]>(s.pool + kHitvBytes + kHithBytes), s.topw, s.part, s.top,
+                  reinterpret_cast<unsigned long long (*)[kSubKeys]>(s.pool + kHitvBytes + kHithBytes), s.topw, s.top,
                   s.wmax, s.wsum, s.wcnt};
   unsigned long long* s_keys = reinterpret_cast<unsigned long long*>(s.pool);   // row merge: partial keys,
   unsigned long long* s_cand = s_keys + kMergeCap;                              // ... then those that can still be chosen

@@ -142,7 +142,6 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
   __shared__ unsigned long long s_red_u64[8];
   __shared__ int s_misc[2];
   __shared__ __attribute__((aligned(16))) unsigned long long s_topw[4][TALON_K_MAX]; // k best keys of each wavefront, sorted
-  __shared__ int s_part[4][64];                         // partial ranks of the list merge
   __shared__ unsigned long long s_top[TALON_K_MAX];
   __shared__ double s_red_f64[8];
   __shared__ float s_red_f32[8];
@@ -237,7 +236,7 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
   chunks = (blocks_per_row + bpc - 1) / bpc;
   const long long n_items = static_cast<long long>(total_rows) * chunks;
   const ScanLds L{reinterpret_cast<uint4 (*)[kHitCap]>(s_pool), reinterpret_cast<int (*)[kHitCap]>(s_pool + kHitvBytes),
-                  reinterpret_cast<unsigned long long (*)[kSubKeys]>(s_pool + kHitvBytes + kHithBytes), s_topw, s_part, s_top,
+                  reinterpret_cast<unsigned long long (*)[kSubKeys]>(s_pool + kHitvBytes + kHithBytes), s_topw, s_top,
                   s_wmax, s_wsum, s_wcnt};
 
   for (long long item = blockIdx.x; item < n_items; item += gridDim.x) {

@@ -205,7 +205,6 @@ struct ScanLds {
   int (*hith)[kHitCap];                      // [4] their tile * 64 + lane tags
   unsigned long long (*ck)[kSubKeys];        // [4] ranking scratch
   unsigned long long (*topw)[TALON_K_MAX];   // [4] k best keys of each wavefront, sorted (16-byte aligned)
-  int (*part)[64];                           // [4] partial ranks of the list merge
   unsigned long long* top;                   // [TALON_K_MAX] the run's k best keys, sorted, zero keys in unused slots
   float* wmax;                               // [4]
   double* wsum;                              // [4]
@@ -370,9 +369,31 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
         // anything is buffered, so that such a row does not rank every one of its vectors.
         tau = fmaxf(tau, kth_of_lanes(gmax, k));
       }
+      // Lanes that hold a candidate, per tile: all four tiles at once where the buffer has room for them
+      // (one test for a group without any, and straight-line code for one with a few; a test per tile
+      // before: 4080 rows of 304 KB 229 us, now 225; three sequences of 48 nodes by the separate calls 66.0, now 65.2).
+      unsigned long long hits[kScanTiles];
+      int n_hits = 0;
 #pragma unroll
-      for (int q = 0; q < kScanTiles; ++q)
-        if (deferred != 0u || !buffer_hits(raw[q], vmax4[q], tb + q)) deferred |= 1u << q;
+      for (int q = 0; q < kScanTiles; ++q) {
+        hits[q] = __ballot(vmax4[q] >= tau);
+        n_hits += __popcll(hits[q]);
+      }
+      if (n_hits != 0) {
+        if (cnt + n_hits <= kHitCap) {
+#pragma unroll
+          for (int q = 0; q < kScanTiles; ++q) {
+            const int pos = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(hits[q] >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(hits[q]), 0));
+            if (vmax4[q] >= tau) { hitv[pos] = raw[q]; hith[pos] = (tb + q) * 64 + lane; }
+            cnt += __popcll(hits[q]);
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < kScanTiles; ++q)
+            if (deferred != 0u || !buffer_hits(raw[q], vmax4[q], tb + q)) deferred |= 1u << q;
+        }
+      }
       tb += kScanTiles;
     } else {
       force = cnt > 0;
@@ -423,9 +444,10 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
             if (r < k) topw[r] = key;
           }
           tcnt = n < k ? n : k;
-          if (tcnt >= k) tau = fmaxf(tau, key_logit(topw[k - 1]));
+          if (base + kSubBatch < cnt && tcnt >= k) tau = fmaxf(tau, key_logit(topw[k - 1]));
         }
         cnt = 0;
+        if (deferred == 0u && tb >= t1) break;   // nothing is left that tau would be compared with
         if (tcnt >= k) tau = float_above(key_logit(topw[k - 1]));
         if (deferred == 0u) break;
 #pragma unroll 1
@@ -458,21 +480,28 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
   __syncthreads();
 
   // ---- merge the four lists (each <= k keys, zero keys in the unused slots) into the
-  // chunk's k best, sorted.  Lane 16w+i of every wavefront holds key i of list w; wavefront v
-  // counts how many keys of list v are greater; the four counts add up to the rank.
+  // chunk's k best, sorted.  Lane 16g+i of wavefront w holds key i of list w and counts how many keys of
+  // list g are greater; the four lanes' counts add up to the rank.
   const int ctot = L.wcnt[0] + L.wcnt[1] + L.wcnt[2] + L.wcnt[3];
   if constexpr (WATCH) {
     if (ctot < 0) return false;   // one wavefront saw the word: the workgroup gives the run up
   }
   if (k <= 16) {
-    const unsigned long long mkey = L.topw[lane >> 4][lane & 15];
-    L.part[wave][lane] = count_greater_pad16(L.topw[wave], 16, mkey);
-    __syncthreads();
-    if (wave == 0) {
-      const int r = L.part[0][lane] + L.part[1][lane] + L.part[2][lane] + L.part[3][lane];
-      if (mkey != 0ull && r < k) L.top[r] = mkey;
-      if (lane >= ctot && lane < k) L.top[lane] = 0ull;   // fewer than k logits in this chunk
-    }
+    const int group = lane >> 4;
+    const unsigned long long mkey = topw[lane & 15];
+    const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(L.topw[group]);
+    ulonglong2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = kp[(u + 2 * group) & 7];   // the four lists start on the same bank
+    int r = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) r += ((v[u].x > mkey) ? 1 : 0) + ((v[u].y > mkey) ? 1 : 0);
+    auto p16 = __builtin_amdgcn_permlane16_swap(r, r, false, false);
+    r = static_cast<int>(p16[0]) + static_cast<int>(p16[1]);
+    auto p32 = __builtin_amdgcn_permlane32_swap(r, r, false, false);
+    r = static_cast<int>(p32[0]) + static_cast<int>(p32[1]);
+    if (lane < 16 && mkey != 0ull && r < k) L.top[r] = mkey;
+    if (tid >= ctot && tid < k) L.top[tid] = 0ull;   // fewer than k logits in this chunk
   } else {
     // long lists: thread t holds key t % 64 of its own wavefront's list and counts against all four
     const unsigned long long mkey = L.topw[wave][lane];
