@@ -1,6 +1,5 @@
 // Rows scanned ahead of the trees that will ask for them: the scanner workgroups, shared by the
-// launch that builds capped trees (ahead.hip) and the one that builds uncapped trees
-// (literal_ahead.hip).
+// launches that build capped and uncapped trees (ahead.hip).
 #pragma once
 
 #include "scan_device.h"

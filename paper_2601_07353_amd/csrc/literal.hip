@@ -1,6 +1,7 @@
 // One layer of Alg. 2 with the pool exactly as the listing writes it (Sec. 5.2, Alg. 2 "Hybrid
 // Expansion Strategy" and "Budget Check"): S_d holds every token of every frontier row, not a
-// fixed number per row.  This is the slow, general form (any budget up to TALON_N_MAX); the
+// fixed number per row.  This is the general form, layer by layer (any budget up to TALON_N_MAX); where all rows are in place,
+// ahead.hip builds the same trees in one launch.  The
 // fast path caps a row at k <= TALON_K_MAX candidates, which is the same tree whenever
 // k >= N - |T|.
 //
