@@ -246,8 +246,8 @@ int talon_build_tree_checked(const int32_t* root_token, const void* logits, int 
  * Alg. 2 with the candidate pool exactly as the listing writes it (Sec. 5.2, "Hybrid Expansion
  * Strategy" and "Budget Check"): S_d holds every token of every frontier row, with no per-row
  * cap, for any budget N <= TALON_N_MAX.  The calls above cap a row at k <= TALON_K_MAX
- * candidates, which gives the same tree whenever k >= N - |T|; this is the general, slower
- * form: per layer one vocabulary scan for the row statistics and the 16 best tokens of every
+ * candidates, which gives the same tree whenever k >= N - |T|; this is the general
+ * form, layer by layer: per layer one vocabulary scan for the row statistics and the 16 best tokens of every
  * row, then per frontier row the tokens that pass the gate (at most the remaining budget of
  * them; rows of which fewer than 16 pass are settled by the scan, the others are read again,
  * with a radix select over the row when more pass than can be taken), then per sequence the
