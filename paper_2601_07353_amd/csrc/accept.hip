@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kThreads, 6) void argmax_scan_kernel(ArgmaxArgs a) 
     }
     const float gmax = fmaxf(fmaxf(vmax[0], vmax[1]), fmaxf(vmax[2], vmax[3]));
     if (gmax > m_l) {
-      s_l = (m_l == kNegInf) ? 0.0 : s_l * static_cast<double>(__expf(m_l - gmax));
+      s_l = rescaled_sum(s_l, m_l, gmax);
       m_l = gmax;
 #pragma unroll
       for (int q = kScanTiles - 1; q >= 0; --q)   // the first of equal ones
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kThreads, 6) void argmax_scan_kernel(ArgmaxArgs a) 
   }
   key = wave_max_u64(key);
   const float wmax = wave_max_f32(m_l);
-  const double wsum = wave_sum_f64((m_l == kNegInf) ? 0.0 : s_l * static_cast<double>(__expf(m_l - wmax)));
+  const double wsum = wave_sum_f64(rescaled_sum(s_l, m_l, wmax));
   if (lane == 0) { s_key[wave] = key; s_max[wave] = wmax; s_sum[wave] = wsum; }
   __syncthreads();
   if (tid == 0) {
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kThreads, 6) void argmax_scan_kernel(ArgmaxArgs a) 
     double csum = 0.0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      if (s_max[w] != kNegInf) csum += s_sum[w] * static_cast<double>(__expf(s_max[w] - cm));
+      csum += rescaled_sum(s_sum[w], s_max[w], cm);
       key = s_key[w] > key ? s_key[w] : key;
     }
     const size_t slot = (static_cast<size_t>(b) * a.N_pad + node) * a.blocks + run;
@@ -149,14 +149,13 @@ __global__ __launch_bounds__(kMergeThreads) void argmax_merge_kernel(ArgmaxArgs 
       const double sr = a.part_sum[slot + r];
       const unsigned long long kr = a.part_key[slot + r];
       const float mn = fmaxf(m, mr);
-      if (mn != kNegInf) sum = (m == kNegInf ? 0.0 : sum * static_cast<double>(__expf(m - mn))) +
-                               (mr == kNegInf ? 0.0 : sr * static_cast<double>(__expf(mr - mn)));
+      sum = rescaled_sum(sum, m, mn) + rescaled_sum(sr, mr, mn);
       m = mn;
       key = kr > key ? kr : key;
     }
     const float own = m;
     m = row16_max_f32(m);
-    sum = row16_sum_f64(own == kNegInf ? 0.0 : sum * static_cast<double>(__expf(own - m)));
+    sum = row16_sum_f64(rescaled_sum(sum, own, m));
     key = row16_max_u64(key);
     if (l == 0) {
       const double lse = static_cast<double>(m) + log_of_sum(sum);

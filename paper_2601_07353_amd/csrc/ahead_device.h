@@ -106,11 +106,9 @@ __device__ __forceinline__ void scan_rows(const ExpandArgs& a, ScannerLds& s, co
           m = mc0;
           for (int c = lane + 64; c < chunks; c += 64) m = fmaxf(m, load_agent(a.part_max + slot0 + c));
           m = wave_max_f32(m);
-          sum = (mc0 != kNegInf) ? sc0 * static_cast<double>(__expf(mc0 - m)) : 0.0;
-          for (int c = lane + 64; c < chunks; c += 64) {
-            const float mc = load_agent(a.part_max + slot0 + c);
-            if (mc != kNegInf) sum += load_agent(a.part_sum + slot0 + c) * static_cast<double>(__expf(mc - m));
-          }
+          sum = rescaled_sum(sc0, mc0, m);
+          for (int c = lane + 64; c < chunks; c += 64)
+            sum += rescaled_sum(load_agent(a.part_sum + slot0 + c), load_agent(a.part_max + slot0 + c), m);
           sum = wave_sum_f64(sum);
           __syncthreads();   // the partial results have been read: slot 0 may be written
         }

@@ -324,11 +324,8 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
         float m = mc0;
         for (int c = lane + 64; c < chunks; c += 64) m = fmaxf(m, load_agent(pm + c));
         m = wave_max_f32(m);
-        double sum = (mc0 != kNegInf) ? sc0 * static_cast<double>(__expf(mc0 - m)) : 0.0;
-        for (int c = lane + 64; c < chunks; c += 64) {
-          const float mc = load_agent(pm + c);
-          if (mc != kNegInf) sum += load_agent(ps + c) * static_cast<double>(__expf(mc - m));
-        }
+        double sum = rescaled_sum(sc0, mc0, m);
+        for (int c = lane + 64; c < chunks; c += 64) sum += rescaled_sum(load_agent(ps + c), load_agent(pm + c), m);
         sum = wave_sum_f64(sum);
         __syncthreads();   // s_keys is staged
         start_tree();

@@ -126,6 +126,13 @@ __device__ __forceinline__ double log_of_sum(double sum) {
   return static_cast<double>(e) * 0.69314718055994530942 + static_cast<double>(__logf(static_cast<float>(f)));
 }
 
+// A partial sum of exp(logit - m), taken to a maximum `to` >= m.  Where m is -inf the sum is zero, or NaN if
+// there was a NaN among the logits (the maximum passes over it): it stays what it is, so that the row is
+// found out whatever else it holds.
+__device__ __forceinline__ double rescaled_sum(double sum, float m, float to) {
+  return m == kNegInf ? sum : sum * static_cast<double>(__expf(m - to));
+}
+
 constexpr int kCandCap = 512;   // keys of a row merge that can still be among the k best, after the filter below
 
 // Rank the keys of `lists` lists of k keys each (in LDS, every list sorted in descending order, zero
@@ -338,7 +345,7 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
       }
       const float gmax = fmaxf(fmaxf(vmax4[0], vmax4[1]), fmaxf(vmax4[2], vmax4[3]));
       if (gmax > m_l) {
-        s_l = (m_l == kNegInf) ? 0.0 : s_l * static_cast<double>(__expf(m_l - gmax));
+        s_l = rescaled_sum(s_l, m_l, gmax);
         m_l = gmax;
       }
       // sum of 2^(x*log2e - c) with c = fl(m*log2e); the rounding of c is a common factor
@@ -471,8 +478,7 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
   {
     const float wmax = wave_max_f32(m_l);
     // rescale factors are <= 1 and only need fp32 accuracy: their error is relative to a part of the sum
-    const double sl = (m_l == kNegInf) ? 0.0 : s_l * static_cast<double>(__expf(m_l - wmax));
-    const double wsum = wave_sum_f64(sl);
+    const double wsum = wave_sum_f64(rescaled_sum(s_l, m_l, wmax));
     if (lane == 0) { L.wmax[wave] = wmax; L.wsum[wave] = wsum; L.wcnt[wave] = given_up ? -(1 << 20) : tcnt; }
     static_assert(TALON_K_MAX == 64, "a list has one slot per lane");
     if (lane >= tcnt) topw[lane] = 0ull;   // unused slots of the list: zero keys
@@ -514,8 +520,7 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
   cm = fmaxf(fmaxf(L.wmax[0], L.wmax[1]), fmaxf(L.wmax[2], L.wmax[3]));
   csum = 0.0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w)
-    if (L.wmax[w] != kNegInf) csum += L.wsum[w] * static_cast<double>(__expf(L.wmax[w] - cm));
+  for (int w = 0; w < 4; ++w) csum += rescaled_sum(L.wsum[w], L.wmax[w], cm);
   __syncthreads();
   return true;
 }
