@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kThreads, 6) void argmax_scan_kernel(ArgmaxArgs a) 
       for (int e = 1; e < EPL; ++e) vmax[q] = fmaxf(vmax[q], x[e]);
     }
     const float gmax = fmaxf(fmaxf(vmax[0], vmax[1]), fmaxf(vmax[2], vmax[3]));
-    if (gmax > m_l) {
+    if (gmax > m_l || (best_tile < 0 && gmax == m_l)) {   // (a row of -inf alone has a token too, its first)
       s_l = rescaled_sum(s_l, m_l, gmax);
       m_l = gmax;
 #pragma unroll
@@ -108,7 +108,8 @@ __global__ __launch_bounds__(kThreads, 6) void argmax_scan_kernel(ArgmaxArgs a) 
 #pragma unroll
     for (int e = EPL - 1; e >= 0; --e)
       if (x[e] == m_l) e0 = e;
-    key = make_key(m_l, (best_tile * kThreads + tid) * EPL + e0);
+    const int token = (best_tile * kThreads + tid) * EPL + e0;
+    if (token < vocab) key = make_key(m_l, token);   // (not the -inf that stands behind the row's end)
   }
   key = wave_max_u64(key);
   const float wmax = wave_max_f32(m_l);

@@ -169,7 +169,7 @@ struct ArgmaxArgs {
   int runs, blocks_per_run;        // runs a row is cut into
   float* part_max;                 // [B*N_pad][blocks] per run: maximum ...
   double* part_sum;                // ... sum of exp(logit - maximum) ...
-  unsigned long long* part_key;    // ... and (sortable maximum << 32 | ~token); 0: no logit above -inf
+  unsigned long long* part_key;    // ... and (sortable maximum << 32 | ~token); 0: nothing but NaN
   int32_t* target_token;           // [B][N_pad]
   float* target_prob;              // [B][N_pad] or NULL
   uint32_t* scan_status;           // [B]

@@ -88,3 +88,26 @@ def test_expansion_reports_every_nan(dtype, V, how):
     assert not status[0] & T.TALON_STATUS_BAD_ROW and n[0] > 1
     for p in range(PLACES):
         assert status[1 + p] & T.TALON_STATUS_BAD_ROW and n[1 + p] == 1, (p, status, n)
+
+
+@pytest.mark.parametrize("dtype,V,N", [("bf16", 50257, 6), ("bf16", 17, 6), ("f32", 20001, 256)])
+def test_target_argmax_leaves_no_stale_token_in_a_row_of_infinities(dtype, V, N):
+    """Nothing but -inf: reported, and the token is the first one, not what the buffer held before."""
+    import torch
+    import paper_2601_07353_amd as T
+    print("case", dtype, V, N, flush=True)
+    x = np.random.default_rng(V).standard_normal((2, N, V), dtype=np.float32)
+    x[1, 2:] = -np.inf
+    logits = on_device(x, dtype)
+    st = T.TreeState(2, N)
+    st.n_nodes.fill_(N)
+    ws = T.make_verify_workspace(2, st.N_pad, V, T.TALON_DTYPE_F32 if dtype == "f32" else T.TALON_DTYPE_BF16)
+    tok = torch.full((2, st.N_pad), -7, dtype=torch.int32, device="cuda")
+    prob = torch.full((2, st.N_pad), -7.0, device="cuda")
+    status = torch.full((2,), -1, dtype=torch.int32, device="cuda")
+    T.talon_target_argmax(logits, st, tok, prob, status, ws)
+    assert status.tolist() == [0, T.TALON_STATUS_BAD_ROW]
+    want = logits.float().argmax(-1).cpu().numpy()
+    want[1, 2:] = 0
+    np.testing.assert_array_equal(tok[:, :N].cpu().numpy(), want)
+    assert torch.isnan(prob[1, 2:N]).all() and not torch.isnan(prob[0]).any()
