@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kThreads, 6) void argmax_scan_kernel(ArgmaxArgs a) 
     }
     // sum of 2^(x*log2e - c) with c = fl(m*log2e); the rounding of c is taken out once per block
     const float kLog2e = 1.4426950408889634f;
-    const float mm = (m_l == kNegInf) ? 0.f : m_l;
+    const float mm = fmaxf(m_l, kLeastMax);
     const float c = mm * kLog2e;
     const float c_err = __builtin_fmaf(mm, kLog2e, -c);
     float acc = 0.f;

@@ -126,6 +126,11 @@ __device__ __forceinline__ double log_of_sum(double sum) {
   return static_cast<double>(e) * 0.69314718055994530942 + static_cast<double>(__logf(static_cast<float>(f)));
 }
 
+// The least maximum that logits are exponentiated against: below it, maximum * log2(e) is no finite float, and a
+// lane that met nothing but a mask of the type's lowest value would make the row's sum a NaN.  (Against
+// this bound such logits add zero, as -inf does; a row without a larger logit cannot be normalised.)
+constexpr float kLeastMax = -2.358e38f;
+
 // A partial sum of exp(logit - m), taken to a maximum `to` >= m.  Where m is -inf the sum is zero, or NaN if
 // there was a NaN among the logits (the maximum passes over it): it stays what it is, so that the row is
 // found out whatever else it holds.
@@ -351,7 +356,7 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
       // sum of 2^(x*log2e - c) with c = fl(m*log2e); the rounding of c is a common factor
       // 2^(c - m*log2e) of the whole group, applied once below
       const float kLog2e = 1.4426950408889634f;
-      const float mm = (m_l == kNegInf) ? 0.f : m_l;
+      const float mm = fmaxf(m_l, kLeastMax);
       const float c = mm * kLog2e;
       const float c_err = __builtin_fmaf(mm, kLog2e, -c);   // m*log2e - c, exact
       float acc = 0.f;

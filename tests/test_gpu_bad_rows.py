@@ -111,3 +111,43 @@ def test_target_argmax_leaves_no_stale_token_in_a_row_of_infinities(dtype, V, N)
     want[1, 2:] = 0
     np.testing.assert_array_equal(tok[:, :N].cpu().numpy(), want)
     assert torch.isnan(prob[1, 2:N]).all() and not torch.isnan(prob[0]).any()
+
+
+@pytest.mark.parametrize("dtype,V,N", [("bf16", 50257, 24), ("f32", 20001, 24), ("bf16", 50257, 256)])
+def test_a_mask_of_the_lowest_value_is_as_good_as_infinities(dtype, V, N):
+    """Rows of which all but a few tokens are masked, with -inf in sequence 0 and with the type's lowest value in
+    sequence 1 (sequence 2: the lowest value behind the first 8192 tokens): the same tokens, none of them bad."""
+    import torch
+    import paper_2601_07353_amd as T
+    print("case", dtype, V, N, flush=True)
+    cfg = small(name="masked", V=V, logits_dtype=dtype, K=4, N=N, Dmax=6, B=4)
+    P = cfg.N_pad
+    low = float(torch.finfo(torch.float32 if dtype == "f32" else torch.bfloat16).min)
+    rng = np.random.default_rng(V)
+    x = np.empty((4, P, V), dtype=np.float32)
+    x[0] = rng.standard_normal((P, V), dtype=np.float32) * 3
+    few = rng.random((P, V)) < 40.0 / V
+    few[:, rng.integers(0, V, 8)] = True      # (no row without a token)
+    x[2] = x[0]
+    x[2, :, 8192:] = low
+    x[3] = np.where(np.arange(V) < 8192, x[0], -np.inf)
+    x[1] = np.where(few, x[0], low)
+    x[0] = np.where(few, x[0], -np.inf)
+    logits = on_device(x, dtype)
+    same = lambda a, b, *ts: [np.testing.assert_array_equal(t[a].cpu().numpy(), t[b].cpu().numpy()) for t in ts]
+    st = T.TreeState(4, N)
+    st.n_nodes.fill_(N)
+    ws = T.make_verify_workspace(4, P, V, T.TALON_DTYPE_F32 if dtype == "f32" else T.TALON_DTYPE_BF16)
+    tok, status = torch.zeros(4, P, dtype=torch.int32, device="cuda"), torch.full((4,), -1, dtype=torch.int32, device="cuda")
+    prob = torch.zeros(4, P, device="cuda")
+    T.talon_target_argmax(logits, st, tok, prob, status, ws)
+    assert status.tolist() == [0] * 4
+    same(0, 1, tok, prob)
+    same(2, 3, tok, prob)
+    for how in (False, "layered", "fused", "split"):
+        st, cand, _, _ = H.run_gpu_expand(cfg, logits, layerwise=how)
+        assert not any(s & T.TALON_STATUS_BAD_ROW for s in st.status.tolist())
+        for a, b in ((0, 1), (2, 3)):
+            n = int(st.n_nodes[a])
+            assert n == int(st.n_nodes[b]) > 1
+            same(a, b, st.token[:, 1:n], st.parent[:, :n], st.prob[:, :n], st.logp[:, :n])
