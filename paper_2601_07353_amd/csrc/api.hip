@@ -784,7 +784,7 @@ int talon_expand_literal_ahead(const void* logits, int dtype, int64_t row_stride
                                    nullptr, nullptr, nullptr, nullptr, workspace, L);
   ea.sel.st = *st; ea.sel.k = kLiteralScanK; ea.sel.log_mu = log(static_cast<double>(mu)); ea.sel.K_init = K_init;
   ea.sel.init_layers = init_layers; ea.sel.max_depth = max_depth;
-  ea.layers = layers;
+  ea.layers = layers < st->N - 1 ? layers : st->N - 1;   // a tree of N nodes has no more (and the kernel adds the depth it starts from)
   ea.spin_ticks = 200000000ull;   // two seconds of the 100 MHz clock: scanners and claimed parts never wait, so these waits end; the bound is a safety net
   const int resident = literal_ahead_grid_limit(dtype);
   if (resident < 1) { set_error("occupancy query for the scan-ahead kernel failed"); return TALON_ERR_RUNTIME; }

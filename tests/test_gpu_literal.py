@@ -434,3 +434,36 @@ def test_rows_scanned_ahead_give_the_layered_trees(shape, steps):
     # of their roundings, 2^-24 each
     np.testing.assert_allclose(got["logp"], want["logp"], rtol=0, atol=24 * 4 * 2.0 ** -24)
     np.testing.assert_allclose(got["prob"], want["prob"], rtol=16 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("N", [60, 130])
+def test_any_number_of_layers_means_the_whole_loop(N):
+    """Trees continued below the root with the largest number a caller can pass: layered, ahead and through the
+    Python call the oracle's trees."""
+    import ctypes
+    import torch
+    import paper_2601_07353_amd as T
+    from tests.test_gpu_parity import small
+    cfg = small(name="literal-all-layers", V=4099, logits_dtype="bf16", K=3, N=N, Dmax=9, B=2, recipe=("gauss", 7.0, 9.0))
+    pool, trees = H.admissible_pool(cfg, lambda i: H.build_pool(cfg, [cfg.seed + 10 * i + b for b in range(cfg.B)]), cap=N - 1)
+    assert min(len(t.layers) for t in trees) > 3
+    dev = H.to_device_logits(pool)
+    lib = T.load_library()
+    lib.talon_expand_literal_ahead.restype = ctypes.c_int
+    for how in ("layered", "ahead", "python"):
+        st = T.TreeState(cfg.B, cfg.N)
+        ws = T.make_literal_workspace(cfg.B, st.N_pad, cfg.V, T.TALON_DTYPE_BF16)
+        T.talon_tree_init(st, torch.from_numpy(H.root_tokens(cfg)).cuda())
+        for layers in (1, 2 ** 31 - 1):
+            args = (layers, ctypes.byref(st.c), cfg.V, cfg.mu, cfg.K, 1, cfg.Dmax, ws.data_ptr(), ws.numel(), None)
+            at = (dev.data_ptr(), T.TALON_DTYPE_BF16, dev.stride(1), dev.stride(0))
+            if how == "layered":
+                assert lib.talon_expand_literal(*at, T.TALON_ROWS_BY_NODE, *args) == T.TALON_OK
+            elif how == "ahead":
+                assert lib.talon_expand_literal_ahead(*at, N - 1, *args) == T.TALON_OK
+            else:
+                T.talon_expand_literal(dev, st, layers, cfg.mu, cfg.K, 1, cfg.Dmax, ws)
+        for b, t in enumerate(trees):
+            assert int(st.n_nodes[b]) == t.n, (how, b)
+            np.testing.assert_array_equal(st.token[b, :t.n].cpu().numpy(), np.asarray(t.token, dtype=np.int32))
+            np.testing.assert_array_equal(st.parent[b, :t.n].cpu().numpy(), np.asarray(t.parent, dtype=np.int32))
