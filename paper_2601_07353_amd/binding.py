@@ -91,7 +91,7 @@ def _load_marshal(lib):
     module = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(module)
     module.bind(tuple(ctypes.cast(getattr(lib, name), c_void_p).value for name in _MARSHALLED), TalonError, torch.float32, torch.bfloat16,
-                _stream, _raw_stream, _current_device, torch.cuda.is_initialized)
+                _int_of, _float_of, _stream, _raw_stream, _current_device, torch.cuda.is_initialized)
     _native = module
 
 
@@ -182,6 +182,20 @@ def _stream(stream):
             return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _as_parameter(ctype, number):
+    """The Python number that a foreign function's argument of this type would take for `number`."""
+    number = getattr(number, "_as_parameter_", number)
+    return number.value if isinstance(number, ctype) else ctype(number).value
+
+
+def _int_of(number):
+    return _as_parameter(c_int32, number)
+
+
+def _float_of(number):
+    return _as_parameter(c_float, number)
 
 
 class TreeState:

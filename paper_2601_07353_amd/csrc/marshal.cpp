@@ -37,7 +37,8 @@ constexpr int kFunctions = sizeof(Abi) / sizeof(void*);
 Abi g_abi;   // (set under the interpreter lock)
 
 // ---- objects of Python handed over once
-PyObject *g_error, *g_float32, *g_bfloat16, *g_stream_of, *g_raw_stream, *g_device, *g_initialized;   // (the last three may be None)
+PyObject *g_error, *g_float32, *g_bfloat16, *g_int_of, *g_float_of, *g_stream_of, *g_raw_stream, *g_device,
+    *g_initialized;   // (the last three may be None)
 // ---- interned names
 PyObject *n_data_ptr, *n_stride, *n_shape, *n_dtype, *n_nbytes, *n_token, *n_logit, *n_prob, *n_edge_logp, *n_row_max, *n_row_lse,
     *n_is_contiguous, *n_numel;
@@ -69,7 +70,7 @@ struct Call {
     if (!r) ok = false;
     return r;
   }
-  long long integer_of(PyObject* o) {
+  long long integer_of(PyObject* o) {   // of a Python int
     if (!ok) return 0;
     if (!PyLong_Check(o)) {
       PyErr_Format(PyExc_TypeError, "an integer is required, not %.100s", Py_TYPE(o)->tp_name);
@@ -78,18 +79,22 @@ struct Call {
     }
     return static_cast<long long>(PyLong_AsUnsignedLongLongMask(o));
   }
-  int32_t i32(PyObject* o) { return static_cast<int32_t>(integer_of(o)); }
-  int64_t i64(PyObject* o) { return integer_of(o); }
+  // A caller's numbers: Python's own at once, others (numpy's, tensors of one element, ctypes', ...) as a
+  // foreign function takes them.
+  int32_t i32(PyObject* o) {
+    if (!ok || PyLong_Check(o)) return static_cast<int32_t>(integer_of(o));
+    PyObject* v = PyObject_CallOneArg(g_int_of, o);
+    if (!v) ok = false;
+    return static_cast<int32_t>(steal_i64(v));
+  }
   float f32(PyObject* o) {
     if (!ok) return 0.f;
-    if (!PyFloat_Check(o) && !PyLong_Check(o)) {
-      PyErr_Format(PyExc_TypeError, "a number is required, not %.100s", Py_TYPE(o)->tp_name);
-      ok = false;
-      return 0.f;
-    }
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) ok = false;
-    return static_cast<float>(v);
+    const bool own = PyFloat_Check(o) || PyLong_Check(o);
+    PyObject* v = own ? o : PyObject_CallOneArg(g_float_of, o);
+    const double d = v ? PyFloat_AsDouble(v) : -1.0;
+    if (d == -1.0 && PyErr_Occurred()) ok = false;
+    if (!own) Py_XDECREF(v);
+    return static_cast<float>(d);
   }
   int64_t steal_i64(PyObject* o) {
     const int64_t v = o ? integer_of(o) : 0;
@@ -149,9 +154,14 @@ struct Call {
     return p;
   }
   int64_t item(PyObject* tuple, Py_ssize_t i) { return ok ? integer_of(PyTuple_GET_ITEM(tuple, i)) : 0; }
-  PyObject* tuple_of(PyObject* t, Py_ssize_t n, const char* message, bool method, PyObject* name) {   // new reference
+  // A tuple of n items (or more, where asked for), new reference.
+  PyObject* tuple_of(PyObject* t, Py_ssize_t n, const char* message, bool method, PyObject* name, bool or_more = false) {
     PyObject* r = method ? call(t, name) : attr(t, name);
-    if (r && (!PyTuple_Check(r) || PyTuple_GET_SIZE(r) != n)) { Py_DECREF(r); r = nullptr; refuse(TALON_ERR_INVALID_ARG, message); }
+    if (r && (!PyTuple_Check(r) || PyTuple_GET_SIZE(r) < n || (PyTuple_GET_SIZE(r) > n && !or_more))) {
+      Py_DECREF(r);
+      r = nullptr;
+      refuse(TALON_ERR_INVALID_ARG, message);
+    }
     return r;
   }
   void contiguous(PyObject* t, const char* message) {
@@ -436,7 +446,11 @@ PyObject* build_tree_mask(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* tree_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!arguments(n, 15)) return nullptr;
   Call c;
-  const Shape4 q(c, a[0], "q must be [B][N_pad][Hq][Dh]"), kt(c, a[3], "k_tree must be [B][N_pad][Hkv][Dh]");
+  const Shape4 q(c, a[0], "q must be [B][N_pad][Hq][Dh]");
+  int32_t Hkv = 0;
+  PyObject* kt = c.tuple_of(a[3], 3, "k_tree must be [B][N_pad][Hkv][Dh]", false, n_shape, true);   // (Dh is q's)
+  if (kt) Hkv = static_cast<int32_t>(c.item(kt, 2));
+  Py_XDECREF(kt);
   const char* text = "q, k_tree, v_tree, mask and out must be contiguous";
   PyObject* const dense[] = {a[0], a[3], a[4], a[9], a[5]};
   for (PyObject* t : dense) c.contiguous(t, text);
@@ -454,18 +468,19 @@ PyObject* tree_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const size_t bytes = a[11] == Py_None ? 0 : c.nbytes(a[11]);
   const float scale = c.f32(a[12]);
   void* s = c.stream(a[13]);
-  const bool own = a[14] == Py_True;
-  RUN(rc, own ? g_abi.tree_attention_static(qp, kp, vp, ktp, vtp, mask, nodes, len, q.d[0], q.d[1], q.d[2], kt.d[2], q.d[3], most, sb, st, sh,
+  const int own = PyObject_IsTrue(a[14]);
+  if (own < 0) c.fail();
+  RUN(rc, own ? g_abi.tree_attention_static(qp, kp, vp, ktp, vtp, mask, nodes, len, q.d[0], q.d[1], q.d[2], Hkv, q.d[3], most, sb, st, sh,
                                             scale, out, lse, s)
-              : g_abi.tree_attention(qp, kp, vp, ktp, vtp, mask, nodes, len, q.d[0], q.d[1], q.d[2], kt.d[2], q.d[3], most, sb, st, sh, scale,
+              : g_abi.tree_attention(qp, kp, vp, ktp, vtp, mask, nodes, len, q.d[0], q.d[1], q.d[2], Hkv, q.d[3], most, sb, st, sh, scale,
                                      out, lse, ws, bytes, s))
   return result(c, rc);
 }
 
-// (addresses of the functions in the order of Abi, TalonError, torch.float32, torch.bfloat16, binding._stream and what it
-// asks: raw handle of a device's current stream, current device, is the GPU initialised)
+// (addresses of the functions in the order of Abi, TalonError, torch.float32, torch.bfloat16, binding._int_of and _float_of,
+// binding._stream and what it asks: raw handle of a device's current stream, current device, is the GPU initialised)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (!arguments(n, 8)) return nullptr;
+  if (!arguments(n, 10)) return nullptr;
   if (!PyTuple_Check(a[0]) || PyTuple_GET_SIZE(a[0]) != kFunctions) {
     PyErr_Format(PyExc_TypeError, "%d addresses expected", kFunctions);
     return nullptr;
@@ -480,8 +495,8 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
   static_assert(sizeof(g_abi) == sizeof(p), "function pointers only");
   memcpy(&g_abi, p, sizeof(p));
-  PyObject** const keep[] = {&g_error, &g_float32, &g_bfloat16, &g_stream_of, &g_raw_stream, &g_device, &g_initialized};
-  for (int i = 0; i < 7; ++i) {
+  PyObject** const keep[] = {&g_error, &g_float32, &g_bfloat16, &g_int_of, &g_float_of, &g_stream_of, &g_raw_stream, &g_device, &g_initialized};
+  for (int i = 0; i < 9; ++i) {
     Py_INCREF(a[1 + i]);
     Py_XDECREF(*keep[i]);
     *keep[i] = a[1 + i];
