@@ -175,7 +175,7 @@ __device__ __forceinline__ void read_part(const ExpandArgs& a, const LiteralAhea
   const uint4* row = reinterpret_cast<const uint4*>(
       static_cast<const char*>(a.logits) +
       (static_cast<int64_t>(b) * a.seq_stride + static_cast<int64_t>(node) * a.row_stride) * (16 / EPL));
-  const int nvec = (a.vocab + EPL - 1) / EPL;
+  const int nvec = a.vocab / EPL;   // whole vectors; the tokens behind the last one are the last part's, one by one (see below)
   const int per = (nvec + parts - 1) / parts;
   const int v_end = (part + 1) * per < nvec ? (part + 1) * per : nvec;
   unsigned long long* buf = s.buf[wave];
@@ -192,7 +192,7 @@ __device__ __forceinline__ void read_part(const ExpandArgs& a, const LiteralAhea
     float top = kNegInf;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-      if (x[e] >= x_lo && v < v_end && v * EPL + e < a.vocab) { bits |= 1u << e; top = fmaxf(top, x[e]); }
+      if (x[e] >= x_lo && v < v_end) { bits |= 1u << e; top = fmaxf(top, x[e]); }
     }
     const unsigned long long hits = __ballot(bits != 0u);
     if (hits == 0ull) return;
@@ -248,12 +248,25 @@ __device__ __forceinline__ void read_part(const ExpandArgs& a, const LiteralAhea
   __syncthreads();
   if (wave == 0) {
     for (int w = 0; w < 4; ++w) floor = s.floor[w] > floor ? s.floor[w] : floor;
-    const int n = wave_cut(all, c0 + c1 + c2 + c3, least, most, s.hist[0], &smallest);
+    int n_all = c0 + c1 + c2 + c3;
+    if (part == parts - 1 && nvec * EPL < a.vocab) {   // fewer than EPL tokens, the last ones of the row: nothing is read beyond them
+      const int tok = nvec * EPL + lane;
+      float x = kNegInf;
+      if (tok < a.vocab) {
+        if constexpr (EPL == 4) x = reinterpret_cast<const float*>(row)[tok];
+        else x = __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t*>(row)[tok]) << 16);
+      }
+      const bool in = tok < a.vocab && x >= x_lo;
+      const unsigned long long ins = __ballot(in);
+      if (in) all[n_all + __popcll(ins & ((1ull << lane) - 1ull))] = make_key(x, tok);
+      n_all += __popcll(ins);
+    }
+    const int n = wave_cut(all, n_all, least, most, s.hist[0], &smallest);
     unsigned long long* out = la.part_key + static_cast<size_t>(b) * la.part_keys_per_seq + static_cast<size_t>(item) * most;
     for (int i = lane; i < n; i += 64) store_agent(out + i, all[i]);
     if (lane == 0) {
       store_agent(la.part_count + static_cast<size_t>(b) * a.N_pad * kLiteralChunks + item, n);
-      store_agent(part_floor(la, a, b) + item, n < c0 + c1 + c2 + c3 && smallest > floor ? smallest : floor);
+      store_agent(part_floor(la, a, b) + item, n < n_all && smallest > floor ? smallest : floor);
     }
     stores_performed();
     if (lane == 0) __hip_atomic_fetch_add(parts_done_word(a, b), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -356,6 +356,7 @@ __global__ __launch_bounds__(kCollectThreads) void literal_collect_kernel(Litera
   int* out_count = whole ? a.row_count + out_row : a.part_count + out_row * kLiteralChunks + c;
   const int v_begin = c * vec_per_chunk;
   const int v_end = v_begin + vec_per_chunk < nvec ? v_begin + vec_per_chunk : nvec;
+  const int v_whole = v_end < a.vocab / EPL ? v_end : a.vocab / EPL;
 
   auto key64 = [](uint32_t k32, uint32_t tk) { return (static_cast<unsigned long long>(k32) << 32) | tk; };
 
@@ -369,10 +370,16 @@ __global__ __launch_bounds__(kCollectThreads) void literal_collect_kernel(Litera
   auto for_each_key = [&](auto&& f) {
     for (int base = v_begin; base < v_end; base += kVecAhead * NT) {
       uint4 raw[kVecAhead];
+      if (base + kVecAhead * NT <= v_whole) {
 #pragma unroll
-      for (int u = 0; u < kVecAhead; ++u) {
-        const int vi = base + u * NT + tid;
-        raw[u] = vi < v_end ? row[vi] : make_uint4(0u, 0u, 0u, 0u);
+        for (int u = 0; u < kVecAhead; ++u) raw[u] = row[base + u * NT + tid];
+      } else {   // (a vector that the row ends in is read token by token: nothing is read beyond the row)
+#pragma unroll
+        for (int u = 0; u < kVecAhead; ++u) {
+          const int vi = base + u * NT + tid;
+          raw[u] = make_uint4(0u, 0u, 0u, 0u);
+          if (vi < v_end) raw[u] = load_vec<EPL>(reinterpret_cast<const char*>(row), vi * EPL, a.vocab);
+        }
       }
 #pragma unroll
       for (int u = 0; u < kVecAhead; ++u) {

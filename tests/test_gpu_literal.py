@@ -467,3 +467,41 @@ def test_any_number_of_layers_means_the_whole_loop(N):
             assert int(st.n_nodes[b]) == t.n, (how, b)
             np.testing.assert_array_equal(st.token[b, :t.n].cpu().numpy(), np.asarray(t.token, dtype=np.int32))
             np.testing.assert_array_equal(st.parent[b, :t.n].cpu().numpy(), np.asarray(t.parent, dtype=np.int32))
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 40003), ("bf16", 20007), ("bf16", 70), ("f32", 20001), ("f32", 4099), ("f32", 18)])
+def test_rows_that_end_with_the_buffer(dtype, V):
+    """The last row of the last sequence ends at its last token, and the tokens behind the row's last whole
+    16-byte vector are among those that a second reading finds: the trees of a padded buffer, layered and ahead."""
+    import ctypes
+    import torch
+    import paper_2601_07353_amd as T
+    print("case", dtype, V, flush=True)
+    B, N, K_init = 2, 100, 40
+    dt, code = (torch.float32, T.TALON_DTYPE_F32) if dtype == "f32" else (torch.bfloat16, T.TALON_DTYPE_BF16)
+    stride, P = (V + 7) // 8 * 8, 128
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V)
+    padded = torch.full((B, P, stride), 60.0, dtype=dt, device="cuda")
+    padded[:, :, :V] = (torch.randn(B, P, V, generator=g, device="cuda") * 0.1).to(dt)
+    padded[:, ::2, V - 2:V] = 0.9      # high enough to be chosen, too low for a row's 16 best
+    padded[:, ::2, :20] = 1.0
+    whole = torch.empty((B * P - 1) * stride + V, dtype=dt, device="cuda")
+    exact = torch.as_strided(whole, (B, P, V), (P * stride, stride, 1))
+    exact.copy_(padded[:, :, :V])
+    lib = T.load_library()
+    lib.talon_expand_literal.restype = lib.talon_expand_literal_ahead.restype = ctypes.c_int
+    ws = T.make_literal_workspace(B, P, V, code)
+    got = []
+    for logits in (padded, exact):
+        for ahead in (False, True):
+            st = T.TreeState(B, N)
+            T.talon_tree_init(st, torch.arange(B, dtype=torch.int32, device="cuda"))
+            fn, row_arg = (lib.talon_expand_literal_ahead, P) if ahead else (lib.talon_expand_literal, T.TALON_ROWS_BY_NODE)
+            assert fn(logits.data_ptr(), code, stride, stride * P, row_arg, 24, ctypes.byref(st.c), V, 0.03, K_init, 1, 24, ws.data_ptr(),
+                      ws.numel(), None) == T.TALON_OK
+            got.append({k: getattr(st, k).cpu().numpy() for k in ("n_nodes", "token", "parent", "depth", "status")})
+    for other in got[1:]:
+        for k, v in got[0].items():
+            np.testing.assert_array_equal(other[k], v, err_msg=k)
+    assert (got[0]["token"][0, 1:N] >= V - 2).sum() >= 2 and (got[0]["n_nodes"] == N).all()
