@@ -154,7 +154,8 @@ int talon_select_budget(const talon_tree_state* st, int32_t k, const int32_t* ca
  * starts, so a selection holds back until all of them have read it; the other workgroups
  * never wait, so this ends whatever else runs on the device (no need for the whole grid to be
  * resident).  Should it not end within two seconds (a workspace that was never initialised),
- * the sequence is marked TALON_STATUS_ABORTED and left as it was.
+ * the sequence is marked TALON_STATUS_ABORTED and left as it was; the workspace has to be initialised
+ * again before its next use (workgroups that start after the wait has run out still count themselves in it).
  */
 int talon_expand_select_layer(const void* logits, int dtype, int64_t row_stride, int64_t seq_stride,
                               int row_mode, int32_t layer, const talon_tree_state* st, int32_t vocab,
@@ -181,11 +182,13 @@ int talon_expand_tree(const void* logits, int dtype, int64_t row_stride, int64_t
 
 /*
  * Bound of the waits inside a single launch, in microseconds (default 200000): between two layers in
- * talon_expand_tree and talon_build_tree, for the rows of a layer in talon_build_tree_ahead.  A launch whose workgroups cannot all be resident (the device
+ * talon_expand_tree and talon_build_tree, for the rows of a layer in talon_build_tree_ahead and, ten times as long, in
+ * talon_expand_literal_ahead (which says how to go on there).  A launch whose workgroups cannot all be resident (the device
  * is shared with other work) ends after this long with TALON_STATUS_ABORTED on every sequence
  * instead of hanging; the caller then re-runs the step layer by layer with
  * talon_tree_init + talon_expand_select_layer on the same workspace.  0 makes every wait give
  * up at once (used by tests of that path).  Process-wide; applies to calls made afterwards.
+ * (The two seconds of talon_expand_select_layer stand by themselves.)
  */
 int talon_set_spin_limit_us(int64_t microseconds);
 
@@ -283,9 +286,11 @@ int talon_expand_literal(const void* logits, int dtype, int64_t row_stride, int6
  * one launch, as in talon_build_tree_ahead, with the 16 best tokens per row; a layer that keeps a
  * row's 16th streams that row a second time, from the lowest score on that can still be chosen.
  * Same tree as talon_expand_literal (row statistics may differ in the last bit of a double);
- * the launch's waits (for rows that are being scanned, bounded by two seconds) do not
- * depend on workgroups being resident together.  Otherwise the call is talon_expand_literal with
- * TALON_ROWS_BY_NODE.  Workspace and errors as there, plus INVALID_ARG for rows < 1.
+ * the launch's waits, for rows and parts of rows that other workgroups are reading, end whatever else runs on the
+ * device, and are bounded by ten times talon_set_spin_limit_us (two seconds by default).  A launch whose bound runs out
+ * all the same marks every sequence TALON_STATUS_ABORTED and leaves every tree after a whole layer: with that bit
+ * cleared, talon_expand_literal, which for more than 64 nodes never waits, or this call goes on from there.
+ * Otherwise the call is talon_expand_literal with TALON_ROWS_BY_NODE.  Workspace and errors as there, plus INVALID_ARG for rows < 1.
  */
 int talon_expand_literal_ahead(const void* logits, int dtype, int64_t row_stride, int64_t seq_stride,
                                int32_t rows, int32_t layers, const talon_tree_state* st, int32_t vocab,

@@ -405,7 +405,7 @@ int literal_ahead_grid_limit(int dtype) {
 }
 
 // Bound of the wait between two layers of the single-launch kernel, in ticks of the 100 MHz
-// wall clock (default 0.2 s; talon_set_spin_limit_us changes it).
+// wall clock (default 0.2 s; talon_set_spin_limit_us changes it); a tenth of that of the uncapped launch ahead.
 std::atomic<long long> g_spin_limit_us{200000};
 unsigned long long spin_limit_ticks() {
   const long long us = g_spin_limit_us.load(std::memory_order_relaxed);
@@ -785,7 +785,7 @@ int talon_expand_literal_ahead(const void* logits, int dtype, int64_t row_stride
   ea.sel.st = *st; ea.sel.k = kLiteralScanK; ea.sel.log_mu = log(static_cast<double>(mu)); ea.sel.K_init = K_init;
   ea.sel.init_layers = init_layers; ea.sel.max_depth = max_depth;
   ea.layers = layers < st->N - 1 ? layers : st->N - 1;   // a tree of N nodes has no more (and the kernel adds the depth it starts from)
-  ea.spin_ticks = 200000000ull;   // two seconds of the 100 MHz clock: scanners and claimed parts never wait, so these waits end; the bound is a safety net
+  ea.spin_ticks = 10ull * spin_limit_ticks();   // scanners and claimed parts never wait, so these waits end; the bound is a safety net
   const int resident = literal_ahead_grid_limit(dtype);
   if (resident < 1) { set_error("occupancy query for the scan-ahead kernel failed"); return TALON_ERR_RUNTIME; }
   // (every row from a sequence's frontier on may be asked for, whatever its depth)

@@ -431,7 +431,9 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
             if (tid == 0) {
               if (gave_up) atomicOr(&a.status[b], static_cast<uint32_t>(TALON_STATUS_ABORTED));
               // the last selection of the launch puts the counters back to zero (every workgroup has
-              // started by now and every selection has seen it, so nobody counts or looks after this)
+              // started by now and every selection has seen it, so nobody counts or looks after this;
+              // unless a wait has run out: workgroups that start later count themselves in words that
+              // stay so, which is why the workspace has to be initialised again then)
               if (static_cast<int>(selected_before) + 1 == active) {
                 for (int x = 0; x < kStartedWords; ++x) store_agent(started_word(a, x), 0u);
                 if (a.B > 1) store_agent(a.exit_ticket + kSelectedWord, 0u);

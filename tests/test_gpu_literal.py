@@ -505,3 +505,46 @@ def test_rows_that_end_with_the_buffer(dtype, V):
         for k, v in got[0].items():
             np.testing.assert_array_equal(other[k], v, err_msg=k)
     assert (got[0]["token"][0, 1:N] >= V - 2).sum() >= 2 and (got[0]["n_nodes"] == N).all()
+
+
+@pytest.mark.parametrize("microseconds", [0, 1, 2, 3, 5])
+def test_a_wait_that_runs_out_leaves_trees_to_go_on_from(microseconds):
+    """The bound of the waits reaches the launch that scans ahead: a call whose bound runs out (here a short one, from
+    the host) ends with every sequence ABORTED after a whole layer; with the bit cleared another call finishes the trees."""
+    import ctypes
+    import torch
+    import paper_2601_07353_amd as T
+    B, V, N, stride = 4, 70001, 200, 70008
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    scale = torch.tensor([6.0, 0.4, 4.0, 0.5], device="cuda")[:, None, None]     # two sequences whose rows are read again
+    logits = (torch.randn(B, 256, stride, generator=g, device="cuda") * scale).bfloat16()[:, :, :V]
+    ws = T.make_literal_workspace(B, 256, V, T.TALON_DTYPE_BF16)
+    st = [T.TreeState(B, N) for _ in range(2)]
+    for s in st:
+        T.talon_tree_init(s, torch.arange(B, dtype=torch.int32, device="cuda"))
+    for _ in range(16):                                                          # (layer by layer: nothing waits)
+        T.talon_expand_literal(logits, st[0], 1, 0.03, 8, 1, 16, ws)
+    T.talon_set_spin_limit_us(microseconds)
+    try:
+        T.talon_expand_literal(logits, st[1], 16, 0.03, 8, 1, 16, ws)
+        torch.cuda.synchronize()
+    finally:
+        T.talon_set_spin_limit_us(200000)
+    want = {k: getattr(st[0], k).cpu().numpy() for k in ("n_nodes", "status", "token", "parent", "depth", "depth_cur")}
+    cut = {k: getattr(st[1], k).cpu().numpy().copy() for k in want}
+    aborted = (cut["status"] & T.TALON_STATUS_ABORTED) != 0
+    print("bound", microseconds, "aborted", aborted, "nodes", cut["n_nodes"], "of", want["n_nodes"], flush=True)
+    assert aborted.all() or not aborted.any()
+    if microseconds == 0:
+        assert aborted.all()
+    for b in range(B):
+        n = int(cut["n_nodes"][b])
+        for k in ("token", "parent", "depth"):
+            np.testing.assert_array_equal(cut[k][b, :n], want[k][b, :n], err_msg=k)
+        assert n == int(want["n_nodes"][b]) or int(want["depth"][b, n]) == int(cut["depth_cur"][b]) + 1     # whole layers
+    st[1].status &= ~T.TALON_STATUS_ABORTED
+    T.talon_expand_literal(logits, st[1], 16, 0.03, 8, 1, 16, ws)
+    for k, v in want.items():
+        got = getattr(st[1], k).cpu().numpy()
+        np.testing.assert_array_equal(got if got.ndim == 1 else got[:, :N], v if v.ndim == 1 else v[:, :N], err_msg=k)
