@@ -77,6 +77,7 @@ struct DeepPickLds {
   unsigned char par[kAheadLists];
 };
 constexpr unsigned int kDeepList = 1u << 31;
+__device__ __forceinline__ DeepPickLds& deep_lds(SelectorLds& s) { return *reinterpret_cast<DeepPickLds*>(s.key); }
 static_assert(sizeof(PartLds) <= sizeof(unsigned long long) * kAheadKeySlots && sizeof(DeepPickLds) <= sizeof(unsigned long long) * kAheadKeySlots,
               "both lie over the key array");
 constexpr size_t kAheadLds = sizeof(ScannerLds) > sizeof(SelectorLds) ? sizeof(ScannerLds) : sizeof(SelectorLds);
@@ -275,9 +276,10 @@ __device__ __forceinline__ void read_part(const ExpandArgs& a, const LiteralAhea
 }
 
 // ---- helper: parts of any sequence's request, its own number's sequence first, until every selector has
-// finished.  (Helpers are the last workgroups of the grid: whoever they wait for has started before them.)
+// finished or, with `leave`, until there are none.  (Helpers are the last workgroups of the grid: whoever they wait
+// for has started before them.)
 template <int EPL>
-__device__ __forceinline__ void help_read(const ExpandArgs& a, const LiteralAhead& la, PartLds& s, const int h) {
+__device__ __forceinline__ void help_read(const ExpandArgs& a, const LiteralAhead& la, PartLds& s, const int h, const bool leave) {
   const int tid = threadIdx.x;
   while (true) {
     if (tid < 64) {
@@ -297,7 +299,7 @@ __device__ __forceinline__ void help_read(const ExpandArgs& a, const LiteralAhea
         }
       }
       if (found == -1) {
-        if (load_agent(a.exit_ticket + kSelectedWord) == static_cast<uint32_t>(a.B)) found = -3;
+        if (leave || load_agent(a.exit_ticket + kSelectedWord) == static_cast<uint32_t>(a.B)) found = -3;
         else __builtin_amdgcn_s_sleep(16);
       }
       if (tid == 0) { s.item = found >= 0 ? item : found; s.count[0] = nb; }
@@ -310,13 +312,12 @@ __device__ __forceinline__ void help_read(const ExpandArgs& a, const LiteralAhea
   }
 }
 
-// The selection of a layer some of whose rows have to be read again: `low`, the lowest path score that can
-// still be chosen; kept (in the threads of row p): candidates that the capped pool keeps of the row up to
-// this thread's.  Appends the nodes and returns their number.
+// The selection of a layer some of whose rows have to be read again (their log-sum-exps in deep_lds, no barrier since):
+// `low`, the lowest path score that can still be chosen; kept (in the threads of row p): candidates that the capped pool keeps of the row up to
+// this thread's.  Appends the nodes and returns their number, -1 if the wait for parts ran out.
 template <int EPL>
 __device__ __forceinline__ int deep_select(const ExpandArgs& a, const LiteralAhead& la, SelectorLds& s, const int b, const int F, const int fb,
-                                           const int n, const int d, const int limit, double low, const int kept, const int p,
-                                           bool* waited_out) {
+                                           const int n, const int d, const int limit, double low, const int kept, const int p) {
   const talon_tree_state& st = a.sel.st;
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
@@ -332,7 +333,7 @@ __device__ __forceinline__ int deep_select(const ExpandArgs& a, const LiteralAhe
   int n_open;
   const int o = block_exclusive_scan_i32(open ? 1 : 0, s.red_i32, &n_open);
   const int nvec = (a.vocab + EPL - 1) / EPL;
-  int parts = 64 / n_open;
+  int parts = la.parts_per_seq / n_open;
   const int by_size = nvec / 512;
   parts = parts < by_size ? parts : by_size;
   parts = parts < 1 ? 1 : (parts > kLiteralChunks ? kLiteralChunks : parts);
@@ -346,7 +347,7 @@ __device__ __forceinline__ int deep_select(const ExpandArgs& a, const LiteralAhe
     if (open) {
       // inside a row the path score rises with the logit: the smallest logit image whose score reaches
       // `low`, by bisection with the very expression the score is computed with
-      const double lp = s.logp[fb + tid], lse = load_agent(a.part_sum + (base + fb + tid) * a.chunks);
+      const double lp = s.logp[fb + tid], lse = deep_lds(s).lse[tid];
       uint32_t l = 0x007FFFFFu, h = 0xFF800000u;   // images of -inf and +inf
       while (l < h) {
         const uint32_t mid = l + ((h - l) >> 1);
@@ -383,10 +384,10 @@ __device__ __forceinline__ int deep_select(const ExpandArgs& a, const LiteralAhe
       }
     }
     __syncthreads();
-    if (s.state & 2) { *waited_out = true; return 0; }
+    if (s.state & 2) return -1;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     // ---- lists of keys: a row's kept candidates, or what its parts left
-    DeepPickLds& L = *reinterpret_cast<DeepPickLds*>(s.key);
+    DeepPickLds& L = deep_lds(s);
     const int32_t* part_count = la.part_count + static_cast<size_t>(b) * a.N_pad * kLiteralChunks;
     const unsigned long long* floors = part_floor(la, a, b);
     const int own_lists = open ? parts : (row_kept > 0 ? 1 : 0);
@@ -453,6 +454,10 @@ __device__ __forceinline__ int deep_select(const ExpandArgs& a, const LiteralAhe
   return n_keep;
 }
 
+// A value that is the same in all lanes, as the scalar that the compiler does not take it for where it comes from LDS
+// (on a vector, both sides of a branch are run through one after the other, with the registers of both).
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // ---- selector: the loop of Alg. 2 for sequence b.
 // exit_ticket(ok): takes the workgroup's exit ticket; called when everything other workgroups
 // of the launch look at has been performed.
@@ -491,6 +496,28 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, const Literal
   if (tid < TALON_N_MAX / 64) s.ready[tid] = 0ull;
   bool own_ready = false;   // row `tid` of the sequence is known to be ready
   __syncthreads();
+  // Appends have been made: the next layer's frontier, and whether there is one.  (known: row `tid` is known to be ready.)
+  auto next_layer = [&](const int n_keep, const bool known) __attribute__((always_inline)) {
+    fb = n;
+    F = n_keep;
+    n += n_keep;
+    ++d;
+    if (n >= st.N) status |= TALON_STATUS_DONE_BUDGET;
+    else if (d >= sa.max_depth) status |= TALON_STATUS_DONE_DEPTH;
+    if (status != 0u || F == 0 || d >= d_end) return false;
+    const unsigned long long ready = __ballot(known);
+    if ((threadIdx.x & 63) == 0) s.ready[threadIdx.x >> 6] = ready;
+    __syncthreads();   // this layer's scores, parents and ready marks are read by the next one
+    return true;
+  };
+  // Uncapped pool: a layer some of whose rows have to be read again is finished outside of the loop, and branches are
+  // taken on scalars.  With the reading inside, what the loop needs after it was spilled in every layer, read again or not
+  // (55 vector registers; four peaked trees of 128 nodes 71.6 us, now 69.4; one of 250 in 13 layers 66.0, 62.2).
+  bool again;
+  int deep_limit = 0, deep_kept = 0, deep_row = 0;
+  double deep_low = 0.0;
+  do {
+  again = false;
   while (active) {
     // ---- scores of the pool.  A frontier row is shared by 2^lt consecutive threads; thread t owns
     // `per` <= 32 consecutive candidates of row t >> lt, so that the threads' candidates follow
@@ -563,7 +590,7 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, const Literal
     }
     if (UNCAPPED && tid == 0) s.want = 0;   // (no row has to be read again)
     anchor = block_max_u64(anchor, s.red_u64);   // (its barriers: every thread's wait has ended)
-    const int found = s.state;
+    const int found = uniform(s.state);
     if (found & 2) { waited_out = true; break; }
     if (found & 1) { status |= TALON_STATUS_BAD_ROW; break; }   // a row that cannot be normalised: stop here
 
@@ -583,61 +610,84 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, const Literal
     int n_keep;
     int pos;
     const unsigned int keep_bits = keep_best<!UNCAPPED>(my, per, anchor, thr, limit, lds, &pos, &n_keep);
-    bool again = false;
+    n_keep = uniform(n_keep);
     if constexpr (UNCAPPED) {
       // Was a row's last candidate kept?  (Of a single row the `limit` best are its first ones.)
       const int last = k - 1 - rank0;
       if (a.vocab > k && !(F == 1 && n_keep == limit) && last >= 0 && last < per && ((keep_bits >> last) & 1u)) s.want = 1;
       __syncthreads();
-      again = s.want != 0;
+      again = uniform(s.want) != 0;
     }
     if (UNCAPPED && again) {
-      if (tid == 0 && n + n_keep >= st.N) store_agent(stop_word(a, b), 1);   // the budget will be spent: no further rows are needed
       double low = init || anchor == 0ull ? -__builtin_huge_val() : sa.log_mu + unsortable_f64(anchor);
-      unsigned long long inv_low = 0ull;   // of the lowest score kept
-      const int kept_last = 31 - __clz(static_cast<int>(keep_bits));   // a row's kept candidates are its first ones
-      if (keep_bits != 0u) {
-        const unsigned long long key = load_agent(row_keys + rank0 + kept_last);
-        inv_low = ~sortable_u64(plogp + (static_cast<double>(unsortable_f32(static_cast<uint32_t>(key >> 32))) - lse));
-      }
-      inv_low = block_max_u64(inv_low, s.red_u64);
-      if (n_keep == limit) low = unsortable_f64(~inv_low);   // nothing below it can be chosen
-      n_keep = deep_select<EPL>(a, la, s, b, F, fb, n, d, limit, low, keep_bits != 0u ? rank0 + kept_last + 1 : 0, p, &waited_out);
-      if (waited_out) break;
-    } else {
-      auto append = [&](const int tok, const float prob, const double score) __attribute__((always_inline)) {
-        const int id = n + pos;
-        s.parent[id] = static_cast<unsigned char>(fb + p);
-        s.logp[id] = score;
-        st.token[base + id] = tok;
-        st.parent[base + id] = fb + p;
-        st.depth[base + id] = d + 1;
-        st.prob[base + id] = prob;
-        st.logp[base + id] = score;
-        ++pos;
-      };
+      // Once it is sure that the budget will be spent no further rows are needed.  How many tokens of a row that is
+      // read again pass at least?  Its probabilities add up to one: the k best hold at most k times the best one's, tokens
+      // that do not pass less than the bound's each, and what is left is shared by tokens of at most the k-th's.
+      int sure = n_keep;
+      if (sure < limit && n + limit >= st.N) {
+        if (tid == 0) s.nfin = 0;
+        if (p < F && rank0 == 0) s.hist[p] = __float_as_int(prob_r[0]);
+        __syncthreads();
+        const int at = k - 1 - rank0;
 #pragma unroll
-      for (int i = 0; i < kRegCand; ++i)
-        if (keep_bits & (1u << i)) append(tok_r[i], prob_r[i], score_r[i]);
-      for (int i = kRegCand; i < per; ++i) {
-        if (!(keep_bits & (1u << i))) continue;
-        const unsigned long long key = load_agent(row_keys + rank0 + i);
-        const double edge = static_cast<double>(unsortable_f32(static_cast<uint32_t>(key >> 32))) - lse;
-        append(static_cast<int32_t>(0xFFFFFFFFu - static_cast<uint32_t>(key)), __expf(static_cast<float>(edge)), plogp + edge);
+        for (int i = 0; i < kRegCand; ++i) {
+          if (i != at || i >= per || !((keep_bits >> i) & 1u)) continue;
+          const float bound = __expf(static_cast<float>(low - plogp));
+          const float rest = 0.9f * (1.f - static_cast<float>(k) * __int_as_float(s.hist[p]) - static_cast<float>(a.vocab) * bound) / prob_r[i];
+          if (rest > 0.f) atomicAdd(&s.nfin, rest < 256.f ? static_cast<int>(rest) : 256);
+        }
+        __syncthreads();
+        sure += uniform(s.nfin);
       }
+      if (tid == 0 && sure >= limit && n + limit >= st.N) store_agent(stop_word(a, b), 1);
+      const int kept_last = 31 - __clz(static_cast<int>(keep_bits));   // a row's kept candidates are its first ones
+      if (n_keep == limit) {   // nothing below the lowest score kept can be chosen
+        unsigned long long inv_low = 0ull;
+        if (keep_bits != 0u) {
+          const unsigned long long key = load_agent(row_keys + rank0 + kept_last);
+          inv_low = ~sortable_u64(plogp + (static_cast<double>(unsortable_f32(static_cast<uint32_t>(key >> 32))) - lse));
+        }
+        low = unsortable_f64(~block_max_u64(inv_low, s.red_u64));
+      }
+      if (p < F && rank0 == 0) deep_lds(s).lse[p] = lse;
+      deep_limit = limit;
+      deep_low = low;
+      deep_kept = keep_bits != 0u ? rank0 + kept_last + 1 : 0;
+      deep_row = p;
+      break;
     }
-    fb = n;
-    F = n_keep;
-    n += n_keep;
-    ++d;
-    if (n >= st.N) status |= TALON_STATUS_DONE_BUDGET;
-    else if (d >= sa.max_depth) status |= TALON_STATUS_DONE_DEPTH;
-    if (status != 0u || F == 0 || d >= d_end) break;
+    auto append = [&](const int tok, const float prob, const double score) __attribute__((always_inline)) {
+      const int id = n + pos;
+      s.parent[id] = static_cast<unsigned char>(fb + p);
+      s.logp[id] = score;
+      st.token[base + id] = tok;
+      st.parent[base + id] = fb + p;
+      st.depth[base + id] = d + 1;
+      st.prob[base + id] = prob;
+      st.logp[base + id] = score;
+      ++pos;
+    };
+#pragma unroll
+    for (int i = 0; i < kRegCand; ++i)
+      if (keep_bits & (1u << i)) append(tok_r[i], prob_r[i], score_r[i]);
+    for (int i = kRegCand; i < per; ++i) {
+      if (!(keep_bits & (1u << i))) continue;
+      const unsigned long long key = load_agent(row_keys + rank0 + i);
+      const double edge = static_cast<double>(unsortable_f32(static_cast<uint32_t>(key >> 32))) - lse;
+      append(static_cast<int32_t>(0xFFFFFFFFu - static_cast<uint32_t>(key)), __expf(static_cast<float>(edge)), plogp + edge);
+    }
     own_ready = own_ready || own == kRowReady;
-    const unsigned long long ready = __ballot(own_ready);
-    if ((tid & 63) == 0) s.ready[tid >> 6] = ready;
-    __syncthreads();   // this layer's scores, parents and ready marks are read by the next one
+    if (!next_layer(n_keep, own_ready)) break;
   }
+  if constexpr (UNCAPPED) {
+    if (again) {
+      const int n_keep = uniform(deep_select<EPL>(a, la, s, b, F, fb, n, d, deep_limit, deep_low, deep_kept, deep_row));
+      own_ready = ((s.ready[threadIdx.x >> 6] >> (threadIdx.x & 63)) & 1ull) != 0ull;
+      if (n_keep < 0) waited_out = true;
+      if (n_keep < 0 || !next_layer(n_keep, own_ready)) break;
+    }
+  }
+  } while (UNCAPPED && again);
   // ---- the sequence needs no further rows; this workgroup has finished with tickets and counters
   if (tid == 0) {
     store_agent(stop_word(a, b), 1);
@@ -718,7 +768,7 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, const Literal
   }
 }
 
-// Workgroups: scanners, then one selector per sequence, then (uncapped pool) helpers.
+// Workgroups: scanners, then one selector per sequence, then (uncapped pool) helpers, those that wait first.
 template <int EPL, bool UNCAPPED>
 __device__ __forceinline__ void ahead_body(const ExpandArgs& a, const LiteralAhead& la) {
   __shared__ __attribute__((aligned(16))) unsigned char s_lds[kAheadLds];
@@ -734,13 +784,13 @@ __device__ __forceinline__ void ahead_body(const ExpandArgs& a, const LiteralAhe
     if (threadIdx.x == 0) before = __hip_atomic_fetch_add(word, ok ? 1u : 0x10001u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
   const int others = static_cast<int>(gridDim.x) - a.B;                  // scanners and helpers
-  const int scanners = UNCAPPED ? others - la.helpers : others;
+  const int scanners = UNCAPPED ? others - la.helpers - la.late_helpers : others;
   const int wg = static_cast<int>(blockIdx.x);
   const bool selector = wg >= scanners && wg < scanners + a.B;
   const uint32_t group = (wg < scanners ? wg : wg - a.B) % kExitGroups;
   if (!selector) {
     if (!UNCAPPED || wg < scanners) scan_rows<EPL, UNCAPPED>(a, *reinterpret_cast<ScannerLds*>(s_lds), wg, scanners, la.first_row);
-    else help_read<EPL>(a, la, *reinterpret_cast<PartLds*>(s_lds), wg - scanners - a.B);
+    else help_read<EPL>(a, la, *reinterpret_cast<PartLds*>(s_lds), wg, wg >= scanners + a.B + la.helpers);
     stores_performed();
     __syncthreads();
     exit_ticket(a.exit_ticket + 1 + group, true);

@@ -647,9 +647,17 @@ int check_literal_args(const void* logits, int dtype, int64_t row_stride, int64_
 // Fewest layers of an uncapped call whose rows are scanned ahead.
 constexpr int kLiteralAheadLayers = 4;
 
-// Workgroups that read parts of rows again: 64 (a request has up to 64 parts, more for more than 64 rows).
-// They come last in the grid, behind the scanners; where the scan takes several rounds, as many scanners
-// fewer are started, so that helpers are there from the beginning.
+// Workgroups that read parts of rows again: 64 that wait for them from the start (a request has up to 64 parts). They
+// come behind the scanners in the grid; where the scan takes several rounds, as many scanners
+// fewer are started, so that helpers are there from the beginning.  Another kLateHelpers start when scanners have left and
+// leave at once when there is nothing to read: where many sequences have flat rows, 64 took four rounds and more over their
+// parts.  (Late ones that wait too hold up the selectors with their polling: 4 peaked trees of 250 nodes 138 us, 160.)
+// A request is cut into as many parts as give the waiting helpers and the selectors three each when every
+// sequence has one: fewer, and single rows wait for one workgroup; more, and each pays the 10 us that a part takes
+// whatever its length.  Flat rows, before (64 helpers, eight parts a row, a scan that
+// went on until the tree was finished) and now: 4 x 250 of 304 KB 180 us, 149; 8 x 160 of 128 KB 176, 154; 16 x 250 of 128 KB
+// 292, 207; every other sequence flat: 164, 148; 136, 127; 233, 215.
+constexpr int kLateHelpers = 448;
 int literal_helpers(int B, int resident, int scanners, long long items, int* scanners_out) {
   const int helpers = 64;
   if (items > scanners && scanners + B + helpers > resident && scanners > 2 * helpers) scanners -= helpers;
@@ -807,12 +815,15 @@ int talon_expand_literal_ahead(const void* logits, int dtype, int64_t row_stride
   ea.ahead_head = plan.head;
   ea.ahead_chunks_head = plan.chunks_head;
   ea.ahead_chunks = plan.chunks;
+  la.late_helpers = kLateHelpers;
+  la.parts_per_seq = 3 * (la.helpers + st->B) / st->B;
+  if (la.parts_per_seq > 64) la.parts_per_seq = 64;
   la.first_row = ea.seq_ticket;
   la.request = reinterpret_cast<unsigned long long*>(w + V.off_keys);
   la.part_key = reinterpret_cast<unsigned long long*>(w + V.off_part_keys);
   la.part_keys_per_seq = V.part_keys_per_seq;
   la.part_count = reinterpret_cast<int32_t*>(w + V.off_part_count);
-  return check_hip(launch_literal_ahead(ea, la, dtype, plan.scanners + st->B + la.helpers, w + L.off_ticket, L.off_max - L.off_ticket,
+  return check_hip(launch_literal_ahead(ea, la, dtype, plan.scanners + st->B + la.helpers + la.late_helpers, w + L.off_ticket, L.off_max - L.off_ticket,
                                         static_cast<hipStream_t>(stream)), "literal scan-ahead launch");
 }
 

@@ -151,7 +151,9 @@ struct LiteralArgs {
 
 // The uncapped pool with rows scanned ahead (ahead.hip).
 struct LiteralAhead {
-  int helpers;                     // workgroups that read parts of rows again
+  int helpers;                     // workgroups that read parts of rows again ...
+  int late_helpers;                // ... and those that start when others have left, and stay while there is work
+  int parts_per_seq;               // most parts of a sequence's request (more only for more rows)
   int32_t* first_row;              // [B] first row to scan
   unsigned long long* request;     // [B][N_pad + 1] rows to read again: header, then node << 32 | logit bound; behind them [B][320] floors of the parts
   unsigned long long* part_key;    // [B][part_keys_per_seq] keys of the parts

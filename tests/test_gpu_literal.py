@@ -377,6 +377,8 @@ AHEAD_SHAPES = [
     (4, 151936, "bf16", 128, 8, 1, 0.03, "mixed"),     # eight parts per row
     (2, 40001, "f32", 256, 2, 1, 0.003, "flat"),       # two rows share 253 children
     (16, 60001, "bf16", 250, 16, 1, 0.03, "mixed"),    # several rounds of rows, helpers from the start
+    (8, 30011, "bf16", 220, 8, 1, 0.03, "flat"),       # the budget is sure to be spent before the rows are read again: late helpers
+    (5, 20002, "f32", 200, 8, 1, 0.03, "steps"),       # ... and it is not, though all 16 best pass: 20 tokens of a row do
 ]
 
 
@@ -401,6 +403,9 @@ def test_rows_scanned_ahead_give_the_layered_trees(shape, steps):
         scale = torch.rand(P, 1, generator=g, device="cuda")
         scale = 0.3 + 0.2 * scale if kind == "flat" or (kind == "mixed" and b % 3 == 1) else 0.5 + 7.5 * scale
         pool[b, :, :V] = (torch.randn(P, V, generator=g, device="cuda") * scale).to(dt) if kind != "equal" else 1.5
+        if kind == "steps":
+            pool[b, :, :V] = (pool[b, :, :V] * 0.01 - 3.0).to(dt)
+            pool[b, :, 100 * b:100 * b + 40:2] = (3.0 + 0.001 * torch.arange(20, device="cuda")).to(dt)
     if B > 2:
         pool[2, 1, V // 2] = float("nan")
     logits = pool[:, :, :V]
