@@ -282,7 +282,7 @@ int talon_expand_literal(const void* logits, int dtype, int64_t row_stride, int6
 /*
  * talon_expand_literal for rows by node id that are all in place: `rows` rows of every sequence may
  * be read from the start of the call on, whatever the tree comes to ask for (rows it does not expand have no
- * effect).  With rows >= N - 1 and at least four layers to go they are scanned ahead of the trees in
+ * effect).  With rows >= N - 1, at least four layers to go and sizes for which it is the faster way they are scanned ahead of the trees in
  * one launch, as in talon_build_tree_ahead, with the 16 best tokens per row; a layer that keeps a
  * row's 16th streams that row a second time, from the lowest score on that can still be chosen.
  * Same tree as talon_expand_literal (row statistics may differ in the last bit of a double);

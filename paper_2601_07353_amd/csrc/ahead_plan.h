@@ -91,4 +91,27 @@ inline AheadPlan ahead_plan(int B, int N, int blocks, int k, int K_init, int ini
   return p;
 }
 
+// Does an uncapped call whose rows are all in place go layer by layer all the same?  least: layers it may build; blocks: of
+// all rows it would scan; capped: trees of at most 64 nodes, whose layered form is the capped loop, first with `cap_tried`
+// candidates per row.
+// * Fewer than four layers: three launches a layer weigh less than rows scanned in vain.  2 x 250 nodes, rows of 257 KB: two
+//   layers 53 us (peaked rows; flat 101), 55 ahead (113), three 83 (107), 56 (114), four 119 (112), 64 (114); 4 x 250 of
+//   304 KB: 56 (109), 91 (147); 90 (115), 95 (147); 130 (121), 101 (149).  (At most eight blocks per scanner would gain from two
+//   or three layers on: 1 x 60 of 257 KB 48, 29; they stay as they were.)
+// * More than 8 blocks per scanner for every layer beyond the first: trees of few layers read a part of what is scanned.
+//   16 x 250 of 128 KB (31 blocks), peaked / flat / every other one: four layers 174, 166, 218 us, 185, 210, 209 ahead; five 238, 172, 266, 206, 209,
+//   214.  8 x 250 of 304 KB (37): four 170, 139, 200, 179, 177, 203; six 282, 151, 291, 207, 178, 211.  16 x 250 of 304 KB (74): five 325,
+//   233, 333, 320, 256, 301; eight 539, 251, 504, 360, 256, 313; twelve 629, 275, 529, 363, 257, 313.  16 x 250 of 513 KB (125): eight 567, 230,
+//   487, 599, 333, 447; twenty-four 707, 326, 582, 608, 335, 448.
+// * Trees of which a top-K layer is all there is to select.  The capped loop has them in one launch where its first number of
+//   candidates holds all children (8 x 33 of 257 KB 32 us, 68 ahead; 26 x 24 33, 116), and needs a second launch beyond (8 x 36: 100,
+//   68; 26 x 48 159, 116).  Above 64 nodes one row is read again by few workgroups, and the other rows are scanned in
+//   vain: 1 x 128 of 257 KB 88, 66; 4 x 100 88, 78; 16 x 100 (25 blocks) 122, 152; 8 x 128 (16) 91, 106; 8 x 144 of 40 KB 79, 90; 1 x 250 of 40 KB 77, 98; 4 x 250 of
+//   257 KB 97, 107.
+inline bool literal_layered(int N, int K_init, int init_layers, int least, long long blocks, int resident, bool capped, int cap_tried) {
+  if (least < 4) return true;
+  if (init_layers > 0 && K_init >= N - 1) return (capped && N - 1 <= cap_tried) || N > 128 || blocks > 12ll * resident;
+  return blocks > 8ll * (least - 1) * resident;
+}
+
 }  // namespace talon

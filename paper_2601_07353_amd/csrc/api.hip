@@ -644,9 +644,6 @@ int check_literal_args(const void* logits, int dtype, int64_t row_stride, int64_
   return TALON_OK;
 }
 
-// Fewest layers of an uncapped call whose rows are scanned ahead.
-constexpr int kLiteralAheadLayers = 4;
-
 // Workgroups that read parts of rows again: 64 that wait for them from the start (a request has up to 64 parts). They
 // come behind the scanners in the grid; where the scan takes several rounds, as many scanners
 // fewer are started, so that helpers are there from the beginning.  Another kLateHelpers start when scanners have left and
@@ -771,21 +768,25 @@ int talon_expand_literal_ahead(const void* logits, int dtype, int64_t row_stride
                                void* stream) {
   if (rows < 1) { set_error("rows=%d must be >= 1", rows); return TALON_ERR_INVALID_ARG; }
   LiteralLayout V;
-  const int least = max_depth < layers ? max_depth : layers;
-  // Layer by layer where rows the trees may ask for are not there, where the workspace has no room for the 16 best
-  // of a row, and for calls of few layers, which would mostly scan rows in vain (three launches a layer, about
-  // 15 us each, against one scan of all rows).
-  // So too small trees of which a top-K layer is all there is to select: the capped loop takes 31 us for 8 sequences of
-  // 30 nodes and 33 for 26 of 19, the scan of all rows 75 and 113.
-  if (check_state(st) || st->N < 2 || rows < st->N - 1 || least < kLiteralAheadLayers ||
-      literal_layout(st->B, st->N_pad, vocab, dtype, &V) || V.k_max < kLiteralScanK ||
-      (V.capped_loop_fits && init_layers > 0 && K_init >= st->N - 1))
+  const auto layer_by_layer = [&]() {
     return talon_expand_literal(logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, layers, st, vocab, mu, K_init,
                                 init_layers, max_depth, workspace, workspace_bytes, stream);
+  };
+  // Layer by layer where rows the trees may ask for are not there, where the workspace has no room for the 16 best
+  // of a row, and where the plan says so.
+  if (check_state(st) || st->N < 2 || rows < st->N - 1 || literal_layout(st->B, st->N_pad, vocab, dtype, &V) || V.k_max < kLiteralScanK)
+    return layer_by_layer();
   ExpandLayout L;
   int rc = check_literal_args(logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, layers, st, vocab, mu, K_init, init_layers,
                               max_depth, workspace, workspace_bytes, V, &L);
   if (rc) return rc;
+  const int resident = literal_ahead_grid_limit(dtype);
+  if (resident < 1) { set_error("occupancy query for the scan-ahead kernel failed"); return TALON_ERR_RUNTIME; }
+  // (every row from a sequence's frontier on may be asked for, whatever its depth)
+  AheadPlan plan = ahead_plan(st->B, st->N, V.scan.chunks, kLiteralScanK, K_init, init_layers, st->N, resident);
+  if (literal_layered(st->N, K_init, init_layers, max_depth < layers ? max_depth : layers, static_cast<long long>(st->B) * plan.rows * V.scan.chunks,
+                      resident, V.capped_loop_fits, kCappedLoopTryK))
+    return layer_by_layer();
   char* w = static_cast<char*>(workspace);
   L = V.scan;
   ExpandArgs ea = make_expand_args(logits, row_stride, seq_stride, TALON_ROWS_BY_NODE, st, vocab, kLiteralScanK, nullptr, nullptr,
@@ -794,18 +795,6 @@ int talon_expand_literal_ahead(const void* logits, int dtype, int64_t row_stride
   ea.sel.init_layers = init_layers; ea.sel.max_depth = max_depth;
   ea.layers = layers < st->N - 1 ? layers : st->N - 1;   // a tree of N nodes has no more (and the kernel adds the depth it starts from)
   ea.spin_ticks = 10ull * spin_limit_ticks();   // scanners and claimed parts never wait, so these waits end; the bound is a safety net
-  const int resident = literal_ahead_grid_limit(dtype);
-  if (resident < 1) { set_error("occupancy query for the scan-ahead kernel failed"); return TALON_ERR_RUNTIME; }
-  // (every row from a sequence's frontier on may be asked for, whatever its depth)
-  AheadPlan plan = ahead_plan(st->B, st->N, L.chunks, kLiteralScanK, K_init, init_layers, st->N, resident);
-  // Layer by layer too where the scan of all rows is long, more than 40 blocks per scanner (650 MB in all): trees of flat
-  // rows end after two layers, and most of it would be in vain.  16 x 249 rows of 200 KB, flat: 240 us, 368 ahead; 16 x 127
-  // of 513 KB in at most four layers: 217, 255 (peaked rows and many layers would gain: 16 x 255 of 304 KB, a depth cap of
-  // 24: 511, 350).  Below that line peaked, mixed and most flat batches are faster ahead: 13 x 59 of 513 KB 524 -> 146, 16 x 71
-  // 327 -> 195, 2 x 249 of 257 KB flat 203 -> 95; 4 x 249 of 304 KB, all flat, is the exception: 130 -> 190.
-  if (static_cast<long long>(st->B) * plan.rows * L.chunks > 40ll * resident)
-    return talon_expand_literal(logits, dtype, row_stride, seq_stride, TALON_ROWS_BY_NODE, layers, st, vocab, mu, K_init,
-                                init_layers, max_depth, workspace, workspace_bytes, stream);
   LiteralAhead la;
   la.helpers = literal_helpers(st->B, resident, plan.scanners,
                                static_cast<long long>(st->B) * (static_cast<long long>(plan.head) * plan.chunks_head +

@@ -21,6 +21,9 @@ void t_ahead(int B, int N, int blocks, int k, int K_init, int init_layers, int m
   const int v[] = {p.layered, p.rows, p.head, p.chunks_head, p.chunks, p.scanners};
   for (int i = 0; i < 6; ++i) out[i] = v[i];
 }
+int t_literal_layered(int N, int K_init, int init_layers, int least, long long blocks, int resident, int capped, int cap_tried) {
+  return talon::literal_layered(N, K_init, init_layers, least, blocks, resident, capped != 0, cap_tried);
+}
 void t_plan(int B, int N_pad, int Hq, int Hkv, int Dh, int L, size_t bytes, long long* out) {
   const talon::AttnPlan p = talon::attention_plan(B, N_pad, Hq, Hkv, Dh, L, bytes);
   const long long v[] = {p.waves, p.row_tiles, p.run_bound, p.split_max, p.split_likely, p.capacity_per_head, p.balance, p.run_single,
@@ -44,6 +47,7 @@ def _lib():
     lib.t_least.restype = ctypes.c_size_t
     lib.t_us.restype = ctypes.c_double
     lib.t_us.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
+    lib.t_literal_layered.argtypes = [ctypes.c_int] * 4 + [ctypes.c_longlong] + [ctypes.c_int] * 3
     lib.t_plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_size_t, ctypes.c_void_p]
     return lib
 
@@ -76,3 +80,9 @@ def ahead_plan(B, N, vocab, dtype, k, max_depth, K_init=None, init_layers=1, res
     _lib().t_ahead(B, N, -(-vocab // per_block), k, K_init or k, init_layers, max_depth, resident, out)
     p = dict(zip(("layered", "rows", "head", "chunks_head", "chunks", "scanners"), out))
     return dict(p, blocks=-(-vocab // per_block))
+
+
+def literal_layered(B, N, vocab, dtype, layers, K_init=8, init_layers=1, resident=1024):
+    """Does the uncapped call with all rows in place go layer by layer?"""
+    p = ahead_plan(B, N, vocab, dtype, 16, N, K_init, init_layers, resident)
+    return bool(_lib().t_literal_layered(N, K_init, init_layers, layers, B * p["rows"] * p["blocks"], resident, N <= 64, 32))

@@ -69,3 +69,23 @@ def test_trees_with_nothing_to_scan_ahead_are_built_layer_by_layer():
     assert not layered(16, 200, 151936, "bf16", 16, 4)
     for B, N, V, k, D in [(1, 16, 1024, 2, 6), (1, 60, 128256, 10, 12), (4, 128, 151936, 8, 16), (16, 256, 151936, 16, 24)]:
         assert not layered(B, N, V, "bf16", k, D)
+
+
+# B, N, vocabulary, layers, K_init, layer by layer?: measured on both sides of each line
+UNCAPPED = [
+    (1, 60, 128256, 3, 8, True), (1, 60, 128256, 4, 8, False),                     # layers
+    (16, 250, 64000, 4, 8, True), (16, 250, 64000, 5, 8, False),                   # ... against blocks per scanner
+    (8, 250, 151936, 5, 8, True), (8, 250, 151936, 6, 8, False),
+    (16, 250, 151936, 8, 8, True), (16, 250, 151936, 12, 8, False),
+    (8, 33, 128256, 6, 32, True), (8, 36, 128256, 6, 35, False),                   # the first layer spends the budget
+    (1, 128, 128256, 6, 127, False), (1, 250, 20000, 6, 249, True), (16, 100, 128256, 6, 99, True), (4, 100, 128256, 6, 99, False),
+]
+
+
+def test_uncapped_calls_go_the_way_that_was_faster():
+    for B, N, vocab, layers, K_init, layered in UNCAPPED:
+        assert P.literal_layered(B, N, vocab, "bf16", layers, K_init) == layered, (B, N, vocab, layers, K_init)
+    # without a top-K layer, rows decide whether the first layer spends the budget
+    assert not P.literal_layered(8, 33, 128256, "bf16", 6, 32, init_layers=0)
+    # no product overflows
+    assert P.literal_layered(256, 256, 2 ** 31 - 1, "f32", 255) and not P.literal_layered(1, 256, 1000, "f32", 2 ** 31 - 1)
