@@ -454,10 +454,6 @@ __device__ __forceinline__ int deep_select(const ExpandArgs& a, const LiteralAhe
   return n_keep;
 }
 
-// A value that is the same in all lanes, as the scalar that the compiler does not take it for where it comes from LDS
-// (on a vector, both sides of a branch are run through one after the other, with the registers of both).
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
 // ---- selector: the loop of Alg. 2 for sequence b.
 // exit_ticket(ok): takes the workgroup's exit ticket; called when everything other workgroups
 // of the launch look at has been performed.

@@ -6,6 +6,11 @@
 
 namespace talon {
 
+// A value that is the same in all lanes, as the scalar that the compiler does not take it for where it comes from LDS: what
+// is computed from it stays in scalar registers, and a branch on it is taken by all lanes or by none (on a vector, both
+// sides are run through one after the other, with the registers of both).
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // ---- cross-lane moves without the LDS crossbar: DPP inside a row of 16 lanes, lane-swap
 // instructions across rows.  Each helper returns the value held by the partner lane.
 template <int CTRL>

@@ -247,9 +247,10 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
       const int mid = (lo + hi) >> 1;
       if (s_prefix[mid] <= rg) lo = mid; else hi = mid;
     }
-    const int b = lo;
-    const int local = rg - s_prefix[b];
-    const int fbegin = s_begin[b];
+    // (scalars: the row's addresses as vectors made the launch over all layers spill)
+    const int b = uniform(lo);
+    const int local = rg - uniform(s_prefix[b]);
+    const int fbegin = uniform(s_begin[b]);
     const int node = fbegin + local;
     const int in_row = a.row_mode == TALON_ROWS_BY_FRONTIER ? local : node;
     const char* row = static_cast<const char*>(a.logits) +

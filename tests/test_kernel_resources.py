@@ -1,4 +1,4 @@
-"""Registers of the attention kernels, as the compiler reports them for gfx950 (no GPU needed)."""
+"""Registers of the kernels, as the compiler reports them for gfx950 (no GPU needed)."""
 import os
 import re
 import subprocess
@@ -36,6 +36,17 @@ def test_attention_kernels_do_not_spill(attention_kernels):
         assert r["VGPRs"] <= 256 and r["ScratchSize"] == 0 and r["VGPRs Spill"] == 0, (key, r)
         if not key[2]:
             assert r["SGPRs Spill"] == 0, (key, r)
+
+
+@pytest.mark.parametrize("source,kernels", [("expand.hip", 6), ("ahead.hip", 2), ("accept.hip", 3)])
+def test_scans_do_not_spill(source, kernels, tmp_path_factory):
+    """The kernels that stream rows for capped trees, and the target argmax: no scratch memory."""
+    out = subprocess.run([B._hipcc(), *B.FLAGS, "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c",
+                          os.path.join(B.CSRC, source), "-o", str(tmp_path_factory.mktemp("o") / "out.o")],
+                         stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, check=True).stdout
+    found = re.findall(r"Function Name: (\S*(?:expand_(?:tree_)?kernel|build_ahead_kernel|argmax_\w+_kernel)\S*).*?ScratchSize \[bytes/lane\]: (\d+)",
+                       out, re.S)
+    assert len(found) == kernels and all(size == "0" for _, size in found), found
 
 
 def _assembly(source, tmp_path_factory):
