@@ -247,10 +247,12 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
       const int mid = (lo + hi) >> 1;
       if (s_prefix[mid] <= rg) lo = mid; else hi = mid;
     }
-    // (scalars: the row's addresses as vectors made the launch over all layers spill)
-    const int b = uniform(lo);
-    const int local = rg - uniform(s_prefix[b]);
-    const int fbegin = uniform(s_begin[b]);
+    // (scalars in the launch over all layers: the row's addresses as vectors made it spill.  The launches of one layer have
+    // the registers, and were 1 % slower with scalars.)
+    const auto scalar = [](int v) { return TREE ? uniform(v) : v; };
+    const int b = scalar(lo);
+    const int local = rg - scalar(s_prefix[b]);
+    const int fbegin = scalar(s_begin[b]);
     const int node = fbegin + local;
     const int in_row = a.row_mode == TALON_ROWS_BY_FRONTIER ? local : node;
     const char* row = static_cast<const char*>(a.logits) +
