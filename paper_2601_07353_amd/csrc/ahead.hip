@@ -305,7 +305,7 @@ __device__ __forceinline__ void help_read(const ExpandArgs& a, const LiteralAhea
       if (tid == 0) { s.item = found >= 0 ? item : found; s.count[0] = nb; }
     }
     __syncthreads();
-    const int item = s.item, b = s.count[0];
+    const int item = uniform(s.item), b = uniform(s.count[0]);
     __syncthreads();
     if (item == -3) return;
     if (item >= 0) read_part<EPL>(a, la, s, b, item);
@@ -370,7 +370,7 @@ __device__ __forceinline__ int deep_select(const ExpandArgs& a, const LiteralAhe
     while (true) {
       if (tid == 0) part.item = static_cast<int>(static_cast<uint32_t>(__hip_atomic_fetch_add(claim_word(a, b), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
       __syncthreads();
-      const int item = part.item;
+      const int item = uniform(part.item);
       __syncthreads();
       if (item >= n_items) break;
       read_part<EPL>(a, la, part, b, item);
