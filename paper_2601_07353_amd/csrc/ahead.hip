@@ -68,7 +68,8 @@ struct PartLds {
   int count[4];
   int item;
 };
-constexpr int kAheadLists = 320;   // 255 rows, and up to 64 parts of rows that are read again
+constexpr int kAheadLists = 320;   // 255 rows, and up to kDeepParts parts of rows that are read again
+static_assert(TALON_N_MAX - 1 + kDeepParts <= kAheadLists, "a list each");
 constexpr int kDeepPool = 2048;
 struct DeepPickLds {
   PickLds<kDeepPool, kAheadLists> pick;
@@ -339,7 +340,7 @@ __device__ __forceinline__ int deep_select(const ExpandArgs& a, const LiteralAhe
   parts = parts < 1 ? 1 : (parts > kLiteralChunks ? kLiteralChunks : parts);
   const int n_items = n_open * parts;
   unsigned long long* request = request_words(la, a, b);
-  int most = (kDeepPool - TALON_N_MAX) / n_items;   // (at most 15 rows have their 16th kept, 64 parts; other rows keep at most 255 in all)
+  int most = (kDeepPool - TALON_N_MAX) / n_items;   // (at most kDeepParts parts; other rows keep at most 255 in all)
   most = most < 64 ? most : 64;
   most = most < limit ? most : limit;
   int n_keep = 0;

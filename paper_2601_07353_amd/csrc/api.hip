@@ -203,7 +203,6 @@ int argmax_blocks_per_run(long long rows, int blocks) {
 // Workspace of talon_expand_literal: the scan's workspace and its outputs (laid out for the
 // most candidates per row the call ever asks the scan for) and the survivors of every
 // frontier row.
-constexpr int kLiteralScanK = 16;
 struct LiteralLayout {
   ExpandLayout scan;
   int k_max;   // candidates per row the layout has room for: kLiteralScanK, or 1 for very wide rows
@@ -644,7 +643,7 @@ int check_literal_args(const void* logits, int dtype, int64_t row_stride, int64_
   return TALON_OK;
 }
 
-// Workgroups that read parts of rows again: 64 that wait for them from the start (a request has up to 64 parts). They
+// Workgroups that read parts of rows again: 64 that wait for them from the start (a request has up to kDeepParts parts). They
 // come behind the scanners in the grid; where the scan takes several rounds, as many scanners
 // fewer are started, so that helpers are there from the beginning.  Another kLateHelpers start when scanners have left and
 // leave at once when there is nothing to read: where many sequences have flat rows, 64 took four rounds and more over their
@@ -806,7 +805,7 @@ int talon_expand_literal_ahead(const void* logits, int dtype, int64_t row_stride
   ea.ahead_chunks = plan.chunks;
   la.late_helpers = kLateHelpers;
   la.parts_per_seq = 3 * (la.helpers + st->B) / st->B;
-  if (la.parts_per_seq > 64) la.parts_per_seq = 64;
+  if (la.parts_per_seq > kDeepParts) la.parts_per_seq = kDeepParts;
   la.first_row = ea.seq_ticket;
   la.request = reinterpret_cast<unsigned long long*>(w + V.off_keys);
   la.part_key = reinterpret_cast<unsigned long long*>(w + V.off_part_keys);

@@ -149,11 +149,16 @@ struct LiteralArgs {
   int32_t* row_ticket;             // [B*N_pad] parts of a row that have finished; zero between launches
 };
 
-// The uncapped pool with rows scanned ahead (ahead.hip).
+// The uncapped pool with rows scanned ahead (ahead.hip): `kLiteralScanK` best of every row.  A row is read again where its last
+// one is kept, and a layer keeps at most N - 1: at most 15 rows, in kDeepParts parts together.
+constexpr int kLiteralScanK = 16;
+constexpr int kDeepParts = 64;
+static_assert((TALON_N_MAX - 1) / kLiteralScanK <= kDeepParts, "a part for every row that is read again");
+static_assert(kDeepParts <= 64 * kLiteralChunks, "their counts lie in 64 rows' part counts");
 struct LiteralAhead {
   int helpers;                     // workgroups that read parts of rows again ...
   int late_helpers;                // ... and those that start when others have left, and stay while there is work
-  int parts_per_seq;               // most parts of a sequence's request (more only for more rows)
+  int parts_per_seq;               // most parts of a sequence's request, at most kDeepParts (more only for more rows)
   int32_t* first_row;              // [B] first row to scan
   unsigned long long* request;     // [B][N_pad + 1] rows to read again: header, then node << 32 | logit bound; behind them [B][320] floors of the parts
   unsigned long long* part_key;    // [B][part_keys_per_seq] keys of the parts
