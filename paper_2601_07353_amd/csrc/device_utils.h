@@ -150,30 +150,6 @@ __device__ __forceinline__ int wave_inclusive_scan_i32(int v) {
 
 // Workgroup-wide helpers for 256 threads.  `scratch` points at >= 8 values of T in LDS.
 // Every helper starts and ends with a barrier, so scratch can be reused back to back.
-__device__ __forceinline__ float block_max_f32(float v, float* scratch) {
-  v = wave_max_f32(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return fmaxf(fmaxf(scratch[0], scratch[1]), fmaxf(scratch[2], scratch[3]));
-}
-
-__device__ __forceinline__ double block_sum_f64(double v, double* scratch) {
-  v = wave_sum_f64(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return (scratch[0] + scratch[1]) + (scratch[2] + scratch[3]);
-}
-
-__device__ __forceinline__ int block_sum_i32(int v, int* scratch) {
-  v = wave_sum_i32(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return scratch[0] + scratch[1] + scratch[2] + scratch[3];
-}
-
 __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v,
                                                             unsigned long long* scratch) {
   v = wave_max_u64(v);

@@ -127,8 +127,6 @@ template <int EPL, int MODE>
 __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch_idx) {
   constexpr bool FUSED = MODE != kModeSplit;
   constexpr bool TREE = MODE == kModeTree;
-  constexpr int NX = kScanTiles * EPL;          // logits per thread per block
-  constexpr int BLOCK = kThreads * NX;          // logits per block
   __shared__ int s_prefix[TALON_B_MAX + 1];     // exclusive prefix of frontier sizes
   __shared__ int s_begin[TALON_B_MAX];          // first frontier node of every sequence
   __shared__ uint32_t s_stat[FUSED && !TREE ? TALON_B_MAX : 1];   // its status when the launch began
@@ -143,8 +141,6 @@ __device__ __forceinline__ int expand_body(const ExpandArgs& a, const int launch
   __shared__ int s_misc[2];
   __shared__ __attribute__((aligned(16))) unsigned long long s_topw[4][TALON_K_MAX]; // k best keys of each wavefront, sorted
   __shared__ unsigned long long s_top[TALON_K_MAX];
-  __shared__ double s_red_f64[8];
-  __shared__ float s_red_f32[8];
   __shared__ int s_red_i32[8];
   __shared__ float s_wmax[4];
   __shared__ double s_wsum[4];

@@ -74,32 +74,6 @@ __device__ __forceinline__ void stores_performed() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// Number of keys in s[0..n) greater than key (LDS broadcast reads, 4 in flight).
-__device__ __forceinline__ int count_greater(const unsigned long long* s, int n, unsigned long long key) {
-  int r = 0;
-  int j = 0;
-  for (; j + 4 <= n; j += 4) {
-    unsigned long long v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = s[j + u];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) r += (v[u] > key) ? 1 : 0;
-  }
-  for (; j < n; ++j) r += (s[j] > key) ? 1 : 0;
-  return r;
-}
-
-// Number of keys greater than `key` in a list sorted in descending order (zeros, if any, at
-// the end): binary search.
-__device__ __forceinline__ int count_greater_sorted(const unsigned long long* s, int n, unsigned long long key) {
-  int lo = 0, hi = n;   // invariant: s[i] > key for i < lo, s[i] <= key for i >= hi
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (s[mid] > key) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
 __device__ __forceinline__ unsigned long long make_key(float x, int token) {
   return (static_cast<unsigned long long>(sortable_u32(x)) << 32) |
          static_cast<unsigned long long>(0xFFFFFFFFu - static_cast<uint32_t>(token));
