@@ -272,6 +272,17 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
         r[q] = load_vec<EPL>(row, ((t + q) * kThreads + tid) * EPL, vocab);
     }
   };
+  // Sums are of 2^(x*log2e - c) with c = fl(m*log2e); the rounding of c is a common factor
+  // 2^(c - m*log2e) of a whole group, applied once at its end.  (Kept with the maximum where there are registers for it: 23
+  // launches of one layer for 16 sequences of 250 nodes 347 us with c worked out in every group, 343; the
+  // scans at four workgroups per compute unit are 0.3 % faster the other way.)
+  const float kLog2e = 1.4426950408889634f;
+  float c = kLeastMax * kLog2e, c_err = 0.f;   // m*log2e and, exactly, m*log2e - c
+  auto against = [&](const float m) {
+    const float mm = fmaxf(m, kLeastMax);
+    c = mm * kLog2e;
+    c_err = __builtin_fmaf(mm, kLog2e, -c);
+  };
   int tb = t0;
   bool done = false;
   // With the selection in the launch the kernel runs three workgroups per compute unit and has
@@ -326,13 +337,9 @@ __device__ __forceinline__ bool scan_chunk(const char* row, const int vocab, con
       if (gmax > m_l) {
         s_l = rescaled_sum(s_l, m_l, gmax);
         m_l = gmax;
+        if constexpr (PREFETCH) against(gmax);
       }
-      // sum of 2^(x*log2e - c) with c = fl(m*log2e); the rounding of c is a common factor
-      // 2^(c - m*log2e) of the whole group, applied once below
-      const float kLog2e = 1.4426950408889634f;
-      const float mm = fmaxf(m_l, kLeastMax);
-      const float c = mm * kLog2e;
-      const float c_err = __builtin_fmaf(mm, kLog2e, -c);   // m*log2e - c, exact
+      if constexpr (!PREFETCH) against(m_l);
       float acc = 0.f;
 #pragma unroll
       for (int q = 0; q < kScanTiles; ++q) {
