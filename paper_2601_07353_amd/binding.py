@@ -389,7 +389,8 @@ def make_literal_workspace(B, N_pad, vocab, dtype) -> torch.Tensor:
 
 def talon_expand_literal(logits, st: TreeState, layers, mu, K_init, init_layers, max_depth, workspace,
                          row_mode=TALON_ROWS_BY_NODE, vocab=None, stream=None):
-    """With rows by node id the library may read any row of `logits` ahead of the trees, as in talon_build_tree."""
+    """With rows by node id the library may read any row of `logits` ahead of the trees, as in talon_build_tree.  (Should a
+    sequence come back ABORTED, its tree stands after a whole layer: clear the bit and call again.)"""
     _native.expand_literal(logits, st.c, layers, mu, K_init, init_layers, max_depth, workspace, row_mode, vocab, stream)
 
 

@@ -619,7 +619,8 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, const Literal
       double low = init || anchor == 0ull ? -__builtin_huge_val() : sa.log_mu + unsortable_f64(anchor);
       // Once it is sure that the budget will be spent no further rows are needed.  How many tokens of a row that is
       // read again pass at least?  Its probabilities add up to one: the k best hold at most k times the best one's, tokens
-      // that do not pass less than the bound's each, and what is left is shared by tokens of at most the k-th's.
+      // that do not pass less than the bound's each, and what is left is shared by tokens of at most the k-th's.  (0.99:
+      // far above the rounding of the three terms, so that a rest of nothing cannot pass for one.)
       int sure = n_keep;
       if (sure < limit && n + limit >= st.N) {
         if (tid == 0) s.nfin = 0;
@@ -630,7 +631,7 @@ __device__ __forceinline__ void select_layers(const ExpandArgs& a, const Literal
         for (int i = 0; i < kRegCand; ++i) {
           if (i != at || i >= per || !((keep_bits >> i) & 1u)) continue;
           const float bound = __expf(static_cast<float>(low - plogp));
-          const float rest = 0.9f * (1.f - static_cast<float>(k) * __int_as_float(s.hist[p]) - static_cast<float>(a.vocab) * bound) / prob_r[i];
+          const float rest = 0.9f * (0.99f - static_cast<float>(k) * __int_as_float(s.hist[p]) - static_cast<float>(a.vocab) * bound) / prob_r[i];
           if (rest > 0.f) atomicAdd(&s.nfin, rest < 256.f ? static_cast<int>(rest) : 256);
         }
         __syncthreads();
